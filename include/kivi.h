@@ -95,7 +95,7 @@ typedef struct kivi_layout {
     int32_t n_q_heads;      /* query heads; a multiple (1x to 128x) of n_kv_heads: up to  */
                             /* 8 query heads per kv-head share one pass over the cache,   */
                             /* wider groups (multi-query attention) run as units of one   */
-                            /* launch (runs of 4 heads) in the matrix-core family's       */
+                            /* launch (pairs of runs of 4 heads) in the matrix-core family's */
                             /* single-launch form, one launch per 8 heads otherwise       */
     int32_t n_kv_heads;     /* key/value heads                                            */
     int32_t head_dim;       /* D; this build supports 128                                 */
@@ -138,14 +138,15 @@ int kivi_cache_sizes(const kivi_layout_t* layout, kivi_cache_sizes_t* sizes);
 typedef struct kivi_decode_plan {
     int32_t family;             /* KIVI_DECODE_VALU or KIVI_DECODE_MFMA                              */
     int32_t launches;           /* kernel launches of one attention call                            */
-    int32_t splits_quantised;   /* pieces of the all-quantised token range per (batch, kv-head)     */
+    int32_t splits_quantised;   /* pieces of the all-quantised token range per (batch, kv-head); with */
+                                /* 3 or more query heads per kv-head a launch may cut finer         */
     int32_t splits_fp16;        /* pieces of the range that holds fp16 rows                         */
     int32_t tiles_per_split_quantised, tiles_per_split_fp16;   /* in 32-token tiles                */
     int32_t units_per_kv_head;  /* 1; 2 or 4 when the query heads of every kv-head are served as    */
                                 /* halves or quarters that read the cache independently (4, 6 or 8  */
                                 /* heads per kv-head, small batches); ceil(heads per kv-head / 4)   */
                                 /* when a wider group (multi-query attention) runs as ONE launch    */
-                                /* whose units are runs of 4 query heads                            */
+                                /* over runs of 4 query heads (two neighbouring ones per pass)      */
 } kivi_decode_plan_t;
 
 /* Host helper: the plan for `cache`'s current state (no launch).  Errors: INVALID_ARG, UNSUPPORTED. */
@@ -301,8 +302,8 @@ int kivi_batch_slice(const kivi_layout_t* layout, const kivi_cache_t* cache, int
  * one launch (which also appends the step's new tokens), the all-quantised parts in a second; both
  * read each sequence's counters from a copy in the workspace, and the shorter sequences' share of
  * the work partition is skipped (where that share is large, or the batch holds as many (batch,
- * kv-head) units as the chip holds wavefronts, the second launch divides the tokens that are there
- * evenly over the wavefronts instead).  A step adds one launch per run of equal sequences that flush
+ * kv-head) units as the chip holds wavefronts, and with 3 or more query heads per kv-head, the second launch
+ * divides the tokens that are there evenly instead).  A step adds one launch per run of equal sequences that flush
  * in it (a sequence flushes every G-th step).
  *   Otherwise (another policy or family, empty slots, sequences without fp16 rows) the batch is
  * walked in runs of consecutive entries with equal state and each run is one call of the uniform

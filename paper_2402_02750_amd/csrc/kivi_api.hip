@@ -235,14 +235,14 @@ int decode_family(const kivi_layout_t* l) {
 //  (2) Between half a unit and one unit per workgroup most workgroups straddle two units and run two
 //      such chains: two launches are 2-12 % faster once the launch is long enough to carry the
 //      second launch's fixed 8-12 us.
-//  (3) Fewer units still, but 3 or more query heads per kv-head and at least two tiles of fp16 rows:
-//      the rows kernel runs every tile of every unit at once where the persistent kernel gives each
-//      fp16-row chunk to one workgroup (and its 4-bit instantiation for 5 to 8 heads spills
-//      registers in the single-launch form only).  Two launches pay from a total amount of work
-//      (units x tiles) and of fp16-row work (units x fp16 tiles) on.
-// The thresholds are fitted to sweeps of both forms over 8-4096 units, contexts 1k-16k, windows
-// 32-192, 1-8 heads per kv-head, 2 and 4 bits (730 shapes): against the better form of each shape
-// these rules lose 0.1-1.2 % on average per instantiation, a single launch everywhere 1.3-7.6 %.
+// With 3 or more query heads per kv-head (decode_tiles_kernel) the fp16 rows have workgroups of their own in
+// either form; as a launch of their own they cost the launch's fixed 7-9 us, beside the others they take
+// residency from workgroups that run much longer.
+//  (3) 5 to 8 heads: from 384 fp16-row tiles on (one launch is still the faster one below 512 units -- 28.1
+//      against 37.4 us at 128 units, context 4000 -- and the slower one from there on: 91 against 75 us at 512 units;
+//      the line is where it was when the fp16 rows were 40 % of such a launch).
+//  (4) 3 or 4 heads: 512 units on (context 4000, 2 bits: 64 against 80 us; context 1000: 36 against 39); even at
+//      384 units and context 4000 (54.0 / 53.2 us), one launch 20 % faster below (23 against 34 us at context 1000).
 bool wants_two_launches(const kivi_layout_t* l, const kivi_cache_t* c, int path) {
     if (path != KIVI_DECODE_MFMA || l->decode_path == KIVI_DECODE_MFMA_ONE) return false;
     const int rep_launch = std::min(l->n_q_heads / l->n_kv_heads, kMaxRep);
@@ -254,59 +254,59 @@ bool wants_two_launches(const kivi_layout_t* l, const kivi_cache_t* c, int path)
     if (!possible) return false;
     if (l->decode_path == KIVI_DECODE_MFMA_TWO) return true;
     const int64_t units = (int64_t)l->batch * l->n_kv_heads;
-    const int resident = mfma_geometry(l->bits, rep_launch).resident_workgroups;
     const int64_t work = units * tiles_total, row_work = units * tiles_b;
+    if (rep_variant == 8) return tiles_b >= 2 && work >= 4000 && row_work >= 384;                    // (3)
+    if (rep_variant == 4) return units >= 512 || (units >= 384 && work >= 40000);                    // (4)
+    const int resident = mfma_geometry(l->bits, rep_launch).resident_workgroups;
     if (units * 4 >= (int64_t)resident * 5) return true;                                             // (1)
-    if (units * 2 > resident && units < resident && tiles_b >= 2 && work >= 24000) return true;      // (2)
-    if (rep_variant < 4) return false;
-    int64_t min_work, min_row_work;                                                                  // (3)
-    int min_tiles_b = 2;
-    if (rep_variant == 8) { min_work = 4000; min_row_work = 384; }
-    else { min_work = l->bits == 4 ? 10000 : 16000; min_row_work = 512; min_tiles_b = 3; }
-    return tiles_b >= min_tiles_b && work >= min_work && row_work >= min_row_work;
+    return units * 2 > resident && units < resident && tiles_b >= 2 && work >= 24000;                // (2)
 }
 
-// With 4, 6 or 8 query heads per kv-head and few chunks per workgroup the single launch lasts about
-// as long as its chunks, and a chunk takes longer the more heads it serves (8 kv-heads, context 4096,
-// batch 1, one chunk per workgroup: 9.8 / 15.2 / 30.0 us with 1 / 4 / 8 heads per kv-head).  Then
-// equal parts of every group run as units of their own on the instantiation for a part's heads:
-// more workgroups, each shorter; the cache is read once per part, which such launches do not notice.
-// Measured (8 kv-heads, batch 1-32, contexts 1k-32k) for limits from 1/2 to 16 chunks per resident
-// workgroup.  Halves of 6 or 8 heads: faster wherever applied up to 4 chunks per workgroup at 2 bits
-// (30.5 -> 18.3 us at batch 1 / context 4096, 69.6 -> 46.8 us at batch 2 / 32k; mixed beyond) and up to
-// 16 at 4 bits, whose 8-head instantiation spills registers (29.5 -> 18.9, 98.5 -> 81.9 us).  Halves of
-// 4 heads at 2 bits: 17.0 -> 13.8 us at batch 1 / 4096, 37.1 -> 24.6 us at batch 1 / 32k; from 128 units
-// on 4 % slower.  Quarters of 8 heads at 2 bits, against halves: 18.3 -> 14.5 us at batch 1 / 4096,
-// 29.7 -> 22.4 us at batch 1 / 16k, 20.4 -> 18.0 us at batch 2 / 4096; even or slower from 32 units on.
+// With 4, 6 or 8 query heads per kv-head and less work than the chip has room for, equal parts of every group run
+// as units of their own (the instantiation for a part's heads needs fewer instructions per tile, and the cache is read
+// once per part, which such launches do not notice).  Limit: one chunk per resident workgroup -- from there on the
+// doubled number of tiles costs more (64 query / 8 kv heads, batch 4, context 16384: 48 us in halves, 31 us whole).
 // log2 of the parts a kv-head's query heads are served in: 0 (whole group), 1 (halves), 2 (quarters)
 int head_split_shift(const kivi_layout_t* l, const SplitPlan& plan, int path, bool two_launches) {
     const int rep_total = l->n_q_heads / l->n_kv_heads;
     if (path != KIVI_DECODE_MFMA || two_launches || (rep_total != 4 && rep_total != 6 && rep_total != 8)) return 0;
-    if (l->group != kTileTokens) return 0;            // G > 32 runs on instantiations of its own, which exist for whole groups only
+    if (l->group != kTileTokens) return 0;
     const int64_t units = (int64_t)l->batch * l->n_kv_heads, chunks = units * plan.n_splits();
     // parts of 2 heads run on the 2-head instantiation: 2 bits only (at 4 bits that instantiation's
     // chunks are not the length the plan was made for)
     const MfmaGeometry g2 = mfma_geometry(l->bits, 2);
     const bool two_heads_possible = g2.chunk_tiles == plan.tiles_per_split_a;
-    if (rep_total == 8 && two_heads_possible && units <= 16 && chunks <= (int64_t)g2.resident_workgroups * 2) return 2;     // quarters
-    if (rep_total == 4)     // 2 + 2: up to 64 units and 4 chunks per workgroup
-        return two_heads_possible && units <= 64 && chunks <= (int64_t)g2.resident_workgroups * 4 ? 1 : 0;
-    const int max_chunks_per_workgroup = l->bits == 4 ? 16 : 4;
-    return chunks <= (int64_t)mfma_geometry(l->bits, 4).resident_workgroups * max_chunks_per_workgroup ? 1 : 0;
+    if (rep_total == 8 && two_heads_possible && units <= 16 && chunks <= g2.resident_workgroups) return 2;     // quarters
+    if (rep_total == 4)     // 2 + 2: up to 64 units
+        return two_heads_possible && units <= 64 && chunks <= g2.resident_workgroups ? 1 : 0;
+    return chunks <= mfma_geometry(l->bits, 4).resident_workgroups ? 1 : 0;
 }
 
-// Runs of kWideGroupRun query heads a kv-head's group is served in by ONE launch of the matrix-core
-// family's single-launch form (1: the group fits one run, or the form is not the single launch:
-// then a wider group takes one launch, or pair of launches, per run).
-// Query heads per run when a wider group is served as units of one launch: 4 (measured against 8 on
-// 71 : 1, 128 : 8 and 32 : 2 head shapes at 2 and 4 bits: 13-20 % faster everywhere -- the four-head
-// instantiation's fp16-row phase and chunks are shorter and there are twice the units to spread).
+// A group wider than kMaxRep heads is served as runs of kWideGroupRun query heads in ONE launch of the single-launch
+// form (1: the group fits one pass, or the form is not the single launch: then one launch, or pair, per kMaxRep
+// heads).  decode_tiles_kernel takes two neighbouring runs in one pass over the cache: its eight head slots cost a
+// tile 15 % more than four.
 constexpr int kWideGroupRun = 4;
 int wide_group_width(const kivi_layout_t*) { return kWideGroupRun; }
 int wide_group_runs(const kivi_layout_t* l, int path, bool two_launches) {
     const int rep_total = l->n_q_heads / l->n_kv_heads;
-    if (path != KIVI_DECODE_MFMA || two_launches || rep_total <= kMaxRep || l->group != kTileTokens) return 1;
+    if (path != KIVI_DECODE_MFMA || two_launches || rep_total <= kMaxRep) return 1;
     return ceil_div(rep_total, wide_group_width(l));
+}
+
+// Which kernel of the matrix-core family serves the layout: decode_tiles_kernel from three query heads per
+// kv-head on (sweep over 8-1024 units, contexts 300-30000, 2 and 4 bits: 1.02-2.0 times as fast as
+// decode_mfma_kernel throughout), and with two heads up to 256 units (1.03-1.19; at 512 units 0.70, that
+// kernel's cheaper tiles win).  With one head per kv-head most of its matrix columns would idle.
+bool uses_tiles(const kivi_layout_t* l) {
+    const int rep = l->n_q_heads / l->n_kv_heads;
+    return rep >= 3 || (rep == 2 && (int64_t)l->batch * l->n_kv_heads <= 256 && l->decode_path != KIVI_DECODE_MFMA_TWO);
+}
+// parts per (batch, query head) that `bytes` of workspace have room for
+int part_rows(const kivi_layout_t* l, size_t bytes) {
+    const size_t row = (size_t)l->batch * l->n_q_heads * (kHeadDim + 2) * sizeof(float);
+    const int n = (int)std::min<size_t>(bytes / row, kTilesMaxParts);
+    return n > 1 ? n & ~1 : n;      // even: the statistics of a row's first part are 16-byte aligned
 }
 
 // Launch the attention of q over cache state `c` (already validated).  k_new / v_new non-null: the
@@ -347,8 +347,11 @@ int enqueue_attention(const kivi_layout_t* l, const kivi_cache_t* c, const void*
     const size_t rows = (size_t)l->batch * l->n_q_heads * p.plan.n_splits();
     if (counter_bytes(l) + rows * (kHeadDim + 2) * sizeof(float) > workspace_bytes) return KIVI_ERR_WORKSPACE;
     p.counters = static_cast<int32_t*>(workspace);
+    const bool tiles = path == KIVI_DECODE_MFMA && uses_tiles(l);
+    p.part_stride = p.plan.n_splits();
+    if (tiles) p.part_stride = part_rows(l, workspace_bytes - counter_bytes(l));
     p.part_o = reinterpret_cast<float*>(static_cast<char*>(workspace) + counter_bytes(l));
-    p.part_ml = p.part_o + rows * kHeadDim;
+    p.part_ml = p.part_o + (size_t)l->batch * l->n_q_heads * p.part_stride * kHeadDim;
 
     hipStream_t hs = static_cast<hipStream_t>(stream);
     // Up to kMaxRep query heads per kv-head go through one launch.  A wider group (multi-query
@@ -361,21 +364,22 @@ int enqueue_attention(const kivi_layout_t* l, const kivi_cache_t* c, const void*
         // a group wider than kMaxRep heads in the single-launch form: its runs of kWideGroupRun heads are
         // units of ONE launch (they read the same cache, which the caches serve after the first)
         p.q_head0 = 0;
-        p.rep_here = wide_group_width(l);
+        p.rep_here = 2 * wide_group_width(l);             // two neighbouring runs share one pass
         p.rep_variant = p.rep_here;
-        return hip_status(launch_decode_mfma(p, hs));
+        p.head_groups = ceil_div(rep_total, p.rep_here);
+        return hip_status(launch_decode_tiles(p, hs));
     }
     if (const int shift = head_split_shift(l, p.plan, path, two)) {
-        p.head_split = shift;
+        p.head_groups = 1 << shift;
         p.q_head0 = 0;
         p.rep_here = rep_total >> shift;
         p.rep_variant = p.rep_here <= 2 ? 2 : 4;
-        return hip_status(launch_decode_mfma(p, hs));
+        return hip_status(launch_decode_tiles(p, hs));
     }
     for (int h0 = 0; h0 < rep_total; h0 += kMaxRep) {
         p.q_head0 = h0;
         p.rep_here = std::min(kMaxRep, rep_total - h0);
-        hipError_t e = path == KIVI_DECODE_MFMA ? launch_decode_mfma(p, hs) : launch_decode_valu(p, hs);
+        hipError_t e = path != KIVI_DECODE_MFMA ? launch_decode_valu(p, hs) : tiles ? launch_decode_tiles(p, hs) : launch_decode_mfma(p, hs);
         if (e == hipErrorNotSupported) return KIVI_ERR_UNSUPPORTED;
         if (int s = hip_status(e)) return s;
         p.k_new = p.v_new = nullptr;
@@ -508,7 +512,47 @@ int ragged_attention_fast(const kivi_layout_t* l, const kivi_cache_t* c, const k
     // heads per kv-head, length spreads from +-12 % to 1 : 80: 0.70-0.96 of the padded plan's time above the
     // threshold, 1.05-1.7 below it).
     const int64_t wasted = units * ceil_div(max_tiles_a, 4) - total;
-    if (slice_waves > 0 && units < slice_waves && units <= kMaxSliceUnits && wasted >= 14000) {
+    const bool tiles = rep_total >= 3;
+    if (tiles) {
+        // decode_tiles_kernel: the unit-major axis of four-tile steps (at least one per unit) in equal
+        // intervals, one per resident workgroup.  Table: {first unit, first step in it, steps, 0} per
+        // workgroup, then the steps before each sequence.
+        total = 0;
+        for (int b = 0; b < l->batch; ++b) total += (int64_t)std::max(1, ceil_div(st[b].n_kq / kTileTokens, 4)) * l->n_kv_heads;
+        if (total > 0x3fffffff) return kNotApplicable;
+        const int stride = std::min(part_rows(l, workspace_bytes > parts_offset ? workspace_bytes - parts_offset : 0), tiles_max_parts(l->bits, rep_launch));
+        int64_t wgs = std::min<int64_t>(std::min(tiles_resident_ragged(l->bits, rep_launch), kMaxSlices), total);
+        // no more parts of a unit than there are rows: an interval of c steps cuts n steps into at most (n - 1) / c + 2 parts
+        const int max_steps = std::max(1, ceil_div(max_tiles_a, 4));
+        if (stride < 4) return kNotApplicable;
+        wgs = std::max<int64_t>(1, std::min(wgs, total * (stride - 3) / max_steps));
+        if ((size_t)wgs * 16 + (size_t)l->batch * 4 > slice_table_bytes(l)) return kNotApplicable;
+        tables.resize(state_ints + (size_t)wgs * 4 + l->batch, 0);
+        int32_t* desc = tables.data() + state_ints;
+        int32_t* before = desc + (size_t)wgs * 4;
+        p.axis_len = (int32_t)(total / wgs);
+        p.axis_rem = (int32_t)(total % wgs);
+        auto wg_start = [&](int64_t x) { return x * p.axis_len + std::min<int64_t>(x, p.axis_rem); };
+        int64_t cum = 0, g = 0;
+        for (int b = 0; b < l->batch; ++b) {
+            const int64_t steps = std::max(1, ceil_div(st[b].n_kq / kTileTokens, 4)), end = cum + steps * l->n_kv_heads;
+            before[b] = (int32_t)cum;
+            for (; g < wgs; ++g) {
+                const int64_t begin = wg_start(g);
+                if (begin >= end) break;
+                desc[4 * g + 0] = (int32_t)((int64_t)b * l->n_kv_heads + (begin - cum) / steps);
+                desc[4 * g + 1] = (int32_t)((begin - cum) % steps);
+                desc[4 * g + 2] = (int32_t)(wg_start(g + 1) - begin);
+                desc[4 * g + 3] = 0;
+            }
+            cum = end;
+        }
+        p.wave_desc = dev_state + state_ints;
+        p.unit_parts = p.wave_desc + (size_t)wgs * 4;
+        p.n_slices = (int32_t)wgs;
+        p.total_cost = total;
+        p.part_stride = stride;
+    } else if (slice_waves > 0 && units < slice_waves && units <= kMaxSliceUnits && wasted >= 14000) {
         const int n_slices = (int)std::min<int64_t>(std::min(slice_waves, kMaxSlices), total);
         tables.resize(state_ints + (size_t)n_slices * 4 + (size_t)units * 2, 0);
         int32_t* desc = tables.data() + state_ints;
@@ -551,7 +595,8 @@ int ragged_attention_fast(const kivi_layout_t* l, const kivi_cache_t* c, const k
             tables.resize(state_ints);
         }
     }
-    const size_t rows = (size_t)l->batch * l->n_q_heads * p.plan.n_splits();
+    if (!tiles) p.part_stride = p.plan.n_splits();
+    const size_t rows = (size_t)l->batch * l->n_q_heads * p.part_stride;
     if (parts_offset + rows * (kHeadDim + 2) * sizeof(float) > workspace_bytes) return KIVI_ERR_WORKSPACE;
     p.counters = reinterpret_cast<int32_t*>(ws);
     p.seq_state = dev_state;
@@ -562,10 +607,11 @@ int ragged_attention_fast(const kivi_layout_t* l, const kivi_cache_t* c, const k
                        hipMemcpyHostToDevice, hs) != hipSuccess)
         return KIVI_ERR_HIP;
     p.rep_variant = rep_launch;
+    p.head_groups = 1;
     for (int h0 = 0; h0 < rep_total; h0 += kMaxRep) {
         p.q_head0 = h0;
         p.rep_here = std::min(kMaxRep, rep_total - h0);
-        const hipError_t e = launch_decode_mfma(p, hs);
+        const hipError_t e = tiles ? launch_decode_tiles(p, hs) : launch_decode_mfma(p, hs);
         if (e == hipErrorNotSupported) return KIVI_ERR_UNSUPPORTED;
         if (int s2 = hip_status(e)) return s2;
         p.k_new = p.v_new = nullptr;
@@ -888,7 +934,7 @@ int kivi_decode_step(const kivi_layout_t* l, kivi_cache_t* c, const void* k_new,
         after.n_vr += 1;
         // In the two-launch form (G = 32) the fp16-row launch quantises the flushed tokens with extra
         // workgroups: a flush step then takes two launches like any other step.
-        if ((nk > 0 || nv > 0) && l->group == kTileTokens && wants_two_launches(l, &after, KIVI_DECODE_MFMA)) {
+        if ((nk > 0 || nv > 0) && l->group == kTileTokens && !uses_tiles(l) && wants_two_launches(l, &after, KIVI_DECODE_MFMA)) {
             const int64_t sh = (int64_t)l->cap_r_tokens * kHeadDim, sb = sh * l->n_kv_heads;
             const RowSource ksrc{static_cast<const __half*>(c->k_resid), sb, sh, kHeadDim, c->k_r_start, l->cap_r_tokens};
             const RowSource vsrc{static_cast<const __half*>(c->v_resid), sb, sh, kHeadDim, c->v_r_start, l->cap_r_tokens};

@@ -1,4 +1,5 @@
-// Decode attention, matrix-core family for gfx950 (KIVI Equation 4 + Algorithm 1 Decoding).
+// Decode attention, matrix-core family for gfx950 (KIVI Equation 4 + Algorithm 1 Decoding), one or two query heads
+// per kv-head (kivi_decode_tiles.hip serves wider groups and smaller batches of two).
 //
 // Why matrix cores for a bandwidth-bound scan: at 2 bits a cached element is 3/8 of a byte, so at
 // HBM speed a compute unit sees ~28 elements per clock while its vector ALUs retire 64 lane-ops
@@ -327,21 +328,16 @@ __device__ __forceinline__ void value_tile_mfma(const uint32_t* w, const __half*
 // number of all-quantised tiles from p.seq_state); an instantiation of its own so that batches of
 // one length pay nothing for it.
 constexpr int kBothPhases = 0, kQuantisedOnly = 1, kQuantisedRagged = 2;
-constexpr int kRuntimeHeadGroups = 15;      // value of HSHIFT: the number of head runs per kv-head is a launch parameter
 
-template <int BITS, int REP, int SLOTS, int OCC, int MODE, int HSHIFT = 0, bool CS = false>
+template <int BITS, int REP, int SLOTS, int OCC, int MODE, bool CS = false>
 __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
     constexpr bool kQOnly = MODE != kBothPhases, kRagged = MODE == kQuantisedRagged;
     constexpr int kSlots = SLOTS;
-    // tile slots staged at once: two where that divides the slots and the registers allow
-    constexpr int kStage = REP > 2 ? 1 : (SLOTS % 2 == 0 ? 2 : SLOTS);
+    constexpr int kStage = 2;                         // tile slots staged at once
     using WL = WaveLds<REP, kStage>;
     constexpr int NC = 2 * REP;                       // live matrix columns: (head, hi/lo)
     constexpr int SS = WL::kStageSlots;
-    // fp16-row chunks: rows held in registers at once, and whether the first tile's value rows are
-    // requested ahead of the logits (both cut for the wider instantiations: register pressure)
-    constexpr int RB = (OCC >= 3 || REP > 4) ? 4 : 8;
-    constexpr bool kPreloadV = OCC < 3 && REP <= 4;
+    constexpr int RB = 8;                             // fp16-row chunks: rows held in registers at once
     __shared__ __align__(16) float sm_q[REP][kHeadDim];               // scale * q
     __shared__ __align__(16) __half sm_qf[NC][kKRow];                 // its hi/lo columns (z-term operand)
     __shared__ WL sm_w[4];
@@ -352,7 +348,7 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
     // Parts that never leave the workgroup: when this workgroup is the only contributor to a unit in
     // both phases, the unit's phase-1 result waits here for phase 2 instead of going through the
     // workspace (no device-scope traffic, no counter).
-    constexpr int kHold = REP <= 2 ? 8 : (REP == 4 ? 4 : 0);
+    constexpr int kHold = 8;
     __shared__ float sm_hold_o[kHold * REP * kHeadDim + 1];
     __shared__ float sm_hold_ml[kHold * REP * 2 + 1];
     __shared__ int sm_hold_unit[kHold + 1];
@@ -368,26 +364,9 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
     const int kg = CS ? p.kg_shift : 0;
     const ValueScaleLane vlane = CS ? value_scale_lane<CS>(lane, kg) : ValueScaleLane{0, 0u};
 
-    // REP is the instantiation's head count; the layout may have fewer query heads per kv-head
-    // (3, 5, 6, 7): the surplus heads run on a zero query and are never stored
-    const int rep = p.rep_here, rep_total = p.n_q_heads / p.n_kv_heads;
-    // HSHIFT > 0: a unit of the work axis is (batch, kv-head, one of 2^HSHIFT equal parts of the
-    // kv-head's query heads) -- unit u reads the cache of (batch, kv-head) u >> HSHIFT and serves the
-    // query heads (u & (2^HSHIFT - 1)) * rep .. + rep of its group; parts, counters and held results go by u.
-    // HSHIFT == kRuntimeHeadGroups: groups wider than REP heads (multi-query attention) in ONE launch --
-    // a unit is (batch, kv-head, one of p.head_groups runs of REP consecutive query heads; the last run
-    // may be shorter): every run reads the same cache, which the chip's caches serve after the first.
-    constexpr bool kRunGroups = HSHIFT == kRuntimeHeadGroups;
-    constexpr int kPartMask = kRunGroups ? 0 : (1 << HSHIFT) - 1;
-    const int n_groups = kRunGroups ? p.head_groups : 1;
-    auto kv_unit = [&](int u) -> int { return kRunGroups ? u / n_groups : u >> HSHIFT; };
-    auto part_of = [&](int u) -> int { return kRunGroups ? u - (u / n_groups) * n_groups : u & kPartMask; };
-    auto first_q_head = [&](int u) -> int {
-        return (kv_unit(u) % p.n_kv_heads) * rep_total + p.q_head0 + part_of(u) * (kRunGroups ? REP : rep);
-    };
-    // live query heads of unit u on this instantiation
-    auto rep_of = [&](int u) -> int { return kRunGroups ? min(REP, rep_total - part_of(u) * REP) : rep; };
-    auto batch_of = [&](int u) -> int { return kv_unit(u) / p.n_kv_heads; };
+    const int rep = p.rep_here, rep_total = p.n_q_heads / p.n_kv_heads;     // rep == REP
+    auto first_q_head = [&](int u) -> int { return (u % p.n_kv_heads) * rep_total + p.q_head0; };
+    auto batch_of = [&](int u) -> int { return u / p.n_kv_heads; };
     // chunks per unit on this launch's cost axis: all-quantised / with fp16 rows
     const int n_a = p.plan.n_splits_a, n_b = kQOnly ? 0 : p.plan.n_splits_b;
     const int cpu = p.plan.n_splits_a + p.plan.n_splits_b;       // workspace rows per (batch, query head)
@@ -456,7 +435,7 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
         j_phys -= j_phys >= nx_lo + nx_len ? nx_len : 0;
         const int tile0 = j_phys * p.plan.tiles_per_split_a;
         nx_nt = min(p.plan.tiles_per_split_a, nx_tiles_a - tile0);
-        nx_base = (int64_t)kv_unit(nx_u) * p.cap_tiles + tile0;
+        nx_base = (int64_t)nx_u * p.cap_tiles + tile0;
         if constexpr (kRagged) {
             if (nx_nt <= 0) nx_base -= tile0;                // an empty chunk: its (masked) slots re-read the unit's tile 0
         }
@@ -532,11 +511,9 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
     };
 
     // kQuantisedOnly: part 0 of the current unit (what the fp16-row launch left), requested when the
-    // unit is entered so that it has arrived long before the unit is left (with eight heads, for want
-    // of registers, only when the unit is left); thread tid holds the values of its elements
+    // unit is entered so that it has arrived long before the unit is left ; thread tid holds the values of its elements
     // idx = tid + 256 k of finish_unit's loop.
     constexpr int kIdx = (REP * kHeadDim + 255) / 256;
-    constexpr bool kPrefetchPart = REP <= 4;
     // kQuantisedOnly also requests the next unit's query one unit ahead and separates the units with
     // LDS-only barriers: the next chunk's data, in flight when a unit is left, then keeps travelling
     // while the workgroup merges, writes the output and stages the next query.  (kBothPhases keeps
@@ -551,7 +528,7 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
         const int b = batch_of(u);
 #pragma unroll
         for (int k = 0; k < kIdx; ++k) {
-            const int idx = min(tid + 256 * k, rep_of(u) * kHeadDim - 1);  // unconditional loads (clamped)
+            const int idx = min(tid + 256 * k, rep * kHeadDim - 1);  // unconditional loads (clamped)
             q_pre[k] = p.q[((int64_t)b * p.n_q_heads + hq0 + idx / kHeadDim) * kHeadDim + idx % kHeadDim];
         }
     };
@@ -561,7 +538,7 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
         const int b = batch_of(u);
 #pragma unroll
         for (int k = 0; k < kIdx; ++k) {
-            const int idx = min(tid + 256 * k, rep_of(u) * kHeadDim - 1);  // unconditional loads (clamped)
+            const int idx = min(tid + 256 * k, rep * kHeadDim - 1);  // unconditional loads (clamped)
             const int64_t row = ((int64_t)b * p.n_q_heads + hq0 + idx / kHeadDim) * cpu;
             pre_m[k] = p.part_ml[row * 2 + 0];
             pre_l[k] = p.part_ml[row * 2 + 1];
@@ -690,21 +667,12 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
                 }
             }
         };
-        if constexpr (kQOnly && kPrefetchPart) {
+        if constexpr (kQOnly) {
 #pragma unroll
             for (int k = 0; k < kIdx; ++k)
-                if (tid + 256 * k < rep_of(u) * kHeadDim) finish_element(tid + 256 * k, pre_m[k], pre_l[k], pre_o[k]);
+                if (tid + 256 * k < rep * kHeadDim) finish_element(tid + 256 * k, pre_m[k], pre_l[k], pre_o[k]);
         } else {
-            for (int idx = tid; idx < rep_of(u) * kHeadDim; idx += 256) {
-                float p0_m = -INFINITY, p0_l = 0.f, p0_o = 0.f;
-                if (merge_rows_parts) {
-                    const int64_t row = ((int64_t)b * p.n_q_heads + hq0 + idx / kHeadDim) * cpu;
-                    p0_m = p.part_ml[row * 2 + 0];
-                    p0_l = p.part_ml[row * 2 + 1];
-                    p0_o = p.part_o[row * kHeadDim + idx % kHeadDim];
-                }
-                finish_element(idx, p0_m, p0_l, p0_o);
-            }
+            for (int idx = tid; idx < rep * kHeadDim; idx += 256) finish_element(idx, -INFINITY, 0.f, 0.f);
         }
         if (n_parts > 1) {
             // The last workgroup to finish this unit merges the parts.  How the parts are published:
@@ -728,7 +696,7 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
             }
             __syncthreads();
             if (sm_last) {
-                for (int idx = tid; idx < rep_of(u) * kHeadDim; idx += 256) {
+                for (int idx = tid; idx < rep * kHeadDim; idx += 256) {
                     const int hh = idx / kHeadDim, c = idx % kHeadDim;
                     const int64_t row = (int64_t)b * p.n_q_heads + hq0 + hh;
                     const float* ml = p.part_ml + row * row_stride * 2;
@@ -780,12 +748,12 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
 #pragma unroll
             for (int k = 0; k < kIdx; ++k) {           // the query was requested one unit ahead
                 const int i = tid + 256 * k;
-                if (i < REP * kHeadDim) stage(i, i / kHeadDim < rep_of(u) ? p.softmax_scale * __half2float(q_pre[k]) : 0.f);
+                if (i < REP * kHeadDim) stage(i, i / kHeadDim < rep ? p.softmax_scale * __half2float(q_pre[k]) : 0.f);
             }
         } else {
             for (int i = tid; i < REP * kHeadDim; i += 256) {
                 const int hh = i / kHeadDim, c = i % kHeadDim;
-                stage(i, hh < rep_of(u) ? p.softmax_scale * __half2float(p.q[((int64_t)b * p.n_q_heads + hq0 + hh) * kHeadDim + c]) : 0.f);
+                stage(i, hh < rep ? p.softmax_scale * __half2float(p.q[((int64_t)b * p.n_q_heads + hq0 + hh) * kHeadDim + c]) : 0.f);
             }
         }
         unit_barrier();
@@ -890,7 +858,7 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
         for (int ck = b_lo; ck < b_hi; ++ck) {
             const int tile0 = p.plan.tiles_a + (ck - u * n_b) * p.plan.tiles_per_split_b;
             const int n_tiles = min(p.plan.tiles_per_split_b, p.plan.tiles_total - tile0);
-            const int64_t unit = kv_unit(u);
+            const int64_t unit = u;
             const bool fused_append = p.k_new != nullptr;
             const int cnt = n_tiles > wave ? (n_tiles - wave + 3) / 4 : 0;
             const int64_t ubase = unit * p.cap_tiles + tile0;
@@ -928,8 +896,7 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
             __half* new_dst = nullptr;
             if (fused_append) {
                 const int last = p.length - 1, last_tile = last / kTileTokens;
-                owns_new = last_tile >= tile0 && last_tile < tile0 + n_tiles && ((last_tile - tile0) & 3) == wave && lane < 32 &&
-                           part_of(u) == 0;           // the parts of a kv-head's group would all store the same rows
+                owns_new = last_tile >= tile0 && last_tile < tile0 + n_tiles && ((last_tile - tile0) & 3) == wave && lane < 32;
                 if (owns_new) {
                     const bool is_v = lane >= 16;
                     const int slot = is_v ? ring_slot(p.v_r_start, last - p.n_vq, p.cap_r)
@@ -938,8 +905,8 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
                     new_dst = const_cast<__half*>(is_v ? p.v_resid : p.k_resid) + (unit * p.cap_r + slot) * kHeadDim + (lane & 15) * 8;
                 }
             }
-            half8 vr0[kPreloadV ? 8 : 1];
-            if (kPreloadV) {
+            half8 vr0[8];
+            {
 #pragma unroll
                 for (int j = 0; j < 8; ++j) vr0[j] = half8{};
                 if (cnt > 0 && p.n_vr > 0 && p.n_vq < (tile0 + wave + 1) * kTileTokens) {
@@ -980,7 +947,7 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
                         }
 #pragma unroll
                         for (int hh = 0; hh < REP; ++hh) {
-                            const half8 qh = hh < rep_of(u) ? *reinterpret_cast<const half8*>(p.q + qrow + hh * kHeadDim + seg * 8) : half8{};
+                            const half8 qh = hh < rep ? *reinterpret_cast<const half8*>(p.q + qrow + hh * kHeadDim + seg * 8) : half8{};
 #pragma unroll
                             for (int j = 0; j < RB; ++j) {
                                 const int tl = (j0 + j) * 4 + row;
@@ -1001,11 +968,8 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
             softmax_step(cnt);
             wave_lds_sync();
             // ---- phase 3: outputs ----
-            // (query heads in groups of at most four: with eight the accumulators of the fp16 rows
-            // would not fit in registers; the rows are then loaded once per group)
-            constexpr int HG = REP > 4 ? 4 : REP;
-#pragma unroll 1
-            for (int h0 = 0; h0 < REP; h0 += HG) {
+            {
+                constexpr int HG = REP, h0 = 0;
                 float racc[HG][8];
 #pragma unroll
             for (int hh = 0; hh < HG; ++hh)
@@ -1015,7 +979,7 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
                 const int tile = tile0 + wave + 4 * i;
                 const int tt = tile * kTileTokens;
                 const int n_vq_here = min(max(p.n_vq - tt, 0), kTileTokens);
-                if (n_vq_here > 0 && h0 == 0) {
+                if (n_vq_here > 0) {
                     uint32_t w[kLaneWords];
                     load_tile_words<BITS>(p.v_codes + (ubase + wave + 4 * i) * kWords, lane, w);
                     __half2 s2, z2;
@@ -1037,7 +1001,7 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
 #pragma unroll
                     for (int j0 = 0; j0 < 8; j0 += RB) {
                         half8 vr[RB];
-                        if (kPreloadV && i == 0) {
+                        if (i == 0) {
 #pragma unroll
                             for (int j = 0; j < RB; ++j) vr[j] = vr0[j];     // requested before the logits were computed
                         } else {
@@ -1107,7 +1071,7 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
     for (int u = ua_lo; u <= ua_hi; ++u) {
         const int a_lo = max(first_a, u * n_a), a_hi = min(last_a, (u + 1) * n_a);
         const bool carried = carry && u == ua_lo;
-        if (kQOnly && kPrefetchPart) request_rows_part(u);
+        if (kQOnly) request_rows_part(u);
         if (!carried) enter_unit(u);
         if (kQOnly && u < ua_hi) request_q(u + 1);
         for (int ck = a_lo; ck < a_hi; ++ck) {
@@ -1184,7 +1148,7 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
 // answer is kept per device (the only state the library keeps; a plain integer per device and
 // instantiation, written once with the same value by whichever thread asks first).
 constexpr int kMaxDevices = 64;
-template <int BITS, int REP, int SLOTS, int OCC, int MODE = kBothPhases, int HSHIFT = 0, bool CS = false>
+template <int BITS, int REP, int SLOTS, int OCC, int MODE = kBothPhases, bool CS = false>
 int resident_workgroups() {
     static std::atomic<int> cached[kMaxDevices];
     int dev = 0, cus = 0, per_cu = 0;
@@ -1195,7 +1159,7 @@ int resident_workgroups() {
         if (c > 0) return c;
     }
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_mfma_kernel<BITS, REP, SLOTS, OCC, MODE, HSHIFT, CS>, 256, 0) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_mfma_kernel<BITS, REP, SLOTS, OCC, MODE, CS>, 256, 0) != hipSuccess ||
         cus <= 0 || per_cu <= 0)
         return 256 * OCC;
     if (keep) cached[dev].store(cus * per_cu, std::memory_order_relaxed);
@@ -1224,7 +1188,7 @@ int resident_workgroups() {
 template <int BITS, int REP, int OCC, bool CS = false, bool SLICES = false>
 __global__ __launch_bounds__(256, OCC) void decode_wave_units_kernel(DecodeParams p) {
     constexpr int kSlots = 4;
-    constexpr int kStage = REP > 2 ? 1 : 2;
+    constexpr int kStage = 2;
     using WL = WaveLds<REP, kStage>;
     constexpr int NC = 2 * REP, SS = WL::kStageSlots;
     constexpr int kWords = kTileTokens * kHeadDim * BITS / 32;
@@ -1596,32 +1560,24 @@ int resident_wave_unit_workgroups() {
     return cus * per_cu;
 }
 
-template <int BITS, int REP, int SLOTS, int OCC, int HSHIFT = 0, bool CS = false>
+template <int BITS, int REP, int SLOTS, int OCC, bool CS = false>
 hipError_t launch_one(DecodeParams p, hipStream_t stream) {
     if (p.plan.tiles_per_split_a != 4 * SLOTS || p.plan.tiles_per_split_b > kMfmaSplitTiles) return hipErrorInvalidValue;
-    const int64_t units = HSHIFT == kRuntimeHeadGroups ? (int64_t)p.batch * p.n_kv_heads * p.head_groups
-                                                        : ((int64_t)p.batch * p.n_kv_heads) << HSHIFT;
+    const int64_t units = (int64_t)p.batch * p.n_kv_heads;
     const int64_t total_a = units * p.plan.n_splits_a, total_b = units * p.plan.n_splits_b;
-    // Cost of an fp16-row chunk in units of an all-quantised chunk: by the bytes they stream, times
-    // a measured factor per instantiation -- with 5 to 8 query heads per kv-head, and with 3 or 4 at
-    // 4 bits, the chain  rows -> logits -> softmax -> rows -> outputs  of an fp16-row chunk takes about
-    // as long as two all-quantised chunks (sweep of the weight from 1 to 5 over 8-512 units, contexts
-    // 1k-16k, windows 64-192: 2 is best for all three, 2-7 % on average and up to 36 % faster than 1;
-    // odd weights leave workgroups with an fp16-row chunk and all-quantised chunks and are slower).
-    // One head or two, and 3 or 4 heads at 2 bits: 1.
-    constexpr int kRowsFactor = (REP > 4 || (REP > 2 && BITS == 4)) ? 2 : 1;
+    // cost of an fp16-row chunk in units of an all-quantised chunk: by the bytes they stream
     const int64_t bytes_a = (int64_t)4 * SLOTS * kTileTokens * 2 * (kHeadDim * BITS / 8 + 16);
     const int64_t bytes_b = (int64_t)p.plan.tiles_per_split_b * kTileTokens * 2 * kHeadDim * 2;
-    p.cost_b = kRowsFactor * (int)std::max<int64_t>(1, (bytes_b + bytes_a / 2) / bytes_a);
+    p.cost_b = (int)std::max<int64_t>(1, (bytes_b + bytes_a / 2) / bytes_a);
     p.cost_unit = p.plan.n_splits_b * p.cost_b + p.plan.n_splits_a;
     p.total_cost = units * p.cost_unit;
     if (p.total_cost <= 0 || p.total_cost > 0x3fffffff || total_a + total_b > 0x7fffffff) return hipErrorInvalidValue;
     p.total_chunks_a = (int)total_a;
     p.total_chunks_b = (int)total_b;
     // every resident workgroup gets an equal share of the cost axis (within one unit of cost)
-    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(resident_workgroups<BITS, REP, SLOTS, OCC, kBothPhases, HSHIFT, CS>(),
+    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(resident_workgroups<BITS, REP, SLOTS, OCC, kBothPhases, CS>(),
                                                                   p.total_cost / p.cost_b));
-    decode_mfma_kernel<BITS, REP, SLOTS, OCC, kBothPhases, HSHIFT, CS><<<grid, 256, 0, stream>>>(p);
+    decode_mfma_kernel<BITS, REP, SLOTS, OCC, kBothPhases, CS><<<grid, 256, 0, stream>>>(p);
     return hipGetLastError();
 }
 
@@ -1647,7 +1603,7 @@ hipError_t launch_two(DecodeParams p, hipStream_t stream) {
     p.total_cost = total_a;
     // One unit per wavefront where that fills the chip evenly: at least as many units as resident
     // wavefronts, and the last round of units at most 12 % short of a full one.
-    if constexpr (REP <= 4 && !CS) {
+    if constexpr (!CS) {
         if (p.wave_desc != nullptr) {
             // equally long slices of the unit-major group axis, one per wavefront (tables made by the host)
             if (p.n_slices < 1 || p.unit_parts == nullptr) return hipErrorInvalidValue;
@@ -1655,7 +1611,7 @@ hipError_t launch_two(DecodeParams p, hipStream_t stream) {
             return hipGetLastError();
         }
     }
-    if constexpr (REP <= 4) {
+    {
         if (!p.seq_state || (!CS && p.ragged_min_tiles >= 1)) {
             const int64_t waves = 4 * (int64_t)resident_wave_unit_workgroups<BITS, REP, OCC, CS>();
             const int64_t rounds = (units + waves - 1) / waves;
@@ -1674,8 +1630,8 @@ hipError_t launch_two(DecodeParams p, hipStream_t stream) {
             decode_mfma_kernel<BITS, REP, SLOTS, OCC, kQuantisedRagged><<<grid, 256, 0, stream>>>(p);
         }
     } else {
-        const int grid = (int)std::min<int64_t>(resident_workgroups<BITS, REP, SLOTS, OCC, kQuantisedOnly, 0, CS>(), total_a);
-        decode_mfma_kernel<BITS, REP, SLOTS, OCC, kQuantisedOnly, 0, CS><<<grid, 256, 0, stream>>>(p);
+        const int grid = (int)std::min<int64_t>(resident_workgroups<BITS, REP, SLOTS, OCC, kQuantisedOnly, CS>(), total_a);
+        decode_mfma_kernel<BITS, REP, SLOTS, OCC, kQuantisedOnly, CS><<<grid, 256, 0, stream>>>(p);
     }
     return hipGetLastError();
 }
@@ -1687,53 +1643,24 @@ template <int B, int R, int S, int O> struct Variant {
 };
 template <class F>
 bool with_variant(int bits, int rep_layout, F&& fn) {
-    // the smallest instantiation that holds the layout's query heads per kv-head
-    const int rep = rep_layout <= 2 ? rep_layout : (rep_layout <= 4 ? 4 : (rep_layout <= 8 ? 8 : 0));
+    const int rep = rep_layout;                     // wider groups: decode_tiles_kernel
     if (bits == 2 && rep == 1) { fn(Variant<2, 1, 4, 2>{}); return true; }
     if (bits == 2 && rep == 2) { fn(Variant<2, 2, 4, 2>{}); return true; }
-    if (bits == 2 && rep == 4) { fn(Variant<2, 4, 4, 2>{}); return true; }
     if (bits == 4 && rep == 1) { fn(Variant<4, 1, 4, 2>{}); return true; }
     if (bits == 4 && rep == 2) { fn(Variant<4, 2, 4, 2>{}); return true; }
-    if (bits == 4 && rep == 4) { fn(Variant<4, 4, 2, 2>{}); return true; }
-    if (bits == 2 && rep == 8) { fn(Variant<2, 8, 4, 2>{}); return true; }
-    if (bits == 4 && rep == 8) { fn(Variant<4, 8, 2, 2>{}); return true; }
-    return false;                       // no instantiation for this shape: the vector-ALU family serves it
+    return false;
 }
 
 }  // namespace
 
 hipError_t launch_decode_mfma(const DecodeParams& p, hipStream_t stream) {
     hipError_t e = hipErrorNotSupported;
-    if ((p.head_groups > 1 || p.head_split > 0) && p.kg_shift > 0) return hipErrorNotSupported;   // G > 32: whole groups, one pass per 8 heads
-    if (p.head_groups > 1) {
-        // runs of 4 (or 8) query heads of every kv-head as units of one single-form launch
-        if (p.two_launches > 0 || p.head_split > 0 || p.q_head0 != 0 || (p.rep_here != 4 && p.rep_here != 8) || p.rep_variant != p.rep_here ||
-            p.seq_state != nullptr || p.head_groups != (p.n_q_heads / p.n_kv_heads + p.rep_here - 1) / p.rep_here)
-            return hipErrorInvalidValue;
-        if (p.bits == 2 && p.rep_here == 8) return launch_one<2, 8, 4, 2, kRuntimeHeadGroups>(p, stream);
-        if (p.bits == 4 && p.rep_here == 8) return launch_one<4, 8, 2, 2, kRuntimeHeadGroups>(p, stream);
-        if (p.bits == 2 && p.rep_here == 4) return launch_one<2, 4, 4, 2, kRuntimeHeadGroups>(p, stream);
-        if (p.bits == 4 && p.rep_here == 4) return launch_one<4, 4, 2, 2, kRuntimeHeadGroups>(p, stream);
-        return hipErrorNotSupported;
-    }
-    if (p.head_split > 0) {
-        // 2^head_split equal parts of every kv-head's query heads as units of their own, on the
-        // instantiation for one part
-        if (p.two_launches > 0 || p.q_head0 != 0 || (p.rep_here << p.head_split) != p.n_q_heads / p.n_kv_heads ||
-            p.rep_variant < p.rep_here)
-            return hipErrorInvalidValue;
-        if (p.head_split == 1 && p.bits == 2 && p.rep_variant == 4) return launch_one<2, 4, 4, 2, 1>(p, stream);
-        if (p.head_split == 1 && p.bits == 4 && p.rep_variant == 4) return launch_one<4, 4, 2, 2, 1>(p, stream);
-        if (p.head_split == 1 && p.bits == 2 && p.rep_variant == 2) return launch_one<2, 2, 4, 2, 1>(p, stream);
-        if (p.head_split == 2 && p.bits == 2 && p.rep_variant == 2) return launch_one<2, 2, 4, 2, 2>(p, stream);
-        return hipErrorNotSupported;
-    }
     if (p.kg_shift > 0) {
         // G = 64 / 128: the instantiations that read one scale / zero-point pair per group
         with_variant(p.bits, p.rep_variant, [&](auto v) {
             using V = decltype(v);
             e = p.two_launches > 0 ? launch_two<V::bits, V::rep, V::slots, V::occ, true>(p, stream)
-                                   : launch_one<V::bits, V::rep, V::slots, V::occ, 0, true>(p, stream);
+                                   : launch_one<V::bits, V::rep, V::slots, V::occ, true>(p, stream);
         });
         return e;
     }
@@ -1749,16 +1676,18 @@ int wave_slices_resident(int bits, int rep) {
     int waves = 0;
     with_variant(bits, rep, [&](auto v) {
         using V = decltype(v);
-        if constexpr (V::rep <= 4) waves = 4 * resident_wave_unit_workgroups<V::bits, V::rep, V::occ, false, true>();
+        waves = 4 * resident_wave_unit_workgroups<V::bits, V::rep, V::occ, false, true>();
     });
     return waves;
 }
 
 MfmaGeometry mfma_geometry(int bits, int rep) {
-    MfmaGeometry g{0, 0};              // chunk_tiles 0: no matrix-core instantiation for this shape
-    with_variant(bits, rep, [&](auto v) {
+    MfmaGeometry g{0, 0};              // chunk_tiles 0: the matrix-core family has nothing for this shape
+    if (rep < 1 || rep > kMaxRep) return g;
+    with_variant(bits, std::min(rep, 2), [&](auto v) {
         using V = decltype(v);
-        g.chunk_tiles = 4 * V::slots;
+        // 3 or more heads (decode_tiles_kernel plans its work itself): the chunk is what plans are reported in
+        g.chunk_tiles = rep > 2 && bits == 4 ? 8 : 4 * V::slots;
         g.resident_workgroups = resident_workgroups<V::bits, V::rep, V::slots, V::occ>();
     });
     return g;

@@ -113,7 +113,7 @@ struct DecodeParams {
     const int32_t* seq_state;
     int32_t kg_shift;           // log2(G / 32): scales and zero-points are stored once per group (keys: row tile >> kg_shift;
                                 // values: 4 >> kg_shift entries per token); > 0 runs on instantiations of its own
-    int32_t head_groups;        // > 1: runs of rep_here (4 or 8) query heads per kv-head served as units of one launch (matrix-core family)
+    int32_t head_groups;        // decode_tiles_kernel: runs of rep_here query heads per kv-head, each a unit of its own (the last may be shorter)
     // Two-launch form, second launch as equally long slices of the unit-major axis of four-tile groups
     // (device arrays made by the host; null: not used): wave_desc[4 s] = {first unit, first group in it,
     // groups, 0} of slice s; unit_parts[2 u] = {first slice touching unit u, slices touching it}.
@@ -125,10 +125,11 @@ struct DecodeParams {
     // extra workgroups of the fp16-row launch instead of a launch of its own; null otherwise.
     const QuantKeyParams* flush_k;
     const QuantValueParams* flush_v;
-    // k > 0 (single launch, 4, 6 or 8 query heads per kv-head, small batches): every kv-head's query
-    // heads are served as 2^k equal parts, each a unit of its own on the instantiation for one part
-    // (rep_variant 2 or 4, rep_here = heads of a part); the cache is read once per part.
-    int32_t head_split;
+    int32_t part_stride;        // workspace rows (parts) per (batch, query head)
+    // decode_tiles_kernel: its first row_wgs workgroups hold the units' fp16 rows, row_split per unit; interval g of the axis of
+    // all-quantised steps (of one unit, cut into unit_wgs intervals; unit_wgs = 0: of all units) has axis_len
+    // steps, one more if g < axis_rem
+    int32_t row_wgs, row_split, unit_wgs, axis_len, axis_rem;
 };
 
 // launchers (each defined next to its kernels); they return hipGetLastError() after the launch
@@ -139,6 +140,12 @@ hipError_t launch_flush_quantize(const QuantKeyParams& kp, const QuantValueParam
 hipError_t launch_copy_rows(const CopyRowsParams& p, hipStream_t stream);
 hipError_t launch_decode_valu(const DecodeParams& p, hipStream_t stream);
 hipError_t launch_decode_mfma(const DecodeParams& p, hipStream_t stream);
+constexpr int kTilesMaxParts = 128;    // decode_tiles_kernel: parts of one (batch, kv-head, run of query heads) unit, at most
+// decode_tiles_kernel (kivi_decode_tiles.hip); with two_launches > 0 the fp16-row launch goes before it
+hipError_t launch_decode_tiles(DecodeParams p, hipStream_t stream);
+// workgroups the device holds of it for a batch of different lengths
+int tiles_resident_ragged(int bits, int rep);
+int tiles_max_parts(int bits, int rep);       // parts of one unit that it merges, at most
 hipError_t launch_residual_rows(const DecodeParams& p, hipStream_t stream);
 // the same launch with extra workgroups that quantise the key group(s) and value tokens of a residual
 // flush (G = 32 only: hipErrorNotSupported otherwise, nothing launched)

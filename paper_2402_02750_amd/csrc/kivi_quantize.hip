@@ -927,8 +927,7 @@ hipError_t launch_rows_and_flush(const DecodeParams& p, const QuantKeyParams& kp
     };
     if (rep == 1) go(std::integral_constant<int, 1>{});
     else if (rep == 2) go(std::integral_constant<int, 2>{});
-    else if (rep == 4) go(std::integral_constant<int, 4>{});
-    else go(std::integral_constant<int, 8>{});
+    else return hipErrorNotSupported;          // 3 or more heads: decode_tiles_kernel, the flush has a launch of its own
     return hipGetLastError();
 }
 

@@ -142,7 +142,7 @@ __device__ __forceinline__ void residual_rows_block(const DecodeParams& p, float
     }
     __builtin_amdgcn_wave_barrier();
     // outputs: lane (seg, row) accumulates channels seg*8.. over rows row + 4j, then the 4 row groups add up
-    const int row_stride = p.plan.n_splits();
+    const int row_stride = p.part_stride;
 #pragma unroll
     for (int hh = 0; hh < REP; ++hh) {
         float o[8];

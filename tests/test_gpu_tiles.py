@@ -1,0 +1,60 @@
+"""GPU parity of the matrix-core kernel for several query heads per kv-head, at the sizes where its split can
+go wrong: every column layout (2, 4 and 8 heads, with idle columns), partial steps, units cut among several
+workgroups, one and two launches, rows and values that end inside a tile, scales outside the ordinary range."""
+import numpy as np
+import pytest
+
+import gpu_harness as gh
+from paper_2402_02750_amd import kivi, workloads
+from paper_2402_02750_amd.workloads import CONFIGS, scaled
+
+pytestmark = pytest.mark.gpu
+
+# (query heads, kv-heads, batch, bits, G, policy, tokens, gain of the keys, gain of the values)
+W, A = kivi.KIVI_FLUSH_WINDOW, kivi.KIVI_FLUSH_ALG1
+CASES = [
+    (4, 2, 1, 2, 32, W, 33, 1, 1),          # one tile quantised at most, one step
+    (6, 2, 1, 4, 32, W, 128 + 32 * 5, 1, 1),    # 3 of 4 head slots, a step of one tile after a full one
+    (10, 2, 1, 2, 32, A, 777, 1, 1),        # 5 of 8 head slots; values end inside a tile
+    (9, 1, 2, 4, 64, W, 2000, 1, 1),        # 9 heads: two runs, the second with one head
+    (71, 1, 1, 2, 128, W, 1300, 1, 1),      # nine runs of a single kv-head
+    (8, 1, 1, 2, 32, W, 9000, 1, 1),        # one unit in many parts
+    (8, 2, 5, 4, 32, A, 2500, 1, 1),        # units cut at uneven places, K and V split differently
+    (32, 4, 40, 2, 32, W, 3300, 1, 1),      # two launches, eight heads
+    (16, 4, 60, 2, 32, W, 4200, 1, 1),      # two launches, four heads
+    (8, 2, 2, 2, 32, W, 900, 60, 1),        # key scales past 64
+    (16, 2, 2, 4, 32, A, 900, 60, 500),     # large value scales
+    (8, 2, 2, 2, 32, W, 900, 1, 2.0 ** -13),    # value scales among fp16's subnormals
+    (16, 2, 2, 4, 32, W, 900, 2.0 ** -10, 1),   # small key scales
+]
+
+
+@pytest.mark.parametrize("hq,hkv,batch,bits,group,policy,tokens,kgain,vgain", CASES)
+def test_tiles(hq, hkv, batch, bits, group, policy, tokens, kgain, vgain):
+    """Against the oracle and against the vector path.  Tolerance: probabilities and operands keep 21 bits or
+    more, fp32 sums of a few thousand terms lose at most 2^-24 of their largest term each; the logits (up to
+    about 50 here) carry 2^-20 of themselves into the probabilities: below 1e-4 of the largest value
+    together.  The vector path is held to the repository's tolerance on the same numbers."""
+    gh.require_gpu()
+    w = scaled(CONFIGS["mistral_gqa"], name="tiles", batch=batch, n_q_heads=hq, n_kv_heads=hkv, bits=bits, group=group,
+               residual=128, seed=31 * hq + bits)
+    print(f"case tiles hq={hq} hkv={hkv} B={batch} bits={bits} G={group} policy={policy} L={tokens} gains {kgain} {vgain}", flush=True)
+    k = (workloads.keys(w, tokens).astype(np.float32) * kgain).astype(np.float16)
+    v = (workloads.values(w, tokens).astype(np.float32) * vgain).astype(np.float16)
+    q = (workloads.queries(w).astype(np.float32) / max(1, kgain)).astype(np.float16)
+    heads = [(0, 0), (batch - 1, hkv - 1), (batch // 2, hkv // 2)]
+    oc = gh.oracle_cache_for_heads(w, k, v, heads, "window" if policy == W else "alg1")
+    ref = gh.oracle_attention_for_heads(w, oc, q, heads)
+    scale = float(np.abs(v.astype(np.float32)).max())
+    outs = {}
+    for path in (kivi.KIVI_DECODE_MFMA, kivi.KIVI_DECODE_MFMA_TWO, kivi.KIVI_DECODE_MFMA_ONE, kivi.KIVI_DECODE_VALU):
+        layout, cache = gh.gpu_prefill(w, k, v, policy, path)
+        outs[path] = gh.gpu_attention(layout, cache, q, w.softmax_scale)
+        got = gh.pick_heads(outs[path], w, heads)
+        if path == kivi.KIVI_DECODE_VALU or (hq == 2 * hkv and path == kivi.KIVI_DECODE_MFMA_TWO):
+            gh.check_close(got / scale, ref / scale, f"path {path}")
+        else:
+            err = np.abs(got - ref).max()
+            assert err <= 1e-4 * scale, f"path {path}: {err:.3e} against {1e-4 * scale:.3e}"
+    # all heads, not only the oracle's: the vector path serves the same cache in its own way
+    gh.check_close(outs[kivi.KIVI_DECODE_MFMA] / scale, outs[kivi.KIVI_DECODE_VALU] / scale, "all heads")
