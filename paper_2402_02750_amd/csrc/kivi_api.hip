@@ -856,19 +856,25 @@ int kivi_prefill(const kivi_layout_t* l, const void* k, int64_t ksb, int64_t ksh
     if (nkq > l->cap_q_tokens || nvq > l->cap_q_tokens || nkr > l->cap_r_tokens || nvr > l->cap_r_tokens)
         return KIVI_ERR_INVALID_ARG;
     hipStream_t hs = static_cast<hipStream_t>(stream);
-    if (nkq > 0) {
-        const RowSource src{static_cast<const __half*>(k), ksb, ksh, kst, 0, 0};
-        if (int s = enqueue_key_quant(l, c, src, nkq, hs)) return s;
-    }
-    if (nvq > 0) {
-        const RowSource src{static_cast<const __half*>(v), vsb, vsh, vst, 0, 0};
-        if (int s = enqueue_value_quant(l, c, src, nvq, hs)) return s;
-    }
+    const RowSource ksrc{static_cast<const __half*>(k), ksb, ksh, kst, 0, 0};
+    const RowSource vsrc{static_cast<const __half*>(v), vsb, vsh, vst, 0, 0};
     CopyRowsParams p{};
     p.cap_r = l->cap_r_tokens; p.n_kv_heads = l->n_kv_heads; p.batch = l->batch;
     p.job[0] = {static_cast<const __half*>(k), ksb, ksh, kst, nkq, static_cast<__half*>(c->k_resid), 0, nkr};
     p.job[1] = {static_cast<const __half*>(v), vsb, vsh, vst, nvq, static_cast<__half*>(c->v_resid), 0, nvr};
-    if (int s = hip_status(launch_copy_rows(p, hs))) return s;
+    const QuantKeyParams kp = key_quant_params(l, c, ksrc, nkq);
+    const QuantValueParams vp = value_quant_params(l, c, vsrc, nvq);
+    if (prefill_possible(kp, vp)) {
+        if (int s = hip_status(launch_prefill(kp, vp, p, hs))) return s;
+    } else {
+        if (nkq > 0) {
+            if (int s = enqueue_key_quant(l, c, ksrc, nkq, hs)) return s;
+        }
+        if (nvq > 0) {
+            if (int s = enqueue_value_quant(l, c, vsrc, nvq, hs)) return s;
+        }
+        if (int s = hip_status(launch_copy_rows(p, hs))) return s;
+    }
     c->n_kq = nkq; c->n_vq = nvq; c->n_kr = nkr; c->n_vr = nvr; c->k_r_start = 0; c->v_r_start = 0;
     return KIVI_OK;
 }

@@ -138,6 +138,9 @@ hipError_t launch_quantize_values(const QuantValueParams& p, hipStream_t stream)
 // key groups and value tokens of one residual flush in a single launch (either part may be empty)
 hipError_t launch_flush_quantize(const QuantKeyParams& kp, const QuantValueParams& vp, hipStream_t stream);
 hipError_t launch_copy_rows(const CopyRowsParams& p, hipStream_t stream);
+// keys, values and residual rows of a prompt in one launch, where the bulk forms serve both (whole tiles, G = 32)
+bool prefill_possible(const QuantKeyParams& kp, const QuantValueParams& vp);
+hipError_t launch_prefill(const QuantKeyParams& kp, const QuantValueParams& vp, const CopyRowsParams& cp, hipStream_t stream);
 hipError_t launch_decode_valu(const DecodeParams& p, hipStream_t stream);
 hipError_t launch_decode_mfma(const DecodeParams& p, hipStream_t stream);
 constexpr int kTilesMaxParts = 128;    // decode_tiles_kernel: parts of one (batch, kv-head, run of query heads) unit, at most

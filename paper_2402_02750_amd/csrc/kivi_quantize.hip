@@ -476,11 +476,10 @@ __device__ __forceinline__ float encode_fast16(_Float16 x, float y, float c0, fl
 // minimum and maximum.  A word of the packed tile (tokens t0 and t0 + 16, 8 or 4 consecutive
 // channels) is shared by 4 (B = 2) or 2 (B = 4) neighbouring lanes.
 template <int BITS>
-__global__ __launch_bounds__(256) void quantize_keys_stream_kernel(QuantKeyParams p) {
+__device__ __forceinline__ void quantize_keys_stream_block(const QuantKeyParams& p, int bx, int h, int b) {
     const int lane = threadIdx.x & 63;
-    const int g = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // group = tile
-    if (g >= p.n_tiles) return;                     // whole wavefronts leave; the kernel has no barrier
-    const int h = blockIdx.y, b = blockIdx.z;
+    const int g = bx * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // group = tile
+    if (g >= p.n_tiles) return;                     // whole wavefronts leave; there is no barrier
     const int64_t unit = (int64_t)b * p.n_kv_heads + h;
     constexpr float levels = (float)((1 << BITS) - 1);
     // (the row address stays wavefront-uniform and the lane adds a 32-bit offset: scalar address arithmetic)
@@ -577,11 +576,10 @@ __global__ __launch_bounds__(256) void quantize_keys_stream_kernel(QuantKeyParam
 // the quad derives the constants of tokens jj and jj + 4 and the others get them by quad broadcasts.
 // A word (8 tokens, channels c and c + 16) is shared by the lanes seg and seg ^ 2.
 template <int BITS>
-__global__ __launch_bounds__(256) void quantize_values_stream_kernel(QuantValueParams p) {
+__device__ __forceinline__ void quantize_values_stream_block(const QuantValueParams& p, int bx, int h, int b) {
     const int lane = threadIdx.x & 63;
-    const int ti = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    if (ti >= p.n_tokens / kTileTokens) return;     // whole wavefronts leave; the kernel has no barrier
-    const int h = blockIdx.y, b = blockIdx.z;
+    const int ti = bx * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (ti >= p.n_tokens / kTileTokens) return;     // whole wavefronts leave; there is no barrier
     const int64_t unit = (int64_t)b * p.n_kv_heads + h;
     constexpr float levels = (float)((1 << BITS) - 1);
     const int dst_tile = p.first_token / kTileTokens + ti;
@@ -741,6 +739,15 @@ __global__ __launch_bounds__(256) void quantize_values_stream_kernel(QuantValueP
         }
 }
 
+template <int BITS>
+__global__ __launch_bounds__(256) void quantize_keys_stream_kernel(QuantKeyParams p) {
+    quantize_keys_stream_block<BITS>(p, blockIdx.x, blockIdx.y, blockIdx.z);
+}
+template <int BITS>
+__global__ __launch_bounds__(256) void quantize_values_stream_kernel(QuantValueParams p) {
+    quantize_values_stream_block<BITS>(p, blockIdx.x, blockIdx.y, blockIdx.z);
+}
+
 template <int BITS, int TG>
 __global__ __launch_bounds__(256) void quantize_keys_kernel(QuantKeyParams p) {
     quantize_key_block<BITS, TG>(p, blockIdx.x, blockIdx.y, blockIdx.z, threadIdx.x);
@@ -782,13 +789,12 @@ __global__ __launch_bounds__(1024) void rows_flush_kernel(DecodeParams p, QuantK
     else quantize_value_block<BITS>(vp, r - n_key_blocks, h, b, threadIdx.x);
 }
 
-__global__ __launch_bounds__(256) void copy_rows_kernel(CopyRowsParams p) {
-    // one thread moves 16 bytes; blockIdx.x covers job 0's rows, then job 1's
+__device__ __forceinline__ void copy_rows_block(const CopyRowsParams& p, int bx, int h, int b) {
+    // one thread moves 16 bytes; bx covers job 0's rows, then job 1's
     const int blocks0 = (p.job[0].n_tokens * 16 + 255) / 256;
-    const int which = (int)blockIdx.x >= blocks0 ? 1 : 0;
+    const int which = bx >= blocks0 ? 1 : 0;
     const CopyRowsParams::Job& j = p.job[which];
-    const int i = ((int)blockIdx.x - (which ? blocks0 : 0)) * 256 + (int)threadIdx.x;
-    const int h = blockIdx.y, b = blockIdx.z;
+    const int i = (bx - (which ? blocks0 : 0)) * 256 + (int)threadIdx.x;
     if (i >= j.n_tokens * 16) return;
     const int t = i >> 4, seg = i & 15;
     const __half* src = j.src + (int64_t)b * j.stride_b + (int64_t)h * j.stride_h
@@ -796,6 +802,24 @@ __global__ __launch_bounds__(256) void copy_rows_kernel(CopyRowsParams p) {
     const int slot = (j.dst_slot0 + t) % p.cap_r;
     __half* dst = j.dst + (((int64_t)b * p.n_kv_heads + h) * p.cap_r + slot) * kHeadDim + seg * 8;
     *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
+}
+__global__ __launch_bounds__(256) void copy_rows_kernel(CopyRowsParams p) { copy_rows_block(p, blockIdx.x, blockIdx.y, blockIdx.z); }
+
+// A prompt's keys, values and residual rows in one launch: along x the copies of the residual rows, then key and
+// value blocks in turn.  As three launches a short prompt is three serial chains of memory round trips of 4-16 us
+// each with most of the chip idle; together they overlap (8 kv-heads, batch 1, 16 001 tokens, 4 bits: 31.3 -> 23.9 us;
+// 300 tokens, 2 bits: 14.3 -> 9.3 us).
+template <int BITS>
+__global__ __launch_bounds__(256) void prefill_kernel(QuantKeyParams kp, QuantValueParams vp, CopyRowsParams cp, int n_copy, int n_key, int n_value) {
+    const int bx = (int)blockIdx.x - n_copy, pairs = 2 * min(n_key, n_value);
+    if (bx < 0) {
+        copy_rows_block(cp, blockIdx.x, blockIdx.y, blockIdx.z);
+        return;
+    }
+    const bool values = bx < pairs ? bx & 1 : n_value > n_key;
+    const int i = bx < pairs ? bx >> 1 : bx - pairs / 2;
+    if (values) quantize_values_stream_block<BITS>(vp, i, blockIdx.y, blockIdx.z);
+    else quantize_keys_stream_block<BITS>(kp, i, blockIdx.y, blockIdx.z);
 }
 
 // Measurement yardstick: plain read-only stream.  Every workgroup reads one contiguous 64 KB piece
@@ -856,6 +880,14 @@ hipError_t launch_quantize_keys(const QuantKeyParams& p, hipStream_t stream) {
     return p.bits == 2 ? launch_keys_bits<2>(p, stream) : launch_keys_bits<4>(p, stream);
 }
 
+// what is left of a run of values after its first n tokens
+QuantValueParams values_after(QuantValueParams p, int n) {
+    p.src.base += (int64_t)n * p.src.stride_t;
+    p.first_token += n;
+    p.n_tokens -= n;
+    return p;
+}
+
 hipError_t launch_quantize_values(const QuantValueParams& p_in, hipStream_t stream) {
     if (p_in.n_tokens <= 0) return hipSuccess;
     QuantValueParams p = p_in;
@@ -868,9 +900,7 @@ hipError_t launch_quantize_values(const QuantValueParams& p_in, hipStream_t stre
         if (p.bits == 2) quantize_values_stream_kernel<2><<<grid, block, 0, stream>>>(pw);
         else quantize_values_stream_kernel<4><<<grid, block, 0, stream>>>(pw);
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-        p.src.base += (int64_t)pw.n_tokens * p.src.stride_t;
-        p.first_token += pw.n_tokens;
-        p.n_tokens -= pw.n_tokens;
+        p = values_after(p, pw.n_tokens);
         if (p.n_tokens == 0) return hipSuccess;
     }
     const int first_tile = p.first_token / kTileTokens;
@@ -879,6 +909,27 @@ hipError_t launch_quantize_values(const QuantValueParams& p_in, hipStream_t stre
     if (p.bits == 2) quantize_values_kernel<2><<<grid, block, 0, stream>>>(p);
     else quantize_values_kernel<4><<<grid, block, 0, stream>>>(p);
     return hipGetLastError();
+}
+
+// Up to 16383 key tiles: a longer prompt is bound by HBM, and its keys are better off in a launch of their own with
+// the eight wavefronts per SIMD that their registers allow (beside the values there are five).  2 bits: 256 units of 62
+// tiles 74.5 us in three launches, 69.6 in one; 128 units of 246 tiles 127.9 against 134.8; 512 units of 124 tiles 256.9
+// against 268.7, and 260.0 with the copies beside the values and the keys alone.
+bool prefill_possible(const QuantKeyParams& kp, const QuantValueParams& vp) {
+    return kp.n_tiles > 0 && (int64_t)kp.n_tiles * kp.n_kv_heads * kp.batch < 16384 && kp.src.ring_cap == 0 && kp.tiles_per_group == 1 && vp.n_tokens >= kTileTokens &&
+           vp.first_token % kTileTokens == 0 && vp.src.ring_cap == 0 && vp.group_blocks == 1;
+}
+
+hipError_t launch_prefill(const QuantKeyParams& kp, const QuantValueParams& vp, const CopyRowsParams& cp, hipStream_t stream) {
+    if (!prefill_possible(kp, vp) || kp.bits != vp.bits) return hipErrorInvalidValue;
+    const int n_copy = (cp.job[0].n_tokens * 16 + 255) / 256 + (cp.job[1].n_tokens * 16 + 255) / 256;
+    const int n_key = (kp.n_tiles + 3) / 4, n_value = (vp.n_tokens / kTileTokens + 3) / 4;      // (the kernel counts whole value tiles only)
+    const dim3 grid(n_copy + n_key + n_value, kp.n_kv_heads, kp.batch), block(256);
+    if (kp.bits == 2) prefill_kernel<2><<<grid, block, 0, stream>>>(kp, vp, cp, n_copy, n_key, n_value);
+    else prefill_kernel<4><<<grid, block, 0, stream>>>(kp, vp, cp, n_copy, n_key, n_value);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    // the values of a last, partly filled tile go the general way
+    return launch_quantize_values(values_after(vp, vp.n_tokens / kTileTokens * kTileTokens), stream);
 }
 
 template <int BITS>
