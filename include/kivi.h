@@ -261,7 +261,8 @@ int kivi_decode_attention_static(const kivi_layout_t* layout, const kivi_cache_t
  * kivi_decode_attention.  On steps where nothing is flushed and the matrix-core family runs, the
  * append costs no launch of its own: the attention (one launch or two, see
  * kivi_decode_plan) reads the new token's rows from k_new / v_new and writes them into the
- * residual rings itself.  On the other steps it enqueues the separate kernels.
+ * residual rings itself.  A flush is a launch of its own before it, or, with one or two query heads per
+ * kv-head and G = 32, part of the fp16-row launch of the two-launch form, which such steps then take.
  *   k_new, v_new   device, fp16 [b][n_kv_heads][128]; they must stay valid until the launch has run
  *   other arguments as for kivi_decode_attention / kivi_flush_residual
  * Errors: INVALID_ARG (also: a ring is full, no capacity left for the flush), UNSUPPORTED,

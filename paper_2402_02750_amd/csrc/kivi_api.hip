@@ -243,7 +243,12 @@ int decode_family(const kivi_layout_t* l) {
 //      the line is where it was when the fp16 rows were 40 % of such a launch).
 //  (4) 3 or 4 heads: 512 units on (context 4000, 2 bits: 64 against 80 us; context 1000: 36 against 39); even at
 //      384 units and context 4000 (54.0 / 53.2 us), one launch 20 % faster below (23 against 34 us at context 1000).
-bool wants_two_launches(const kivi_layout_t* l, const kivi_cache_t* c, int path) {
+// `flush`: the step also flushes and the fp16-row launch could carry that out (G = 32).
+//  (0) One or two heads: a flush has to end before the launch that reads its tiles, so the single-launch form takes
+//      two launches as well, the first of them nearly empty.  Riding with the fp16 rows it costs nothing of its own:
+//      one head, context 4096, batch 1 / 4 / 8 / 16: 17.7 -> 16.7, 27.9 -> 22.2, 36.9 -> 31.4, 50.3 -> 48.9 us; 4 units,
+//      context 1024: 14.0 either way; two heads, 256 units: 41.0 -> 35.4 us.
+bool wants_two_launches(const kivi_layout_t* l, const kivi_cache_t* c, int path, bool flush = false) {
     if (path != KIVI_DECODE_MFMA || l->decode_path == KIVI_DECODE_MFMA_ONE) return false;
     const int rep_launch = std::min(l->n_q_heads / l->n_kv_heads, kMaxRep);
     const int rep_variant = rep_launch <= 2 ? rep_launch : (rep_launch <= 4 ? 4 : 8);
@@ -253,6 +258,7 @@ bool wants_two_launches(const kivi_layout_t* l, const kivi_cache_t* c, int path)
                           residual_rows_possible(tiles_b, rep_variant);
     if (!possible) return false;
     if (l->decode_path == KIVI_DECODE_MFMA_TWO) return true;
+    if (flush && rep_variant <= 2) return true;                                                      // (0)
     const int64_t units = (int64_t)l->batch * l->n_kv_heads;
     const int64_t work = units * tiles_total, row_work = units * tiles_b;
     if (rep_variant == 8) return tiles_b >= 2 && work >= 4000 && row_work >= 384;                    // (3)
@@ -337,7 +343,7 @@ int enqueue_attention(const kivi_layout_t* l, const kivi_cache_t* c, const void*
     const int path = decode_family(l);
     if ((k_new || v_new) && path != KIVI_DECODE_MFMA) return KIVI_ERR_UNSUPPORTED;
     p.k_new = static_cast<const __half*>(k_new); p.v_new = static_cast<const __half*>(v_new);
-    const bool two = wants_two_launches(l, c, path);
+    const bool two = wants_two_launches(l, c, path, flush_k || flush_v);
     p.plan = plan_splits(l, c, path == KIVI_DECODE_MFMA, two);
     p.two_launches = two ? 1 : 0;
     p.head_groups = wide_group_runs(l, path, two);
@@ -347,7 +353,7 @@ int enqueue_attention(const kivi_layout_t* l, const kivi_cache_t* c, const void*
     const size_t rows = (size_t)l->batch * l->n_q_heads * p.plan.n_splits();
     if (counter_bytes(l) + rows * (kHeadDim + 2) * sizeof(float) > workspace_bytes) return KIVI_ERR_WORKSPACE;
     p.counters = static_cast<int32_t*>(workspace);
-    const bool tiles = path == KIVI_DECODE_MFMA && uses_tiles(l);
+    const bool tiles = path == KIVI_DECODE_MFMA && uses_tiles(l) && !flush_k;
     p.part_stride = p.plan.n_splits();
     if (tiles) p.part_stride = part_rows(l, workspace_bytes - counter_bytes(l));
     p.part_o = reinterpret_cast<float*>(static_cast<char*>(workspace) + counter_bytes(l));
@@ -938,9 +944,9 @@ int kivi_decode_step(const kivi_layout_t* l, kivi_cache_t* c, const void* k_new,
         after = flushed;
         after.n_kr += 1;
         after.n_vr += 1;
-        // In the two-launch form (G = 32) the fp16-row launch quantises the flushed tokens with extra
-        // workgroups: a flush step then takes two launches like any other step.
-        if ((nk > 0 || nv > 0) && l->group == kTileTokens && !uses_tiles(l) && wants_two_launches(l, &after, KIVI_DECODE_MFMA)) {
+        // With one or two query heads per kv-head (G = 32) the fp16-row launch of the two-launch form quantises the
+        // flushed tokens with extra workgroups: a flush step takes two launches in all.
+        if ((nk > 0 || nv > 0) && l->group == kTileTokens && l->n_q_heads <= 2 * l->n_kv_heads && wants_two_launches(l, &after, KIVI_DECODE_MFMA, true)) {
             const int64_t sh = (int64_t)l->cap_r_tokens * kHeadDim, sb = sh * l->n_kv_heads;
             const RowSource ksrc{static_cast<const __half*>(c->k_resid), sb, sh, kHeadDim, c->k_r_start, l->cap_r_tokens};
             const RowSource vsrc{static_cast<const __half*>(c->v_resid), sb, sh, kHeadDim, c->v_r_start, l->cap_r_tokens};

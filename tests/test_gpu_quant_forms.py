@@ -78,3 +78,33 @@ def test_flush(batch, heads, group, bits):
     torch.cuda.synchronize()
     assert flushes == 4
     assert _bytes(stepped, PACKED) == _bytes(whole, PACKED)
+
+
+@pytest.mark.parametrize("batch,hq,hkv,tokens,residual,bits", [
+    (1, 4, 4, 63, 32, 2),           # the first flush: nothing was quantised before
+    (1, 4, 2, 1023, 32, 4),         # two heads per kv-head, few units
+    (2, 3, 3, 4095, 128, 2),
+    (1, 2, 1, 1024 + 479 + 32, 480, 2),     # fifteen tiles of fp16 rows after the flush
+    (40, 16, 8, 1023, 128, 4),      # more units than the two-head tile kernel serves
+])
+def test_flush_step(batch, hq, hkv, tokens, residual, bits):
+    """A step that flushes: the automatic choice carries the flush out in the fp16-row launch, the single-launch form
+    before it.  Cache arrays equal byte for byte; outputs as far apart as two launch forms of one attention."""
+    torch = gh.require_gpu()
+    print(f"case flush step B={batch} heads {hq}/{hkv} L={tokens} R={residual} bits={bits}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(tokens + bits)
+    k, v = (torch.randn(batch, hkv, tokens + 1, 128, dtype=torch.float16, device="cuda", generator=gen) for _ in range(2))
+    q = torch.randn(batch, hq, 128, dtype=torch.float16, device="cuda", generator=gen)
+    caches, outs = [], []
+    for path in (kivi.KIVI_DECODE_AUTO, kivi.KIVI_DECODE_MFMA_ONE):
+        layout = kivi.make_layout(batch, hq, hkv, bits, residual, gh.round_up(tokens + 1, 32), gh.round_up(residual + 32, 32), decode_path=path)
+        cache, out = _zeroed(layout), torch.empty(batch, hq, 128, dtype=torch.float32, device="cuda")
+        kivi.kivi_prefill(layout, k, v, tokens, cache, W)
+        before = cache.c.n_kq
+        kivi.kivi_decode_step(layout, cache, k[:, :, tokens].contiguous(), v[:, :, tokens].contiguous(), q, 128 ** -0.5, out, W)
+        torch.cuda.synchronize()
+        assert cache.c.n_kq == before + 32
+        caches.append(cache)
+        outs.append(out.cpu().numpy())
+    assert _bytes(caches[0], PACKED + ("k_resid", "v_resid")) == _bytes(caches[1], PACKED + ("k_resid", "v_resid"))
+    gh.check_close(outs[0], outs[1], "two launches against one")
