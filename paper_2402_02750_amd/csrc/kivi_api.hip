@@ -2,6 +2,7 @@
 // No allocation, no synchronisation; the only state kept between calls is, per device, the address
 // of the static scratch array below (and the occupancy answers next to the decode kernels).
 #include "kivi_internal.h"
+#include "kivi_tiles_plan.h"
 
 #include <algorithm>
 #include <vector>
@@ -521,42 +522,25 @@ int ragged_attention_fast(const kivi_layout_t* l, const kivi_cache_t* c, const k
     const bool tiles = rep_total >= 3;
     if (tiles) {
         // decode_tiles_kernel: the unit-major axis of four-tile steps (at least one per unit) in equal
-        // intervals, one per resident workgroup.  Table: {first unit, first step in it, steps, 0} per
-        // workgroup, then the steps before each sequence.
-        total = 0;
-        for (int b = 0; b < l->batch; ++b) total += (int64_t)std::max(1, ceil_div(st[b].n_kq / kTileTokens, 4)) * l->n_kv_heads;
-        if (total > 0x3fffffff) return kNotApplicable;
-        const int stride = std::min(part_rows(l, workspace_bytes > parts_offset ? workspace_bytes - parts_offset : 0), tiles_max_parts(l->bits, rep_launch));
-        int64_t wgs = std::min<int64_t>(std::min(tiles_resident_ragged(l->bits, rep_launch), kMaxSlices), total);
-        // no more parts of a unit than there are rows: an interval of c steps cuts n steps into at most (n - 1) / c + 2 parts
-        const int max_steps = std::max(1, ceil_div(max_tiles_a, 4));
-        if (stride < 4) return kNotApplicable;
-        wgs = std::max<int64_t>(1, std::min(wgs, total * (stride - 3) / max_steps));
-        if ((size_t)wgs * 16 + (size_t)l->batch * 4 > slice_table_bytes(l)) return kNotApplicable;
-        tables.resize(state_ints + (size_t)wgs * 4 + l->batch, 0);
-        int32_t* desc = tables.data() + state_ints;
-        int32_t* before = desc + (size_t)wgs * 4;
-        p.axis_len = (int32_t)(total / wgs);
-        p.axis_rem = (int32_t)(total % wgs);
-        auto wg_start = [&](int64_t x) { return x * p.axis_len + std::min<int64_t>(x, p.axis_rem); };
-        int64_t cum = 0, g = 0;
+        // intervals, one per resident workgroup, as far as the units' parts fit (kivi_tiles_plan.h).  (The table fits
+        // where the slices' would: at most kMaxSlices entries, and 4 bytes per sequence instead of 8 per unit.)
+        static thread_local std::vector<int32_t> steps;
+        steps.resize((size_t)l->batch);
+        int64_t all = 0;
         for (int b = 0; b < l->batch; ++b) {
-            const int64_t steps = std::max(1, ceil_div(st[b].n_kq / kTileTokens, 4)), end = cum + steps * l->n_kv_heads;
-            before[b] = (int32_t)cum;
-            for (; g < wgs; ++g) {
-                const int64_t begin = wg_start(g);
-                if (begin >= end) break;
-                desc[4 * g + 0] = (int32_t)((int64_t)b * l->n_kv_heads + (begin - cum) / steps);
-                desc[4 * g + 1] = (int32_t)((begin - cum) % steps);
-                desc[4 * g + 2] = (int32_t)(wg_start(g + 1) - begin);
-                desc[4 * g + 3] = 0;
-            }
-            cum = end;
+            steps[(size_t)b] = std::max(1, ceil_div(st[b].n_kq / kTileTokens, kStepTiles));
+            all += (int64_t)steps[(size_t)b] * l->n_kv_heads;
         }
+        if (all > 0x3fffffff) return kNotApplicable;
+        const int stride = std::min(part_rows(l, workspace_bytes > parts_offset ? workspace_bytes - parts_offset : 0), tiles_max_parts(l->bits, rep_launch));
+        if (stride < 2) return KIVI_ERR_WORKSPACE;
+        const RaggedCut cut = cut_ragged(steps, l->n_kv_heads, std::min(tiles_resident_ragged(l->bits, rep_launch), kMaxSlices), stride, tables);
+        p.axis_len = cut.axis.len;
+        p.axis_rem = cut.axis.rem;
+        p.unit_wgs = cut.whole_units ? 1 : 0;
         p.wave_desc = dev_state + state_ints;
-        p.unit_parts = p.wave_desc + (size_t)wgs * 4;
-        p.n_slices = (int32_t)wgs;
-        p.total_cost = total;
+        p.unit_parts = p.wave_desc + (size_t)cut.workgroups * RaggedCut::kWords;
+        p.n_slices = (int32_t)cut.workgroups;
         p.part_stride = stride;
     } else if (slice_waves > 0 && units < slice_waves && units <= kMaxSliceUnits && wasted >= 14000) {
         const int n_slices = (int)std::min<int64_t>(std::min(slice_waves, kMaxSlices), total);

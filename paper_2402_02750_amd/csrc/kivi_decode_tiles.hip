@@ -56,6 +56,7 @@
 // bits 8e-6 of the output (there 1e-4: codes are placed high in the mantissa here, and the matrix unit aligns
 // products by their nominal exponent).
 #include "kivi_internal.h"
+#include "kivi_tiles_plan.h"
 
 #include <hip/hip_fp16.h>
 
@@ -199,7 +200,7 @@ __device__ __forceinline__ half8 value_fragment(const uint32_t* w, int pair, int
     return f.h;
 }
 
-constexpr int kWaves = 4;                      // wavefronts per workgroup
+constexpr int kWaves = kStepTiles;             // wavefronts per workgroup
 constexpr int kLdsBytes = 160 * 1024 / 3 / 1280 * 1280;    // three workgroups per compute unit (LDS is given out in pieces of 1280 bytes)
 // parts of one unit, at most (their statistics meet in LDS)
 constexpr int max_parts_of(int bits, int hp) { return bits == 4 && hp == 8 ? kTilesMaxParts / 2 : kTilesMaxParts; }
@@ -256,14 +257,10 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
     const int tiles_b = kRagged ? 0 : p.plan.tiles_total - tiles_a_plan;
     const int n_row_wgs = p.row_wgs;                                   // the first workgroups: fp16 rows, row_split per unit
     const int wg = (int)blockIdx.x - n_row_wgs;
-    // interval g of an axis: axis_len steps, one more for the first axis_rem.  The axis is one unit, cut into
-    // unit_wgs intervals (workgroup = unit * unit_wgs + interval), or, with unit_wgs = 0, all units one after the other.
-    const int axis_len = p.axis_len, axis_rem = p.axis_rem, unit_wgs = p.unit_wgs;
-    auto wg_start = [&](int g) -> int { return g * axis_len + min(g, axis_rem); };
-    auto owner = [&](int pos) -> int {
-        const int cut = axis_rem * (axis_len + 1);
-        return pos < cut ? (int)((uint32_t)pos / (uint32_t)(axis_len + 1)) : axis_rem + (int)((uint32_t)(pos - cut) / (uint32_t)axis_len);
-    };
+    // The axis is one unit, cut into unit_wgs intervals (workgroup = unit * unit_wgs + interval), or, with unit_wgs = 0,
+    // all units one after the other.  kQuantisedRagged: always all units; unit_wgs = 1: no unit is cut.
+    const StepAxis axis{p.axis_len, p.axis_rem};
+    const int unit_wgs = p.unit_wgs;
     // steps of a unit, and where they begin on the axis
     auto steps_of = [&](int u) -> int {
         if constexpr (kRagged) return max((table(p.seq_state, 4 * batch_of(u)) / kTileTokens + kWaves - 1) / kWaves, 1);
@@ -838,12 +835,12 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
         const int live = live_heads(u);
         int parts = 0, mine = 0;
         const int steps = steps_of(u);
-        if (!kRagged && unit_wgs > 0) {
+        if (unit_wgs > 0) {
             parts = unit_wgs;
             mine = wg - u * unit_wgs;
         } else if (steps > 0) {
-            const int at = axis_start(u), g0 = owner(at);
-            parts = owner(at + steps - 1) - g0 + 1;
+            const int at = axis_start(u), g0 = axis.owner(at);
+            parts = axis.owner(at + steps - 1) - g0 + 1;
             mine = wg - g0;
         }
         if (tiles_b > 0) {
@@ -1087,13 +1084,13 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
     } else if (unit_wgs > 0) {
         u = wg / unit_wgs;
         const int g = wg - u * unit_wgs;
-        first = wg_start(g);
-        left = wg_start(g + 1) - first;
+        first = axis.start(g);
+        left = axis.start(g + 1) - first;
     } else {
-        const int pos0 = wg_start(wg);
+        const int pos0 = axis.start(wg);
         u = pos0 / n_a;
         first = pos0 - u * n_a;
-        left = wg_start(wg + 1) - pos0;
+        left = axis.start(wg + 1) - pos0;
     }
     copy_query(u, 0);
     // cursor of the next tile to copy: the interval's steps, unit by unit

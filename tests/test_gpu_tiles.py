@@ -1,6 +1,7 @@
 """GPU parity of the matrix-core kernel for several query heads per kv-head, at the sizes where its split can
 go wrong: every column layout (2, 4 and 8 heads, with idle columns), partial steps, units cut among several
-workgroups, one and two launches, rows and values that end inside a tile, scales outside the ordinary range."""
+workgroups, one and two launches, rows and values that end inside a tile, scales outside the ordinary range, sequences
+of different lengths."""
 import numpy as np
 import pytest
 
@@ -58,3 +59,66 @@ def test_tiles(hq, hkv, batch, bits, group, policy, tokens, kgain, vgain):
             assert err <= 1e-4 * scale, f"path {path}: {err:.3e} against {1e-4 * scale:.3e}"
     # all heads, not only the oracle's: the vector path serves the same cache in its own way
     gh.check_close(outs[kivi.KIVI_DECODE_MFMA] / scale, outs[kivi.KIVI_DECODE_VALU] / scale, "all heads")
+
+
+# (query heads, kv-heads, bits, tokens of every sequence)
+RAGGED_CASES = [
+    (32, 8, 2, [20000]),                        # 157 steps per unit, more than there are rows for parts
+    (64, 8, 4, [10000]),                        # the same with the smaller limit of eight heads at 4 bits
+    (28, 4, 4, [2600, 2600, 2600, 12800]),      # seven heads, a long sequence last: its units meet the shorter intervals
+    (8, 2, 2, [25600, 2000, 2000]),             # ... first
+    (12, 4, 4, [700, 40, 4000, 1]),             # three heads; sequences without quantised tokens
+    (16, 4, 4, [33, 5000, 129]),                # four heads, last steps of one, two and four tiles
+    (10, 1, 2, [900, 900, 15000]),              # ten heads of one kv-head: two pairs of launches
+]
+
+
+@pytest.mark.parametrize("hq,hkv,bits,tokens", RAGGED_CASES)
+def test_tiles_ragged(hq, hkv, bits, tokens):
+    """Sequences of different lengths: a decoding step and an attention call against the oracle (tolerance as in
+    test_tiles) and, all heads, against the vector path; nothing is written past the workspace."""
+    torch = gh.require_gpu()
+    batch, total = len(tokens), max(tokens) + 1
+    w = scaled(CONFIGS["mistral_gqa"], name="tilesragged", batch=batch, n_q_heads=hq, n_kv_heads=hkv, bits=bits, residual=64,
+               seed=77 * hq + bits)
+    print(f"case tiles ragged hq={hq} hkv={hkv} bits={bits} L={tokens}", flush=True)
+    k, v = workloads.keys(w, total), workloads.values(w, total)
+    kt, vt = torch.from_numpy(k).cuda(), torch.from_numpy(v).cuda()
+    heads = sorted({0, hkv // 2, hkv - 1})
+    scale = float(np.abs(v.astype(np.float32)).max())
+    outs = {}
+    for path in (kivi.KIVI_DECODE_MFMA, kivi.KIVI_DECODE_VALU):
+        layout = kivi.make_layout(batch, hq, hkv, bits, w.residual, gh.round_up(total, 32), 128, decode_path=path)
+        cache = kivi.Cache(layout)
+        size = cache.workspace.numel()
+        room = torch.full((size + 65536,), 0x5A, dtype=torch.uint8, device="cuda")
+        cache.workspace = room[:size].zero_()
+        states = kivi.make_states(batch)
+        for b, n in enumerate(tokens):
+            part = kivi.CacheSlice(cache, b, 1)
+            kivi.kivi_prefill(part.layout, kt[b:b + 1], vt[b:b + 1], n, part)
+            states[b] = part.state()
+        new = [torch.stack([x[b, :, n] for b, n in enumerate(tokens)]).contiguous() for x in (kt, vt)]
+        results = []
+        for step in (0, 1):
+            out = torch.full((batch, hq, 128), float("nan"), dtype=torch.float32, device="cuda")
+            q = torch.from_numpy(workloads.queries(w, step)).cuda()
+            if step == 0:
+                kivi.kivi_decode_step_ragged(layout, cache, states, *new, q, w.softmax_scale, out)
+            else:
+                kivi.kivi_decode_attention_ragged(layout, cache, states, q, w.softmax_scale, out)
+            torch.cuda.synchronize()
+            results.append(out.cpu().numpy())
+        assert (room[size:] == 0x5A).all()
+        outs[path] = results
+    got, other = outs[kivi.KIVI_DECODE_MFMA], outs[kivi.KIVI_DECODE_VALU]
+    for step in (0, 1):
+        gh.check_close(got[step] / scale, other[step] / scale, f"step {step}, all heads")
+        q = workloads.queries(w, step)
+        for b, n in enumerate(tokens):
+            at = [(b, h) for h in heads]
+            oc = gh.oracle_cache_for_heads(w, k[:, :, :n], v[:, :, :n], at, "window")
+            oc.append(np.stack([k[b, h, n] for b, h in at])[:, None], np.stack([v[b, h, n] for b, h in at])[:, None])
+            ref = gh.oracle_attention_for_heads(w, oc, q, at)
+            err = np.abs(gh.pick_heads(got[step], w, at) - ref).max()
+            assert err <= 1e-4 * scale, f"step {step} sequence {b}: {err:.3e} against {1e-4 * scale:.3e}"

@@ -1,0 +1,110 @@
+"""How the grouped-query decode kernel's work is cut (csrc/kivi_tiles_plan.h), compiled for the host and checked without
+a device: every step is somebody's, and no unit has more parts than the workspace has rows and the kernel merges."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+SOURCE = r"""
+#include "kivi_tiles_plan.h"
+using namespace kivi;
+namespace {
+std::vector<int32_t> table, parts, done;
+// 0, or what is wrong with the cut of `steps`; most: the most parts a unit has
+int check(const std::vector<int32_t>& steps, int heads, int max_wgs, int rows, int* most) {
+    table.clear();
+    const RaggedCut cut = cut_ragged(steps, heads, max_wgs, rows, table);
+    const int units = (int)steps.size() * heads, wgs = (int)cut.workgroups;
+    if (wgs < 1 || wgs > max_wgs || table.size() != (size_t)wgs * 4 + steps.size()) return 1;
+    const int32_t* before = table.data() + (size_t)wgs * 4;
+    auto axis_start = [&](int u) { return before[u / heads] + u % heads * steps[u / heads]; };
+    auto first_of = [&](int u) { return cut.axis.owner(axis_start(u)); };
+    auto parts_of = [&](int u) { return cut.whole_units ? 1 : cut.axis.owner(axis_start(u) + steps[u / heads] - 1) - first_of(u) + 1; };
+    parts.assign(units, 0);
+    done.assign(units, 0);
+    for (int g = 0; g < wgs; ++g) {                     // as the kernel walks its interval
+        int u = table[4 * g], first = table[4 * g + 1], left = table[4 * g + 2];
+        if (left < 1) return 2;
+        for (; left > 0; ++u, first = 0) {
+            if (u >= units || first != done[u]) return 3;
+            const int n = std::min(steps[u / heads] - first, left);
+            if (n < 1) return 4;
+            done[u] += n;
+            left -= n;
+            const int mine = cut.whole_units ? 0 : g - first_of(u);
+            if (mine != parts[u]) return 5;              // its row among the unit's parts
+            ++parts[u];
+        }
+    }
+    for (int u = 0; u < units; ++u) {
+        if (done[u] != steps[u / heads]) return 6;
+        if (parts[u] != parts_of(u)) return 7;           // what the merge waits for
+        if (parts[u] > rows - 1) return 8;               // (row 0 belongs to the fp16 rows)
+        *most = std::max(*most, parts[u]);
+    }
+    return 0;
+}
+}
+extern "C" int check_equal(int n, int sequences, int heads, int max_wgs, int rows, int* most) {
+    return check(std::vector<int32_t>(sequences, n), heads, max_wgs, rows, most);
+}
+extern "C" int check_steps(const int32_t* steps, int sequences, int heads, int max_wgs, int rows, int* most) {
+    return check(std::vector<int32_t>(steps, steps + sequences), heads, max_wgs, rows, most);
+}
+extern "C" int check_range(int n_max, int units_max, int max_wgs, int rows, int* at) {
+    for (int n = 1; n <= n_max; ++n)
+        for (int units = 1; units <= units_max; ++units) {
+            int most = 0;
+            if (const int e = check(std::vector<int32_t>(1, n), units, max_wgs, rows, &most)) { at[0] = n; at[1] = units; return e; }
+        }
+    return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("tiles_plan")
+    src, lib = d / "plan.cpp", d / "plan.so"
+    src.write_text(SOURCE)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I",
+                    os.path.join(ROOT, "paper_2402_02750_amd", "csrc"), str(src), "-o", str(lib)], check=True)
+    return ctypes.CDLL(str(lib))
+
+
+# workgroups at once: a device with a few compute units, two or three workgroups on each of 256, the table's limit
+RESIDENT = (5, 64, 256, 512, 768, 4096)
+
+
+@pytest.mark.parametrize("rows", [2, 4, 6, 38, 64, 128])
+def test_ragged_cut(plan, rows):
+    """Sequences of 1 to 300 steps (up to 38 400 tokens), 1 to 16 units."""
+    at = (ctypes.c_int * 2)()
+    for wgs in RESIDENT:
+        error = plan.check_range(300, 16, wgs, rows, at)
+        assert error == 0, f"check {error}: {at[0]} steps, {at[1]} units, {wgs} workgroups, {rows} rows"
+
+
+@pytest.mark.parametrize("rows", [2, 4, 38, 64, 128])
+@pytest.mark.parametrize("steps", [[20, 20, 20, 99], [15, 15, 15, 200], [1, 300, 1, 1], [1, 1, 1000], [2047] * 3, [1] * 70,
+                                   [7, 1, 61, 62, 4, 157]])
+def test_ragged_cut_mixed(plan, steps, rows):
+    """Short sequences before and after a long one, and contexts up to 262 000 tokens."""
+    arr = (ctypes.c_int32 * len(steps))(*steps)
+    for heads in (1, 2, 4, 8):
+        for wgs in RESIDENT:
+            most = ctypes.c_int(0)
+            error = plan.check_steps(arr, len(steps), heads, wgs, rows, ctypes.byref(most))
+            assert error == 0, f"check {error}: {steps}, {heads} heads, {wgs} workgroups, {rows} rows"
+
+
+def test_ragged_cut_uses_the_rows(plan):
+    """Limiting the parts leaves no chip idle that the limit would not: 8 units of 157 steps take two steps per workgroup at
+    127 parts, and as many workgroups as there are where that is no more parts than fit."""
+    most = ctypes.c_int(0)
+    assert plan.check_equal(157, 1, 8, 768, 128, ctypes.byref(most)) == 0 and 70 <= most.value <= 80
+    most = ctypes.c_int(0)
+    assert plan.check_equal(60, 1, 8, 768, 64, ctypes.byref(most)) == 0 and most.value == 60
