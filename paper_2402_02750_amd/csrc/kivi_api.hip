@@ -440,11 +440,22 @@ constexpr int kNotApplicable = 1;       // (internal) the fast path does not ser
 // counters from a device array; the split plan is the longest sequence's, a shorter one's surplus
 // chunks and tiles are masked.  Served: K and V split alike in every sequence, at least one fp16
 // row and at most 16 tiles of them per sequence, at least one quantised tile somewhere in the
-// batch.  `st`: the states the attention sees (after append and flush).  Returns kNotApplicable
-// (nothing launched) for any other batch.
-int ragged_attention_fast(const kivi_layout_t* l, const kivi_cache_t* c, const kivi_seq_state_t* st, const void* q,
-                          float softmax_scale, float* out, void* workspace, size_t workspace_bytes,
-                          const void* k_new, const void* v_new, void* stream) {
+// batch.
+// ragged_plan decides everything that can refuse the batch, on the host and without a launch (a step plans before it
+// flushes): `st` are the states the attention sees (after append and flush); kNotApplicable for any other batch.
+// ragged_launch then carries the plan out.
+struct RaggedPlan {
+    DecodeParams p;             // all but the addresses and the query
+    bool tiles;                 // decode_tiles_kernel
+    size_t parts_offset;        // of the parts in the workspace
+    // what the kernels read per call, int32: the sequences' counters (state_ints with the padding), then the work
+    // tables, if any: the workgroups' (or slices') from state_ints on, the sequences' (units') from unit_table on
+    std::vector<int32_t> tables;
+    size_t state_ints, unit_table;
+    std::vector<int32_t> steps;
+};
+
+int ragged_plan(const kivi_layout_t* l, const kivi_seq_state_t* st, size_t workspace_bytes, RaggedPlan& plan) {
     if (decode_family(l) != KIVI_DECODE_MFMA || l->decode_path == KIVI_DECODE_MFMA_ONE) return kNotApplicable;
     if (l->cap_q_tokens < kTileTokens || l->group != kTileTokens) return kNotApplicable;
     const int rep_total = l->n_q_heads / l->n_kv_heads;
@@ -463,23 +474,13 @@ int ragged_attention_fast(const kivi_layout_t* l, const kivi_cache_t* c, const k
     const MfmaGeometry g = mfma_geometry(l->bits, rep_launch);
     if (g.chunk_tiles == 0) return kNotApplicable;
 
-    DecodeParams p{};
-    p.k_codes = static_cast<const uint32_t*>(c->k_codes);
-    p.k_scale = static_cast<const __half*>(c->k_scale);
-    p.k_zero = static_cast<const __half*>(c->k_zero);
-    p.v_codes = static_cast<const uint32_t*>(c->v_codes);
-    p.v_scale = static_cast<const __half*>(c->v_scale);
-    p.v_zero = static_cast<const __half*>(c->v_zero);
-    p.k_resid = static_cast<const __half*>(c->k_resid);
-    p.v_resid = static_cast<const __half*>(c->v_resid);
-    p.k_new = static_cast<const __half*>(k_new); p.v_new = static_cast<const __half*>(v_new);
+    DecodeParams& p = plan.p;
+    p = DecodeParams{};
     // the scalar counters describe the longest sequence (the kernels take each sequence's own from seq_state)
     p.n_kq = p.n_vq = max_tiles_a * kTileTokens;
     p.n_kr = p.n_vr = max_tiles_b * kTileTokens;
     p.length = p.n_kq + p.n_kr;
     p.cap_tiles = l->cap_q_tokens / kTileTokens; p.cap_r = l->cap_r_tokens;
-    p.q = static_cast<const __half*>(q); p.out = out;
-    p.softmax_scale = softmax_scale;
     p.batch = l->batch; p.n_q_heads = l->n_q_heads; p.n_kv_heads = l->n_kv_heads; p.bits = l->bits;
     p.kg_shift = l->group == 32 ? 0 : (l->group == 64 ? 1 : 2);
     p.plan.tiles_a = max_tiles_a;
@@ -489,9 +490,7 @@ int ragged_attention_fast(const kivi_layout_t* l, const kivi_cache_t* c, const k
     p.plan.n_splits_a = ceil_div(max_tiles_a, g.chunk_tiles);
     p.plan.n_splits_b = 1;
     p.two_launches = 1;
-    char* ws = static_cast<char*>(workspace);
-    const size_t parts_offset = counter_bytes(l) + seq_state_bytes(l) + slice_table_bytes(l);
-    hipStream_t hs = static_cast<hipStream_t>(stream);
+    const size_t parts_offset = plan.parts_offset = counter_bytes(l) + seq_state_bytes(l) + slice_table_bytes(l);
 
     // Fewer units than the chip holds wavefronts, every sequence with quantised tokens, at most 4 heads
     // per launch: the second launch runs as equally long slices of the unit-major axis of four-tile
@@ -502,15 +501,15 @@ int ragged_attention_fast(const kivi_layout_t* l, const kivi_cache_t* c, const k
     // Everything the kernels read per call goes to the device in ONE copy (a copy is an operation of its
     // own on the stream): the sequences' counters, then -- if used -- the slice table and the unit table.
     // (An asynchronous copy out of pageable memory has taken its source when the call returns.)
-    static thread_local std::vector<int32_t> tables;
-    const size_t state_ints = seq_state_bytes(l) / sizeof(int32_t);
+    std::vector<int32_t>& tables = plan.tables;
+    const size_t state_ints = plan.state_ints = seq_state_bytes(l) / sizeof(int32_t);
+    plan.unit_table = 0;
     tables.assign(state_ints, 0);
     for (int b = 0; b < l->batch; ++b) {
         const kivi_seq_state_t& x = st[b];
         tables[4 * (size_t)b + 0] = x.n_kq; tables[4 * (size_t)b + 1] = x.n_kr;
         tables[4 * (size_t)b + 2] = x.k_r_start; tables[4 * (size_t)b + 3] = x.v_r_start;
     }
-    int32_t* dev_state = reinterpret_cast<int32_t*>(ws + counter_bytes(l));
     int64_t total = 0;                                      // groups of four tiles over all units
     for (int b = 0; b < l->batch; ++b) total += (int64_t)ceil_div(st[b].n_kq / kTileTokens, 4) * l->n_kv_heads;
     // The slices cost a fixed ~18 us more than the padded plan (short slices, parts through memory for
@@ -519,12 +518,12 @@ int ragged_attention_fast(const kivi_layout_t* l, const kivi_cache_t* c, const k
     // heads per kv-head, length spreads from +-12 % to 1 : 80: 0.70-0.96 of the padded plan's time above the
     // threshold, 1.05-1.7 below it).
     const int64_t wasted = units * ceil_div(max_tiles_a, 4) - total;
-    const bool tiles = rep_total >= 3;
+    const bool tiles = plan.tiles = rep_total >= 3;
     if (tiles) {
         // decode_tiles_kernel: the unit-major axis of four-tile steps (at least one per unit) in equal
         // intervals, one per resident workgroup, as far as the units' parts fit (kivi_tiles_plan.h).  (The table fits
         // where the slices' would: at most kMaxSlices entries, and 4 bytes per sequence instead of 8 per unit.)
-        static thread_local std::vector<int32_t> steps;
+        std::vector<int32_t>& steps = plan.steps;
         steps.resize((size_t)l->batch);
         int64_t all = 0;
         for (int b = 0; b < l->batch; ++b) {
@@ -538,8 +537,7 @@ int ragged_attention_fast(const kivi_layout_t* l, const kivi_cache_t* c, const k
         p.axis_len = cut.axis.len;
         p.axis_rem = cut.axis.rem;
         p.unit_wgs = cut.whole_units ? 1 : 0;
-        p.wave_desc = dev_state + state_ints;
-        p.unit_parts = p.wave_desc + (size_t)cut.workgroups * RaggedCut::kWords;
+        plan.unit_table = state_ints + (size_t)cut.workgroups * RaggedCut::kWords;
         p.n_slices = (int32_t)cut.workgroups;
         p.part_stride = stride;
     } else if (slice_waves > 0 && units < slice_waves && units <= kMaxSliceUnits && wasted >= 14000) {
@@ -577,8 +575,7 @@ int ragged_attention_fast(const kivi_layout_t* l, const kivi_cache_t* c, const k
         }
         const size_t rows_s = (size_t)l->batch * l->n_q_heads * (max_parts + 1);
         if (parts_offset + rows_s * (kHeadDim + 2) * sizeof(float) <= workspace_bytes) {
-            p.wave_desc = dev_state + state_ints;
-            p.unit_parts = p.wave_desc + (size_t)n_slices * 4;
+            plan.unit_table = state_ints + (size_t)n_slices * 4;
             p.n_slices = n_slices;
             p.plan.n_splits_a = max_parts;              // workspace rows per (batch, query head): the fp16-row part + one per slice
         } else {
@@ -588,20 +585,45 @@ int ragged_attention_fast(const kivi_layout_t* l, const kivi_cache_t* c, const k
     if (!tiles) p.part_stride = p.plan.n_splits();
     const size_t rows = (size_t)l->batch * l->n_q_heads * p.part_stride;
     if (parts_offset + rows * (kHeadDim + 2) * sizeof(float) > workspace_bytes) return KIVI_ERR_WORKSPACE;
-    p.counters = reinterpret_cast<int32_t*>(ws);
-    p.seq_state = dev_state;
     p.ragged_min_tiles = min_tiles_a;
-    p.part_o = reinterpret_cast<float*>(ws + parts_offset);
-    p.part_ml = p.part_o + rows * kHeadDim;
-    if (hipMemcpyAsync(dev_state, tables.data(), (p.wave_desc ? tables.size() : (size_t)l->batch * 4) * sizeof(int32_t),
-                       hipMemcpyHostToDevice, hs) != hipSuccess)
-        return KIVI_ERR_HIP;
     p.rep_variant = rep_launch;
     p.head_groups = 1;
+    return KIVI_OK;
+}
+
+int ragged_launch(const kivi_layout_t* l, const kivi_cache_t* c, const RaggedPlan& plan, const void* q, float softmax_scale, float* out,
+                  void* workspace, const void* k_new, const void* v_new, void* stream) {
+    DecodeParams p = plan.p;
+    p.k_codes = static_cast<const uint32_t*>(c->k_codes);
+    p.k_scale = static_cast<const __half*>(c->k_scale);
+    p.k_zero = static_cast<const __half*>(c->k_zero);
+    p.v_codes = static_cast<const uint32_t*>(c->v_codes);
+    p.v_scale = static_cast<const __half*>(c->v_scale);
+    p.v_zero = static_cast<const __half*>(c->v_zero);
+    p.k_resid = static_cast<const __half*>(c->k_resid);
+    p.v_resid = static_cast<const __half*>(c->v_resid);
+    p.k_new = static_cast<const __half*>(k_new); p.v_new = static_cast<const __half*>(v_new);
+    p.q = static_cast<const __half*>(q); p.out = out;
+    p.softmax_scale = softmax_scale;
+    char* ws = static_cast<char*>(workspace);
+    hipStream_t hs = static_cast<hipStream_t>(stream);
+    int32_t* dev_state = reinterpret_cast<int32_t*>(ws + counter_bytes(l));
+    p.counters = reinterpret_cast<int32_t*>(ws);
+    p.seq_state = dev_state;
+    if (plan.unit_table) {
+        p.wave_desc = dev_state + plan.state_ints;
+        p.unit_parts = dev_state + plan.unit_table;
+    }
+    p.part_o = reinterpret_cast<float*>(ws + plan.parts_offset);
+    p.part_ml = p.part_o + (size_t)l->batch * l->n_q_heads * p.part_stride * kHeadDim;
+    if (hipMemcpyAsync(dev_state, plan.tables.data(), (plan.unit_table ? plan.tables.size() : (size_t)l->batch * 4) * sizeof(int32_t),
+                       hipMemcpyHostToDevice, hs) != hipSuccess)
+        return KIVI_ERR_HIP;
+    const int rep_total = l->n_q_heads / l->n_kv_heads;
     for (int h0 = 0; h0 < rep_total; h0 += kMaxRep) {
         p.q_head0 = h0;
         p.rep_here = std::min(kMaxRep, rep_total - h0);
-        const hipError_t e = tiles ? launch_decode_tiles(p, hs) : launch_decode_mfma(p, hs);
+        const hipError_t e = plan.tiles ? launch_decode_tiles(p, hs) : launch_decode_mfma(p, hs);
         if (e == hipErrorNotSupported) return KIVI_ERR_UNSUPPORTED;
         if (int s2 = hip_status(e)) return s2;
         p.k_new = p.v_new = nullptr;
@@ -609,12 +631,18 @@ int ragged_attention_fast(const kivi_layout_t* l, const kivi_cache_t* c, const k
     return KIVI_OK;
 }
 
+// the calling thread's plan (its tables keep their memory from call to call)
+RaggedPlan& thread_plan() {
+    static thread_local RaggedPlan plan;
+    return plan;
+}
+
 // One decoding step of every sequence of a batch of different lengths in one pair of attention
 // launches (plus one flush launch per run of equal sequences that flush in this step, which is rare:
 // a sequence flushes every G-th step).  Served when every sequence's flush leaves the new token in
 // the window (then the flush can run out of the rings before the attention appends the token) and
-// the states after the step suit ragged_attention_fast.  Returns kNotApplicable with nothing launched
-// and nothing changed otherwise.
+// ragged_plan takes the states after the step.  Returns kNotApplicable with nothing launched and nothing changed
+// otherwise.
 int ragged_step_fast(const kivi_layout_t* l, const kivi_cache_t* c, kivi_seq_state_t* states, const void* k_new,
                      const void* v_new, const void* q, float softmax_scale, int32_t policy, float* out,
                      void* workspace, size_t workspace_bytes, void* stream) {
@@ -639,22 +667,12 @@ int ragged_step_fast(const kivi_layout_t* l, const kivi_cache_t* c, kivi_seq_sta
         after[b] = kivi_seq_state_t{sc.n_kq + nk, sc.n_vq + nv, (sc.k_r_start + nk) % l->cap_r_tokens, sc.n_kr - nk + 1,
                                     (sc.v_r_start + nv) % l->cap_r_tokens, sc.n_vr - nv + 1};
     }
-    // dry run of the attention's own conditions (no launch): the same checks it will make
-    {
-        const int rep_launch = std::min(l->n_q_heads / l->n_kv_heads, kMaxRep);
-        const int rep_variant = rep_launch <= 2 ? rep_launch : (rep_launch <= 4 ? 4 : 8);
-        if (l->decode_path == KIVI_DECODE_MFMA_ONE || l->cap_q_tokens < kTileTokens || l->group != kTileTokens) return kNotApplicable;
-        int max_tiles_a = 0, max_tiles_b = 0;
-        for (int b = 0; b < l->batch; ++b) {
-            const kivi_seq_state_t& x = after[b];
-            if (x.n_kq != x.n_vq || x.n_kr != x.n_vr || x.n_kr < 1 || x.n_kq % kTileTokens != 0) return kNotApplicable;
-            max_tiles_a = std::max(max_tiles_a, x.n_kq / kTileTokens);
-            max_tiles_b = std::max(max_tiles_b, ceil_div(x.n_kq + x.n_kr, kTileTokens) - x.n_kq / kTileTokens);
-        }
-        if (max_tiles_a < 1 || !residual_rows_possible(max_tiles_b, rep_variant)) return kNotApplicable;
-        const size_t rows = (size_t)l->batch * l->n_q_heads * (ceil_div(max_tiles_a, mfma_geometry(l->bits, rep_launch).chunk_tiles) + 1);
-        if (counter_bytes(l) + seq_state_bytes(l) + slice_table_bytes(l) + rows * (kHeadDim + 2) * sizeof(float) > workspace_bytes) return KIVI_ERR_WORKSPACE;
-    }
+    // the attention's plan: everything that can refuse the step is known before anything is launched
+    RaggedPlan& plan = thread_plan();
+    if (int s = ragged_plan(l, after, workspace_bytes, plan)) return s;
+    // (a step has always asked for room for the longest sequence's splits, also where the plan makes do with less)
+    const size_t rows = (size_t)l->batch * l->n_q_heads * (ceil_div(plan.p.plan.tiles_a, plan.p.plan.tiles_per_split_a) + 1);
+    if (plan.parts_offset + rows * (kHeadDim + 2) * sizeof(float) > workspace_bytes) return KIVI_ERR_WORKSPACE;
     // pass 2: the flushes, one launch per run of consecutive sequences with equal state that flush
     hipStream_t hs = static_cast<hipStream_t>(stream);
     for (int b0 = 0; b0 < l->batch;) {
@@ -667,8 +685,7 @@ int ragged_step_fast(const kivi_layout_t* l, const kivi_cache_t* c, kivi_seq_sta
         }
         b0 = b1;
     }
-    if (int s = ragged_attention_fast(l, c, after, q, softmax_scale, out, workspace, workspace_bytes, k_new, v_new, stream))
-        return s == kNotApplicable ? KIVI_ERR_UNSUPPORTED : s;       // cannot happen after the dry run
+    if (int s = ragged_launch(l, c, plan, q, softmax_scale, out, workspace, k_new, v_new, stream)) return s;
     for (int b = 0; b < l->batch; ++b) states[b] = after[b];
     return KIVI_OK;
 }
@@ -998,7 +1015,7 @@ int kivi_decode_launches_ragged(const kivi_layout_t* l, const kivi_seq_state_t* 
     const int path = decode_family(l);
     const int rep_total = l->n_q_heads / l->n_kv_heads;
     const int head_groups = ceil_div(rep_total, kMaxRep);
-    // the conditions of ragged_attention_fast
+    // the conditions of ragged_plan
     bool fast = path == KIVI_DECODE_MFMA && l->decode_path != KIVI_DECODE_MFMA_ONE && l->cap_q_tokens >= kTileTokens &&
                 l->group == kTileTokens;
     int max_tiles_a = 0, max_tiles_b = 0;
@@ -1046,7 +1063,9 @@ int kivi_decode_attention_ragged(const kivi_layout_t* l, const kivi_cache_t* c, 
             ok = kivi_batch_slice(l, c, b, 1, &states[b], &sl, &sc) == KIVI_OK;     // validates the sequence's counters
         }
         if (ok) {
-            const int s = ragged_attention_fast(l, c, states, q, softmax_scale, out, workspace, workspace_bytes, nullptr, nullptr, stream);
+            RaggedPlan& plan = thread_plan();
+            const int s = ragged_plan(l, states, workspace_bytes, plan);
+            if (s == KIVI_OK) return ragged_launch(l, c, plan, q, softmax_scale, out, workspace, nullptr, nullptr, stream);
             if (s != kNotApplicable) return s;
         }
     }

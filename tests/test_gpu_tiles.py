@@ -122,3 +122,59 @@ def test_tiles_ragged(hq, hkv, bits, tokens):
             ref = gh.oracle_attention_for_heads(w, oc, q, at)
             err = np.abs(gh.pick_heads(got[step], w, at) - ref).max()
             assert err <= 1e-4 * scale, f"step {step} sequence {b}: {err:.3e} against {1e-4 * scale:.3e}"
+
+
+@pytest.mark.parametrize("hq,hkv,bits", [(8, 2, 2), (16, 2, 4), (12, 2, 4)])
+def test_tiles_ragged_small_workspace(hq, hkv, bits):
+    """A ragged step that flushes, with room for few parts per head: served as with the full workspace from as many rows on
+    as the longest sequence has splits, refused before anything is launched below; the attention alone needs two.
+    (Tolerance: another cut of the same work adds the same terms, 22 bits each, in another order.)"""
+    torch = gh.require_gpu()
+    tokens, residual = [479, 300, 95], 64           # the first and the last flush in this step
+    batch, total = len(tokens), max(tokens) + 1
+    w = scaled(CONFIGS["mistral_gqa"], name="tilesws", batch=batch, n_q_heads=hq, n_kv_heads=hkv, bits=bits, residual=residual, seed=hq)
+    kt, vt = torch.from_numpy(workloads.keys(w, total)).cuda(), torch.from_numpy(workloads.values(w, total)).cuda()
+    q = torch.from_numpy(workloads.queries(w, 0)).cuda()
+    new = [torch.stack([x[b, :, n] for b, n in enumerate(tokens)]).contiguous() for x in (kt, vt)]
+    layout = kivi.make_layout(batch, hq, hkv, bits, residual, gh.round_up(total, 32), 96)
+    row = batch * hq * 130 * 4
+    full = kivi.kivi_decode_workspace_bytes(layout)
+    base = full - ((layout.cap_q_tokens // 32 + 3) // 4 + layout.cap_r_tokens // 32 + 2) * row
+    tiles_per_split = 16 if bits == 2 else 8
+    need = -(-((480 - residual) // 32) // tiles_per_split) + 1
+    results = {}
+    for rows in (None, 4, 3, 2, 1):
+        print(f"case tiles workspace hq={hq} hkv={hkv} bits={bits} rows={rows}", flush=True)
+        cache = kivi.Cache(layout)
+        size = full if rows is None else base + rows * row
+        room = torch.full((full + row,), 0x5A, dtype=torch.uint8, device="cuda")
+        cache.workspace = room[:size].zero_()
+        for buf in cache.buffers.values():
+            buf.zero_()
+        states = kivi.make_states(batch)
+        for b, n in enumerate(tokens):
+            part = kivi.CacheSlice(cache, b, 1)
+            kivi.kivi_prefill(part.layout, kt[b:b + 1], vt[b:b + 1], n, part)
+            states[b] = part.state()
+        before = bytes(states), {n: x.clone() for n, x in cache.buffers.items()}
+        outs = [torch.zeros(batch, hq, 128, dtype=torch.float32, device="cuda") for _ in range(2)]
+        if rows is not None and rows < need:
+            with pytest.raises(kivi.KiviError, match="WORKSPACE"):
+                kivi.kivi_decode_step_ragged(layout, cache, states, *new, q, w.softmax_scale, outs[0])
+            torch.cuda.synchronize()
+            assert bytes(states) == before[0]
+            assert all(torch.equal(cache.buffers[n], x) for n, x in before[1].items())
+        else:
+            kivi.kivi_decode_step_ragged(layout, cache, states, *new, q, w.softmax_scale, outs[0])
+            assert [s.n_kq for s in states] == [416, 224, 32]
+        if rows is None or rows >= 2:
+            kivi.kivi_decode_attention_ragged(layout, cache, states, q, w.softmax_scale, outs[1])
+        else:
+            with pytest.raises(kivi.KiviError, match="WORKSPACE"):
+                kivi.kivi_decode_attention_ragged(layout, cache, states, q, w.softmax_scale, outs[1])
+        torch.cuda.synchronize()
+        assert (room[size:] == 0x5A).all()
+        results[rows] = [o.cpu().numpy() for o in outs]
+        if rows is not None and rows >= need:
+            for got, ref in zip(results[rows], results[None]):
+                assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max(), f"{rows} rows"
