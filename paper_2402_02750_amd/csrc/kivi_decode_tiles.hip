@@ -1162,10 +1162,6 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
     wait_copies<0>();                                  // no copy may land in LDS that has been given back
 }
 
-// Fewest steps of a workgroup where there are workgroups enough for less: with one step each, batch 1 at context
-// 4000 leaves 31 parts per unit to merge (32 query / 8 kv heads 14.9 -> 12.5 us, 64 / 8 at 4 bits 15.9 -> 12.7 us);
-// with three the steps themselves get long (context 1000: 11.4 -> 11.9 us).
-constexpr int kMinSteps = 2;
 constexpr int kMaxDevices = 64;
 // workgroups the current device holds at once (an occupancy query, kept per device)
 template <int BITS, int HP, int MODE, bool CS>
@@ -1207,48 +1203,21 @@ hipError_t launch_mode(DecodeParams p, hipStream_t stream) {
         decode_tiles_kernel<BITS, HP, MODE, CS><<<p.n_slices, 64 * kWaves, 0, stream>>>(p);
         return hipGetLastError();
     }
-    const int n_a = (p.plan.tiles_a + kWaves - 1) / kWaves;
-    const bool rows = p.plan.tiles_total > p.plan.tiles_a;
-    const int64_t total = units * n_a;
-    if (total > 0x3fffffff || units > 0x1fffffff || (total == 0 && !rows)) return hipErrorInvalidValue;
-    // Workgroups for a unit's fp16 rows: a wavefront per tile (a second tile is another 2-5 us in a chain that the
-    // launch's end waits for) unless that takes more than a quarter of the residency.
-    const int row_tiles = p.plan.tiles_total - p.plan.tiles_a, resident = resident_workgroups<BITS, HP, MODE, CS>();
-    p.row_split = std::max(1, std::min({(row_tiles + kWaves - 1) / kWaves, (int)std::max<int64_t>(1, resident / 4 / units), p.part_stride / 2}));
-    p.row_wgs = rows ? (int)units * p.row_split : 0;
-    const bool two = p.two_launches > 0 && rows && total > 0;      // the fp16 rows in a launch of their own
-    // One interval per workgroup that is resident beside the fp16 rows' (which end early), but not so short
-    // that a unit would have more parts than the workspace has rows for.  With several workgroups per unit each
-    // one's interval lies in one unit: a workgroup that straddles two enters and leaves both (4-7 us each, on the
-    // critical path of the launch).  Otherwise all units are one axis (an interval of c steps cuts a unit into
-    // at most (n_a - 1) / c + 2 parts).
-    const int max_parts = std::min(p.part_stride, max_parts_of(BITS, HP)) - (rows ? p.row_split : 0);
-    int64_t grid = 0;
-    p.unit_wgs = 0;
-    if (total > 0) {
-        if (max_parts < 1) return hipErrorInvalidValue;
-        grid = std::min<int64_t>(two ? resident : std::max(resident - p.row_wgs, resident / 2), total);
-        if (grid >= 3 * units || max_parts == 1) {
-            p.unit_wgs = (int)std::min<int64_t>(max_parts, std::max<int64_t>(std::min<int64_t>(grid / units, n_a / kMinSteps), 1));
-            grid = units * p.unit_wgs;
-            p.axis_len = n_a / p.unit_wgs;
-            p.axis_rem = n_a % p.unit_wgs;
-        } else {
-            while (grid > 1 && std::min<int64_t>(grid, (n_a - 1) / (total / grid) + 2) > max_parts)
-                grid = std::min<int64_t>(grid - 1, total / (total / grid + 1));
-            p.axis_len = (int)(total / grid);
-            p.axis_rem = (int)(total % grid);
-        }
-    } else {
-        p.axis_len = 1;
-        p.axis_rem = 0;
-    }
+    UniformCut cut;
+    const bool two = p.two_launches > 0 && p.plan.tiles_total > p.plan.tiles_a && p.plan.tiles_a > 0;      // the fp16 rows in a launch of their own
+    if (!cut_uniform(units, p.plan.tiles_a, p.plan.tiles_total, resident_workgroups<BITS, HP, MODE, CS>(), p.part_stride, max_parts_of(BITS, HP), two, cut))
+        return hipErrorInvalidValue;
+    p.row_split = cut.row_split;
+    p.row_wgs = cut.row_wgs;
+    p.unit_wgs = cut.unit_wgs;
+    p.axis_len = cut.axis.len;
+    p.axis_rem = cut.axis.rem;
     if (two) {
         decode_tiles_kernel<BITS, HP, MODE, CS><<<(unsigned)p.row_wgs, 64 * kWaves, 0, stream>>>(p);
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
         p.row_wgs = 0;
     }
-    decode_tiles_kernel<BITS, HP, MODE, CS><<<(unsigned)(grid + p.row_wgs), 64 * kWaves, 0, stream>>>(p);
+    decode_tiles_kernel<BITS, HP, MODE, CS><<<(unsigned)(cut.intervals + p.row_wgs), 64 * kWaves, 0, stream>>>(p);
     return hipGetLastError();
 }
 

@@ -91,4 +91,54 @@ inline RaggedCut cut_ragged(const std::vector<int32_t>& steps, int n_kv_heads, i
     return cut;
 }
 
+// A batch of one length: `rows`, the workgroups of the units' fp16 rows, `row_split` per unit, and intervals of the
+// all-quantised steps, `intervals` in all: `unit_wgs` per unit of its own steps, or (0) of all units' steps.
+struct UniformCut {
+    int row_split = 1, row_wgs = 0, unit_wgs = 0;
+    StepAxis axis{1, 0};
+    int64_t intervals = 0;
+};
+
+// Fewest steps of a workgroup where there are workgroups enough for less: with one step each, batch 1 at context
+// 4000 leaves 31 parts per unit to merge (32 query / 8 kv heads 14.9 -> 12.5 us, 64 / 8 at 4 bits 15.9 -> 12.7 us);
+// with three the steps themselves get long (context 1000: 11.4 -> 11.9 us).
+constexpr int kMinSteps = 2;
+
+// resident: workgroups the device holds at once; stride, parts_limit: see the top; own_launch: the fp16 rows run in a
+// launch of their own.  False: no cut fits.
+inline bool cut_uniform(int64_t units, int tiles_a, int tiles_total, int resident, int stride, int parts_limit, bool own_launch, UniformCut& cut) {
+    const int n_a = (tiles_a + kStepTiles - 1) / kStepTiles, row_tiles = tiles_total - tiles_a;
+    const int64_t total = units * n_a;
+    const bool rows = row_tiles > 0;
+    const int room = std::min(stride, parts_limit);
+    if (total > 0x3fffffff || units > 0x1fffffff || (total == 0 && !rows)) return false;
+    // Workgroups for a unit's fp16 rows: a wavefront per tile (a second tile is another 2-5 us in a chain that the
+    // launch's end waits for) unless that takes more than a quarter of the residency, and at most half of the unit's
+    // parts (a window of 8000 and more tokens asks for more than eight heads at 4 bits have).
+    cut.row_split = std::max(1, std::min({(row_tiles + kStepTiles - 1) / kStepTiles, (int)std::max<int64_t>(1, resident / 4 / units), room / 2}));
+    cut.row_wgs = rows ? (int)units * cut.row_split : 0;
+    // One interval per workgroup that is resident beside the fp16 rows' (which end early), but not so short
+    // that a unit would have more parts than there is room for.  With several workgroups per unit each
+    // one's interval lies in one unit: a workgroup that straddles two enters and leaves both (4-7 us each, on the
+    // critical path of the launch).  Otherwise all units are one axis (an interval of c steps cuts a unit into
+    // at most (n_a - 1) / c + 2 parts).
+    const int max_parts = room - (rows ? cut.row_split : 0);
+    cut.unit_wgs = 0;
+    cut.axis = StepAxis{1, 0};
+    cut.intervals = 0;
+    if (total == 0) return cut.row_split <= room;
+    if (max_parts < 1) return false;
+    int64_t n = std::min<int64_t>(own_launch ? resident : std::max(resident - cut.row_wgs, resident / 2), total);
+    if (n >= 3 * units || max_parts == 1) {
+        cut.unit_wgs = (int)std::min<int64_t>(max_parts, std::max<int64_t>(std::min<int64_t>(n / units, n_a / kMinSteps), 1));
+        n = units * cut.unit_wgs;
+        cut.axis = StepAxis{n_a / cut.unit_wgs, n_a % cut.unit_wgs};
+    } else {
+        while (n > 1 && std::min<int64_t>(n, (n_a - 1) / (total / n) + 2) > max_parts) n = std::min<int64_t>(n - 1, total / (total / n + 1));
+        cut.axis = StepAxis{(int32_t)(total / n), (int32_t)(total % n)};
+    }
+    cut.intervals = n;
+    return true;
+}
+
 }  // namespace kivi

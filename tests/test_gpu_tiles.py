@@ -178,3 +178,21 @@ def test_tiles_ragged_small_workspace(hq, hkv, bits):
         if rows is not None and rows >= need:
             for got, ref in zip(results[rows], results[None]):
                 assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max(), f"{rows} rows"
+
+
+@pytest.mark.parametrize("hq,hkv,bits,quantised", [(14, 2, 4, 640), (8, 1, 4, 0), (7, 1, 2, 96)])
+def test_tiles_large_window(hq, hkv, bits, quantised):
+    """A window of 8192 fp16 tokens and few units: the rows may take no more than half of a unit's parts.  Against the oracle,
+    tolerance as in test_tiles."""
+    gh.require_gpu()
+    w = scaled(CONFIGS["mistral_gqa"], name="tileswindow", batch=1, n_q_heads=hq, n_kv_heads=hkv, bits=bits, residual=8192, seed=5 * hq)
+    tokens = 8192 + quantised
+    print(f"case tiles window hq={hq} hkv={hkv} bits={bits} L={tokens}", flush=True)
+    k, v, q = workloads.keys(w, tokens), workloads.values(w, tokens), workloads.queries(w)
+    heads = [(0, h) for h in range(hkv)]
+    ref = gh.oracle_attention_for_heads(w, gh.oracle_cache_for_heads(w, k, v, heads, "window"), q, heads)
+    scale = float(np.abs(v.astype(np.float32)).max())
+    layout, cache = gh.gpu_prefill(w, k, v, W, kivi.KIVI_DECODE_AUTO)
+    assert cache.c.n_kq == quantised
+    err = np.abs(gh.pick_heads(gh.gpu_attention(layout, cache, q, w.softmax_scale), w, heads) - ref).max()
+    assert err <= 1e-4 * scale, f"{err:.3e} against {1e-4 * scale:.3e}"

@@ -54,6 +54,46 @@ extern "C" int check_equal(int n, int sequences, int heads, int max_wgs, int row
 extern "C" int check_steps(const int32_t* steps, int sequences, int heads, int max_wgs, int rows, int* most) {
     return check(std::vector<int32_t>(steps, steps + sequences), heads, max_wgs, rows, most);
 }
+// the same for a batch of one length: tiles_a quantised tiles, row_tiles with fp16 rows
+extern "C" int check_uniform(int units, int tiles_a, int row_tiles, int resident, int stride, int limit, int own_launch, int* out) {
+    UniformCut cut;
+    if (!cut_uniform(units, tiles_a, tiles_a + row_tiles, resident, stride, limit, own_launch, cut)) return 1;
+    const int n_a = (tiles_a + 3) / 4, room = std::min(stride, limit), row_parts = row_tiles ? cut.row_split : 0;
+    out[0] = cut.row_split;
+    out[1] = (int)cut.intervals;
+    if (cut.row_wgs != units * row_parts || (row_tiles && cut.row_split < 1)) return 2;
+    if (n_a == 0) return cut.intervals == 0 && row_parts <= room ? 0 : 3;
+    done.assign(units, 0);
+    parts.assign(units, 0);
+    for (int g = 0; g < (int)cut.intervals; ++g) {
+        int u, first, left;
+        if (cut.unit_wgs > 0) {
+            u = g / cut.unit_wgs;
+            const int k = g % cut.unit_wgs;
+            first = cut.axis.start(k);
+            left = cut.axis.start(k + 1) - first;
+        } else {
+            u = cut.axis.start(g) / n_a;
+            first = cut.axis.start(g) % n_a;
+            left = cut.axis.start(g + 1) - cut.axis.start(g);
+        }
+        if (left < 1) return 4;
+        for (; left > 0; ++u, first = 0) {
+            if (u >= units || first != done[u]) return 5;
+            const int n = std::min(n_a - first, left);
+            done[u] += n;
+            left -= n;
+            const int g0 = cut.unit_wgs > 0 ? u * cut.unit_wgs : cut.axis.owner(u * n_a);
+            if (g - g0 != parts[u]) return 6;
+            ++parts[u];
+        }
+    }
+    for (int u = 0; u < units; ++u) {
+        const int waited = cut.unit_wgs > 0 ? cut.unit_wgs : cut.axis.owner(u * n_a + n_a - 1) - cut.axis.owner(u * n_a) + 1;
+        if (done[u] != n_a || parts[u] != waited || parts[u] + row_parts > room) return 7;
+    }
+    return 0;
+}
 extern "C" int check_range(int n_max, int units_max, int max_wgs, int rows, int* at) {
     for (int n = 1; n <= n_max; ++n)
         for (int units = 1; units <= units_max; ++units) {
@@ -108,3 +148,26 @@ def test_ragged_cut_uses_the_rows(plan):
     assert plan.check_equal(157, 1, 8, 768, 128, ctypes.byref(most)) == 0 and 70 <= most.value <= 80
     most = ctypes.c_int(0)
     assert plan.check_equal(60, 1, 8, 768, 64, ctypes.byref(most)) == 0 and most.value == 60
+
+
+@pytest.mark.parametrize("stride,limit", [(2, 128), (2, 64), (6, 64), (12, 128), (38, 128), (128, 64), (128, 128)])
+def test_uniform_cut(plan, stride, limit):
+    """Every window up to 9000 fp16 rows beside every length, from one unit to more than the device holds workgroups; one launch
+    and two."""
+    out = (ctypes.c_int * 2)()
+    for own_launch in (0, 1):
+        for resident in (3, 256, 512, 768):
+            for units in (1, 2, 3, 5, 8, 31, 96, 200, 256, 300, 700, 1100):
+                for tiles_a in (0, 1, 3, 4, 5, 29, 128, 257, 1000, 4001):
+                    for row_tiles in (0, 1, 4, 5, 16, 17, 129, 257, 282):
+                        if tiles_a + row_tiles == 0:
+                            continue
+                        error = plan.check_uniform(units, tiles_a, row_tiles, resident, stride, limit, own_launch, out)
+                        assert error == 0, f"check {error}: {units} units, {tiles_a} + {row_tiles} tiles, {resident} workgroups"
+
+
+def test_uniform_cut_large_window(plan):
+    """Two units with a window of 8192 tokens and 640 quantised ones: eight heads at 4 bits have 64 parts per unit, half of them
+    for the rows."""
+    out = (ctypes.c_int * 2)()
+    assert plan.check_uniform(2, 20, 257, 768, 128, 64, 0, out) == 0 and tuple(out) == (32, 4)
