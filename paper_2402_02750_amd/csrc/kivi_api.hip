@@ -301,6 +301,13 @@ int wide_group_runs(const kivi_layout_t* l, int path, bool two_launches) {
     return ceil_div(rep_total, wide_group_width(l));
 }
 
+// Launches of one attention call: a group wider than kMaxRep heads takes one pass per kMaxRep heads, except in the
+// matrix-core family's single-launch form, where the runs are units of one launch.
+int attention_launches(const kivi_layout_t* l, int path, bool two_launches) {
+    const int passes = wide_group_runs(l, path, two_launches) > 1 ? 1 : ceil_div(l->n_q_heads / l->n_kv_heads, kMaxRep);
+    return path == KIVI_DECODE_MFMA ? (two_launches ? 2 : 1) * passes : passes + 1;      // vector-ALU family: decodes + merge
+}
+
 // Which kernel of the matrix-core family serves the layout: decode_tiles_kernel from three query heads per
 // kv-head on (sweep over 8-1024 units, contexts 300-30000, 2 and 4 bits: 1.02-2.0 times as fast as
 // decode_mfma_kernel throughout), and with two heads up to 256 units (1.03-1.19; at 512 units 0.70, that
@@ -760,12 +767,8 @@ int kivi_decode_plan(const kivi_layout_t* l, const kivi_cache_t* c, kivi_decode_
     const bool two = wants_two_launches(l, c, path);
     const SplitPlan plan = plan_splits(l, c, path == KIVI_DECODE_MFMA, two);
     out->family = path;
-    // launches: a group wider than kMaxRep heads takes one pass per run of kMaxRep heads, except in the
-    // matrix-core family's single-launch form, where the runs are units of one launch
-    const int rep_total = l->n_q_heads / l->n_kv_heads;
     const int runs = wide_group_runs(l, path, two);
-    const int passes = runs > 1 ? 1 : ceil_div(rep_total, kMaxRep);
-    out->launches = path == KIVI_DECODE_MFMA ? (two ? 2 : 1) * passes : passes + 1;      // vector-ALU family: decodes + merge
+    out->launches = attention_launches(l, path, two);
     out->units_per_kv_head = runs > 1 ? runs : 1 << head_split_shift(l, plan, path, two);
     out->splits_quantised = plan.n_splits_a;
     out->splits_fp16 = plan.n_splits_b;
@@ -1042,9 +1045,7 @@ int kivi_decode_launches_ragged(const kivi_layout_t* l, const kivi_seq_state_t* 
             sl.batch = b1 - b0;
             kivi_cache_t sc{};
             sc.n_kq = x.n_kq; sc.n_vq = x.n_vq; sc.n_kr = x.n_kr; sc.n_vr = x.n_vr;
-            const bool two = wants_two_launches(&sl, &sc, path);
-            const bool split = head_split_shift(&sl, plan_splits(&sl, &sc, path == KIVI_DECODE_MFMA, two), path, two) > 0;
-            total += path == KIVI_DECODE_MFMA ? (split ? 1 : head_groups * (two ? 2 : 1)) : head_groups + 1;
+            total += attention_launches(&sl, path, wants_two_launches(&sl, &sc, path));
         }
         b0 = b1;
     }

@@ -310,3 +310,23 @@ def test_decode_launches_ragged(lib):
     bad[1] = kivi.kivi_seq_state_t(32, 0, 0, 5, 0, 5)
     n = ctypes.c_int32(0)
     assert lib.kivi_decode_launches_ragged(ctypes.byref(l), bad, ctypes.byref(n)) == kivi.KIVI_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("group", [32, 64, 128])
+@pytest.mark.parametrize("hq,hkv", [(4, 4), (16, 8), (32, 8), (64, 8), (71, 1), (128, 8)])
+@pytest.mark.parametrize("path", [kivi.KIVI_DECODE_AUTO, kivi.KIVI_DECODE_MFMA_ONE, kivi.KIVI_DECODE_MFMA_TWO, kivi.KIVI_DECODE_VALU])
+def test_decode_launches_run_by_run(lib, hq, hkv, group, path):
+    """A batch that goes run by run makes the launches that kivi_decode_plan reports for each run: one for any number of
+    heads per kv-head in the single-launch form."""
+    l = kivi.make_layout(3, hq, hkv, 2, 128, 4096, 256, group=group, decode_path=path)
+    st = kivi.make_states(3)
+    split = [(1024, 130), (1024, 130), (2048, 70)]
+    for b, (nq, nr) in enumerate(split):
+        st[b] = kivi.kivi_seq_state_t(nq, nq - 5, 0, nr, 0, nr + 5)         # K and V split differently: no common pair of launches
+    expected = 0
+    for batch, (nq, nr) in ((2, split[0]), (1, split[2])):
+        run = kivi.make_layout(batch, hq, hkv, 2, 128, 4096, 256, group=group, decode_path=path)
+        expected += kivi.kivi_decode_plan(run, _fake_cache(n_kq=nq, n_vq=nq - 5, n_kr=nr, n_vr=nr + 5)).launches
+    assert kivi.kivi_decode_launches_ragged(l, st) == expected
+    if path != kivi.KIVI_DECODE_VALU:
+        assert expected == 2
