@@ -87,9 +87,12 @@ constexpr int kQueryExp = 8;                   // largest |q'| lies in [2^8, 2^9
 constexpr uint32_t kKeyScaleLimit = 0x54005400u;       // two times fp16 64.0
 constexpr int kKeyScaleShift = 9;              // a tile with a larger key scale takes s 2^-9
 // Value side: p' = p 2^kProbExp, value scales taken as s 2^-ks with s 2^-ks < 2^kValueTop, so that
-// p' s < 2^16 with the slack.  4-bit codes: scales are 5 times smaller for the same data.
+// p' s < 2^16 with the slack.  4-bit codes: scales are 5 times smaller for the same data.  Scales down to 2^-kValueWindow of
+// that need no shift.  Larger ones are taken as they are too while their products stay below 2^11 (kProductLimit).
 template <int BITS> constexpr int kProbExp = BITS == 2 ? 8 : 11;
 template <int BITS> constexpr int kValueTop = BITS == 2 ? 3 : 0;
+constexpr int kValueWindow = 7;
+constexpr float kProductLimit = 2048.f;
 
 template <int CTRL>
 __device__ __forceinline__ float dpp(float x) {
@@ -336,6 +339,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
     float4v acc[8];                    // value code sums: acc[u][i] = channel 16 u + 4 kb + i, column n
     float4v zsum;                      // value zero-point sums: zsum[i] = channel group i, column n
     float mref, l_lane;                // reference (log2 domain) of the probabilities; this lane's sum
+    int n_live;                        // query heads of the unit (the columns of idle slots hold a query of zeros)
     int ks;                            // value scales enter as s 2^-ks
     bool ks_set;
     uint32_t value_limit;              // fp16 pair 2^(ks + kValueTop)
@@ -355,6 +359,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
     // query operands; raw[cb]: channels 32 cb + 8 kb .. + 7 of this lane's head
     auto set_query = [&](const half8 (&raw)[4], int live) {
         typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
+        n_live = live;
         ushort2v top = {0, 0};                                          // |q| as integers
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb)
@@ -485,28 +490,26 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
         for (int u8 = 0; u8 < 8; ++u8)
             acc[u8] = __builtin_amdgcn_mfma_f32_16x16x32_f16(value_fragment<BITS>(w, u8 >> 1, u8 & 1), f[(u8 >> 1) * NS / 4].h, acc[u8], 0, 0, 0);
     };
-    // the scales' exponent (wave-uniform): on the unit's first tile, and when a scale leaves the range
-    auto adjust_value_exponent = [&](uint32_t s2) {        // s2: two scales of the tile per lane
+    // Exponent ks of the value scales (wave-uniform) that puts the largest of a tile's below 2^kValueTop; s2: two of them per lane
+    auto wanted_exponent = [&](uint32_t s2) -> int {
         float mx = fmaxf((float)half2_of(s2)[0], (float)half2_of(s2)[1]);
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) mx = fmaxf(mx, __shfl_xor(mx, d));
         const int e = (int)(__float_as_uint(mx) >> 23) - 126;              // mx < 2^e (mx = 0: e = -126)
-        // scales within 7 bits below the limit need no shift
-        int want = max(e - kValueTop<BITS>, -24);
-        if (!ks_set && want <= 0 && want > -7) want = 0;
-        if (!ks_set || want > ks) {
-            if (ks_set) {
-                const float f = __uint_as_float((uint32_t)(127 + ks - want) << 23);
+        return __builtin_amdgcn_readfirstlane(max(e - kValueTop<BITS>, -24));
+    };
+    auto set_value_exponent = [&](int want) {
+        if (ks_set) {
+            const float f = __uint_as_float((uint32_t)(127 + ks - want) << 23);
 #pragma unroll
-                for (int u8 = 0; u8 < 8; ++u8) acc[u8] *= f;
-            }
-            ks = __builtin_amdgcn_readfirstlane(want);
-            ks_set = true;
-            // largest fp16 below 2^(ks + kValueTop), at most the largest finite number
-            const int top = ks + kValueTop<BITS> + 15;                      // biased fp16 exponent
-            const uint32_t lim = top >= 31 ? 0x7BFFu : top <= 0 ? 0u : (uint32_t)(top << 10) - 1;
-            value_limit = __builtin_amdgcn_readfirstlane(lim | lim << 16);
+            for (int u8 = 0; u8 < 8; ++u8) acc[u8] *= f;
         }
+        ks = want;
+        ks_set = true;
+        // largest fp16 below 2^(ks + kValueTop), at most the largest finite number
+        const int top = ks + kValueTop<BITS> + 15;                          // biased fp16 exponent
+        const uint32_t lim = top >= 31 ? 0x7BFFu : top <= 0 ? 0u : (uint32_t)(top << 10) - 1;
+        value_limit = lim | lim << 16;
     };
     auto max_pairs = [&](uint32_t a, uint32_t b) -> uint32_t {              // non-negative fp16 compare as integers
         typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
@@ -523,6 +526,35 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
 #pragma unroll
                 for (int r = 0; r < 4; ++r) sv[s][r] = sv[s][r] * half2v{f1, f1} * half2v{f2, f2};
         }
+    };
+
+    // Fits ks to a tile: load(sv) reads its scales, s2: two of them per lane.  ks starts at 0, or lower where the unit's first
+    // tile has small scales only.  It rises when a scale passes the limit AND its products with the probabilities are
+    // large: a token with large values that nobody attends to must not take bits from the others of its tile.  It falls
+    // back when all scales of a tile are far below the limit: nor from the tiles after it (value of 40 000 among values
+    // of 1/16, probability 0: 3e-3 of the output when ks followed the scales alone).
+    auto fit_value_exponent = [&](uint32_t s2, auto&& load, const Frag& fa, const Frag& fb) {
+        const bool high = any_above(s2, value_limit);
+        if (!high && (ks <= 0 || any_above(s2, (uint32_t)(ks + kValueTop<BITS> - kValueWindow + 15) * 0x04000400u))) return;
+        const int want = wanted_exponent(s2);
+        int next = max(want, 0);
+        if (high) {
+            next = ks_set && ks >= 0 ? ks : want > -kValueWindow ? 0 : want;
+            if (want > next) {
+                half2v sv[NS][4];
+                load(sv);
+                float top = 0.f;
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const half2v p2 = is_lo ? fa.p[r] : fb.p[r];
+                        top = fmaxf(top, fmaxf((float)p2[0] * (float)sv[s][r][0], (float)p2[1] * (float)sv[s][r][1]));
+                    }
+                if (__any(head < n_live && top > kProductLimit * __uint_as_float((uint32_t)(127 + next) << 23))) next = want;
+            }
+        }
+        set_value_exponent(next);
     };
 
     // raw key sums of a tile for this lane's four tokens; returns their factor
@@ -631,7 +663,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
         softmax(x, cx, zk, 0xfu, pv, rescale_acc);
         Frag fa, fb, z;
         split_probabilities(pv, fa, fb);
-        if (any_above(s2, value_limit)) adjust_value_exponent(s2);
+        fit_value_exponent(s2, [&](half2v (&to)[NS][4]) { gather_scales(sl + kScaleOff + 512, to); }, fa, fb);
         half2v sv[NS][4];
         gather_scales(sl + kScaleOff + 512, sv);
         gather_pairs(sl + kScaleOff + 768, n & 3, z.p);
@@ -777,17 +809,22 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
                 if (t0 < n_vq_here) s2 |= *reinterpret_cast<const uint16_t*>(srow + 2 * i0);
                 if (t1 < n_vq_here) s2 |= (uint32_t)*reinterpret_cast<const uint16_t*>(srow + 2 * i1) << 16;
             }
-            if (any_above(s2, value_limit)) adjust_value_exponent(s2);
+            auto load_scales = [&](half2v (&to)[NS][4]) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int s = 0; s < NS; ++s) {
+                        const int t0 = kb * 8 + 2 * r, g = HP == 2 ? my_group : HP == 4 ? 2 * s + my_group : s;
+                        to[s][r] = half2_of(entry(srow, t0, g) | entry(srow, t0 + 1, g) << 16);
+                    }
+            };
+            fit_value_exponent(s2, load_scales, fa, fb);
             half2v sv[NS][4];
+            load_scales(sv);
             Frag z;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int t0 = kb * 8 + 2 * r;
-#pragma unroll
-                for (int s = 0; s < NS; ++s) {
-                    const int g = HP == 2 ? my_group : HP == 4 ? 2 * s + my_group : s;
-                    sv[s][r] = half2_of(entry(srow, t0, g) | entry(srow, t0 + 1, g) << 16);
-                }
                 z.r[r] = entry(zrow, t0, n & 3) | entry(zrow, t0 + 1, n & 3) << 16;
             }
             zsum = __builtin_amdgcn_mfma_f32_16x16x32_f16(z.h, fb.h, zsum, 0, 0, 0);

@@ -196,3 +196,29 @@ def test_tiles_large_window(hq, hkv, bits, quantised):
     assert cache.c.n_kq == quantised
     err = np.abs(gh.pick_heads(gh.gpu_attention(layout, cache, q, w.softmax_scale), w, heads) - ref).max()
     assert err <= 1e-4 * scale, f"{err:.3e} against {1e-4 * scale:.3e}"
+
+
+@pytest.mark.parametrize("path", [kivi.KIVI_DECODE_MFMA, kivi.KIVI_DECODE_MFMA_TWO], ids=["mfma", "mfma2"])
+@pytest.mark.parametrize("outlier,size,every", [(40000, 2.0 ** -4, 5000), (1000, 2.0 ** -8, 5000), (40000, 2.0 ** -4, 32), (1000, 2.0 ** -8, 320)])
+@pytest.mark.parametrize("hq,hkv,bits,group,policy", [(8, 2, 2, 32, W), (16, 2, 4, 32, W), (6, 2, 2, 32, A), (10, 2, 4, 64, W), (4, 2, 4, 32, W)])
+def test_value_outliers(hq, hkv, bits, group, policy, outlier, size, every, path):
+    """Tokens with very large values and no probability take no bits from the others.  Tolerance: p (z + s code) of an
+    ordinary token keeps 21 bits of p and 22 of the product, and sums add no more than 2^-22 of the largest share:
+    2^-20 of the largest ordinary value."""
+    gh.require_gpu()
+    tokens = 1500
+    w = scaled(CONFIGS["mistral_gqa"], name="outliers", batch=1, n_q_heads=hq, n_kv_heads=hkv, bits=bits, group=group, residual=128, seed=3 * hq + bits)
+    print(f"case value outliers hq={hq} hkv={hkv} bits={bits} G={group} policy={policy} {outlier} among {size} every {every} path={path}", flush=True)
+    k, v, q = workloads.keys(w, tokens), workloads.values(w, tokens), workloads.queries(w)
+    q = np.broadcast_to(q[:, :1] * np.float16(0.3), q.shape).copy()          # all heads alike, so that one key suits no head
+    v = (v.astype(np.float32) * size).astype(np.float16)
+    largest = float(np.abs(v.astype(np.float32)).max())
+    for t in range(7, tokens - 128, every):
+        k[:, :, t] = -40 * np.sign(q[0, 0].astype(np.float32))
+        v[:, :, t] = outlier * np.sign(v[:, :, t].astype(np.float32))
+    heads = [(0, h) for h in range(hkv)]
+    oc = gh.oracle_cache_for_heads(w, k, v, heads, "window" if policy == W else "alg1")
+    ref = gh.oracle_attention_for_heads(w, oc, q, heads)
+    layout, cache = gh.gpu_prefill(w, k, v, policy, path)
+    err = np.abs(gh.pick_heads(gh.gpu_attention(layout, cache, q, w.softmax_scale), w, heads) - ref).max()
+    assert err <= 2.0 ** -20 * largest, f"{err:.3e} against {2.0 ** -20 * largest:.3e}"
