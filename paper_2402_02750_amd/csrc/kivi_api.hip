@@ -543,7 +543,6 @@ int ragged_plan(const kivi_layout_t* l, const kivi_seq_state_t* st, size_t works
         const RaggedCut cut = cut_ragged(steps, l->n_kv_heads, std::min(tiles_resident_ragged(l->bits, rep_launch), kMaxSlices), stride, tables);
         p.axis_len = cut.axis.len;
         p.axis_rem = cut.axis.rem;
-        p.unit_wgs = cut.whole_units ? 1 : 0;
         plan.unit_table = state_ints + (size_t)cut.workgroups * RaggedCut::kWords;
         p.n_slices = (int32_t)cut.workgroups;
         p.part_stride = stride;

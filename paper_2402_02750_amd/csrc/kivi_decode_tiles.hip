@@ -261,7 +261,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
     const int n_row_wgs = p.row_wgs;                                   // the first workgroups: fp16 rows, row_split per unit
     const int wg = (int)blockIdx.x - n_row_wgs;
     // The axis is one unit, cut into unit_wgs intervals (workgroup = unit * unit_wgs + interval), or, with unit_wgs = 0,
-    // all units one after the other.  kQuantisedRagged: always all units; unit_wgs = 1: no unit is cut.
+    // all units one after the other (kQuantisedRagged: always).
     const StepAxis axis{p.axis_len, p.axis_rem};
     const int unit_wgs = p.unit_wgs;
     // steps of a unit, and where they begin on the axis
@@ -339,10 +339,9 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
     float4v acc[8];                    // value code sums: acc[u][i] = channel 16 u + 4 kb + i, column n
     float4v zsum;                      // value zero-point sums: zsum[i] = channel group i, column n
     float mref, l_lane;                // reference (log2 domain) of the probabilities; this lane's sum
-    int n_live;                        // query heads of the unit (the columns of idle slots hold a query of zeros)
     int ks;                            // value scales enter as s 2^-ks
     bool ks_set;
-    uint32_t value_limit;              // fp16 pair 2^(ks + kValueTop)
+    uint32_t value_limit;              // fp16 pair: tiles with larger scales go to fit_value_exponent; below 2^(ks + kValueTop), or 0 with ks > 0
     half2v qz[4][4], qk[4][4], qa[4][4];   // query: q 2^a; times 1 / position factor; the same, 0 in the hi columns
     float c_code, c_zero;              // logit (log2 domain) = code sum * c_code + zero sum * c_zero
 
@@ -356,10 +355,9 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
         ks_set = false;
         value_limit = 0;
     };
-    // query operands; raw[cb]: channels 32 cb + 8 kb .. + 7 of this lane's head
-    auto set_query = [&](const half8 (&raw)[4], int live) {
+    // query operands; raw[cb]: channels 32 cb + 8 kb .. + 7 of this lane's head (idle slots repeat the last head)
+    auto set_query = [&](const half8 (&raw)[4]) {
         typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
-        n_live = live;
         ushort2v top = {0, 0};                                          // |q| as integers
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb)
@@ -372,7 +370,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
         float mx = (float)__builtin_bit_cast(_Float16, (unsigned short)max(top[0], top[1]));
         mx = fmaxf(mx, __shfl_xor(mx, 16));
         mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const bool on = head < live && mx > 0.f;
+        const bool on = mx > 0.f;
         // 2^a mx in [2^8, 2^9) (a query below 2^-20 stays smaller), as two factors that fp16 holds
         const int a = on ? min(kQueryExp + 127 - (int)(__float_as_uint(mx) >> 23), 28) : 0, a1 = a / 2;
         const _Float16 up1 = on ? (_Float16)__uint_as_float((uint32_t)(127 + a1) << 23) : (_Float16)0.f;
@@ -498,6 +496,12 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
         const int e = (int)(__float_as_uint(mx) >> 23) - 126;              // mx < 2^e (mx = 0: e = -126)
         return __builtin_amdgcn_readfirstlane(max(e - kValueTop<BITS>, -24));
     };
+    // two times the largest fp16 below 2^(k + kValueTop), at most the largest finite number
+    auto top_scale = [&](int k) -> uint32_t {
+        const int top = k + kValueTop<BITS> + 15;                           // biased fp16 exponent
+        const uint32_t lim = top >= 31 ? 0x7BFFu : top <= 0 ? 0u : (uint32_t)(top << 10) - 1;
+        return lim | lim << 16;
+    };
     auto set_value_exponent = [&](int want) {
         if (ks_set) {
             const float f = __uint_as_float((uint32_t)(127 + ks - want) << 23);
@@ -506,10 +510,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
         }
         ks = want;
         ks_set = true;
-        // largest fp16 below 2^(ks + kValueTop), at most the largest finite number
-        const int top = ks + kValueTop<BITS> + 15;                          // biased fp16 exponent
-        const uint32_t lim = top >= 31 ? 0x7BFFu : top <= 0 ? 0u : (uint32_t)(top << 10) - 1;
-        value_limit = lim | lim << 16;
+        value_limit = ks > 0 ? 0 : top_scale(ks);
     };
     auto max_pairs = [&](uint32_t a, uint32_t b) -> uint32_t {              // non-negative fp16 compare as integers
         typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
@@ -534,8 +535,12 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
     // back when all scales of a tile are far below the limit: nor from the tiles after it (value of 40 000 among values
     // of 1/16, probability 0: 3e-3 of the output when ks followed the scales alone).
     auto fit_value_exponent = [&](uint32_t s2, auto&& load, const Frag& fa, const Frag& fb) {
-        const bool high = any_above(s2, value_limit);
-        if (!high && (ks <= 0 || any_above(s2, (uint32_t)(ks + kValueTop<BITS> - kValueWindow + 15) * 0x04000400u))) return;
+        if (!any_above(s2, value_limit)) return;
+        bool high = true;
+        if (ks > 0) {
+            high = any_above(s2, top_scale(ks));
+            if (!high && any_above(s2, (uint32_t)(ks + kValueTop<BITS> - kValueWindow + 15) * 0x04000400u)) return;
+        }
         const int want = wanted_exponent(s2);
         int next = max(want, 0);
         if (high) {
@@ -551,7 +556,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
                         const half2v p2 = is_lo ? fa.p[r] : fb.p[r];
                         top = fmaxf(top, fmaxf((float)p2[0] * (float)sv[s][r][0], (float)p2[1] * (float)sv[s][r][1]));
                     }
-                if (__any(head < n_live && top > kProductLimit * __uint_as_float((uint32_t)(127 + next) << 23))) next = want;
+                if (__any(top > kProductLimit * __uint_as_float((uint32_t)(127 + next) << 23))) next = want;
             }
         }
         set_value_exponent(next);
@@ -872,7 +877,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
         const int live = live_heads(u);
         int parts = 0, mine = 0;
         const int steps = steps_of(u);
-        if (unit_wgs > 0) {
+        if (!kRagged && unit_wgs > 0) {
             parts = unit_wgs;
             mine = wg - u * unit_wgs;
         } else if (steps > 0) {
@@ -1074,7 +1079,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
                 for (int cb = 0; cb < 4; ++cb) raw[cb] = *reinterpret_cast<const half8*>(src + cb * 32);
                 load_key_rows(unit, tt, kr);
                 load_value_rows(unit, tt, vr);
-                set_query(raw, live);
+                set_query(raw);
                 float x[4], pv[4];
                 row_logits(kr, x);
                 uint32_t alive = 0;
@@ -1105,7 +1110,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb) raw[cb] = *reinterpret_cast<const half8*>(src + cb * 32);
             reset_state();
-            set_query(raw, live);
+            set_query(raw);
             for (int tile = tile0; tile < p.plan.tiles_total; tile += kWaves * p.row_split) general_tile(u, tile);
             leave_unit(u, true, write_acc);
             return;
@@ -1176,7 +1181,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb) raw[cb] = *reinterpret_cast<const half8*>(&sm_q[q_buf][min(head, live_heads(u) - 1) * 256 + cb * 64 + kb * 16]);
             reset_state();
-            set_query(raw, live_heads(u));
+            set_query(raw);
         }
         if (left > 0) copy_query(u + 1, q_buf ^ 1);
         if constexpr (kRagged) copy_rows_part(u);

@@ -129,7 +129,7 @@ struct DecodeParams {
     // decode_tiles_kernel: its first row_wgs workgroups hold the units' fp16 rows, row_split per unit; interval g of the axis of
     // all-quantised steps (of one unit, cut into unit_wgs intervals; unit_wgs = 0: of all units) has axis_len
     // steps, one more if g < axis_rem.  Batches of different lengths: wave_desc[4 g] = {first unit, first step in it,
-    // steps, 0} of workgroup g, unit_parts[b] = steps before sequence b; unit_wgs = 1: whole units (kivi_tiles_plan.h)
+    // steps, 0} of workgroup g, unit_parts[b] = steps before sequence b (kivi_tiles_plan.h)
     int32_t row_wgs, row_split, unit_wgs, axis_len, axis_rem;
 };
 

@@ -40,7 +40,7 @@ inline int64_t shortest_interval(int64_t n, int max_parts) { return (n - 1) / (m
 struct RaggedCut {
     int64_t workgroups = 0;
     StepAxis axis{1, 0};
-    bool whole_units = false;          // room for a single part: every workgroup takes whole units
+    bool whole_units = false;          // room for a single part: every workgroup takes whole units, and the axis is one interval
     // {first unit, first step in it, steps, 0} per workgroup, then the steps before each sequence
     static constexpr int kWords = 4;
 };
@@ -62,31 +62,37 @@ inline RaggedCut cut_ragged(const std::vector<int32_t>& steps, int n_kv_heads, i
     // that counts: the longer intervals come first, so the last units meet the shorter ones only
     if (!cut.whole_units && cut.workgroups > max_parts)
         cut.workgroups = std::max<int64_t>(max_parts, std::min(cut.workgroups, total / shortest_interval(max_steps, max_parts)));
-    cut.axis = StepAxis{(int32_t)(total / cut.workgroups), (int32_t)(total % cut.workgroups)};
+    cut.axis = cut.whole_units ? StepAxis{0x3fffffff, 0} : StepAxis{(int32_t)(total / cut.workgroups), (int32_t)(total % cut.workgroups)};
 
     const size_t base = out.size();
     out.resize(base + (size_t)cut.workgroups * RaggedCut::kWords + steps.size(), 0);
     int32_t* desc = out.data() + base;
     int32_t* before = desc + (size_t)cut.workgroups * RaggedCut::kWords;
-    int64_t cum = 0, g = 0;
+    int32_t cum = 0;
     for (size_t b = 0; b < steps.size(); ++b) {
-        const int64_t n = steps[b], unit0 = (int64_t)b * n_kv_heads, end = cum + n * n_kv_heads;
-        before[b] = (int32_t)cum;
-        for (; g < cut.workgroups; ++g) {
-            int64_t begin = cut.axis.start((int)g), length = cut.axis.start((int)g + 1) - begin;
-            if (cut.whole_units) {
-                const int64_t u0 = g * units / cut.workgroups, u1 = (g + 1) * units / cut.workgroups;
-                if (u0 >= unit0 + n_kv_heads) break;
-                begin = cum + (u0 - unit0) * n;
-                length = 0;
-                for (int64_t u = u0; u < u1; ++u) length += steps[(size_t)(u / n_kv_heads)];
+        before[b] = cum;
+        cum += steps[b] * n_kv_heads;
+    }
+    // (a walk without divisions: a step waits for this table)
+    const StepAxis whole{(int32_t)(units / cut.workgroups), (int32_t)(units % cut.workgroups)};
+    size_t b = 0;
+    int32_t unit = 0, head = 0, first = 0;          // where the interval begins; head: of sequence b
+    for (int32_t g = 0; g < (int32_t)cut.workgroups; ++g, desc += RaggedCut::kWords) {
+        desc[0] = unit;
+        desc[1] = first;
+        int32_t left = cut.axis.len + (g < cut.axis.rem), length = left;
+        if (cut.whole_units) {
+            left = length = 0;
+            for (int32_t n = whole.len + (g < whole.rem); n > 0; --n, ++unit) {
+                length += steps[b];
+                if (++head == n_kv_heads) { head = 0; ++b; }
             }
-            if (begin >= end) break;
-            desc[4 * g + 0] = (int32_t)(unit0 + (begin - cum) / n);
-            desc[4 * g + 1] = (int32_t)((begin - cum) % n);
-            desc[4 * g + 2] = (int32_t)length;
         }
-        cum = end;
+        desc[2] = length;
+        for (first += left; b < steps.size() && first >= steps[b]; ++unit) {
+            first -= steps[b];
+            if (++head == n_kv_heads) { head = 0; ++b; }
+        }
     }
     return cut;
 }

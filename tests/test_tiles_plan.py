@@ -22,7 +22,7 @@ int check(const std::vector<int32_t>& steps, int heads, int max_wgs, int rows, i
     const int32_t* before = table.data() + (size_t)wgs * 4;
     auto axis_start = [&](int u) { return before[u / heads] + u % heads * steps[u / heads]; };
     auto first_of = [&](int u) { return cut.axis.owner(axis_start(u)); };
-    auto parts_of = [&](int u) { return cut.whole_units ? 1 : cut.axis.owner(axis_start(u) + steps[u / heads] - 1) - first_of(u) + 1; };
+    auto parts_of = [&](int u) { return cut.axis.owner(axis_start(u) + steps[u / heads] - 1) - first_of(u) + 1; };
     parts.assign(units, 0);
     done.assign(units, 0);
     for (int g = 0; g < wgs; ++g) {                     // as the kernel walks its interval
