@@ -15,8 +15,8 @@
 //           hi columns (operand = RN(q' s)) and A = q' in the lo columns (operand = the remainder,
 //           which is exact unless it leaves fp16's range).  q' is the query times a power of two
 //           that puts its largest element into [2^8, 2^9): with s < 64 nothing overflows and the
-//           remainder keeps 2^-33 of the largest product.  A tile with a larger scale (wave-uniform
-//           branch) takes s 2^-9.
+//           remainder keeps 2^-33 of the largest product.  In a tile with a larger scale (wave-uniform
+//           branch) the heads whose products would overflow take s 2^-9.
 //   logits: a column pair's hi and lo sums meet by one rotation inside the 16 lanes of a row;
 //           every lane then has eight logits of its head.  Softmax against a running maximum with
 //           4 bits of slack: the state is rescaled only when a logit passes the reference by 2^4.
@@ -85,14 +85,15 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kSlack = 4;                      // log2 headroom of the running softmax reference
 constexpr int kQueryExp = 8;                   // largest |q'| lies in [2^8, 2^9)
 constexpr uint32_t kKeyScaleLimit = 0x54005400u;       // two times fp16 64.0
-constexpr int kKeyScaleShift = 9;              // a tile with a larger key scale takes s 2^-9
+constexpr int kKeyScaleShift = 9;              // a head for which such a tile has products above kProductLimit takes s 2^-9
+constexpr uint32_t kProductLimit = 0x78007800u;        // two times fp16 2^15
 // Value side: p' = p 2^kProbExp, value scales taken as s 2^-ks with s 2^-ks < 2^kValueTop, so that
 // p' s < 2^16 with the slack.  4-bit codes: scales are 5 times smaller for the same data.  Scales down to 2^-kValueWindow of
-// that need no shift.  Larger ones are taken as they are too while their products stay below 2^11 (kProductLimit).
+// that need no shift.  Larger ones are taken as they are too while their products stay below 2^11 (kValueProductLimit).
 template <int BITS> constexpr int kProbExp = BITS == 2 ? 8 : 11;
 template <int BITS> constexpr int kValueTop = BITS == 2 ? 3 : 0;
 constexpr int kValueWindow = 7;
-constexpr float kProductLimit = 2048.f;
+constexpr float kValueProductLimit = 2048.f;
 
 template <int CTRL>
 __device__ __forceinline__ float dpp(float x) {
@@ -556,16 +557,30 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
                         const half2v p2 = is_lo ? fa.p[r] : fb.p[r];
                         top = fmaxf(top, fmaxf((float)p2[0] * (float)sv[s][r][0], (float)p2[1] * (float)sv[s][r][1]));
                     }
-                if (__any(top > kProductLimit * __uint_as_float((uint32_t)(127 + next) << 23))) next = want;
+                if (__any(top > kValueProductLimit * __uint_as_float((uint32_t)(127 + next) << 23))) next = want;
             }
         }
         set_value_exponent(next);
     };
 
-    // raw key sums of a tile for this lane's four tokens; returns their factor
+    // Raw key sums of a tile for this lane's four tokens; returns their factor.  big: the tile has scales past the limit.
+    // Where the query makes such a channel's products leave fp16's range, all scales enter times 2^-kKeyScaleShift
+    // for that head (small ones then lose bits, far below the large product); a channel that the query hardly
+    // looks at costs the others nothing.
     auto key_products = [&](const uint32_t* w, Frag (&s)[4], bool big, float (&x)[4]) -> float {
+        bool shift = false;
         if (big) {
-            const half2v f = {(_Float16)(1.f / (1 << kKeyScaleShift)), (_Float16)(1.f / (1 << kKeyScaleShift))};
+            uint32_t top = kProductLimit;
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) top = max_pairs(top, __builtin_bit_cast(uint32_t, qk[cb][r] * s[cb].p[r]) & 0x7FFF7FFFu);
+            constexpr uint64_t kHeadLanes = HP == 8 ? 0x0101010101010101ull : HP == 4 ? 0x1111111111111111ull : 0x5555555555555555ull;
+            int h = head;
+            asm volatile("" : "+v"(h));                                    // (else the mask is kept in registers for all tiles)
+            shift = (__builtin_amdgcn_ballot_w64(top != kProductLimit) & (kHeadLanes << h)) != 0;
+            const _Float16 f1 = shift ? (_Float16)(1.f / (1 << kKeyScaleShift)) : (_Float16)1.f;
+            const half2v f = {f1, f1};
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
@@ -584,7 +599,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
             d1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(key_fragment<BITS>(w, cb, 1), f.h, d1, 0, 0, 0);
         }
         own_half(d0, d1, true, x);
-        return big ? c_code * (float)(1 << kKeyScaleShift) : c_code;
+        return shift ? c_code * (float)(1 << kKeyScaleShift) : c_code;
     };
     auto query_frag = [&](int cb) -> half8 {
         Frag f;

@@ -222,3 +222,31 @@ def test_value_outliers(hq, hkv, bits, group, policy, outlier, size, every, path
     layout, cache = gh.gpu_prefill(w, k, v, policy, path)
     err = np.abs(gh.pick_heads(gh.gpu_attention(layout, cache, q, w.softmax_scale), w, heads) - ref).max()
     assert err <= 2.0 ** -20 * largest, f"{err:.3e} against {2.0 ** -20 * largest:.3e}"
+
+
+@pytest.mark.parametrize("large,small,looks", [(1000, 2.0 ** -5, 0), (1000, 2.0 ** -5, 1), (4000, 2.0 ** -3, 0)])
+@pytest.mark.parametrize("hq,hkv,bits,group,policy", [(8, 2, 2, 32, W), (16, 2, 4, 32, W), (6, 2, 2, 32, A), (10, 2, 4, 64, W), (4, 2, 4, 32, W)])
+def test_key_outliers(hq, hkv, bits, group, policy, large, small, looks):
+    """A key channel 2^15 times larger than the others, at which the queries hardly look, takes no bits from them, also where
+    another head of the group looks at it (`looks`).  Tolerance as in test_value_outliers: logits of up to about 4 carry
+    2^-22 of their largest product, and fp32's rounding, into the probabilities."""
+    gh.require_gpu()
+    tokens = 1500
+    w = scaled(CONFIGS["mistral_gqa"], name="keyoutliers", batch=1, n_q_heads=hq, n_kv_heads=hkv, bits=bits, group=group, residual=128, seed=5 * hq + bits)
+    print(f"case key outliers hq={hq} hkv={hkv} bits={bits} G={group} policy={policy} {large} among {small} looks={looks}", flush=True)
+    rng = np.random.default_rng(hq + bits)
+    k = (rng.standard_normal((1, hkv, tokens, 128)) * small).astype(np.float16)
+    k[..., 5] = (rng.uniform(-1, 1, (1, hkv, tokens)) * large).astype(np.float16)
+    v, q = workloads.values(w, tokens), (rng.standard_normal((1, hq, 128)) / small).astype(np.float16)
+    q[..., 5] = q[..., 5] * np.float16(small / large)
+    if looks:                                           # the first head of every group
+        q[:, ::w.q_per_kv, 5] = 0.01
+    heads = [(0, h) for h in range(hkv)]
+    oc = gh.oracle_cache_for_heads(w, k, v, heads, "window" if policy == W else "alg1")
+    ref = gh.oracle_attention_for_heads(w, oc, q, heads)
+    layout, cache = gh.gpu_prefill(w, k, v, policy, kivi.KIVI_DECODE_MFMA)
+    err = np.abs(gh.pick_heads(gh.gpu_attention(layout, cache, q, w.softmax_scale), w, heads) - ref)
+    if looks:
+        err = err[:, 1:]                                # (the looking head's probabilities hang on logits of thousands)
+    bound = 2.0 ** -20 * float(np.abs(v.astype(np.float32)).max())
+    assert err.max() <= bound, f"{err.max():.3e} against {bound:.3e}"
