@@ -136,13 +136,17 @@ __device__ __forceinline__ int table(const int32_t* base, int i) {
     return reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(base))[i];
 }
 
-// Asynchronous copy of 16 bytes per lane: lane l's bytes land at LDS offset lds + 16 l.
+// Asynchronous copy of 16 bytes per lane: lane l's bytes land at LDS offset lds + 16 l.  (m0 holds the offset; it is a reserved
+// register, so the compiler warns that it will not keep a value in it across the statement: nor shall it.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void copy_to_lds(const void* base, uint32_t lane_offset, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(lane_offset), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(lane_offset), "s"(base) : "memory", "m0");
 }
 __device__ __forceinline__ void copy_to_lds(const void* lane_ptr, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds), "v"(lane_ptr) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds), "v"(lane_ptr) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 // Outputs (two channels at po, two 64 channels further) of the parts first, first + 1, ..., 0 past the last part: all
 // device-scope loads are issued before the first is used.  (Two pairs apart and not four channels in a row, so that a
 // wavefront's load covers whole memory segments.)  `first` is wave-uniform: what is not there is not loaded.
