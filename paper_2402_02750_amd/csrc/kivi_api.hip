@@ -294,11 +294,10 @@ int head_split_shift(const kivi_layout_t* l, const SplitPlan& plan, int path, bo
 // heads).  decode_tiles_kernel takes two neighbouring runs in one pass over the cache: its eight head slots cost a
 // tile 15 % more than four.
 constexpr int kWideGroupRun = 4;
-int wide_group_width(const kivi_layout_t*) { return kWideGroupRun; }
 int wide_group_runs(const kivi_layout_t* l, int path, bool two_launches) {
     const int rep_total = l->n_q_heads / l->n_kv_heads;
     if (path != KIVI_DECODE_MFMA || two_launches || rep_total <= kMaxRep) return 1;
-    return ceil_div(rep_total, wide_group_width(l));
+    return ceil_div(rep_total, kWideGroupRun);
 }
 
 // Launches of one attention call: a group wider than kMaxRep heads takes one pass per kMaxRep heads, except in the
@@ -378,7 +377,7 @@ int enqueue_attention(const kivi_layout_t* l, const kivi_cache_t* c, const void*
         // a group wider than kMaxRep heads in the single-launch form: its runs of kWideGroupRun heads are
         // units of ONE launch (they read the same cache, which the caches serve after the first)
         p.q_head0 = 0;
-        p.rep_here = 2 * wide_group_width(l);             // two neighbouring runs share one pass
+        p.rep_here = 2 * kWideGroupRun;             // two neighbouring runs share one pass
         p.rep_variant = p.rep_here;
         p.head_groups = ceil_div(rep_total, p.rep_here);
         return hip_status(launch_decode_tiles(p, hs));

@@ -364,8 +364,7 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
     const int kg = CS ? p.kg_shift : 0;
     const ValueScaleLane vlane = CS ? value_scale_lane<CS>(lane, kg) : ValueScaleLane{0, 0u};
 
-    const int rep = p.rep_here, rep_total = p.n_q_heads / p.n_kv_heads;     // rep == REP
-    auto first_q_head = [&](int u) -> int { return (u % p.n_kv_heads) * rep_total + p.q_head0; };
+    auto first_q_head = [&](int u) -> int { return (u % p.n_kv_heads) * REP; };
     auto batch_of = [&](int u) -> int { return u / p.n_kv_heads; };
     // chunks per unit on this launch's cost axis: all-quantised / with fp16 rows
     const int n_a = p.plan.n_splits_a, n_b = kQOnly ? 0 : p.plan.n_splits_b;
@@ -528,7 +527,7 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
         const int b = batch_of(u);
 #pragma unroll
         for (int k = 0; k < kIdx; ++k) {
-            const int idx = min(tid + 256 * k, rep * kHeadDim - 1);  // unconditional loads (clamped)
+            const int idx = min(tid + 256 * k, REP * kHeadDim - 1);  // unconditional loads (clamped)
             q_pre[k] = p.q[((int64_t)b * p.n_q_heads + hq0 + idx / kHeadDim) * kHeadDim + idx % kHeadDim];
         }
     };
@@ -538,7 +537,7 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
         const int b = batch_of(u);
 #pragma unroll
         for (int k = 0; k < kIdx; ++k) {
-            const int idx = min(tid + 256 * k, rep * kHeadDim - 1);  // unconditional loads (clamped)
+            const int idx = min(tid + 256 * k, REP * kHeadDim - 1);  // unconditional loads (clamped)
             const int64_t row = ((int64_t)b * p.n_q_heads + hq0 + idx / kHeadDim) * cpu;
             pre_m[k] = p.part_ml[row * 2 + 0];
             pre_l[k] = p.part_ml[row * 2 + 1];
@@ -670,9 +669,9 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
         if constexpr (kQOnly) {
 #pragma unroll
             for (int k = 0; k < kIdx; ++k)
-                if (tid + 256 * k < rep * kHeadDim) finish_element(tid + 256 * k, pre_m[k], pre_l[k], pre_o[k]);
+                if (tid + 256 * k < REP * kHeadDim) finish_element(tid + 256 * k, pre_m[k], pre_l[k], pre_o[k]);
         } else {
-            for (int idx = tid; idx < rep * kHeadDim; idx += 256) finish_element(idx, -INFINITY, 0.f, 0.f);
+            for (int idx = tid; idx < REP * kHeadDim; idx += 256) finish_element(idx, -INFINITY, 0.f, 0.f);
         }
         if (n_parts > 1) {
             // The last workgroup to finish this unit merges the parts.  How the parts are published:
@@ -696,7 +695,7 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
             }
             __syncthreads();
             if (sm_last) {
-                for (int idx = tid; idx < rep * kHeadDim; idx += 256) {
+                for (int idx = tid; idx < REP * kHeadDim; idx += 256) {
                     const int hh = idx / kHeadDim, c = idx % kHeadDim;
                     const int64_t row = (int64_t)b * p.n_q_heads + hq0 + hh;
                     const float* ml = p.part_ml + row * row_stride * 2;
@@ -748,12 +747,12 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
 #pragma unroll
             for (int k = 0; k < kIdx; ++k) {           // the query was requested one unit ahead
                 const int i = tid + 256 * k;
-                if (i < REP * kHeadDim) stage(i, i / kHeadDim < rep ? p.softmax_scale * __half2float(q_pre[k]) : 0.f);
+                if (i < REP * kHeadDim) stage(i, p.softmax_scale * __half2float(q_pre[k]));
             }
         } else {
             for (int i = tid; i < REP * kHeadDim; i += 256) {
                 const int hh = i / kHeadDim, c = i % kHeadDim;
-                stage(i, hh < rep ? p.softmax_scale * __half2float(p.q[((int64_t)b * p.n_q_heads + hq0 + hh) * kHeadDim + c]) : 0.f);
+                stage(i, p.softmax_scale * __half2float(p.q[((int64_t)b * p.n_q_heads + hq0 + hh) * kHeadDim + c]));
             }
         }
         unit_barrier();
@@ -947,7 +946,7 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
                         }
 #pragma unroll
                         for (int hh = 0; hh < REP; ++hh) {
-                            const half8 qh = hh < rep ? *reinterpret_cast<const half8*>(p.q + qrow + hh * kHeadDim + seg * 8) : half8{};
+                            const half8 qh = *reinterpret_cast<const half8*>(p.q + qrow + hh * kHeadDim + seg * 8);
 #pragma unroll
                             for (int j = 0; j < RB; ++j) {
                                 const int tl = (j0 + j) * 4 + row;
@@ -968,11 +967,9 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
             softmax_step(cnt);
             wave_lds_sync();
             // ---- phase 3: outputs ----
-            {
-                constexpr int HG = REP, h0 = 0;
-                float racc[HG][8];
+            float racc[REP][8];
 #pragma unroll
-            for (int hh = 0; hh < HG; ++hh)
+            for (int hh = 0; hh < REP; ++hh)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) racc[hh][e] = 0.f;
             for (int i = 0; i < cnt; ++i) {
@@ -1013,8 +1010,8 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
                             const int tl = (j0 + j) * 4 + (lane >> 4);
                             const bool use = tl >= n_vq_here && tt + tl < p.length;
 #pragma unroll
-                            for (int hh = 0; hh < HG; ++hh) {
-                                const float pt = use ? wl.lr[2 * (h0 + hh)][i * kTileTokens + tl] : 0.f;
+                            for (int hh = 0; hh < REP; ++hh) {
+                                const float pt = use ? wl.lr[2 * hh][i * kTileTokens + tl] : 0.f;
 #pragma unroll
                                 for (int e = 0; e < 8; ++e) racc[hh][e] = fmaf(pt, (float)vr[j][e], racc[hh][e]);
                             }
@@ -1025,7 +1022,7 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
             // lane (seg, row) holds channels seg*8.. of every 4th row: add the four row groups into LDS
             wave_lds_sync();
 #pragma unroll
-            for (int hh = 0; hh < HG; ++hh) {
+            for (int hh = 0; hh < REP; ++hh) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     float rr = racc[hh][e];
@@ -1033,14 +1030,13 @@ __global__ __launch_bounds__(256, OCC) void decode_mfma_kernel(DecodeParams p) {
                     racc[hh][e] = rr;
                 }
                 if (lane < 16) {
-                    float* dst = &sm_r[wave][h0 + hh][lane * 8];
+                    float* dst = &sm_r[wave][hh][lane * 8];
                     float4 a = *reinterpret_cast<float4*>(dst), c = *reinterpret_cast<float4*>(dst + 4);
                     a.x += racc[hh][0]; a.y += racc[hh][1]; a.z += racc[hh][2]; a.w += racc[hh][3];
                     c.x += racc[hh][4]; c.y += racc[hh][5]; c.z += racc[hh][6]; c.w += racc[hh][7];
                     *reinterpret_cast<float4*>(dst) = a;
                     *reinterpret_cast<float4*>(dst + 4) = c;
                 }
-            }
             }
             wave_lds_sync();
             if (owns_new) *reinterpret_cast<uint4*>(new_dst) = new_row;
@@ -1205,7 +1201,6 @@ __global__ __launch_bounds__(256, OCC) void decode_wave_units_kernel(DecodeParam
     WL& wl = sm_w[wave];
     const int kg = CS ? p.kg_shift : 0;
     const ValueScaleLane vlane = CS ? value_scale_lane<CS>(lane, kg) : ValueScaleLane{0, 0u};
-    const int rep = p.rep_here, rep_total = p.n_q_heads / p.n_kv_heads;
     const int units = p.batch * p.n_kv_heads;
     const int n_waves = (int)gridDim.x * 4, gw = (int)blockIdx.x * 4 + wave;
     // all-quantised tiles of a unit (>= 1): the plan's, or -- a batch of different lengths -- the
@@ -1223,7 +1218,7 @@ __global__ __launch_bounds__(256, OCC) void decode_wave_units_kernel(DecodeParam
         sl_count = __builtin_amdgcn_readfirstlane(p.wave_desc[4 * gw + 2]);
     }
 
-    auto first_q_head = [&](int u) -> int { return (u % p.n_kv_heads) * rep_total + p.q_head0; };
+    auto first_q_head = [&](int u) -> int { return (u % p.n_kv_heads) * REP; };
     auto batch_of = [&](int u) -> int { return u / p.n_kv_heads; };
 
     uint32_t kw[kSlots][kLaneWords], vw[kSlots][kLaneWords];
@@ -1292,7 +1287,7 @@ __global__ __launch_bounds__(256, OCC) void decode_wave_units_kernel(DecodeParam
         const int64_t row0 = (int64_t)batch_of(u) * p.n_q_heads + first_q_head(u);
 #pragma unroll
         for (int k = 0; k < kIdx; ++k) {
-            const int64_t row = row0 + min(k >> 1, rep - 1);
+            const int64_t row = row0 + (k >> 1);
             const int c = lane + 64 * (k & 1);
             q_pre[k] = p.q[row * kHeadDim + c];
             pre_m[k] = p.part_ml[row * row_stride * 2 + 0];
@@ -1361,7 +1356,7 @@ __global__ __launch_bounds__(256, OCC) void decode_wave_units_kernel(DecodeParam
 #pragma unroll
         for (int k = 0; k < kIdx; ++k) {
             const int hh = k >> 1, c = lane + 64 * (k & 1);
-            const float x = hh < rep ? p.softmax_scale * __half2float(q_pre[k]) : 0.f;
+            const float x = p.softmax_scale * __half2float(q_pre[k]);
             __half hi, lo;
             split_hi_lo(x, hi, lo);
             sm_q[wave][hh][c] = x;
@@ -1467,17 +1462,15 @@ __global__ __launch_bounds__(256, OCC) void decode_wave_units_kernel(DecodeParam
 #pragma unroll
             for (int k = 0; k < kIdx; ++k) {
                 const int hh = k >> 1, c = lane + 64 * (k & 1);
-                if (hh < rep) {
-                    float mm = m_run[hh], ll = l_w[hh];
-                    float oo = fmaf(join_hi_lo(wl.lr[2 * hh][c], wl.lr[2 * hh + 1][c]), kUnscale, sm_zs[wave][hh][c >> 5]);
-                    if (um[k] > -INFINITY) {                 // the fp16-row launch's part (the window is never empty in this form)
-                        const float mn = fmaxf(mm, um[k]);
-                        const float f_old = __expf(mm - mn), f_new = __expf(um[k] - mn);
-                        ll = fmaf(ll, f_old, ul[k] * f_new);
-                        oo = fmaf(oo, f_old, uo[k] * f_new);
-                    }
-                    p.out[(row0 + hh) * kHeadDim + c] = oo / ll;
+                float mm = m_run[hh], ll = l_w[hh];
+                float oo = fmaf(join_hi_lo(wl.lr[2 * hh][c], wl.lr[2 * hh + 1][c]), kUnscale, sm_zs[wave][hh][c >> 5]);
+                if (um[k] > -INFINITY) {                 // the fp16-row launch's part (the window is never empty in this form)
+                    const float mn = fmaxf(mm, um[k]);
+                    const float f_old = __expf(mm - mn), f_new = __expf(um[k] - mn);
+                    ll = fmaf(ll, f_old, ul[k] * f_new);
+                    oo = fmaf(oo, f_old, uo[k] * f_new);
                 }
+                p.out[(row0 + hh) * kHeadDim + c] = oo / ll;
             }
         } else {
             // several slices share the unit: this one's part goes to the workspace (slot 0 is the fp16-row
@@ -1487,14 +1480,12 @@ __global__ __launch_bounds__(256, OCC) void decode_wave_units_kernel(DecodeParam
 #pragma unroll
             for (int k = 0; k < kIdx; ++k) {
                 const int hh = k >> 1, c = lane + 64 * (k & 1);
-                if (hh < rep) {
-                    const float oo = fmaf(join_hi_lo(wl.lr[2 * hh][c], wl.lr[2 * hh + 1][c]), kUnscale, sm_zs[wave][hh][c >> 5]);
-                    const int64_t prow = (row0 + hh) * row_stride + slot;
-                    device_store(p.part_o + prow * kHeadDim + c, oo);
-                    if (c == 0) {
-                        device_store(p.part_ml + prow * 2 + 0, m_run[hh]);
-                        device_store(p.part_ml + prow * 2 + 1, l_w[hh]);
-                    }
+                const float oo = fmaf(join_hi_lo(wl.lr[2 * hh][c], wl.lr[2 * hh + 1][c]), kUnscale, sm_zs[wave][hh][c >> 5]);
+                const int64_t prow = (row0 + hh) * row_stride + slot;
+                device_store(p.part_o + prow * kHeadDim + c, oo);
+                if (c == 0) {
+                    device_store(p.part_ml + prow * 2 + 0, m_run[hh]);
+                    device_store(p.part_ml + prow * 2 + 1, l_w[hh]);
                 }
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1505,34 +1496,32 @@ __global__ __launch_bounds__(256, OCC) void decode_wave_units_kernel(DecodeParam
 #pragma unroll
                 for (int k = 0; k < kIdx; ++k) {
                     const int hh = k >> 1, c = lane + 64 * (k & 1);
-                    if (hh < rep) {
-                        const int64_t prow = (row0 + hh) * row_stride;
-                        float mm = um[k], ll = ul[k], oo = uo[k];          // slot 0: written by the previous launch
-                        if (!(mm > -INFINITY)) { mm = -INFINITY; ll = 0.f; oo = 0.f; }
-                        // eight parts at a time: the device-scope loads of a batch are all issued before
-                        // the first is used (each is a trip to memory, not to a cache)
-                        for (int i0 = 1; i0 <= n_parts; i0 += 8) {
-                            float mv[8], lv[8], ov[8];
+                    const int64_t prow = (row0 + hh) * row_stride;
+                    float mm = um[k], ll = ul[k], oo = uo[k];          // slot 0: written by the previous launch
+                    if (!(mm > -INFINITY)) { mm = -INFINITY; ll = 0.f; oo = 0.f; }
+                    // eight parts at a time: the device-scope loads of a batch are all issued before
+                    // the first is used (each is a trip to memory, not to a cache)
+                    for (int i0 = 1; i0 <= n_parts; i0 += 8) {
+                        float mv[8], lv[8], ov[8];
 #pragma unroll
-                            for (int j = 0; j < 8; ++j) {
-                                const int i = min(i0 + j, n_parts);
-                                mv[j] = device_load(p.part_ml + (prow + i) * 2 + 0);
-                                lv[j] = device_load(p.part_ml + (prow + i) * 2 + 1);
-                                ov[j] = device_load(p.part_o + (prow + i) * kHeadDim + c);
-                            }
+                        for (int j = 0; j < 8; ++j) {
+                            const int i = min(i0 + j, n_parts);
+                            mv[j] = device_load(p.part_ml + (prow + i) * 2 + 0);
+                            lv[j] = device_load(p.part_ml + (prow + i) * 2 + 1);
+                            ov[j] = device_load(p.part_o + (prow + i) * kHeadDim + c);
+                        }
 #pragma unroll
-                            for (int j = 0; j < 8; ++j) {
-                                if (i0 + j <= n_parts && mv[j] > -INFINITY) {
-                                    const float mn = fmaxf(mm, mv[j]);
-                                    const float f_old = __expf(mm - mn), f_new = __expf(mv[j] - mn);   // mm = -inf: f_old = 0
-                                    ll = fmaf(ll, f_old, lv[j] * f_new);
-                                    oo = fmaf(oo, f_old, ov[j] * f_new);
-                                    mm = mn;
-                                }
+                        for (int j = 0; j < 8; ++j) {
+                            if (i0 + j <= n_parts && mv[j] > -INFINITY) {
+                                const float mn = fmaxf(mm, mv[j]);
+                                const float f_old = __expf(mm - mn), f_new = __expf(mv[j] - mn);   // mm = -inf: f_old = 0
+                                ll = fmaf(ll, f_old, lv[j] * f_new);
+                                oo = fmaf(oo, f_old, ov[j] * f_new);
+                                mm = mn;
                             }
                         }
-                        p.out[(row0 + hh) * kHeadDim + c] = oo / ll;
                     }
+                    p.out[(row0 + hh) * kHeadDim + c] = oo / ll;
                 }
                 if (lane == 0) __hip_atomic_store(p.counters + u, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
@@ -1642,8 +1631,7 @@ template <int B, int R, int S, int O> struct Variant {
     static constexpr int bits = B, rep = R, slots = S, occ = O;
 };
 template <class F>
-bool with_variant(int bits, int rep_layout, F&& fn) {
-    const int rep = rep_layout;                     // wider groups: decode_tiles_kernel
+bool with_variant(int bits, int rep, F&& fn) {         // (groups of 3 and more heads: decode_tiles_kernel)
     if (bits == 2 && rep == 1) { fn(Variant<2, 1, 4, 2>{}); return true; }
     if (bits == 2 && rep == 2) { fn(Variant<2, 2, 4, 2>{}); return true; }
     if (bits == 4 && rep == 1) { fn(Variant<4, 1, 4, 2>{}); return true; }
@@ -1655,6 +1643,7 @@ bool with_variant(int bits, int rep_layout, F&& fn) {
 
 hipError_t launch_decode_mfma(const DecodeParams& p, hipStream_t stream) {
     hipError_t e = hipErrorNotSupported;
+    if (p.rep_here != p.rep_variant || p.q_head0 != 0 || p.n_q_heads != p.rep_here * p.n_kv_heads) return hipErrorInvalidValue;
     if (p.kg_shift > 0) {
         // G = 64 / 128: the instantiations that read one scale / zero-point pair per group
         with_variant(p.bits, p.rep_variant, [&](auto v) {
