@@ -360,7 +360,7 @@ int enqueue_attention(const kivi_layout_t* l, const kivi_cache_t* c, const void*
     const size_t rows = (size_t)l->batch * l->n_q_heads * p.plan.n_splits();
     if (counter_bytes(l) + rows * (kHeadDim + 2) * sizeof(float) > workspace_bytes) return KIVI_ERR_WORKSPACE;
     p.counters = static_cast<int32_t*>(workspace);
-    const bool tiles = path == KIVI_DECODE_MFMA && uses_tiles(l) && !flush_k;
+    const bool tiles = path == KIVI_DECODE_MFMA && uses_tiles(l) && !(flush_k && l->n_q_heads <= 2 * l->n_kv_heads);
     p.part_stride = p.plan.n_splits();
     if (tiles) p.part_stride = part_rows(l, workspace_bytes - counter_bytes(l));
     p.part_o = reinterpret_cast<float*>(static_cast<char*>(workspace) + counter_bytes(l));
@@ -946,9 +946,11 @@ int kivi_decode_step(const kivi_layout_t* l, kivi_cache_t* c, const void* k_new,
         after = flushed;
         after.n_kr += 1;
         after.n_vr += 1;
-        // With one or two query heads per kv-head (G = 32) the fp16-row launch of the two-launch form quantises the
-        // flushed tokens with extra workgroups: a flush step takes two launches in all.
-        if ((nk > 0 || nv > 0) && l->group == kTileTokens && l->n_q_heads <= 2 * l->n_kv_heads && wants_two_launches(l, &after, KIVI_DECODE_MFMA, true)) {
+        // In the two-launch form (G = 32) of up to four query heads per kv-head the fp16-row launch quantises the flushed
+        // tokens with extra workgroups: a flush step takes two launches in all.  (3 and 4 heads, 512 units: 40.5 -> 38.7 us at
+        // 1023 tokens, 51.1 -> 49.5 at 2175, 4 bits 42.2 -> 40.5; 5 to 8 heads would lose 5-6 us: residual_rows_kernel takes
+        // longer than that kernel's own rows and a flush launch together.)
+        if ((nk > 0 || nv > 0) && l->group == kTileTokens && l->n_q_heads <= 4 * l->n_kv_heads && wants_two_launches(l, &after, KIVI_DECODE_MFMA, true)) {
             const int64_t sh = (int64_t)l->cap_r_tokens * kHeadDim, sb = sh * l->n_kv_heads;
             const RowSource ksrc{static_cast<const __half*>(c->k_resid), sb, sh, kHeadDim, c->k_r_start, l->cap_r_tokens};
             const RowSource vsrc{static_cast<const __half*>(c->v_resid), sb, sh, kHeadDim, c->v_r_start, l->cap_r_tokens};

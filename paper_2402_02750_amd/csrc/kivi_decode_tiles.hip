@@ -1266,14 +1266,17 @@ hipError_t launch_mode(DecodeParams p, hipStream_t stream) {
     }
     UniformCut cut;
     const bool two = p.two_launches > 0 && p.plan.tiles_total > p.plan.tiles_a && p.plan.tiles_a > 0;      // the fp16 rows in a launch of their own
-    if (!cut_uniform(units, p.plan.tiles_a, p.plan.tiles_total, resident_workgroups<BITS, HP, MODE, CS>(), p.part_stride, max_parts_of(BITS, HP), two, cut))
+    if (!cut_uniform(units, p.plan.tiles_a, p.plan.tiles_total, resident_workgroups<BITS, HP, MODE, CS>(), p.part_stride, max_parts_of(BITS, HP), two, p.rows_for_tiles, cut))
         return hipErrorInvalidValue;
     p.row_split = cut.row_split;
     p.row_wgs = cut.row_wgs;
     p.unit_wgs = cut.unit_wgs;
     p.axis_len = cut.axis.len;
     p.axis_rem = cut.axis.rem;
-    if (two) {
+    if (p.rows_for_tiles) {
+        if (!two) return hipErrorInvalidValue;
+        p.row_wgs = 0;
+    } else if (two) {
         decode_tiles_kernel<BITS, HP, MODE, CS><<<(unsigned)p.row_wgs, 64 * kWaves, 0, stream>>>(p);
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
         p.row_wgs = 0;
@@ -1293,6 +1296,12 @@ hipError_t launch_decode_tiles(DecodeParams p, hipStream_t stream) {
         if (p.head_groups != 1 || p.two_launches == 0) return hipErrorInvalidValue;
         if (hipError_t e = launch_residual_rows(p, stream); e != hipSuccess) return e;
         p.k_new = p.v_new = nullptr;
+    }
+    if (p.flush_k && p.flush_v) {
+        // a step that flushes: one launch for the fp16 rows (which append the new token) and the tokens that leave the window
+        if (p.seq_state || p.head_groups != 1 || p.two_launches == 0) return hipErrorInvalidValue;
+        p.rows_for_tiles = 1;
+        if (hipError_t e = launch_rows_and_flush(p, *p.flush_k, *p.flush_v, stream); e != hipSuccess) return e;
     }
     hipError_t e = hipErrorNotSupported;
     with_tiles_variant(p.bits, p.rep_here, [&](auto b, auto h) {

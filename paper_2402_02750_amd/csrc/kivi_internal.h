@@ -131,6 +131,9 @@ struct DecodeParams {
     // steps, one more if g < axis_rem.  Batches of different lengths: wave_desc[4 g] = {first unit, first step in it,
     // steps, 0} of workgroup g, unit_parts[b] = steps before sequence b (kivi_tiles_plan.h)
     int32_t row_wgs, row_split, unit_wgs, axis_len, axis_rem;
+    // the fp16-row launch that carries a flush, before decode_tiles_kernel: its part is the first of those that kernel merges
+    // (maximum in the log2 domain, counted as finished)
+    int32_t rows_for_tiles;
 };
 
 // launchers (each defined next to its kernels); they return hipGetLastError() after the launch

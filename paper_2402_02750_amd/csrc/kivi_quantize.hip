@@ -957,8 +957,8 @@ hipError_t launch_rows_and_flush(const DecodeParams& p, const QuantKeyParams& kp
                                  hipStream_t stream) {
     const int tiles_b = p.plan.tiles_total - p.plan.tiles_a;
     const int64_t units = (int64_t)p.batch * p.n_kv_heads;
-    const int rep = p.rep_variant;
-    if (kp.tiles_per_group != 1 || vp.group_blocks != 1 || rep > 2) return hipErrorNotSupported;      // (3 or more heads: decode_tiles_kernel, the flush has a launch of its own)
+    const int rep = p.rep_variant <= 2 ? p.rep_variant : (p.rep_variant <= 4 ? 4 : 8);
+    if (kp.tiles_per_group != 1 || vp.group_blocks != 1 || rep > 4) return hipErrorNotSupported;
     if (!residual_rows_possible(tiles_b, rep) || p.plan.n_splits_b != 1 || p.n_kq != p.n_vq) return hipErrorInvalidValue;
     if (kp.bits != vp.bits || kp.n_tiles < 0 || vp.n_tokens < 0 || kp.n_tiles + vp.n_tokens <= 0) return hipErrorInvalidValue;
     const int n_key_blocks = kp.n_tiles;
@@ -977,7 +977,8 @@ hipError_t launch_rows_and_flush(const DecodeParams& p, const QuantKeyParams& kp
         else rows_flush_kernel<R, 4><<<grid, block, lds, stream>>>(p, kp, vp, tiles_b, n_key_blocks, n_value_blocks);
     };
     if (rep == 1) go(std::integral_constant<int, 1>{});
-    else go(std::integral_constant<int, 2>{});
+    else if (rep == 2) go(std::integral_constant<int, 2>{});
+    else go(std::integral_constant<int, 4>{});
     return hipGetLastError();
 }
 

@@ -111,8 +111,9 @@ struct UniformCut {
 constexpr int kMinSteps = 2;
 
 // resident: workgroups the device holds at once; stride, parts_limit: see the top; own_launch: the fp16 rows run in a
-// launch of their own.  False: no cut fits.
-inline bool cut_uniform(int64_t units, int tiles_a, int tiles_total, int resident, int stride, int parts_limit, bool own_launch, UniformCut& cut) {
+// launch of their own; one_row_part: which is not this kernel and leaves one part.  False: no cut fits.
+inline bool cut_uniform(int64_t units, int tiles_a, int tiles_total, int resident, int stride, int parts_limit, bool own_launch,
+                        bool one_row_part, UniformCut& cut) {
     const int n_a = (tiles_a + kStepTiles - 1) / kStepTiles, row_tiles = tiles_total - tiles_a;
     const int64_t total = units * n_a;
     const bool rows = row_tiles > 0;
@@ -122,6 +123,7 @@ inline bool cut_uniform(int64_t units, int tiles_a, int tiles_total, int residen
     // launch's end waits for) unless that takes more than a quarter of the residency, and at most half of the unit's
     // parts (a window of 8000 and more tokens asks for more than eight heads at 4 bits have).
     cut.row_split = std::max(1, std::min({(row_tiles + kStepTiles - 1) / kStepTiles, (int)std::max<int64_t>(1, resident / 4 / units), room / 2}));
+    if (one_row_part) cut.row_split = 1;
     cut.row_wgs = rows ? (int)units * cut.row_split : 0;
     // One interval per workgroup that is resident beside the fp16 rows' (which end early), but not so short
     // that a unit would have more parts than there is room for.  With several workgroups per unit each

@@ -86,6 +86,11 @@ def test_flush(batch, heads, group, bits):
     (2, 3, 3, 4095, 128, 2),
     (1, 2, 1, 1024 + 479 + 32, 480, 2),     # fifteen tiles of fp16 rows after the flush
     (40, 16, 8, 1023, 128, 4),      # more units than the two-head tile kernel serves
+    (24, 64, 8, 1055, 128, 2),      # eight heads: a launch for the flush, one for the rows, one for the rest
+    (64, 32, 8, 1055, 128, 4),      # four heads: the rows' launch carries the flush for the tile kernel
+    (64, 32, 8, 1024 + 479 + 32, 480, 2),   # sixteen tiles of rows for four heads: the most that such a launch takes
+    (64, 24, 8, 1023, 32, 2),       # three of four slots, one tile of fp16 rows
+    (64, 24, 8, 1023, 96, 4),       # two tiles
 ])
 def test_flush_step(batch, hq, hkv, tokens, residual, bits):
     """A step that flushes: the automatic choice carries the flush out in the fp16-row launch, the single-launch form

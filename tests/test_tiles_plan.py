@@ -57,7 +57,7 @@ extern "C" int check_steps(const int32_t* steps, int sequences, int heads, int m
 // the same for a batch of one length: tiles_a quantised tiles, row_tiles with fp16 rows
 extern "C" int check_uniform(int units, int tiles_a, int row_tiles, int resident, int stride, int limit, int own_launch, int* out) {
     UniformCut cut;
-    if (!cut_uniform(units, tiles_a, tiles_a + row_tiles, resident, stride, limit, own_launch, cut)) return 1;
+    if (!cut_uniform(units, tiles_a, tiles_a + row_tiles, resident, stride, limit, own_launch & 1, own_launch >> 1, cut)) return 1;
     const int n_a = (tiles_a + 3) / 4, room = std::min(stride, limit), row_parts = row_tiles ? cut.row_split : 0;
     out[0] = cut.row_split;
     out[1] = (int)cut.intervals;
@@ -155,7 +155,7 @@ def test_uniform_cut(plan, stride, limit):
     """Every window up to 9000 fp16 rows beside every length, from one unit to more than the device holds workgroups; one launch
     and two."""
     out = (ctypes.c_int * 2)()
-    for own_launch in (0, 1):
+    for own_launch in (0, 1, 3):                # 3: the rows leave one part
         for resident in (3, 256, 512, 768):
             for units in (1, 2, 3, 5, 8, 31, 96, 200, 256, 300, 700, 1100):
                 for tiles_a in (0, 1, 3, 4, 5, 29, 128, 257, 1000, 4001):
