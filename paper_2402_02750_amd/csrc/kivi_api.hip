@@ -244,11 +244,17 @@ int decode_family(const kivi_layout_t* l) {
 //      the line is where it was when the fp16 rows were 40 % of such a launch).
 //  (4) 3 or 4 heads: 512 units on (context 4000, 2 bits: 64 against 80 us; context 1000: 36 against 39); even at
 //      384 units and context 4000 (54.0 / 53.2 us), one launch 20 % faster below (23 against 34 us at context 1000).
+//  (5) Neither for short contexts while the units are fewer than the resident workgroups: 512 units, 15 tiles, one launch
+//      against two: 3 heads 28.3 / 30.0 us (4 bits 29.4 / 31.4), 8 heads 35.0 / 37.1 (4 bits 46.3 / 51.9); with 31 tiles
+//      38.5 / 35.1 and 62.4 / 58.2, and at 1024 units and 15 tiles 48.3 / 44.7 and 78.3 / 70.0.
 // `flush`: the step also flushes and the fp16-row launch could carry that out (G = 32).
 //  (0) One or two heads: a flush has to end before the launch that reads its tiles, so the single-launch form takes
 //      two launches as well, the first of them nearly empty.  Riding with the fp16 rows it costs nothing of its own:
-//      one head, context 4096, batch 1 / 4 / 8 / 16: 17.7 -> 16.7, 27.9 -> 22.2, 36.9 -> 31.4, 50.3 -> 48.9 us; 4 units,
-//      context 1024: 14.0 either way; two heads, 256 units: 41.0 -> 35.4 us.
+//      one head, context 4095, batch 1 / 4 / 8 / 16 of 32-40 heads: 17.8 -> 17.1, 31.5 -> 28.3, 36.3 -> 31.4, 50.6 -> 49.3 us.
+//      Not for a few units with long contexts, where the single launch is so much the faster one (8 units, 4 bits, 1055
+//      tokens: 13.9 against 14.8 us, 4095 tokens 15.0 / 16.0; the same at 32 units; two launches still at 479: 13.0 / 13.7), nor
+//      for two heads while decode_tiles_kernel serves them well (8 units, 1055 tokens, 4 bits: 13.7 / 17.2 us; 64 units
+//      17.1 / 17.7; even at 128; 256 units, 4095 tokens 40.7 / 35.7).
 bool wants_two_launches(const kivi_layout_t* l, const kivi_cache_t* c, int path, bool flush = false) {
     if (path != KIVI_DECODE_MFMA || l->decode_path == KIVI_DECODE_MFMA_ONE) return false;
     const int rep_launch = std::min(l->n_q_heads / l->n_kv_heads, kMaxRep);
@@ -259,9 +265,11 @@ bool wants_two_launches(const kivi_layout_t* l, const kivi_cache_t* c, int path,
                           residual_rows_possible(tiles_b, rep_variant);
     if (!possible) return false;
     if (l->decode_path == KIVI_DECODE_MFMA_TWO) return true;
-    if (flush && rep_variant <= 2) return true;                                                      // (0)
     const int64_t units = (int64_t)l->batch * l->n_kv_heads;
+    if (flush && rep_variant == 1 && (units >= 32 || tiles_total <= 32)) return true;                // (0)
+    if (flush && rep_variant == 2 && units > 128) return true;
     const int64_t work = units * tiles_total, row_work = units * tiles_b;
+    if (rep_variant >= 4 && units < 768 && tiles_total <= 20) return false;                          // (5)
     if (rep_variant == 8) return tiles_b >= 2 && work >= 4000 && row_work >= 384;                    // (3)
     if (rep_variant == 4) return units >= 512 || (units >= 384 && work >= 40000);                    // (4)
     const int resident = mfma_geometry(l->bits, rep_launch).resident_workgroups;
@@ -949,7 +957,7 @@ int kivi_decode_step(const kivi_layout_t* l, kivi_cache_t* c, const void* k_new,
         // In the two-launch form (G = 32) of up to four query heads per kv-head the fp16-row launch quantises the flushed
         // tokens with extra workgroups: a flush step takes two launches in all.  (3 and 4 heads, 512 units: 40.5 -> 38.7 us at
         // 1023 tokens, 51.1 -> 49.5 at 2175, 4 bits 42.2 -> 40.5; 5 to 8 heads would lose 5-6 us: residual_rows_kernel takes
-        // longer than that kernel's own rows and a flush launch together.)
+        // longer than that kernel's own rows and a flush launch together.  One and two heads: see wants_two_launches.)
         if ((nk > 0 || nv > 0) && l->group == kTileTokens && l->n_q_heads <= 4 * l->n_kv_heads && wants_two_launches(l, &after, KIVI_DECODE_MFMA, true)) {
             const int64_t sh = (int64_t)l->cap_r_tokens * kHeadDim, sb = sh * l->n_kv_heads;
             const RowSource ksrc{static_cast<const __half*>(c->k_resid), sb, sh, kHeadDim, c->k_r_start, l->cap_r_tokens};
