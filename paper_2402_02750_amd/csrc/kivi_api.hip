@@ -308,13 +308,6 @@ int wide_group_runs(const kivi_layout_t* l, int path, bool two_launches) {
     return ceil_div(rep_total, kWideGroupRun);
 }
 
-// Launches of one attention call: a group wider than kMaxRep heads takes one pass per kMaxRep heads, except in the
-// matrix-core family's single-launch form, where the runs are units of one launch.
-int attention_launches(const kivi_layout_t* l, int path, bool two_launches) {
-    const int passes = wide_group_runs(l, path, two_launches) > 1 ? 1 : ceil_div(l->n_q_heads / l->n_kv_heads, kMaxRep);
-    return path == KIVI_DECODE_MFMA ? (two_launches ? 2 : 1) * passes : passes + 1;      // vector-ALU family: decodes + merge
-}
-
 // Which kernel of the matrix-core family serves the layout: decode_tiles_kernel from three query heads per
 // kv-head on (sweep over 8-1024 units, contexts 300-30000, 2 and 4 bits: 1.02-2.0 times as fast as
 // decode_mfma_kernel throughout), and with two heads up to 256 units (1.03-1.19; at 512 units 0.70, that
@@ -323,6 +316,24 @@ bool uses_tiles(const kivi_layout_t* l) {
     const int rep = l->n_q_heads / l->n_kv_heads;
     return rep >= 3 || (rep == 2 && (int64_t)l->batch * l->n_kv_heads <= 256 && l->decode_path != KIVI_DECODE_MFMA_TWO);
 }
+// K and V split at different tokens (Algorithm 1's policy), decode_tiles_kernel: the tiles that are not all quantised in a
+// launch of their own, as in the two-launch form, where they would take the residency of the others in one.  From 512 units
+// on and not for short contexts (1500 tokens, 4 heads, 512 / 1024 units: 55.7 -> 46.8, 93.0 -> 82.3 us; 8 heads, 512 units
+// 66.9 -> 56.6; 500 tokens 36.7 / 37.5 and 58.6 / 60.9; 256 units, 1500 tokens 26.7 / 34.5).
+bool rows_launch_for_uneven_split(const kivi_layout_t* l, const kivi_cache_t* c, int path) {
+    return path == KIVI_DECODE_MFMA && l->decode_path != KIVI_DECODE_MFMA_ONE && uses_tiles(l) && l->n_q_heads <= kMaxRep * l->n_kv_heads &&
+           c->n_kq != c->n_vq && std::min(c->n_kq, c->n_vq) >= kTileTokens && (int64_t)l->batch * l->n_kv_heads >= 512 &&
+           ceil_div(c->n_kq + c->n_kr, kTileTokens) > 20;
+}
+
+// Launches of one attention call: a group wider than kMaxRep heads takes one pass per kMaxRep heads, except in the
+// matrix-core family's single-launch form, where the runs are units of one launch.
+int attention_launches(const kivi_layout_t* l, const kivi_cache_t* c, int path, bool two_launches) {
+    if (rows_launch_for_uneven_split(l, c, path)) return 2;
+    const int passes = wide_group_runs(l, path, two_launches) > 1 ? 1 : ceil_div(l->n_q_heads / l->n_kv_heads, kMaxRep);
+    return path == KIVI_DECODE_MFMA ? (two_launches ? 2 : 1) * passes : passes + 1;      // vector-ALU family: decodes + merge
+}
+
 // parts per (batch, query head) that `bytes` of workspace have room for
 int part_rows(const kivi_layout_t* l, size_t bytes) {
     const size_t row = (size_t)l->batch * l->n_q_heads * (kHeadDim + 2) * sizeof(float);
@@ -369,6 +380,7 @@ int enqueue_attention(const kivi_layout_t* l, const kivi_cache_t* c, const void*
     if (counter_bytes(l) + rows * (kHeadDim + 2) * sizeof(float) > workspace_bytes) return KIVI_ERR_WORKSPACE;
     p.counters = static_cast<int32_t*>(workspace);
     const bool tiles = path == KIVI_DECODE_MFMA && uses_tiles(l) && !(flush_k && l->n_q_heads <= 2 * l->n_kv_heads);
+    if (tiles && rows_launch_for_uneven_split(l, c, path)) p.two_launches = 1;
     p.part_stride = p.plan.n_splits();
     if (tiles) p.part_stride = part_rows(l, workspace_bytes - counter_bytes(l));
     p.part_o = reinterpret_cast<float*>(static_cast<char*>(workspace) + counter_bytes(l));
@@ -774,7 +786,7 @@ int kivi_decode_plan(const kivi_layout_t* l, const kivi_cache_t* c, kivi_decode_
     const SplitPlan plan = plan_splits(l, c, path == KIVI_DECODE_MFMA, two);
     out->family = path;
     const int runs = wide_group_runs(l, path, two);
-    out->launches = attention_launches(l, path, two);
+    out->launches = attention_launches(l, c, path, two);
     out->units_per_kv_head = runs > 1 ? runs : 1 << head_split_shift(l, plan, path, two);
     out->splits_quantised = plan.n_splits_a;
     out->splits_fp16 = plan.n_splits_b;
@@ -1053,7 +1065,7 @@ int kivi_decode_launches_ragged(const kivi_layout_t* l, const kivi_seq_state_t* 
             sl.batch = b1 - b0;
             kivi_cache_t sc{};
             sc.n_kq = x.n_kq; sc.n_vq = x.n_vq; sc.n_kr = x.n_kr; sc.n_vr = x.n_vr;
-            total += attention_launches(&sl, path, wants_two_launches(&sl, &sc, path));
+            total += attention_launches(&sl, &sc, path, wants_two_launches(&sl, &sc, path));
         }
         b0 = b1;
     }

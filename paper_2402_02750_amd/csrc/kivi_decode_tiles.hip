@@ -661,30 +661,31 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
         }
     };
     // ---- one tile whose keys and values are all quantised, from an LDS slot ----
-    auto quantised_tile = [&](const unsigned char* sl) {
-        float x[4], pv[4];
-        float zk, cx;
-        {
-            uint32_t w[2 * BITS];
+    // raw key sums x and the zero-points' share zk of the logits; returns the sums' factor
+    auto slot_logits = [&](const unsigned char* sl, float (&x)[4], float& zk) -> float {
+        uint32_t w[2 * BITS];
 #pragma unroll
-            for (int pl = 0; pl < kPlanes; ++pl) {
-                const uint4v v = *reinterpret_cast<const uint4v*>(sl + pl * 1024 + (kb * 16 + row_pos) * 16);
-                w[4 * pl + 0] = v[0]; w[4 * pl + 1] = v[1]; w[4 * pl + 2] = v[2]; w[4 * pl + 3] = v[3];
-            }
-            const bool big = any_above(*reinterpret_cast<const uint32_t*>(sl + kScaleOff + lane * 4), kKeyScaleLimit);
-            float4v dz = {0.f, 0.f, 0.f, 0.f};
-            Frag s[4];
-#pragma unroll
-            for (int cb = 0; cb < 4; ++cb) {
-                s[cb].h = *reinterpret_cast<const half8*>(sl + kScaleOff + cb * 64 + kb * 16);
-                const half8 z = *reinterpret_cast<const half8*>(sl + kScaleOff + 256 + cb * 64 + kb * 16);
-                dz = __builtin_amdgcn_mfma_f32_16x16x32_f16(z, query_frag(cb), dz, 0, 0, 0);
-            }
-            cx = key_products(w, s, big, x);
-            zk = dz[0] * c_zero;
+        for (int pl = 0; pl < kPlanes; ++pl) {
+            const uint4v v = *reinterpret_cast<const uint4v*>(sl + pl * 1024 + (kb * 16 + row_pos) * 16);
+            w[4 * pl + 0] = v[0]; w[4 * pl + 1] = v[1]; w[4 * pl + 2] = v[2]; w[4 * pl + 3] = v[3];
         }
-        const uint32_t s2 = *reinterpret_cast<const uint32_t*>(sl + kScaleOff + 512 + (CS ? min(lane * 4, (256 >> kg) - 4) : lane * 4));
-        softmax(x, cx, zk, 0xfu, pv, rescale_acc);
+        const bool big = any_above(*reinterpret_cast<const uint32_t*>(sl + kScaleOff + lane * 4), kKeyScaleLimit);
+        float4v dz = {0.f, 0.f, 0.f, 0.f};
+        Frag s[4];
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+            s[cb].h = *reinterpret_cast<const half8*>(sl + kScaleOff + cb * 64 + kb * 16);
+            const half8 z = *reinterpret_cast<const half8*>(sl + kScaleOff + 256 + cb * 64 + kb * 16);
+            dz = __builtin_amdgcn_mfma_f32_16x16x32_f16(z, query_frag(cb), dz, 0, 0, 0);
+        }
+        const float cx = key_products(w, s, big, x);
+        zk = dz[0] * c_zero;
+        return cx;
+    };
+    auto slot_scales = [&](const unsigned char* sl) -> uint32_t {          // two of the tile's value scales per lane
+        return *reinterpret_cast<const uint32_t*>(sl + kScaleOff + 512 + (CS ? min(lane * 4, (256 >> kg) - 4) : lane * 4));
+    };
+    auto slot_outputs = [&](const unsigned char* sl, uint32_t s2, const float (&pv)[4]) {
         Frag fa, fb, z;
         split_probabilities(pv, fa, fb);
         fit_value_exponent(s2, [&](half2v (&to)[NS][4]) { gather_scales(sl + kScaleOff + 512, to); }, fa, fb);
@@ -700,6 +701,13 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
             w[4 * pl + 0] = v[0]; w[4 * pl + 1] = v[1]; w[4 * pl + 2] = v[2]; w[4 * pl + 3] = v[3];
         }
         value_products(w, sv, fa, fb);
+    };
+    auto quantised_tile = [&](const unsigned char* sl) {
+        float x[4], pv[4], zk;
+        const float cx = slot_logits(sl, x, zk);
+        const uint32_t s2 = slot_scales(sl);
+        softmax(x, cx, zk, 0xfu, pv, rescale_acc);
+        slot_outputs(sl, s2, pv);
     };
 
     // ---- fp16 rows of a tile: keys as matrix operands, values for the fp32 products ----
@@ -773,36 +781,24 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
             *reinterpret_cast<uint4v*>(const_cast<__half*>(is_v ? p.v_resid : p.k_resid) + (unit * p.cap_r + ring) * kHeadDim + n * 8) = v;
         }
     };
-    // one tile that holds fp16 rows, or in which K and V are split differently
+    // one tile that holds fp16 rows, or in which K and V are split differently: what is packed of it goes through an LDS
+    // slot like any other tile (reading its scales one by one into registers instead took 1.3 times as long, 1.5 times
+    // with G > 32: 64 x 32 / 8 heads, 1500 tokens, Algorithm 1's policy)
     auto general_tile = [&](int u, int tile) {
         const int64_t unit = kv_unit(u);
         const int tt = tile * kTileTokens, last = p.length - 1;
-        const int64_t row = unit * p.cap_tiles + tile;
+        unsigned char* sl = &sm_ring[wave][0][0];
         float x[4], pv[4];
         float zk = 0.f, cx = c_zero;
         const int tok = tok0 + (is_lo ? 16 : 0);                       // this lane's tokens: tok + i
+        const int n_vq_here = min(max(p.n_vq - tt, 0), kTileTokens);
+        if (tt < p.n_kq || n_vq_here > 0) {                             // (the tile lies within the packed arrays' capacity)
+            copy_tile(unit * p.cap_tiles + tile, 0);
+            wait_copies<0>();
+        }
         if (tt < p.n_kq) {
-            uint32_t w[2 * BITS];
-            const unsigned char* kc = reinterpret_cast<const unsigned char*>(p.k_codes) + row * kCodeBytes;
-#pragma unroll
-            for (int pl = 0; pl < kPlanes; ++pl) {
-                const uint4v v = *reinterpret_cast<const uint4v*>(kc + pl * 1024 + (kb * 16 + row_pos) * 16);
-                w[4 * pl + 0] = v[0]; w[4 * pl + 1] = v[1]; w[4 * pl + 2] = v[2]; w[4 * pl + 3] = v[3];
-            }
-            const __half* srow = p.k_scale + (row >> kg) * kHeadDim;
-            const __half* zrow = p.k_zero + (row >> kg) * kHeadDim;
-            const bool big = any_above(*reinterpret_cast<const uint32_t*>(srow + lane * 2), kKeyScaleLimit);
-            float4v dz = {0.f, 0.f, 0.f, 0.f};
-            Frag s[4];
-#pragma unroll
-            for (int cb = 0; cb < 4; ++cb) {
-                s[cb].h = *reinterpret_cast<const half8*>(srow + cb * 32 + kb * 8);
-                dz = __builtin_amdgcn_mfma_f32_16x16x32_f16(*reinterpret_cast<const half8*>(zrow + cb * 32 + kb * 8), query_frag(cb), dz, 0, 0, 0);
-            }
-            cx = key_products(w, s, big, x);
-            zk = dz[0] * c_zero;
+            cx = slot_logits(sl, x, zk);
         } else {
-            // the query's columns hold the same head twice, so hi and lo column agree and nothing is added up
             half8 kr[2][4];
             load_key_rows(unit, tt, kr);
             row_logits(kr, x);
@@ -811,61 +807,29 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
 #pragma unroll
         for (int i = 0; i < 4; ++i) live |= (tt + tok + i <= last ? 1u : 0u) << i;
         softmax(x, cx, zk, live, pv, rescale_acc);
-        const int n_vq_here = min(max(p.n_vq - tt, 0), kTileTokens);
         if (n_vq_here > 0) {
+            if (n_vq_here < kTileTokens) {
+                // scales and zero-points of tokens that are not quantised yet may hold anything: 0
+                const int per_token = CS ? 4 >> kg : 4;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int at = 2 * lane + i;
+                    if (at < kTileTokens * per_token && at >= n_vq_here * per_token) {
+                        reinterpret_cast<uint16_t*>(sl + kScaleOff + 512)[at] = 0;
+                        reinterpret_cast<uint16_t*>(sl + kScaleOff + 768)[at] = 0;
+                    }
+                }
+                wave_lds_sync();
+            }
             float pq[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) pq[i] = tok + i < n_vq_here ? pv[i] : 0.f;
-            Frag fa, fb;
-            split_probabilities(pq, fa, fb);
-            // scales and zero-points of tokens that are not quantised yet may hold anything: 0
-            const int kt = CS ? 8 >> kg : 8;                            // bytes per token of the scale arrays
-            const unsigned char* srow = reinterpret_cast<const unsigned char*>(p.v_scale) + row * kTileTokens * kt;
-            const unsigned char* zrow = reinterpret_cast<const unsigned char*>(p.v_zero) + row * kTileTokens * kt;
-            const int groups = CS ? 4 >> kg : 4;
-            auto entry = [&](const unsigned char* base, int token, int group) -> uint32_t {
-                return token < n_vq_here ? *reinterpret_cast<const uint16_t*>(base + token * kt + (CS ? group >> kg : group) * 2) : 0u;
-            };
-            uint32_t s2 = 0;                                            // two of the tile's scales per lane, for the range check
-            {
-                const int i0 = min(2 * lane, kTileTokens * groups - 1), i1 = min(2 * lane + 1, kTileTokens * groups - 1);
-                const int t0 = i0 / groups, t1 = i1 / groups;
-                if (t0 < n_vq_here) s2 |= *reinterpret_cast<const uint16_t*>(srow + 2 * i0);
-                if (t1 < n_vq_here) s2 |= (uint32_t)*reinterpret_cast<const uint16_t*>(srow + 2 * i1) << 16;
-            }
-            auto load_scales = [&](half2v (&to)[NS][4]) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-#pragma unroll
-                    for (int s = 0; s < NS; ++s) {
-                        const int t0 = kb * 8 + 2 * r, g = HP == 2 ? my_group : HP == 4 ? 2 * s + my_group : s;
-                        to[s][r] = half2_of(entry(srow, t0, g) | entry(srow, t0 + 1, g) << 16);
-                    }
-            };
-            fit_value_exponent(s2, load_scales, fa, fb);
-            half2v sv[NS][4];
-            load_scales(sv);
-            Frag z;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int t0 = kb * 8 + 2 * r;
-                z.r[r] = entry(zrow, t0, n & 3) | entry(zrow, t0 + 1, n & 3) << 16;
-            }
-            zsum = __builtin_amdgcn_mfma_f32_16x16x32_f16(z.h, fb.h, zsum, 0, 0, 0);
-            scale_values(sv);
-            uint32_t w[2 * BITS];
-            const unsigned char* vc = reinterpret_cast<const unsigned char*>(p.v_codes) + row * kCodeBytes;
-#pragma unroll
-            for (int pl = 0; pl < kPlanes; ++pl) {
-                const uint4v v = *reinterpret_cast<const uint4v*>(vc + pl * 1024 + lane16);
-                w[4 * pl + 0] = v[0]; w[4 * pl + 1] = v[1]; w[4 * pl + 2] = v[2]; w[4 * pl + 3] = v[3];
-            }
-            value_products(w, sv, fa, fb);
+            slot_outputs(sl, slot_scales(sl), pq);
         }
         if (n_vq_here < kTileTokens && p.n_vr > 0) {
-            // (rows in LDS: the ring, which these workgroups do not use otherwise)
-            float (*rows)[kHeadDim] = reinterpret_cast<float (*)[kHeadDim]>(&sm_ring[wave][0][0]);
-            static_assert(sizeof(float) * HP * kHeadDim <= NB * kSlotBytes, "one row per head");
+            // (rows in LDS: the rest of the ring)
+            float (*rows)[kHeadDim] = reinterpret_cast<float (*)[kHeadDim]>(&sm_ring[wave][1][0]);
+            static_assert(sizeof(float) * HP * kHeadDim <= (NB - 1) * kSlotBytes, "one row per head");
             const float f = __uint_as_float((uint32_t)(127 - ks) << 23) * (1.0f / kValueUnscale);
             half8 vr[8];
             load_value_rows(unit, tt, vr);

@@ -23,6 +23,8 @@ CASES = [
     (8, 2, 5, 4, 32, A, 2500, 1, 1),        # units cut at uneven places, K and V split differently
     (32, 4, 40, 2, 32, W, 3300, 1, 1),      # two launches, eight heads
     (16, 4, 60, 2, 32, W, 4200, 1, 1),      # two launches, four heads
+    (16, 4, 130, 2, 32, A, 901, 1, 1),      # split differently, more units than 512: a launch for the tiles that hold rows
+    (32, 4, 129, 4, 64, A, 1000, 1, 1),     # ... eight heads
     (8, 2, 2, 2, 32, W, 900, 60, 1),        # key scales past 64
     (16, 2, 2, 4, 32, A, 900, 60, 500),     # large value scales
     (8, 2, 2, 2, 32, W, 900, 1, 2.0 ** -13),    # value scales among fp16's subnormals
@@ -250,3 +252,29 @@ def test_key_outliers(hq, hkv, bits, group, policy, large, small, looks):
         err = err[:, 1:]                                # (the looking head's probabilities hang on logits of thousands)
     bound = 2.0 ** -20 * float(np.abs(v.astype(np.float32)).max())
     assert err.max() <= bound, f"{err.max():.3e} against {bound:.3e}"
+
+
+@pytest.mark.parametrize("group", [32, 64, 128])
+@pytest.mark.parametrize("hq,bits", [(2, 2), (4, 4), (7, 2), (8, 4)])
+def test_unwritten_scales(hq, bits, group):
+    """Values that end inside a tile (Algorithm 1's policy): what the packed arrays hold past them does not count, be it
+    zeros or NaN.  Same bytes out."""
+    torch = gh.require_gpu()
+    print(f"case unwritten scales hq={hq} bits={bits} G={group}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(hq + group)
+    for tokens in (256 + 1, 256 + 31, 256 + 77, 256 + 128):
+        k, v = (torch.randn(2, 1, tokens, 128, dtype=torch.float16, device="cuda", generator=gen) for _ in range(2))
+        q = torch.randn(2, hq, 128, dtype=torch.float16, device="cuda", generator=gen)
+        outs = []
+        for fill in (0, 0xFF):
+            layout = kivi.make_layout(2, hq, 1, bits, 128, 512, 256, group=group)
+            cache = kivi.Cache(layout)
+            for buf in cache.buffers.values():
+                buf.fill_(fill)
+            kivi.kivi_prefill(layout, k, v, tokens, cache, A)
+            assert cache.c.n_vq == tokens - 128 and cache.c.n_kq != cache.c.n_vq or tokens == 384
+            out = torch.empty(2, hq, 128, dtype=torch.float32, device="cuda")
+            kivi.kivi_decode_attention(layout, cache, q, 128 ** -0.5, out)
+            torch.cuda.synchronize()
+            outs.append(out)
+        assert torch.isfinite(outs[1]).all() and torch.equal(outs[0], outs[1]), f"{tokens} tokens"
