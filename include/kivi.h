@@ -87,7 +87,7 @@ extern "C" {
                                     /* (KIVI_DECODE_MFMA and AUTO pick the form from the shape: two  */
                                     /* launches when a workgroup would otherwise own parts of several*/
                                     /* (batch, kv-head) units, or with 3 or more query heads per     */
-                                    /* kv-head and enough fp16 rows; kivi_decode_plan tells which)   */
+                                    /* kv-head and enough units or fp16 rows; kivi_decode_plan tells) */
 
 /* Static description of one attention layer's cache (host struct). */
 typedef struct kivi_layout {
@@ -137,7 +137,8 @@ int kivi_cache_sizes(const kivi_layout_t* layout, kivi_cache_sizes_t* sizes);
  * group of up to 8 query heads per kv-head, and how the token axis is cut. */
 typedef struct kivi_decode_plan {
     int32_t family;             /* KIVI_DECODE_VALU or KIVI_DECODE_MFMA                              */
-    int32_t launches;           /* kernel launches of one attention call                            */
+    int32_t launches;           /* kernel launches of one attention call (a decoding step's flush is */
+                                /* not counted, see kivi_decode_step)                               */
     int32_t splits_quantised;   /* pieces of the all-quantised token range per (batch, kv-head); with */
                                 /* 3 or more query heads per kv-head a launch may cut finer         */
     int32_t splits_fp16;        /* pieces of the range that holds fp16 rows                         */
@@ -261,8 +262,9 @@ int kivi_decode_attention_static(const kivi_layout_t* layout, const kivi_cache_t
  * kivi_decode_attention.  On steps where nothing is flushed and the matrix-core family runs, the
  * append costs no launch of its own: the attention (one launch or two, see
  * kivi_decode_plan) reads the new token's rows from k_new / v_new and writes them into the
- * residual rings itself.  A flush is a launch of its own before it, or, with one or two query heads per
- * kv-head and G = 32, part of the fp16-row launch of the two-launch form, which such steps then take.
+ * residual rings itself.  A flush is a launch of its own before it, or, with up to four query heads per
+ * kv-head and G = 32, part of the fp16-row launch of the two-launch form (which steps that flush take more often
+ * than others with one or two heads: from 32 or 129 units on, and one head with up to 32 tiles).
  *   k_new, v_new   device, fp16 [b][n_kv_heads][128]; they must stay valid until the launch has run
  *   other arguments as for kivi_decode_attention / kivi_flush_residual
  * Errors: INVALID_ARG (also: a ring is full, no capacity left for the flush), UNSUPPORTED,

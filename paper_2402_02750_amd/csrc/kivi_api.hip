@@ -287,8 +287,8 @@ int head_split_shift(const kivi_layout_t* l, const SplitPlan& plan, int path, bo
     if (path != KIVI_DECODE_MFMA || two_launches || (rep_total != 4 && rep_total != 6 && rep_total != 8)) return 0;
     if (l->group != kTileTokens) return 0;
     const int64_t units = (int64_t)l->batch * l->n_kv_heads, chunks = units * plan.n_splits();
-    // parts of 2 heads run on the 2-head instantiation: 2 bits only (at 4 bits that instantiation's
-    // chunks are not the length the plan was made for)
+    // parts of 2 heads: 2 bits only, where these limits were measured (the comparison is of the chunks that plans are
+    // reported in; decode_tiles_kernel cuts its work itself)
     const MfmaGeometry g2 = mfma_geometry(l->bits, 2);
     const bool two_heads_possible = g2.chunk_tiles == plan.tiles_per_split_a;
     if (rep_total == 8 && two_heads_possible && units <= 16 && chunks <= g2.resident_workgroups) return 2;     // quarters
@@ -309,9 +309,10 @@ int wide_group_runs(const kivi_layout_t* l, int path, bool two_launches) {
 }
 
 // Which kernel of the matrix-core family serves the layout: decode_tiles_kernel from three query heads per
-// kv-head on (sweep over 8-1024 units, contexts 300-30000, 2 and 4 bits: 1.02-2.0 times as fast as
-// decode_mfma_kernel throughout), and with two heads up to 256 units (1.03-1.19; at 512 units 0.70, that
-// kernel's cheaper tiles win).  With one head per kv-head most of its matrix columns would idle.
+// kv-head on (sweeps over 8-1024 units, contexts 200-30 000, 2 and 4 bits, G = 32 to 128, both policies: 1.0-2.7 times as
+// fast as decode_mfma_kernel was; slower only at 512 units: 0.94-0.95 on steps that flush with 5 to 8 heads at 4 bits, up to
+// 1055 tokens, and 0.87-0.97 with K and V split differently and 4 heads), and with two heads up to 256 units (1.03-1.19; at
+// 512 units 0.70, that kernel's cheaper tiles win).  With one head per kv-head most of its matrix columns would idle.
 bool uses_tiles(const kivi_layout_t* l) {
     const int rep = l->n_q_heads / l->n_kv_heads;
     return rep >= 3 || (rep == 2 && (int64_t)l->batch * l->n_kv_heads <= 256 && l->decode_path != KIVI_DECODE_MFMA_TWO);
