@@ -807,8 +807,9 @@ __global__ __launch_bounds__(256) void copy_rows_kernel(CopyRowsParams p) { copy
 
 // A prompt's keys, values and residual rows in one launch: along x the copies of the residual rows, then key and
 // value blocks in turn.  As three launches a short prompt is three serial chains of memory round trips of 4-16 us
-// each with most of the chip idle; together they overlap (8 kv-heads, batch 1, 16 001 tokens, 4 bits: 31.3 -> 23.9 us;
-// 300 tokens, 2 bits: 14.3 -> 9.3 us).
+// each with most of the chip idle; together they overlap (8 kv-heads, batch 1, 16 001 tokens, 4 bits: 30.9 -> 23.2 us;
+// 300 tokens, 2 bits: 14.6 -> 9.4 us).  A long one is bound by HBM either way, with two launches' start and tail less
+// (512 units of 4096 tokens 257.8 -> 249.7 us, 4 bits 285.6 -> 271.2; 128 units of 8000 128-145 -> 125-134).
 template <int BITS>
 __global__ __launch_bounds__(256) void prefill_kernel(QuantKeyParams kp, QuantValueParams vp, CopyRowsParams cp, int n_copy, int n_key, int n_value) {
     const int bx = (int)blockIdx.x - n_copy, pairs = 2 * min(n_key, n_value);       // (a block past the last finds no tile)
@@ -911,12 +912,11 @@ hipError_t launch_quantize_values(const QuantValueParams& p_in, hipStream_t stre
     return hipGetLastError();
 }
 
-// Up to 16383 key tiles: a longer prompt is bound by HBM, and its keys are better off in a launch of their own with
-// the eight wavefronts per SIMD that their registers allow (beside the values there are five).  2 bits: 256 units of 62
-// tiles 74.5 us in three launches, 69.6 in one; 128 units of 246 tiles 127.9 against 134.8; 512 units of 124 tiles 256.9
-// against 268.7, and 260.0 with the copies beside the values and the keys alone.
+// Where the register-resident forms serve both keys and values; at 2 bits up to 65 535 key tiles: with more, rows of all
+// heads in turn ([b, t, h, d]) are up to 1 % faster in three launches (512 units of 128 tiles 248.3 us against 250.9, 2048 of
+// 60 503.3 / 507.1; 512 of 121 tiles 254.4 / 250.7, 128 of 250 133.8 / 130.6).  4 bits: 565.0 / 549.7 us at 2048 units of 60.
 bool prefill_possible(const QuantKeyParams& kp, const QuantValueParams& vp) {
-    return kp.n_tiles > 0 && (int64_t)kp.n_tiles * kp.n_kv_heads * kp.batch < 16384 && kp.src.ring_cap == 0 && kp.tiles_per_group == 1 && vp.n_tokens >= kTileTokens &&
+    return kp.n_tiles > 0 && (kp.bits == 4 || (int64_t)kp.n_tiles * kp.n_kv_heads * kp.batch < 65536) && kp.src.ring_cap == 0 && kp.tiles_per_group == 1 && vp.n_tokens >= kTileTokens &&
            vp.first_token % kTileTokens == 0 && vp.src.ring_cap == 0 && vp.group_blocks == 1;
 }
 
