@@ -310,8 +310,8 @@ int wide_group_runs(const kivi_layout_t* l, int path, bool two_launches) {
 
 // Which kernel of the matrix-core family serves the layout: decode_tiles_kernel from three query heads per
 // kv-head on (sweeps over 8-1024 units, contexts 200-30 000, 2 and 4 bits, G = 32 to 128, both policies: 1.0-2.7 times as
-// fast as decode_mfma_kernel was; slower only at 512 units: 0.94-0.95 on steps that flush with 5 to 8 heads at 4 bits, up to
-// 1055 tokens, and 0.87-0.97 with K and V split differently and 4 heads), and with two heads up to 256 units (1.03-1.19; at
+// fast as decode_mfma_kernel was; slower only at 512 units: 0.93-0.96 on steps that flush with 5 to 8 heads at 4 bits, up to
+// 1055 tokens, and 0.88-0.97 with K and V split differently, mostly with 4 heads), and with two heads up to 256 units (1.03-1.19; at
 // 512 units 0.70, that kernel's cheaper tiles win).  With one head per kv-head most of its matrix columns would idle.
 bool uses_tiles(const kivi_layout_t* l) {
     const int rep = l->n_q_heads / l->n_kv_heads;

@@ -29,8 +29,12 @@
 //           instruction of group g fills the columns of the other groups with sums that nobody reads).
 //   zero-points: keys by a 16x16x128 product (all rows alike, so every lane gets its head's sum),
 //           values by one with the rows = channel groups.
-// What is left per tile at HP = 4 is ~230 vector instructions for up to four heads (HP = 8: ~280 for
-// up to eight) where decode_mfma_kernel issued ~330 and ~620.
+//   Both exponents hold for ordinary data at no cost per tile.  Larger key scales and value scales are looked at
+//   together with what they meet -- the query's channel, the probabilities -- and scaled down only if the products need
+//   it; the value exponent falls back when large scales are past.  (Error against 64 bits with a key channel 2^15
+//   times larger than the others, or values of 40 000 among values of 1/16: 1e-6 to 5e-6 of the output.)
+// Counted over whole launches (2 bits, G = 32; rows, merges and all): 328 vector instructions per tile at HP = 4 for four
+// heads, 455 at HP = 8 for eight, 443 for runs of eight of 71.
 //
 // Packed data: `global_load_lds` copies a tile (codes, and the four scale / zero-point rows with one
 // instruction) straight into the wavefront's own ring of LDS slots, NB tiles ahead, across unit
@@ -41,20 +45,21 @@
 // waits stricter.
 //
 // Tiles that hold fp16 rows (and tiles in which K and V are split differently) are served by workgroups
-// of their own in the same launch, one or more per unit: key rows are matrix operands as they are; value rows meet
-// the fp32 probabilities in 16x16x4 fp32 products.  (Inside the pipelined workgroups that path cost 30 us:
+// of their own in the same launch (or one before it), one or more per unit: key rows are matrix operands as they are; value
+// rows meet the fp32 probabilities in 16x16x4 fp32 products; packed parts go through a ring slot.  (Inside the pipelined workgroups that path cost 30 us:
 // its loads queue behind the copies in flight and its registers do not fit beside the loop's.)
 //
 // Work: every (batch, kv-head, run of query heads) unit has its steps (4 tiles, one per wavefront of a
-// workgroup) on an axis that is cut into one interval per resident workgroup; a workgroup that
+// workgroup) on an axis that is cut into one interval per resident workgroup (kivi_tiles_plan.h); a workgroup that
 // owns part of a unit leaves a part (m, l, o[128]) per head in the workspace, the last one merges.
 //
-// Bound: issue of vector instructions (three wavefronts per SIMD; the copies alone would stream twice as fast);
-// short launches by the fixed ~5 us of start, ~3 us to leave a unit and the merge.  Measured against
-// decode_mfma_kernel, whole steps: 32 query / 8 kv heads, batch 4, 32 767 tokens, 2 bits 47.7 -> 36.2 us
-// (2.85 TB/s); 64 / 8 heads 48.3 -> 30.7 us; 71 / 1 heads, batch 16, 4095 tokens 70.6 -> 34.3 us.  Error against 64
-// bits 8e-6 of the output (there 1e-4: codes are placed high in the mantissa here, and the matrix unit aligns
-// products by their nominal exponent).
+// Bound: about half by issue of vector instructions (three wavefronts per SIMD; by the counters 18 us of the 31-35 us
+// launch at 32 query / 8 kv heads, batch 4, 32 767 tokens, 2 bits; 12 of 30 at 64 / 8; the copies alone would stream twice as
+// fast), for the rest by what each launch pays once: ~5 us until the first tile is there, ~3 us to leave a unit, the merge.
+// Measured against decode_mfma_kernel, whole steps: 32 / 8 heads 47.2 -> 35.1 us (2.9 TB/s); 64 / 8 heads, batch 4, 16 377
+// tokens 48.4 -> 30.3 us; 71 / 1 heads, batch 16, 4095 tokens 70.6 -> 33.9 us.  Error against 64 bits 5e-6 to 1e-5 of the
+// output (there 1e-4: codes are placed high in the mantissa here, and the matrix unit aligns products by their nominal
+// exponent).
 #include "kivi_internal.h"
 #include "kivi_tiles_plan.h"
 
