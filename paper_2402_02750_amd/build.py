@@ -13,7 +13,7 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libkivi_hip.so")
 
 SOURCES = ["kivi_api.hip", "kivi_quantize.hip", "kivi_decode_valu.hip", "kivi_decode_mfma.hip",
-           "kivi_decode_tiles.hip", "kivi_decode_rows.hip"]
+           "kivi_decode_tiles.hip", "kivi_decode_one.hip", "kivi_decode_rows.hip"]
 
 COMMON_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wextra",

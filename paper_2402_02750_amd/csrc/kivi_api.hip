@@ -382,8 +382,10 @@ int enqueue_attention(const kivi_layout_t* l, const kivi_cache_t* c, const void*
     p.counters = static_cast<int32_t*>(workspace);
     const bool tiles = path == KIVI_DECODE_MFMA && uses_tiles(l) && !(flush_k && l->n_q_heads <= 2 * l->n_kv_heads);
     if (tiles && rows_launch_for_uneven_split(l, c, path)) p.two_launches = 1;
+    // One query head per kv-head: a single launch whatever the plan, which its workspace rows always fit.
+    const bool one = path == KIVI_DECODE_MFMA && l->decode_path != KIVI_DECODE_MFMA_TWO && l->n_q_heads == l->n_kv_heads && c->n_kq == c->n_vq && !flush_k;
     p.part_stride = p.plan.n_splits();
-    if (tiles) p.part_stride = part_rows(l, workspace_bytes - counter_bytes(l));
+    if (tiles || one) p.part_stride = part_rows(l, workspace_bytes - counter_bytes(l));
     p.part_o = reinterpret_cast<float*>(static_cast<char*>(workspace) + counter_bytes(l));
     p.part_ml = p.part_o + (size_t)l->batch * l->n_q_heads * p.part_stride * kHeadDim;
 
@@ -403,6 +405,7 @@ int enqueue_attention(const kivi_layout_t* l, const kivi_cache_t* c, const void*
         p.head_groups = ceil_div(rep_total, p.rep_here);
         return hip_status(launch_decode_tiles(p, hs));
     }
+    if (one) return hip_status(launch_decode_one(p, hs));
     if (const int shift = head_split_shift(l, p.plan, path, two)) {
         p.head_groups = 1 << shift;
         p.q_head0 = 0;

@@ -1,0 +1,721 @@
+// Decode attention, matrix-core family, one query head per kv-head, K and V split at the same token (KIVI Equation 4 and
+// Algorithm 1 Decoding): fp16 rows and quantised tiles of a cache in ONE launch, every byte through asynchronous copies.
+//
+// A unit is a (batch entry, kv-head).  Its work is a list of steps: first the fp16 rows of the window, then the
+// quantised tiles.  A step gives every wavefront of a workgroup one slot of its own LDS ring: PT tiles (codes, scales,
+// zero-points), or the K and V rows of NT tokens -- both are NI copies of 1 KB, so the wait for the oldest slot is one vmcnt
+// with a constant and rows and tiles follow each other without a border.  A workgroup takes a run of a unit's steps; with
+// several per unit each leaves a part (m, l, o[128]) in the workspace and the last one merges.  Workgroups are not
+// persistent: whole units need no merge, and a new one's start is hidden behind the others of its compute unit.
+//
+// Arithmetic (as in decode_tiles_kernel, whose comments say why the exponents are what they are): a code left in place
+// inside an fp16 lane is the exact subnormal code * 4^r * 2^-24; the matrix instruction multiplies it with q_c s_c (keys) or
+// p_t s_t,g (values), split into fp16 hi + remainder in two matrix columns.  With one head 14 of 16 columns would be copies
+// if every lane made the eight elements of its own column.  Instead a lane makes two elements (two channels of the key
+// operand; one token, two groups of the value operand) with two or three packed instructions, and the columns are
+// filled through LDS; the value side's columns hold the four channel groups at once, so that a tile takes one operand.
+// Each lane's softmax work is one token (of 32, every token in two lanes), the one whose operand it makes.
+//
+// PT = 2 at 2 bits: the two tiles' chains (LDS, matrix unit, LDS, matrix unit: 0.9 us alone) overlap in one wavefront.  Three
+// workgroups per compute unit hold 147 KB (2 bits) or 123 KB (4 bits) of copies in flight.  (Measured against two with three slots
+// each, eight or sixteen wavefronts, one tile and four slots at 2 bits: this shape within 3 % of the best everywhere.)
+//
+// Bound: HBM.  A launch that only copies what this one reads takes 29.7 us for 512 units of 124 tiles at 2 bits (6.6 TB/s), rows and
+// all 35; this kernel 39.5 (decode_mfma_kernel 46).  What is left is start (2 us to the first tile), the last step and the
+// merge (3 us).  Whole steps, 2 bits, decode_mfma_kernel -> this one: 32 units x 3000 tokens 12.8 -> 9.5 us, 128 x 4000 22.8 ->
+// 16.2, 256 x 1000 22.7 -> 11.2, 256 x 4000 31.1 -> 24.7, 512 x 1000 23.7 -> 17.7, 512 x 4000 46.3 -> 39.6, 768 x 4000 69.6 -> 58.7,
+// 2048 x 2000 92.4 -> 86.0; 4 bits: 256 x 4000 40.7 -> 33.2, 320 x 8000 75.5 -> 72.6, 1024 x 4000 112.3 -> 111.3.
+// Error against 64 bits: 3e-6 to 1.2e-5 of the output (decode_mfma_kernel 5e-5 to 2.5e-4).
+#include "kivi_internal.h"
+#include "kivi_tiles_plan.h"
+
+#include <hip/hip_fp16.h>
+
+#include <algorithm>
+#include <atomic>
+
+namespace kivi {
+namespace {
+
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float float4v __attribute__((ext_vector_type(4)));
+typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
+
+union Frag {            // one lane's share of a 16x16x32 fp16 operand: eight halves
+    half8 h;
+    half2v p[4];
+    uint32_t r[4];
+};
+
+constexpr float kKeyUnscale = 4194304.0f;      // 2^22: key codes enter as code * 4^r * 2^-22
+constexpr float kValueUnscale = 262144.0f;     // 2^18: value codes enter as code * 2^-18 (times 4 in registers 1 and 3 at 2 bits)
+constexpr float kLog2e = 1.4426950408889634f;
+constexpr int kSlack = 4;                      // log2 headroom of the running softmax reference
+constexpr int kQueryExp = 8;                   // largest |q'| lies in [2^8, 2^9)
+constexpr uint32_t kKeyScaleLimit = 0x54005400u;       // two times fp16 64.0
+constexpr int kKeyScaleShift = 9;              // a slot with larger scales whose products pass kProductLimit takes s 2^-9
+constexpr uint32_t kProductLimit = 0x78007800u;        // two times fp16 2^15
+// Value side: p' = p 2^kProbExp, scales taken as s 2^-ks with s 2^-ks < 2^kValueTop; larger ones as they are while their
+// products with p' stay below kValueProductLimit; ks falls back when a slot's scales are 2^-kValueWindow of that
+template <int BITS> constexpr int kProbExp = BITS == 2 ? 8 : 11;
+template <int BITS> constexpr int kValueTop = BITS == 2 ? 3 : 0;
+constexpr int kValueWindow = 7;
+constexpr float kValueProductLimit = 2048.f;
+
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppRor4 = 0x124, kDppRor8 = 0x128;
+
+// sum / maximum over the lanes that differ in bits 4 and 5
+__device__ __forceinline__ float add_rows(float x) {
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(x), false, false);
+    x = __int_as_float(a[0]) + __int_as_float(a[1]);
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
+    return __int_as_float(b[0]) + __int_as_float(b[1]);
+}
+__device__ __forceinline__ float max_rows(float x) {
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(x), false, false);
+    x = fmaxf(__int_as_float(a[0]), __int_as_float(a[1]));
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
+    return fmaxf(__int_as_float(b[0]), __int_as_float(b[1]));
+}
+__device__ __forceinline__ float row_sum(float x) {
+    x += dpp<kDppXor1>(x);
+    x += dpp<kDppXor2>(x);
+    x += dpp<kDppHalfMirror>(x);
+    return x + dpp<kDppRor8>(x);
+}
+__device__ __forceinline__ float wave_sum(float x) { return add_rows(row_sum(x)); }
+__device__ __forceinline__ float wave_max(float x) {
+    x = fmaxf(x, dpp<kDppXor1>(x));
+    x = fmaxf(x, dpp<kDppXor2>(x));
+    x = fmaxf(x, dpp<kDppHalfMirror>(x));
+    return max_rows(fmaxf(x, dpp<kDppRor8>(x)));
+}
+
+__device__ __forceinline__ int ring_slot(int start, int i, int cap) {
+    int s = start + i;
+    s -= (s >= cap) ? cap : 0;
+    return s;
+}
+
+// Workgroup barrier that orders LDS traffic only (a __syncthreads() would also wait for the copies in flight).
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+__device__ __forceinline__ void wave_lds_sync() {      // LDS instructions of one wavefront execute in order
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+}
+// device-scope accesses for the parts (see decode_mfma_kernel: published without cache flushes)
+__device__ __forceinline__ void device_store(float* p, float2 v) {
+    __hip_atomic_store(reinterpret_cast<uint64_t*>(p), __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 device_load(const float* p) {
+    return __builtin_bit_cast(float2, __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// Asynchronous copy of 16 bytes per lane: lane l's bytes land at LDS offset lds + 16 l.  (From inline asm: the compiler would
+// make every LDS read wait for all copies in flight; they have no output registers, and further vector-memory
+// operations only make the explicit waits stricter.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void copy_to_lds(const void* base, uint32_t lane_offset, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(lane_offset), "s"(base) : "memory", "m0");
+}
+__device__ __forceinline__ void copy_to_lds(const void* lane_ptr, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds), "v"(lane_ptr) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+template <int N>
+__device__ __forceinline__ void wait_copies() {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+__device__ __forceinline__ half2v pack_rtz(float a, float b) { return __builtin_bit_cast(half2v, __builtin_amdgcn_cvt_pkrtz(a, b)); }
+__device__ __forceinline__ half2v half2_of(uint32_t x) { return __builtin_bit_cast(half2v, x); }
+
+// Code fragments of tile coordinate u = 2 pair + odd: codes as high in the mantissa as they go (keys at bits 2, 4, 6, 8 or 2, 6;
+// values at 6, 8 or 6), see decode_tiles_kernel
+template <int BITS>
+__device__ __forceinline__ half8 key_fragment(const uint32_t* w, int pair, int odd) {
+    Frag f;
+    if constexpr (BITS == 2) {
+        const uint32_t x = odd ? w[pair] >> 6 : w[pair] << 2;
+        f.r[0] = x & 0x000C000Cu; f.r[1] = x & 0x00300030u;
+        f.r[2] = x & 0x00C000C0u; f.r[3] = x & 0x03000300u;
+    } else {
+        const uint32_t x0 = odd ? w[pair * 2] >> 6 : w[pair * 2] << 2, x1 = odd ? w[pair * 2 + 1] >> 6 : w[pair * 2 + 1] << 2;
+        f.r[0] = x0 & 0x003C003Cu; f.r[1] = x0 & 0x03C003C0u;
+        f.r[2] = x1 & 0x003C003Cu; f.r[3] = x1 & 0x03C003C0u;
+    }
+    return f.h;
+}
+template <int BITS>
+__device__ __forceinline__ half8 value_fragment(const uint32_t* w, int pair, int odd) {
+    Frag f;
+    if constexpr (BITS == 2) {
+        const uint32_t x = odd ? w[pair] >> 2 : w[pair] << 6, y = odd ? w[pair] >> 6 : w[pair] << 2;
+        f.r[0] = x & 0x00C000C0u; f.r[1] = x & 0x03000300u;
+        f.r[2] = y & 0x00C000C0u; f.r[3] = y & 0x03000300u;
+    } else {
+        const uint32_t w0 = w[pair * 2], w1 = w[pair * 2 + 1];
+        f.r[0] = (odd ? w0 >> 2 : w0 << 6) & 0x03C003C0u; f.r[1] = (odd ? w0 >> 6 : w0 << 2) & 0x03C003C0u;
+        f.r[2] = (odd ? w1 >> 2 : w1 << 6) & 0x03C003C0u; f.r[3] = (odd ? w1 >> 6 : w1 << 2) & 0x03C003C0u;
+    }
+    return f.h;
+}
+
+template <int BITS, int PT, int NB, int WV>
+struct Shape {
+    static constexpr int kCodeBytes = kTileTokens * kHeadDim * BITS / 8;
+    static constexpr int kTileBytes = 2 * kCodeBytes + 1024;
+    static constexpr int kSlotBytes = PT * kTileBytes;
+    static constexpr int kPlanes = BITS / 2;
+    static constexpr int NI = PT * (2 * kPlanes + 1);          // copy instructions per slot
+    static constexpr int NT = 2 * NI;                          // tokens whose fp16 rows (K and V) fill a slot
+    static constexpr int kStepTiles = WV * PT, kStepRows = WV * NT;
+    // operands of a tile: key side hi (128 halves), 16 halves of skew, lo; value side 8 columns of 32 tokens
+    static constexpr int kKeyColumn = 144, kOperandHalves = 272;
+    static constexpr int kWaveBytes = NB * kSlotBytes + PT * kOperandHalves * 2;
+    static constexpr int kLds = WV * kWaveBytes + WV * 8 + 16;
+};
+
+template <int BITS, int PT, int NB, int WV, int OCC, bool CS>
+__global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(DecodeParams p) {
+    using S = Shape<BITS, PT, NB, WV>;
+    constexpr int NI = S::NI, NT = S::NT, NR = (NT + 3) / 4;
+    __shared__ __align__(16) unsigned char sm[S::kLds];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, kb = lane >> 4;
+    const bool is_lo = n >= 8;
+    const int kg = CS ? p.kg_shift : 0;
+    unsigned char* ring = sm + wave * S::kWaveBytes;
+    _Float16* operand = reinterpret_cast<_Float16*>(ring + NB * S::kSlotBytes);
+    unsigned char* sm_query = ring + NB * S::kSlotBytes;                        // (until the first operands are made)
+    float (*sm_ml)[2] = reinterpret_cast<float (*)[2]>(sm + WV * S::kWaveBytes);
+    int& sm_last = *reinterpret_cast<int*>(sm + WV * S::kWaveBytes + WV * 8);
+    const uint32_t ring_lds = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)ring);
+
+    // ---- this workgroup's run of its unit's steps: rows [b0, b1), tiles [a0, a1) ----
+    const int u = blockIdx.x / p.unit_wgs, part = blockIdx.x % p.unit_wgs;
+    const int tiles = p.plan.tiles_a;
+    const int n_kr = p.n_kr;
+    const StepAxis axis{p.axis_len, p.axis_rem};
+    const int s0 = axis.start(part), s1 = axis.start(part + 1);
+    const int nr = (n_kr + S::kStepRows - 1) / S::kStepRows;
+    const int b0 = min(s0, nr), b1 = min(s1, nr), a0 = max(s0, nr) - nr, a1 = max(s1, nr) - nr;
+    const int len_a = a1 - a0, todo0 = s1 - s0;
+    const int64_t unit = u;
+
+    // ---- copies ----
+    const uint32_t lane16 = lane * 16;
+    const int64_t tile0 = unit * p.cap_tiles;
+    // lanes 0-15 k_scale, 16-31 k_zero, 32-47 v_scale, 48-63 v_zero
+    const char* sc = reinterpret_cast<const char*>(kb == 0 ? p.k_scale : kb == 1 ? p.k_zero : kb == 2 ? p.v_scale : p.v_zero);
+    sc += CS && kb >= 2 ? min(n * 16, (256 >> kg) - 16) : n * 16;
+    auto copy_tiles = [&](int t0, int slot) {
+        const uint32_t dst = ring_lds + slot * S::kSlotBytes;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");             // the slot's last readers have their data
+#pragma unroll
+        for (int t = 0; t < PT; ++t) {
+            const int64_t tile = tile0 + min(t0 + t, tiles - 1);
+            const char* kc = reinterpret_cast<const char*>(p.k_codes) + tile * S::kCodeBytes;
+            const char* vc = reinterpret_cast<const char*>(p.v_codes) + tile * S::kCodeBytes;
+#pragma unroll
+            for (int pl = 0; pl < S::kPlanes; ++pl) {
+                copy_to_lds(kc + pl * 1024, lane16, dst + t * S::kTileBytes + pl * 1024);
+                copy_to_lds(vc + pl * 1024, lane16, dst + t * S::kTileBytes + S::kCodeBytes + pl * 1024);
+            }
+            int64_t off = tile * 256;
+            if constexpr (CS) off = kb < 2 ? (tile >> kg) * 256 : (tile * 256) >> kg;
+            copy_to_lds(sc + off, dst + t * S::kTileBytes + 2 * S::kCodeBytes);
+        }
+    };
+    // key rows of the window's tokens t0 .. t0 + NT - 1, then value rows, 256 bytes each (past the end the last token's again;
+    // the newest token's out of k_new / v_new)
+    auto copy_rows = [&](int t0, int slot) {
+        const uint32_t dst = ring_lds + slot * S::kSlotBytes;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            const int r = 4 * j + kb;
+            const bool is_v = r >= NT;
+            const int t = min(t0 + (is_v ? r - NT : r), n_kr - 1);
+            const __half* src = (is_v ? p.v_resid : p.k_resid) + (unit * p.cap_r + ring_slot(is_v ? p.v_r_start : p.k_r_start, t, p.cap_r)) * kHeadDim;
+            if (p.k_new && t == n_kr - 1) src = (is_v ? p.v_new : p.k_new) + unit * kHeadDim;
+            copy_to_lds(src + n * 8, dst + j * 1024);
+        }
+    };
+    // the query
+    if (lane < 16) copy_to_lds(p.q + unit * kHeadDim + n * 8, (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)sm_query));
+    // Tiles in an order rotated by the unit: workgroups in lockstep that all read the same relative offset of their units
+    // would meet on few memory channels for unlucky strides (a copy alone: 32.3 -> 29.8 us at 512 units).
+    int nx_a = len_a > 0 ? a0 + (int)((uint32_t)(u * 5) % (uint32_t)len_a) : 0, nx_left = todo0, nx_b = b0;
+    auto advance_copy = [&](int slot) {
+        if (nx_left <= 0) return;
+        if (nx_b < b1) {
+            copy_rows(nx_b * S::kStepRows + wave * NT, slot);
+            ++nx_b;
+        } else {
+            copy_tiles(nx_a * S::kStepTiles + wave * PT, slot);
+            if (++nx_a == a1) nx_a = a0;
+        }
+        --nx_left;
+    };
+#pragma unroll 1
+    for (int i = 0; i < NB; ++i) advance_copy(i);
+
+    // ---- state ----
+    // own_tok, own_pair: the token (of every tile) and the channel groups 2 own_pair, + 1 whose value operand this lane makes
+    const int own_i = (n >> 1) & 3, own_pair = n & 1, own_tok = kb * 4 + own_i + (is_lo ? 16 : 0);
+    const float own_exp = BITS == 2 ? (float)(own_i & 2) : 0.f;            // log2 of that token's code position factor
+    const int my_group = (n & 1) * 2 + ((n >> 1) & 1);
+    float4v acc[8];
+    // acc[u][i]: value code sums of channel 16 u + 4 kb + i, column n (of use where its group is u >> 1); z_own: zero-point sums of
+    // this lane's tokens and groups; r_out: the fp16 rows' outputs of channels 8 n .. over rows kb, kb + 4, ..; mref: reference
+    // (log2) of the probabilities, l_lane, r_l: sums of this lane's
+    float z_own[2] = {0.f, 0.f}, r_out[8], r_l = 0.f, l_lane = 0.f, mref = -INFINITY;
+#pragma unroll
+    for (int u8 = 0; u8 < 8; ++u8) acc[u8] = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) r_out[e] = 0.f;
+    int ks = 0;
+    bool ks_set = false;
+    uint32_t value_limit = 0;
+
+    const int in_flight = min(todo0, NB);
+    if (in_flight == NB) wait_copies<NB * NI>();       // the query has arrived, the first slots are on their way
+    else wait_copies<NI>();
+    float c_code, c_zero;
+    half2v q_own, qk_own;
+    const half8 q_row = *reinterpret_cast<const half8*>(sm_query + n * 16);
+    {
+        const half2v raw = *reinterpret_cast<const half2v*>(sm_query + lane * 4);
+        const float mx = wave_max(fmaxf(fabsf((float)raw[0]), fabsf((float)raw[1])));
+        const bool on = mx > 0.f;
+        const int a = on ? min(kQueryExp + 127 - (int)(__float_as_uint(mx) >> 23), 28) : 0, ah = a / 2;
+        const _Float16 up1 = on ? (_Float16)__uint_as_float((uint32_t)(127 + ah) << 23) : (_Float16)0.f;
+        const _Float16 up2 = (_Float16)__uint_as_float((uint32_t)(127 + a - ah) << 23);
+        c_zero = p.softmax_scale * kLog2e * __uint_as_float((uint32_t)(127 - a) << 23);
+        c_code = c_zero * kKeyUnscale;
+        q_own = raw * half2v{up1, up1} * half2v{up2, up2};
+        const _Float16 pf = (_Float16)__uint_as_float((uint32_t)(127 - (BITS == 2 ? 2 * (lane & 3) : 4 * (lane & 1))) << 23);
+        qk_own = q_own * half2v{pf, pf};
+    }
+
+    auto rescale = [&](float f) {
+#pragma unroll
+        for (int u8 = 0; u8 < 8; ++u8) acc[u8] *= f;
+        z_own[0] *= f;
+        z_own[1] *= f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) r_out[e] *= f;
+        r_l *= f;
+        l_lane *= f;
+    };
+    auto raise_reference = [&](float top) {                                 // top: a lane's largest logit
+        const float mnew = fmaxf(mref, wave_max(top));
+        rescale(mref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mref - mnew));
+        mref = mnew;
+    };
+    auto max_pairs = [&](uint32_t a, uint32_t b) -> uint32_t {              // non-negative fp16 compare as integers
+        typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ushort2v, a), __builtin_bit_cast(ushort2v, b)));
+    };
+    auto any_above = [&](uint32_t s2, uint32_t limit) -> bool { return __any(max_pairs(s2, limit) != limit); };
+    auto top_scale = [&](int k) -> uint32_t {
+        const int top = k + kValueTop<BITS> + 15;                           // biased fp16 exponent
+        const uint32_t lim = top >= 31 ? 0x7BFFu : top <= 0 ? 0u : (uint32_t)(top << 10) - 1;
+        return lim | lim << 16;
+    };
+    auto fit_value_exponent = [&](uint32_t s2, auto&& top_product) {
+        if (!any_above(s2, value_limit)) return;
+        bool high = true;
+        if (ks > 0) {
+            high = any_above(s2, top_scale(ks));
+            if (!high && any_above(s2, (uint32_t)(ks + kValueTop<BITS> - kValueWindow + 15) * 0x04000400u)) return;
+        }
+        const float mx = wave_max(fmaxf((float)half2_of(s2)[0], (float)half2_of(s2)[1]));
+        const int want = __builtin_amdgcn_readfirstlane(max((int)(__float_as_uint(mx) >> 23) - 126 - kValueTop<BITS>, -24));
+        int next = max(want, 0);
+        if (high) {
+            next = ks_set && ks >= 0 ? ks : want > -kValueWindow ? 0 : want;
+            if (want > next && __any(top_product() > kValueProductLimit * __uint_as_float((uint32_t)(127 + next) << 23))) next = want;
+        }
+        if (ks_set) {
+            const float f = __uint_as_float((uint32_t)(127 + ks - next) << 23);
+#pragma unroll
+            for (int u8 = 0; u8 < 8; ++u8) acc[u8] *= f;
+        }
+        ks = next;
+        ks_set = true;
+        value_limit = ks > 0 ? 0 : top_scale(ks);
+    };
+    auto own_of = [&](const float4v& x) -> float {
+        const float a = own_i & 1 ? x[1] : x[0], b = own_i & 1 ? x[3] : x[2];
+        return own_i & 2 ? b : a;
+    };
+
+    auto load_codes = [&](const unsigned char* at, uint32_t (&w)[2 * BITS]) {
+#pragma unroll
+        for (int pl = 0; pl < S::kPlanes; ++pl) {
+            const uint4v v = *reinterpret_cast<const uint4v*>(at + pl * 1024 + lane16);
+            w[4 * pl + 0] = v[0]; w[4 * pl + 1] = v[1]; w[4 * pl + 2] = v[2]; w[4 * pl + 3] = v[3];
+        }
+    };
+    const int value_at = CS ? own_tok * (8 >> kg) + ((2 * own_pair) >> kg) * 2 : own_tok * 8 + own_pair * 4;
+    auto value_pair = [&](const unsigned char* at) -> uint32_t {
+        if constexpr (CS) {
+            const uint32_t h = *reinterpret_cast<const uint16_t*>(at + value_at);
+            return h | h << 16;
+        } else {
+            return *reinterpret_cast<const uint32_t*>(at + value_at);
+        }
+    };
+    // PT tiles of a slot; live: those that are there
+    auto quantised = [&](const unsigned char* sl, int live) {
+        constexpr int kS = 2 * S::kCodeBytes;
+        uint32_t kw[PT][2 * BITS], vw[PT][2 * BITS], s_raw[PT], v_raw[PT], top = 0;
+        half2v s[PT], z[PT], vz[PT];
+#pragma unroll
+        for (int t = 0; t < PT; ++t) {
+            const unsigned char* at = sl + t * S::kTileBytes;
+            s_raw[t] = *reinterpret_cast<const uint32_t*>(at + kS + lane * 4);
+            z[t] = half2_of(*reinterpret_cast<const uint32_t*>(at + kS + 256 + lane * 4));
+            load_codes(at, kw[t]);
+            v_raw[t] = value_pair(at + kS + 512);
+            vz[t] = half2_of(value_pair(at + kS + 768));
+            load_codes(at + S::kCodeBytes, vw[t]);
+            s[t] = half2_of(s_raw[t]);
+            top = max_pairs(top, s_raw[t]);
+        }
+        float cx = c_code;
+        if (any_above(top, kKeyScaleLimit)) {
+            uint32_t a = 0;
+#pragma unroll
+            for (int t = 0; t < PT; ++t) a = max_pairs(a, __builtin_bit_cast(uint32_t, qk_own * s[t]) & 0x7FFF7FFFu);
+            if (any_above(a, kProductLimit)) {
+                const _Float16 f1 = (_Float16)(1.f / (1 << kKeyScaleShift));
+#pragma unroll
+                for (int t = 0; t < PT; ++t) s[t] *= half2v{f1, f1};
+                cx = c_code * (float)(1 << kKeyScaleShift);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < PT; ++t) {
+            const half2v hi = qk_own * s[t], lo = __builtin_elementwise_fma(qk_own, s[t], -hi);
+            _Float16* b = operand + t * S::kOperandHalves;
+            *reinterpret_cast<half2v*>(b + 2 * lane) = hi;
+            *reinterpret_cast<half2v*>(b + S::kKeyColumn + 2 * lane) = lo;
+        }
+        wave_lds_sync();
+        half8 f[PT][4];
+#pragma unroll
+        for (int t = 0; t < PT; ++t)
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb)
+                f[t][cb] = *reinterpret_cast<const half8*>(operand + t * S::kOperandHalves + (is_lo ? S::kKeyColumn : 0) + cb * 32 + kb * 8);
+        float zk[PT];
+#pragma unroll
+        for (int t = 0; t < PT; ++t) zk[t] = wave_sum(__builtin_amdgcn_fdot2(q_own, z[t], 0.f, false)) * c_zero;
+        float4v d[PT][2];
+#pragma unroll
+        for (int t = 0; t < PT; ++t) d[t][0] = d[t][1] = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+            for (int t = 0; t < PT; ++t) {
+                d[t][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(key_fragment<BITS>(kw[t], cb, 0), f[t][cb], d[t][0], 0, 0, 0);
+                d[t][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(key_fragment<BITS>(kw[t], cb, 1), f[t][cb], d[t][1], 0, 0, 0);
+            }
+        // this lane's token of every tile: probability over the code's position factor
+        float x[PT], pv[PT], mx = -INFINITY;
+#pragma unroll
+        for (int t = 0; t < PT; ++t) {
+            const float x0 = own_of(d[t][0]), x1 = own_of(d[t][1]);
+            x[t] = fmaf((is_lo ? x1 : x0) + dpp<kDppRor8>(is_lo ? x0 : x1), cx, zk[t]);
+            if (t > 0 && t >= live) x[t] = -INFINITY;
+            mx = fmaxf(mx, x[t]);
+        }
+        if (__any(mx > mref + (float)kSlack)) raise_reference(mx);
+        const float off = (float)kProbExp<BITS> - own_exp - mref;
+        uint32_t vtop = 0;
+#pragma unroll
+        for (int t = 0; t < PT; ++t) {
+            pv[t] = __builtin_amdgcn_exp2f(x[t] + off);
+            l_lane += pv[t];
+            if (t == 0 || t < live) vtop = max_pairs(vtop, v_raw[t]);
+        }
+        fit_value_exponent(vtop, [&]() {
+            float m = 0.f;
+#pragma unroll
+            for (int t = 0; t < PT; ++t) m = fmaxf(m, pv[t] * fmaxf((float)half2_of(v_raw[t])[0], (float)half2_of(v_raw[t])[1]));
+            return m;
+        });
+        _Float16 k1 = (_Float16)1.f, k2 = (_Float16)1.f;
+        if (ks != 0) {          // 2^-ks as two factors: each is a normal fp16 number for every ks in [-24, 16]
+            k1 = (_Float16)__uint_as_float((uint32_t)(127 - ks / 2) << 23);
+            k2 = (_Float16)__uint_as_float((uint32_t)(127 - ks + ks / 2) << 23);
+#pragma unroll
+            for (int t = 0; t < PT; ++t) v_raw[t] = __builtin_bit_cast(uint32_t, half2_of(v_raw[t]) * half2v{k1, k1} * half2v{k2, k2});
+        }
+#pragma unroll
+        for (int t = 0; t < PT; ++t) {
+            const half2v ph = pack_rtz(pv[t], pv[t]);
+            float rest;
+            asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(rest) : "v"(ph), "v"(pv[t]));
+            const half2v pl = pack_rtz(rest, rest), sv = half2_of(v_raw[t]);
+            const half2v hi = ph * sv, lo = __builtin_elementwise_fma(pl, sv, __builtin_elementwise_fma(ph, sv, -hi));
+            z_own[0] = fmaf(pv[t], (float)vz[t][0], z_own[0]);
+            z_own[1] = fmaf(pv[t], (float)vz[t][1], z_own[1]);
+            _Float16* col = operand + t * S::kOperandHalves + own_pair * 4 * 32 + own_tok;         // columns (group, hi / lo)
+            col[0] = hi[0];
+            col[32] = lo[0];
+            col[64] = hi[1];
+            col[96] = lo[1];
+        }
+        wave_lds_sync();
+        half8 fv[PT];
+#pragma unroll
+        for (int t = 0; t < PT; ++t)
+            fv[t] = *reinterpret_cast<const half8*>(operand + t * S::kOperandHalves + (my_group * 2 + (is_lo ? 1 : 0)) * 32 + kb * 8);
+#pragma unroll
+        for (int t = 0; t < PT; ++t)
+#pragma unroll
+            for (int u8 = 0; u8 < 8; ++u8)
+                acc[u8] = __builtin_amdgcn_mfma_f32_16x16x32_f16(value_fragment<BITS>(vw[t], u8 >> 1, u8 & 1), fv[t], acc[u8], 0, 0, 0);
+        wave_lds_sync();
+    };
+    // NT tokens' fp16 rows; lane (n, kb) takes channels 8 n .. of rows kb, kb + 4, ..
+    auto fp16_rows = [&](const unsigned char* sl, int left) {
+        const float c_row = p.softmax_scale * kLog2e;
+        float x[NR], mx = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < NR; ++j) {
+            Frag k, q;
+            k.h = *reinterpret_cast<const half8*>(sl + (4 * j + kb) * 256 + n * 16);
+            q.h = q_row;
+            float a = 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) a = __builtin_amdgcn_fdot2(k.p[r], q.p[r], a, false);
+            x[j] = 4 * j + kb < min(left, NT) ? row_sum(a) * c_row : -INFINITY;
+            mx = fmaxf(mx, x[j]);
+        }
+        if (__any(mx > mref + (float)kSlack)) raise_reference(mx);
+#pragma unroll
+        for (int j = 0; j < NR; ++j) {
+            const float pr = __builtin_amdgcn_exp2f(x[j] + ((float)kProbExp<BITS> - mref));
+            r_l += pr;
+            const half8 v = *reinterpret_cast<const half8*>(sl + NT * 256 + min(4 * j + kb, NT - 1) * 256 + n * 16);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) r_out[e] = fmaf(pr, (float)v[e], r_out[e]);
+        }
+        if (p.k_new && left <= NT && kb < 2) {                                    // the newest token's rows go to the rings
+            const uint4v row = *reinterpret_cast<const uint4v*>(sl + (kb * NT + left - 1) * 256 + n * 16);
+            const int at = ring_slot(kb ? p.v_r_start : p.k_r_start, n_kr - 1, p.cap_r);
+            *reinterpret_cast<uint4v*>(const_cast<__half*>(kb ? p.v_resid : p.k_resid) + (unit * p.cap_r + at) * kHeadDim + n * 8) = row;
+        }
+    };
+    // The instruction arbiter favours the oldest wavefront of a SIMD.  Where all workgroups start at once the younger ones would
+    // end late and alone (512 units: 28 against 36 us), so a wavefront's priority falls with the share of its work that is done (39.6 ->
+    // 38.7 us); with more workgroups than fit at once the oldest ones' head start is what hides the others' starts (2048
+    // units: 87 us as it is, 91 with falling priorities).
+    const int quarter = p.one_round ? todo0 >> 2 : 0x1fffffff;
+    auto wait_oldest = [&](int todo) {
+        if (todo > 3 * quarter) __builtin_amdgcn_s_setprio(3);
+        else if (todo > 2 * quarter) __builtin_amdgcn_s_setprio(2);
+        else if (todo > quarter) __builtin_amdgcn_s_setprio(1);
+        else __builtin_amdgcn_s_setprio(0);
+        if (todo >= NB) wait_copies<(NB - 1) * NI>();
+        else wait_copies<0>();
+    };
+    int slot = 0, todo = todo0, at_a = len_a > 0 ? a0 + (int)((uint32_t)(u * 5) % (uint32_t)len_a) : 0;
+#pragma unroll 1
+    for (int j = b0; j < b1; ++j) {
+        wait_oldest(todo);
+        const int left = n_kr - (j * S::kStepRows + wave * NT);
+        if (left > 0) fp16_rows(ring + slot * S::kSlotBytes, left);
+        advance_copy(slot);
+        slot = slot + 1 == NB ? 0 : slot + 1;
+        --todo;
+    }
+#pragma unroll 1
+    for (int j = 0; j < len_a; ++j) {
+        wait_oldest(todo);
+        const int live = tiles - (at_a * S::kStepTiles + wave * PT);
+        if (live > 0) quantised(ring + slot * S::kSlotBytes, live);
+        if (++at_a == a1) at_a = a0;
+        advance_copy(slot);
+        slot = slot + 1 == NB ? 0 : slot + 1;
+        --todo;
+    }
+
+    // ---- merge the wavefronts (their rings are free) ----
+    float* o_wave = reinterpret_cast<float*>(ring);
+    {
+        const float l = wave_sum(l_lane * (own_i & 2 && BITS == 2 ? 2.f : 0.5f) + r_l * (1.f / 16));
+        if (lane == 0) {
+            sm_ml[wave][0] = mref;
+            sm_ml[wave][1] = l;
+        }
+        float zo[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            float t = z_own[k] * (own_i & 2 && BITS == 2 ? 4.f : 1.f);
+            t += dpp<kDppXor2>(t);
+            t += dpp<kDppRor4>(t);
+            t += dpp<kDppRor8>(t);
+            zo[k] = add_rows(t);
+        }
+        const float up = kValueUnscale * __uint_as_float((uint32_t)(127 + ks) << 23);
+#pragma unroll
+        for (int u8 = 0; u8 < 8; ++u8) {
+            float4v o;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = fmaf(acc[u8][i] + dpp<kDppRor8>(acc[u8][i]), up, zo[(u8 >> 1) & 1]);
+            if (n < 4 && my_group == u8 >> 1) *reinterpret_cast<float4v*>(&o_wave[u8 * 16 + kb * 4]) = o;
+        }
+        float r[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) r[e] = add_rows(r_out[e]);
+        wave_lds_sync();
+        if (kb == 0) {
+            float4v* o = reinterpret_cast<float4v*>(&o_wave[n * 8]);
+            o[0] += float4v{r[0], r[1], r[2], r[3]};
+            o[1] += float4v{r[4], r[5], r[6], r[7]};
+        }
+    }
+    lds_barrier();
+    const int parts = p.unit_wgs;
+    float m = -INFINITY, ll = 0.f;
+#pragma unroll
+    for (int w = 0; w < WV; ++w) m = fmaxf(m, sm_ml[w][0]);
+    float2 oo = {0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < WV; ++w) {
+        const float mw = sm_ml[w][0];
+        const float f = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - m);
+        const float2 x = *reinterpret_cast<const float2*>(sm + w * S::kWaveBytes + lane * 8);
+        ll = fmaf(sm_ml[w][1], f, ll);
+        oo.x = fmaf(x.x, f, oo.x);
+        oo.y = fmaf(x.y, f, oo.y);
+    }
+    m -= (float)kProbExp<BITS>;
+    float* out = p.out + unit * kHeadDim + 2 * lane;
+    if (parts == 1) {
+        if (wave == 0) *reinterpret_cast<float2*>(out) = make_float2(oo.x / ll, oo.y / ll);
+        return;
+    }
+    const int64_t prow = unit * p.part_stride;
+    if (wave == 0) {
+        device_store(p.part_o + (prow + part) * kHeadDim + 2 * lane, oo);
+        if (lane == 0) device_store(p.part_ml + (prow + part) * 2, make_float2(m, ll));
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (lane == 0) {
+            const int done = __hip_atomic_fetch_add(p.counters + u, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            sm_last = done == parts - 1;
+        }
+    }
+    lds_barrier();
+    if (!sm_last) return;
+    // ---- the last workgroup merges: wavefront w takes parts w, w + 4, ..; lane: two channels ----
+    {
+        constexpr int kBatch = 8;
+        const float* po = p.part_o + prow * kHeadDim + 2 * lane;
+        float2 ov[kBatch];
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) ov[j] = device_load(po + (int64_t)min(wave + WV * j, parts - 1) * kHeadDim);
+        float2 st[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) st[k] = device_load(p.part_ml + (prow + min(lane + 64 * k, parts - 1)) * 2);
+        const float mm = wave_max(fmaxf(st[0].x, st[1].x));
+        float wt[2], lsum = 0.f;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            wt[k] = lane + 64 * k < parts && st[k].x != -INFINITY ? __builtin_amdgcn_exp2f(st[k].x - mm) : 0.f;
+            lsum = fmaf(st[k].y, wt[k], lsum);
+        }
+        lsum = wave_sum(lsum);
+        float2 o = {0.f, 0.f};
+        for (int i0 = 0; wave + i0 < parts; i0 += WV * kBatch) {
+            if (i0 > 0) {
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j) ov[j] = device_load(po + (int64_t)min(wave + i0 + WV * j, parts - 1) * kHeadDim);
+            }
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                const int i = wave + i0 + WV * j;                                // (weights are 0 past the last part)
+                const float w = __int_as_float(i < 64 ? __builtin_amdgcn_readlane(__float_as_int(wt[0]), i & 63) : __builtin_amdgcn_readlane(__float_as_int(wt[1]), i & 63));
+                if (i < parts) {
+                    o.x = fmaf(ov[j].x, w, o.x);
+                    o.y = fmaf(ov[j].y, w, o.y);
+                }
+            }
+        }
+        *reinterpret_cast<float2*>(sm + wave * S::kWaveBytes + 1024 + lane * 8) = o;
+        lds_barrier();
+        if (wave == 0) {
+#pragma unroll
+            for (int w = 1; w < WV; ++w) {
+                const float2 x = *reinterpret_cast<const float2*>(sm + w * S::kWaveBytes + 1024 + lane * 8);
+                o.x += x.x;
+                o.y += x.y;
+            }
+            *reinterpret_cast<float2*>(out) = make_float2(o.x / lsum, o.y / lsum);
+            if (lane == 0) __hip_atomic_store(p.counters + u, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+}
+
+constexpr int kMaxDevices = 64;
+// compute units of the current device (kept per device)
+int compute_units() {
+    static std::atomic<int> cached[kMaxDevices];
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 256;
+    const bool keep = dev >= 0 && dev < kMaxDevices;
+    if (keep) {
+        const int c = cached[dev].load(std::memory_order_relaxed);
+        if (c > 0) return c;
+    }
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
+    if (keep) cached[dev].store(cus, std::memory_order_relaxed);
+    return cus;
+}
+
+template <int BITS, int PT, int NB, int WV, int OCC, bool CS>
+hipError_t launch(DecodeParams p, hipStream_t stream) {
+    using S = Shape<BITS, PT, NB, WV>;
+    static_assert(S::kLds <= 160 * 1024 / OCC / 1280 * 1280, "workgroups per compute unit (LDS is given out in pieces of 1280 bytes)");
+    static_assert(NB == 2 && PT <= 2, "waits and softmax of a slot");
+    const int64_t units = (int64_t)p.batch * p.n_kv_heads;
+    const int steps = (p.plan.tiles_a + S::kStepTiles - 1) / S::kStepTiles + (p.n_kr + S::kStepRows - 1) / S::kStepRows;
+    const int cus = compute_units();
+    const int w = one_head_parts(units, steps, cus, std::min(p.part_stride, kOneHeadMaxParts), BITS == 2 ? 8 : 12);
+    if (steps < 1 || units * w > 0x7fffffff) return hipErrorInvalidValue;
+    p.unit_wgs = w;
+    p.axis_len = steps / w;
+    p.axis_rem = steps % w;
+    p.one_round = units * w <= (int64_t)cus * OCC;
+    decode_one_kernel<BITS, PT, NB, WV, OCC, CS><<<(unsigned)(units * w), 64 * WV, 0, stream>>>(p);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_decode_one(const DecodeParams& p, hipStream_t stream) {
+    if (p.n_q_heads != p.n_kv_heads || p.n_kq != p.n_vq || p.n_kr != p.n_vr || p.part_stride < 1) return hipErrorInvalidValue;
+    const bool cs = p.kg_shift > 0;
+    if (p.bits == 2) return cs ? launch<2, 2, 2, 4, 3, true>(p, stream) : launch<2, 2, 2, 4, 3, false>(p, stream);
+    return cs ? launch<4, 1, 2, 4, 3, true>(p, stream) : launch<4, 1, 2, 4, 3, false>(p, stream);
+}
+
+}  // namespace kivi

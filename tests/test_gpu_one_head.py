@@ -1,0 +1,66 @@
+"""GPU parity of decode_one_kernel (one query head per kv-head) at the sizes where it can go wrong: windows that end inside
+a slot, a step or a ring, tiles that do not fill a step, units in one, several and many parts, more units than fit the chip at
+once, scales outside the ordinary range."""
+import numpy as np
+import pytest
+
+import gpu_harness as gh
+from paper_2402_02750_amd import kivi, workloads
+from paper_2402_02750_amd.workloads import CONFIGS, scaled
+
+pytestmark = pytest.mark.gpu
+
+# (heads, batch, bits, G, residual, prompt tokens, steps, gain of the keys, gain of the values)
+CASES = [
+    (1, 1, 2, 32, 32, 1, 3, 1, 1),              # nothing quantised, two to four rows
+    (2, 1, 4, 32, 32, 63, 2, 1, 1),             # ... a window of two tiles; a flush in the second step
+    (3, 1, 2, 32, 32, 32 + 32 * 1, 12, 1, 1),   # one tile; 33 to 44 rows
+    (2, 2, 2, 32, 32, 32 + 32 * 8, 17, 1, 1),   # a full step of tiles; rows past 48: a second step of rows
+    (2, 2, 4, 32, 64, 64 + 32 * 9, 9, 1, 1),    # ... of the other width, one tile more
+    (5, 3, 2, 32, 128, 1000, 40, 1, 1),         # a ring that wraps, two flushes, two parts a unit and more
+    (4, 1, 2, 32, 32, 30000, 2, 1, 1),          # many parts
+    (4, 1, 4, 32, 32, 30000, 2, 1, 1),
+    (2, 1, 2, 32, 1024, 3000, 3, 1, 1),         # a large window: most steps are rows
+    (32, 9, 2, 32, 128, 1300, 2, 1, 1),         # one part a unit, not all compute units alike
+    (32, 26, 4, 32, 32, 900, 2, 1, 1),          # a few more units than fit at once
+    (3, 2, 2, 64, 128, 2001, 3, 1, 1),
+    (3, 2, 4, 128, 128, 2001, 3, 1, 1),
+    (2, 2, 2, 32, 64, 900, 2, 60, 1),           # key scales past 64
+    (2, 2, 4, 32, 64, 900, 2, 60, 500),         # large value scales
+    (2, 2, 2, 32, 64, 900, 2, 1, 2.0 ** -13),   # value scales among fp16's subnormals
+    (2, 2, 4, 32, 64, 900, 2, 2.0 ** -10, 1),   # small key scales
+]
+
+
+@pytest.mark.parametrize("heads,batch,bits,group,residual,tokens,steps,kgain,vgain", CASES)
+def test_one_head(heads, batch, bits, group, residual, tokens, steps, kgain, vgain):
+    """Decoding steps from a prompt, every step against the oracle; the cache's state after the last.  Tolerance as for
+    decode_tiles_kernel, whose exponents and splits these are: probabilities and operands keep 21 bits, sums and
+    logits in fp32: below 1e-4 of the largest value together."""
+    torch = gh.require_gpu()
+    total = tokens + steps
+    w = scaled(CONFIGS["llama7b"], name="onehead", batch=batch, n_q_heads=heads, n_kv_heads=heads, bits=bits, group=group,
+               residual=residual, seed=17 * heads + bits + tokens)
+    print(f"case one head h={heads} b={batch} B={bits} G={group} R={residual} L={tokens}+{steps} gains {kgain} {vgain}", flush=True)
+    k = (workloads.keys(w, total).astype(np.float32) * kgain).astype(np.float16)
+    v = (workloads.values(w, total).astype(np.float32) * vgain).astype(np.float16)
+    scale = float(np.abs(v.astype(np.float32)).max())
+    at = sorted({(0, 0), (batch - 1, heads - 1), (batch // 2, heads // 2)})
+    oc = gh.oracle_cache_for_heads(w, k[:, :, :tokens], v[:, :, :tokens], at, "window")
+    layout, cache = gh.gpu_prefill(w, k[:, :, :tokens], v[:, :, :tokens], kivi.KIVI_FLUSH_WINDOW, kivi.KIVI_DECODE_AUTO, extra_q_tokens=steps)
+    _, other = gh.gpu_prefill(w, k[:, :, :tokens], v[:, :, :tokens], kivi.KIVI_FLUSH_WINDOW, kivi.KIVI_DECODE_VALU, extra_q_tokens=steps)
+    for step in range(steps):
+        q = (workloads.queries(w, step).astype(np.float32) / max(1, kgain)).astype(np.float16)
+        new = [np.ascontiguousarray(x[:, :, tokens + step]) for x in (k, v)]
+        kn, vn, qt = [torch.from_numpy(x).cuda() for x in (*new, q)]
+        out = torch.full((batch, heads, 128), float("nan"), dtype=torch.float32, device="cuda")
+        kivi.kivi_decode_step(layout, cache, kn, vn, qt, w.softmax_scale, out)
+        oc.append(np.stack([k[b, h, tokens + step] for b, h in at])[:, None], np.stack([v[b, h, tokens + step] for b, h in at])[:, None])
+        ref = gh.oracle_attention_for_heads(w, oc, q, at)
+        got = out.cpu().numpy()
+        err = np.abs(gh.pick_heads(got, w, at) - ref).max()
+        assert err <= 1e-4 * scale, f"step {step}: {err:.3e} against {1e-4 * scale:.3e}"
+        ref_all = torch.empty_like(out)        # all heads: the vector path on a cache of its own
+        kivi.kivi_decode_step(other.layout, other, kn, vn, qt, w.softmax_scale, ref_all)
+        gh.check_close(got / scale, ref_all.cpu().numpy() / scale, f"step {step}, all heads")
+    gh.compare_quantized_state(cache, oc, at)
