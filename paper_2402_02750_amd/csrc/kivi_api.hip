@@ -248,13 +248,11 @@ int decode_family(const kivi_layout_t* l) {
 //      against two: 3 heads 28.3 / 30.0 us (4 bits 29.4 / 31.4), 8 heads 35.0 / 37.1 (4 bits 46.3 / 51.9); with 31 tiles
 //      38.5 / 35.1 and 62.4 / 58.2, and at 1024 units and 15 tiles 48.3 / 44.7 and 78.3 / 70.0.
 // `flush`: the step also flushes and the fp16-row launch could carry that out (G = 32).
-//  (0) One or two heads: a flush has to end before the launch that reads its tiles, so the single-launch form takes
-//      two launches as well, the first of them nearly empty.  Riding with the fp16 rows it costs nothing of its own:
-//      one head, context 4095, batch 1 / 4 / 8 / 16 of 32-40 heads: 17.8 -> 17.1, 31.5 -> 28.3, 36.3 -> 31.4, 50.6 -> 49.3 us.
-//      Not for a few units with long contexts, where the single launch is so much the faster one (8 units, 4 bits, 1055
-//      tokens: 13.9 against 14.8 us, 4095 tokens 15.0 / 16.0; the same at 32 units; two launches still at 479: 13.0 / 13.7), nor
-//      for two heads while decode_tiles_kernel serves them well (8 units, 1055 tokens, 4 bits: 13.7 / 17.2 us; 64 units
-//      17.1 / 17.7; even at 128; 256 units, 4095 tokens 40.7 / 35.7).
+//  (0) Two heads: a flush has to end before the launch that reads its tiles, so the single-launch form takes
+//      two launches as well, the first of them nearly empty.  Riding with the fp16 rows it costs nothing of its own.
+//      Not while decode_tiles_kernel serves them well (8 units, 1055 tokens, 4 bits: 13.7 / 17.2 us; 64 units 17.1 / 17.7;
+//      even at 128; 256 units, 4095 tokens 40.7 / 35.7).  (One head: decode_one_kernel, a single launch whatever this says
+//      unless the caller asks for two.)
 bool wants_two_launches(const kivi_layout_t* l, const kivi_cache_t* c, int path, bool flush = false) {
     if (path != KIVI_DECODE_MFMA || l->decode_path == KIVI_DECODE_MFMA_ONE) return false;
     const int rep_launch = std::min(l->n_q_heads / l->n_kv_heads, kMaxRep);
@@ -266,8 +264,7 @@ bool wants_two_launches(const kivi_layout_t* l, const kivi_cache_t* c, int path,
     if (!possible) return false;
     if (l->decode_path == KIVI_DECODE_MFMA_TWO) return true;
     const int64_t units = (int64_t)l->batch * l->n_kv_heads;
-    if (flush && rep_variant == 1 && (units >= 32 || tiles_total <= 32)) return true;                // (0)
-    if (flush && rep_variant == 2 && units > 128) return true;
+    if (flush && rep_variant == 2 && units > 128) return true;                                       // (0)
     const int64_t work = units * tiles_total, row_work = units * tiles_b;
     if (rep_variant >= 4 && units < 768 && tiles_total <= 20) return false;                          // (5)
     if (rep_variant == 8) return tiles_b >= 2 && work >= 4000 && row_work >= 384;                    // (3)
@@ -344,7 +341,7 @@ int part_rows(const kivi_layout_t* l, size_t bytes) {
 
 // Launch the attention of q over cache state `c` (already validated).  k_new / v_new non-null: the
 // rows of token length-1 are not in the rings yet and the (matrix-core) kernel puts them there.
-// flush_k / flush_v non-null (two-launch form only): the residual flush that produced state `c` has
+// flush_k / flush_v non-null (two-launch form, or one query head per kv-head): the residual flush that produced state `c` has
 // not been launched yet; the fp16-row launch carries it out with extra workgroups.
 int enqueue_attention(const kivi_layout_t* l, const kivi_cache_t* c, const void* q, float softmax_scale,
                       float* out, void* workspace, size_t workspace_bytes, const void* k_new, const void* v_new,
@@ -374,7 +371,9 @@ int enqueue_attention(const kivi_layout_t* l, const kivi_cache_t* c, const void*
     p.plan = plan_splits(l, c, path == KIVI_DECODE_MFMA, two);
     p.two_launches = two ? 1 : 0;
     p.head_groups = wide_group_runs(l, path, two);
-    if ((flush_k || flush_v) && !(two && flush_k && flush_v)) return KIVI_ERR_INVALID_ARG;
+    // One query head per kv-head: a single launch whatever the plan, which its workspace rows always fit.
+    const bool one = path == KIVI_DECODE_MFMA && l->decode_path != KIVI_DECODE_MFMA_TWO && l->n_q_heads == l->n_kv_heads && c->n_kq == c->n_vq;
+    if ((flush_k || flush_v) && !((two || one) && flush_k && flush_v)) return KIVI_ERR_INVALID_ARG;
     p.flush_k = flush_k;
     p.flush_v = flush_v;
     const size_t rows = (size_t)l->batch * l->n_q_heads * p.plan.n_splits();
@@ -382,8 +381,6 @@ int enqueue_attention(const kivi_layout_t* l, const kivi_cache_t* c, const void*
     p.counters = static_cast<int32_t*>(workspace);
     const bool tiles = path == KIVI_DECODE_MFMA && uses_tiles(l) && !(flush_k && l->n_q_heads <= 2 * l->n_kv_heads);
     if (tiles && rows_launch_for_uneven_split(l, c, path)) p.two_launches = 1;
-    // One query head per kv-head: a single launch whatever the plan, which its workspace rows always fit.
-    const bool one = path == KIVI_DECODE_MFMA && l->decode_path != KIVI_DECODE_MFMA_TWO && l->n_q_heads == l->n_kv_heads && c->n_kq == c->n_vq && !flush_k;
     p.part_stride = p.plan.n_splits();
     if (tiles || one) p.part_stride = part_rows(l, workspace_bytes - counter_bytes(l));
     p.part_o = reinterpret_cast<float*>(static_cast<char*>(workspace) + counter_bytes(l));
@@ -973,8 +970,13 @@ int kivi_decode_step(const kivi_layout_t* l, kivi_cache_t* c, const void* k_new,
         // In the two-launch form (G = 32) of up to four query heads per kv-head the fp16-row launch quantises the flushed
         // tokens with extra workgroups: a flush step takes two launches in all.  (3 and 4 heads, 512 units: 40.5 -> 38.7 us at
         // 1023 tokens, 51.1 -> 49.5 at 2175, 4 bits 42.2 -> 40.5; 5 to 8 heads would lose 5-6 us: residual_rows_kernel takes
-        // longer than that kernel's own rows and a flush launch together.  One and two heads: see wants_two_launches.)
-        if ((nk > 0 || nv > 0) && l->group == kTileTokens && l->n_q_heads <= 4 * l->n_kv_heads && wants_two_launches(l, &after, KIVI_DECODE_MFMA, true)) {
+        // longer than that kernel's own rows and a flush launch together.  Two heads: see wants_two_launches.)
+        // One query head per kv-head: a flush of one tile, which is what every flushing step after the first has, rides in
+        // the attention's only launch (decode_one_kernel, which has both sides' figures).
+        const bool in_one = l->n_q_heads == l->n_kv_heads && l->decode_path != KIVI_DECODE_MFMA_TWO;
+        if ((nk > 0 || nv > 0) && l->group == kTileTokens &&
+            (in_one ? nk == kTileTokens && nv == kTileTokens && after.n_kq == after.n_vq
+                    : l->n_q_heads <= 4 * l->n_kv_heads && wants_two_launches(l, &after, KIVI_DECODE_MFMA, true))) {
             const int64_t sh = (int64_t)l->cap_r_tokens * kHeadDim, sb = sh * l->n_kv_heads;
             const RowSource ksrc{static_cast<const __half*>(c->k_resid), sb, sh, kHeadDim, c->k_r_start, l->cap_r_tokens};
             const RowSource vsrc{static_cast<const __half*>(c->v_resid), sb, sh, kHeadDim, c->v_r_start, l->cap_r_tokens};

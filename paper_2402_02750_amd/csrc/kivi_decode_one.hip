@@ -20,6 +20,13 @@
 // workgroups per compute unit hold 147 KB (2 bits) or 123 KB (4 bits) of copies in flight.  (Measured against two with three slots
 // each, eight or sixteen wavefronts, one tile and four slots at 2 bits: this shape within 3 % of the best everywhere.)
 //
+// FLUSH (G = 32): the step in which the oldest 32 tokens leave the window takes this one launch too.  The last wavefront of a unit's
+// last workgroup quantises them out of the rings into the cache and into its own slot and attends to them there; the
+// others take its share of the rows and tiles meanwhile, the next item that nobody has (with fixed shares: 44.4 instead of 42.7 us
+// at 512 units x 4000, a fifth wavefront: two workgroups per compute unit instead of three).  Against a launch of its
+// own before the attention (4.5-5 us): 8 units x 512 tokens 13.6 -> 9.4 us, 256 x 4095 31.2 -> 25.6, 512 x 4095 49.0 -> 42.2; 4 bits, 256
+// x 4095 40.5 -> 34.3, 320 x 8191 78.3 -> 77.0.
+//
 // Bound: HBM.  A launch that only copies what this one reads takes 29.7 us for 512 units of 124 tiles at 2 bits (6.6 TB/s), rows and
 // all 35; this kernel 39.5 (decode_mfma_kernel 46).  What is left is start (2 us to the first tile), the last step and the
 // merge (3 us).  Whole steps, 2 bits, decode_mfma_kernel -> this one: 32 units x 3000 tokens 12.8 -> 9.5 us, 128 x 4000 22.8 ->
@@ -27,6 +34,7 @@
 // 2048 x 2000 92.4 -> 86.0; 4 bits: 256 x 4000 40.7 -> 33.2, 320 x 8000 75.5 -> 72.6, 1024 x 4000 112.3 -> 111.3.
 // Error against 64 bits: 3e-6 to 1.2e-5 of the output (decode_mfma_kernel 5e-5 to 2.5e-4).
 #include "kivi_internal.h"
+#include "kivi_quantize_tile.h"
 #include "kivi_tiles_plan.h"
 
 #include <hip/hip_fp16.h>
@@ -37,7 +45,7 @@
 namespace kivi {
 namespace {
 
-typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+using tile::half2v;
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
@@ -49,7 +57,9 @@ union Frag {            // one lane's share of a 16x16x32 fp16 operand: eight ha
 };
 
 constexpr float kKeyUnscale = 4194304.0f;      // 2^22: key codes enter as code * 4^r * 2^-22
-constexpr float kValueUnscale = 262144.0f;     // 2^18: value codes enter as code * 2^-18 (times 4 in registers 1 and 3 at 2 bits)
+// value codes enter as code * 2^-18, times 4 in registers 1 and 3 (2 bits), or as code * 2^-22, times 16 there (4 bits)
+template <int BITS> constexpr float kValueUnscale = BITS == 2 ? 262144.0f : 4194304.0f;
+template <int BITS> constexpr float kValueFactor = BITS == 2 ? 4.f : 16.f;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kSlack = 4;                      // log2 headroom of the running softmax reference
 constexpr int kQueryExp = 8;                   // largest |q'| lies in [2^8, 2^9)
@@ -123,14 +133,15 @@ __device__ __forceinline__ float2 device_load(const float* p) {
 
 // Asynchronous copy of 16 bytes per lane: lane l's bytes land at LDS offset lds + 16 l.  (From inline asm: the compiler would
 // make every LDS read wait for all copies in flight; they have no output registers, and further vector-memory
-// operations only make the explicit waits stricter.)
+// operations only make the explicit waits stricter.  The instruction needs five wait states after a vector instruction has
+// written its scalar operand, a readlane out of a spill say; the compiler does not look into the block for that.)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void copy_to_lds(const void* base, uint32_t lane_offset, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(lane_offset), "s"(base) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(lane_offset), "s"(base) : "memory", "m0");
 }
 __device__ __forceinline__ void copy_to_lds(const void* lane_ptr, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds), "v"(lane_ptr) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds), "v"(lane_ptr) : "memory", "m0");
 }
 #pragma clang diagnostic pop
 template <int N>
@@ -142,7 +153,8 @@ __device__ __forceinline__ half2v pack_rtz(float a, float b) { return __builtin_
 __device__ __forceinline__ half2v half2_of(uint32_t x) { return __builtin_bit_cast(half2v, x); }
 
 // Code fragments of tile coordinate u = 2 pair + odd: codes as high in the mantissa as they go (keys at bits 2, 4, 6, 8 or 2, 6;
-// values at 6, 8 or 6), see decode_tiles_kernel
+// values at 6, 8 or 2, 6), see decode_tiles_kernel.  (4-bit values all at bit 6: 64 instead of 48 instructions a tile, launches 1 %
+// longer, error 2.5e-6 instead of 1.2e-5 of the output; 2-bit values at 2, 4, 6, 8: no faster, 4e-5 instead of 7e-6.)
 template <int BITS>
 __device__ __forceinline__ half8 key_fragment(const uint32_t* w, int pair, int odd) {
     Frag f;
@@ -165,9 +177,7 @@ __device__ __forceinline__ half8 value_fragment(const uint32_t* w, int pair, int
         f.r[0] = x & 0x00C000C0u; f.r[1] = x & 0x03000300u;
         f.r[2] = y & 0x00C000C0u; f.r[3] = y & 0x03000300u;
     } else {
-        const uint32_t w0 = w[pair * 2], w1 = w[pair * 2 + 1];
-        f.r[0] = (odd ? w0 >> 2 : w0 << 6) & 0x03C003C0u; f.r[1] = (odd ? w0 >> 6 : w0 << 2) & 0x03C003C0u;
-        f.r[2] = (odd ? w1 >> 2 : w1 << 6) & 0x03C003C0u; f.r[3] = (odd ? w1 >> 6 : w1 << 2) & 0x03C003C0u;
+        return key_fragment<BITS>(w, pair, odd);
     }
     return f.h;
 }
@@ -181,15 +191,19 @@ struct Shape {
     static constexpr int NI = PT * (2 * kPlanes + 1);          // copy instructions per slot
     static constexpr int NT = 2 * NI;                          // tokens whose fp16 rows (K and V) fill a slot
     static constexpr int kStepTiles = WV * PT, kStepRows = WV * NT;
+    // what a flush weighs as a part's work: a step at 2 bits, two of half the tiles at 4 (320 units x 8191, 4 bits: 78.7 us with
+    // one, 77.0 with two or three; 32 x 8191 at 2 bits: 24.4, 24.6, 25.2 us with one, two, three)
+    static constexpr int kFlushSteps = 2 / PT;
     // operands of a tile: key side hi (128 halves), 16 halves of skew, lo; value side 8 columns of 32 tokens
     static constexpr int kKeyColumn = 144, kOperandHalves = 272;
     static constexpr int kWaveBytes = NB * kSlotBytes + PT * kOperandHalves * 2;
     static constexpr int kLds = WV * kWaveBytes + WV * 8 + 16;
 };
 
-template <int BITS, int PT, int NB, int WV, int OCC, bool CS>
+template <int BITS, int PT, int NB, int WV, int OCC, bool CS, bool FLUSH>
 __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(DecodeParams p) {
     using S = Shape<BITS, PT, NB, WV>;
+    static_assert(!(CS && FLUSH), "a flush in this launch: G = 32");
     constexpr int NI = S::NI, NT = S::NT, NR = (NT + 3) / 4;
     __shared__ __align__(16) unsigned char sm[S::kLds];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -198,21 +212,27 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
     const bool is_lo = n >= 8;
     const int kg = CS ? p.kg_shift : 0;
     unsigned char* ring = sm + wave * S::kWaveBytes;
-    _Float16* operand = reinterpret_cast<_Float16*>(ring + NB * S::kSlotBytes);
     unsigned char* sm_query = ring + NB * S::kSlotBytes;                        // (until the first operands are made)
+    _Float16* operand = reinterpret_cast<_Float16*>(sm_query);
     float (*sm_ml)[2] = reinterpret_cast<float (*)[2]>(sm + WV * S::kWaveBytes);
     int& sm_last = *reinterpret_cast<int*>(sm + WV * S::kWaveBytes + WV * 8);
+    int& sm_next = *reinterpret_cast<int*>(sm + WV * S::kWaveBytes + WV * 8 + 4);
     const uint32_t ring_lds = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)ring);
 
-    // ---- this workgroup's run of its unit's steps: rows [b0, b1), tiles [a0, a1) ----
+    // ---- this workgroup's run of its unit's steps ----
     const int u = blockIdx.x / p.unit_wgs, part = blockIdx.x % p.unit_wgs;
-    const int tiles = p.plan.tiles_a;
+    // FLUSH: the last wavefront of a unit's last workgroup quantises the tokens that leave the window before it takes its share
+    const bool flush_here = FLUSH && part == p.unit_wgs - 1, flushes = flush_here && wave == WV - 1;
+    const int tiles = p.plan.tiles_a - FLUSH;                                    // (the flushed tile is the last)
     const int n_kr = p.n_kr;
     const StepAxis axis{p.axis_len, p.axis_rem};
-    const int s0 = axis.start(part), s1 = axis.start(part + 1);
+    const int real = axis.start(p.unit_wgs) - (FLUSH ? S::kFlushSteps : 0);      // (the flush counts as the last steps)
+    const int s0 = min(axis.start(part), real), s1 = min(axis.start(part + 1), real);
     const int nr = (n_kr + S::kStepRows - 1) / S::kStepRows;
-    const int b0 = min(s0, nr), b1 = min(s1, nr), a0 = max(s0, nr) - nr, a1 = max(s1, nr) - nr;
-    const int len_a = a1 - a0, todo0 = s1 - s0;
+    const int a0 = max(s0 - nr, 0), len_a = max(s1 - nr, 0) - a0;
+    // An item is one wavefront's slot of a step.  A wavefront takes every WV-th, or -- a workgroup that flushes, whose last
+    // wavefront comes late -- the next one that nobody has.
+    const int n_items = (s1 - s0) * WV, n_row_items = min(max(nr - s0, 0), s1 - s0) * WV;
     const int64_t unit = u;
 
     // ---- copies ----
@@ -258,25 +278,72 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
     if (lane < 16) copy_to_lds(p.q + unit * kHeadDim + n * 8, (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)sm_query));
     // Tiles in an order rotated by the unit: workgroups in lockstep that all read the same relative offset of their units
     // would meet on few memory channels for unlucky strides (a copy alone: 32.3 -> 29.8 us at 512 units).
-    int nx_a = len_a > 0 ? a0 + (int)((uint32_t)(u * 5) % (uint32_t)len_a) : 0, nx_left = todo0, nx_b = b0;
-    auto advance_copy = [&](int slot) {
-        if (nx_left <= 0) return;
-        if (nx_b < b1) {
-            copy_rows(nx_b * S::kStepRows + wave * NT, slot);
-            ++nx_b;
-        } else {
-            copy_tiles(nx_a * S::kStepTiles + wave * PT, slot);
-            if (++nx_a == a1) nx_a = a0;
-        }
-        --nx_left;
+    const int rot = len_a > 0 ? (int)((uint32_t)(u * 5) % (uint32_t)len_a) : 0;
+    auto row_of = [&](int item) -> int { return (s0 + item / WV) * S::kStepRows + item % WV * NT; };      // first token in the window
+    auto tile_of = [&](int item) -> int {
+        int a = (item - n_row_items) / WV + rot;
+        a -= a >= len_a ? len_a : 0;
+        return (a0 + a) * S::kStepTiles + item % WV * PT;
     };
-#pragma unroll 1
-    for (int i = 0; i < NB; ++i) advance_copy(i);
+    auto copy_item = [&](int item, int slot) {
+        if (item < n_row_items) copy_rows(row_of(item), slot);
+        else if (item < n_items) copy_tiles(tile_of(item), slot);
+    };
+    const int starters = flush_here ? WV - 1 : WV;
+    int now = flushes ? n_items : wave, next = now + starters;
+    copy_item(now, 0);
+    copy_item(next, 1);
+    if constexpr (FLUSH) {
+        if (tid == 0) sm_next = 2 * starters;
+        lds_barrier();
+    }
+
+    // ---- the tokens that leave the window in this step: quantised out of the rings into the cache and into this
+    // wavefront's slot, where it attends to them like to any tile ----
+    if constexpr (FLUSH) {
+        if (flushes) {
+            __builtin_amdgcn_s_setprio(3);             // (the longest chain of a short launch)
+            half2v x[kTileTokens];
+            tile::ValueRow y[8];
+            const int fk = p.k_r_start - kTileTokens, fv = p.v_r_start - kTileTokens;
+            const int k0 = fk < 0 ? fk + p.cap_r : fk, v0 = fv < 0 ? fv + p.cap_r : fv;
+            const char* kr = reinterpret_cast<const char*>(p.k_resid + unit * p.cap_r * kHeadDim);
+            const __half* vr = p.v_resid + unit * p.cap_r * kHeadDim + n * 8;
+#pragma unroll
+            for (int t = 0; t < kTileTokens; ++t) x[t] = *reinterpret_cast<const half2v*>(kr + (uint32_t)(ring_slot(k0, t, p.cap_r) * (kHeadDim * 2) + lane * 4));
+#pragma unroll
+            for (int i = 0; i < 8; ++i) y[i].v4 = *reinterpret_cast<const uint4v*>(vr + ring_slot(v0, kb * 8 + i, p.cap_r) * kHeadDim);
+            const int64_t at = tile0 + tiles;
+            uint32_t* kcodes = const_cast<uint32_t*>(p.k_codes) + at * (S::kCodeBytes / 4);
+            uint32_t* vcodes = const_cast<uint32_t*>(p.v_codes) + at * (S::kCodeBytes / 4);
+            uint32_t* lds = reinterpret_cast<uint32_t*>(ring);
+            _Float16* lds_scales = reinterpret_cast<_Float16*>(ring + 2 * S::kCodeBytes);      // k_scale, k_zero, v_scale, v_zero
+            auto put_pair = [&](const __half* array, int which, half2v v) {
+                *reinterpret_cast<half2v*>(const_cast<__half*>(array) + at * kHeadDim + 2 * lane) = v;
+                *reinterpret_cast<half2v*>(lds_scales + which * 128 + 2 * lane) = v;
+            };
+            tile::quantize_key_tile<BITS>(x, lane,
+                [&](half2v s2, half2v z2) {
+                    put_pair(p.k_scale, 0, s2);
+                    put_pair(p.k_zero, 1, z2);
+                },
+                [&](int i, uint32_t w) { kcodes[i] = lds[i] = w; });
+            tile::quantize_value_tile<BITS>(y, lane,
+                [&](int i, _Float16 s, _Float16 z) {
+                    reinterpret_cast<_Float16*>(const_cast<__half*>(p.v_scale))[at * 128 + i] = s;
+                    reinterpret_cast<_Float16*>(const_cast<__half*>(p.v_zero))[at * 128 + i] = z;
+                    lds_scales[256 + i] = s;
+                    lds_scales[384 + i] = z;
+                },
+                [&](int i, uint32_t w) { vcodes[i] = lds[S::kCodeBytes / 4 + i] = w; });
+            wave_lds_sync();
+        }
+    }
 
     // ---- state ----
     // own_tok, own_pair: the token (of every tile) and the channel groups 2 own_pair, + 1 whose value operand this lane makes
     const int own_i = (n >> 1) & 3, own_pair = n & 1, own_tok = kb * 4 + own_i + (is_lo ? 16 : 0);
-    const float own_exp = BITS == 2 ? (float)(own_i & 2) : 0.f;            // log2 of that token's code position factor
+    const float own_exp = own_i & 2 ? (BITS == 2 ? 2.f : 4.f) : 0.f;       // log2 of that token's code position factor
     const int my_group = (n & 1) * 2 + ((n >> 1) & 1);
     float4v acc[8];
     // acc[u][i]: value code sums of channel 16 u + 4 kb + i, column n (of use where its group is u >> 1); z_own: zero-point sums of
@@ -291,9 +358,11 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
     bool ks_set = false;
     uint32_t value_limit = 0;
 
-    const int in_flight = min(todo0, NB);
-    if (in_flight == NB) wait_copies<NB * NI>();       // the query has arrived, the first slots are on their way
-    else wait_copies<NI>();
+    // the query has arrived, the first slots are on their way
+    if (next < n_items) wait_copies<2 * NI>();
+    else if (now < n_items) wait_copies<NI>();
+    else if (!flushes) wait_copies<0>();               // (the rows of a flush have come after the query)
+    asm volatile("" ::: "memory");
     float c_code, c_zero;
     half2v q_own, qk_own;
     const half8 q_row = *reinterpret_cast<const half8*>(sm_query + n * 16);
@@ -380,13 +449,14 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
             return *reinterpret_cast<const uint32_t*>(at + value_at);
         }
     };
-    // PT tiles of a slot; live: those that are there
-    auto quantised = [&](const unsigned char* sl, int live) {
+    // N tiles of a slot; live: those that are there
+    auto quantised = [&](auto count, const unsigned char* sl, int live) {
+        constexpr int N = decltype(count)::value;
         constexpr int kS = 2 * S::kCodeBytes;
-        uint32_t kw[PT][2 * BITS], vw[PT][2 * BITS], s_raw[PT], v_raw[PT], top = 0;
-        half2v s[PT], z[PT], vz[PT];
+        uint32_t kw[N][2 * BITS], vw[N][2 * BITS], s_raw[N], v_raw[N], top = 0;
+        half2v s[N], z[N], vz[N];
 #pragma unroll
-        for (int t = 0; t < PT; ++t) {
+        for (int t = 0; t < N; ++t) {
             const unsigned char* at = sl + t * S::kTileBytes;
             s_raw[t] = *reinterpret_cast<const uint32_t*>(at + kS + lane * 4);
             z[t] = half2_of(*reinterpret_cast<const uint32_t*>(at + kS + 256 + lane * 4));
@@ -401,45 +471,45 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
         if (any_above(top, kKeyScaleLimit)) {
             uint32_t a = 0;
 #pragma unroll
-            for (int t = 0; t < PT; ++t) a = max_pairs(a, __builtin_bit_cast(uint32_t, qk_own * s[t]) & 0x7FFF7FFFu);
+            for (int t = 0; t < N; ++t) a = max_pairs(a, __builtin_bit_cast(uint32_t, qk_own * s[t]) & 0x7FFF7FFFu);
             if (any_above(a, kProductLimit)) {
                 const _Float16 f1 = (_Float16)(1.f / (1 << kKeyScaleShift));
 #pragma unroll
-                for (int t = 0; t < PT; ++t) s[t] *= half2v{f1, f1};
+                for (int t = 0; t < N; ++t) s[t] *= half2v{f1, f1};
                 cx = c_code * (float)(1 << kKeyScaleShift);
             }
         }
 #pragma unroll
-        for (int t = 0; t < PT; ++t) {
+        for (int t = 0; t < N; ++t) {
             const half2v hi = qk_own * s[t], lo = __builtin_elementwise_fma(qk_own, s[t], -hi);
             _Float16* b = operand + t * S::kOperandHalves;
             *reinterpret_cast<half2v*>(b + 2 * lane) = hi;
             *reinterpret_cast<half2v*>(b + S::kKeyColumn + 2 * lane) = lo;
         }
         wave_lds_sync();
-        half8 f[PT][4];
+        half8 f[N][4];
 #pragma unroll
-        for (int t = 0; t < PT; ++t)
+        for (int t = 0; t < N; ++t)
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb)
                 f[t][cb] = *reinterpret_cast<const half8*>(operand + t * S::kOperandHalves + (is_lo ? S::kKeyColumn : 0) + cb * 32 + kb * 8);
-        float zk[PT];
+        float zk[N];
 #pragma unroll
-        for (int t = 0; t < PT; ++t) zk[t] = wave_sum(__builtin_amdgcn_fdot2(q_own, z[t], 0.f, false)) * c_zero;
-        float4v d[PT][2];
+        for (int t = 0; t < N; ++t) zk[t] = wave_sum(__builtin_amdgcn_fdot2(q_own, z[t], 0.f, false)) * c_zero;
+        float4v d[N][2];
 #pragma unroll
-        for (int t = 0; t < PT; ++t) d[t][0] = d[t][1] = float4v{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < N; ++t) d[t][0] = d[t][1] = float4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
-            for (int t = 0; t < PT; ++t) {
+            for (int t = 0; t < N; ++t) {
                 d[t][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(key_fragment<BITS>(kw[t], cb, 0), f[t][cb], d[t][0], 0, 0, 0);
                 d[t][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(key_fragment<BITS>(kw[t], cb, 1), f[t][cb], d[t][1], 0, 0, 0);
             }
         // this lane's token of every tile: probability over the code's position factor
-        float x[PT], pv[PT], mx = -INFINITY;
+        float x[N], pv[N], mx = -INFINITY;
 #pragma unroll
-        for (int t = 0; t < PT; ++t) {
+        for (int t = 0; t < N; ++t) {
             const float x0 = own_of(d[t][0]), x1 = own_of(d[t][1]);
             x[t] = fmaf((is_lo ? x1 : x0) + dpp<kDppRor8>(is_lo ? x0 : x1), cx, zk[t]);
             if (t > 0 && t >= live) x[t] = -INFINITY;
@@ -449,7 +519,7 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
         const float off = (float)kProbExp<BITS> - own_exp - mref;
         uint32_t vtop = 0;
 #pragma unroll
-        for (int t = 0; t < PT; ++t) {
+        for (int t = 0; t < N; ++t) {
             pv[t] = __builtin_amdgcn_exp2f(x[t] + off);
             l_lane += pv[t];
             if (t == 0 || t < live) vtop = max_pairs(vtop, v_raw[t]);
@@ -457,7 +527,7 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
         fit_value_exponent(vtop, [&]() {
             float m = 0.f;
 #pragma unroll
-            for (int t = 0; t < PT; ++t) m = fmaxf(m, pv[t] * fmaxf((float)half2_of(v_raw[t])[0], (float)half2_of(v_raw[t])[1]));
+            for (int t = 0; t < N; ++t) m = fmaxf(m, pv[t] * fmaxf((float)half2_of(v_raw[t])[0], (float)half2_of(v_raw[t])[1]));
             return m;
         });
         _Float16 k1 = (_Float16)1.f, k2 = (_Float16)1.f;
@@ -465,10 +535,10 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
             k1 = (_Float16)__uint_as_float((uint32_t)(127 - ks / 2) << 23);
             k2 = (_Float16)__uint_as_float((uint32_t)(127 - ks + ks / 2) << 23);
 #pragma unroll
-            for (int t = 0; t < PT; ++t) v_raw[t] = __builtin_bit_cast(uint32_t, half2_of(v_raw[t]) * half2v{k1, k1} * half2v{k2, k2});
+            for (int t = 0; t < N; ++t) v_raw[t] = __builtin_bit_cast(uint32_t, half2_of(v_raw[t]) * half2v{k1, k1} * half2v{k2, k2});
         }
 #pragma unroll
-        for (int t = 0; t < PT; ++t) {
+        for (int t = 0; t < N; ++t) {
             const half2v ph = pack_rtz(pv[t], pv[t]);
             float rest;
             asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(rest) : "v"(ph), "v"(pv[t]));
@@ -483,12 +553,12 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
             col[96] = lo[1];
         }
         wave_lds_sync();
-        half8 fv[PT];
+        half8 fv[N];
 #pragma unroll
-        for (int t = 0; t < PT; ++t)
+        for (int t = 0; t < N; ++t)
             fv[t] = *reinterpret_cast<const half8*>(operand + t * S::kOperandHalves + (my_group * 2 + (is_lo ? 1 : 0)) * 32 + kb * 8);
 #pragma unroll
-        for (int t = 0; t < PT; ++t)
+        for (int t = 0; t < N; ++t)
 #pragma unroll
             for (int u8 = 0; u8 < 8; ++u8)
                 acc[u8] = __builtin_amdgcn_mfma_f32_16x16x32_f16(value_fragment<BITS>(vw[t], u8 >> 1, u8 & 1), fv[t], acc[u8], 0, 0, 0);
@@ -528,40 +598,60 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
     // end late and alone (512 units: 28 against 36 us), so a wavefront's priority falls with the share of its work that is done (39.6 ->
     // 38.7 us); with more workgroups than fit at once the oldest ones' head start is what hides the others' starts (2048
     // units: 87 us as it is, 91 with falling priorities).
-    const int quarter = p.one_round ? todo0 >> 2 : 0x1fffffff;
-    auto wait_oldest = [&](int todo) {
-        if (todo > 3 * quarter) __builtin_amdgcn_s_setprio(3);
-        else if (todo > 2 * quarter) __builtin_amdgcn_s_setprio(2);
-        else if (todo > quarter) __builtin_amdgcn_s_setprio(1);
+    const int quarter = p.one_round ? n_items >> 2 : 0x1fffffff;
+    // the item after `next`: asked for before an item's work is done, looked at after it
+    auto ask = [&]() -> int {
+        int v = next + WV;
+        if constexpr (FLUSH) {
+            if (lane == 0) v = __hip_atomic_fetch_add(&sm_next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        return v;
+    };
+    auto begin = [&]() {
+        const int left = n_items - now;
+        if (left > 3 * quarter) __builtin_amdgcn_s_setprio(3);
+        else if (left > 2 * quarter) __builtin_amdgcn_s_setprio(2);
+        else if (left > quarter) __builtin_amdgcn_s_setprio(1);
         else __builtin_amdgcn_s_setprio(0);
-        if (todo >= NB) wait_copies<(NB - 1) * NI>();
+        if (next < n_items) wait_copies<NI>();
         else wait_copies<0>();
     };
-    int slot = 0, todo = todo0, at_a = len_a > 0 ? a0 + (int)((uint32_t)(u * 5) % (uint32_t)len_a) : 0;
-#pragma unroll 1
-    for (int j = b0; j < b1; ++j) {
-        wait_oldest(todo);
-        const int left = n_kr - (j * S::kStepRows + wave * NT);
-        if (left > 0) fp16_rows(ring + slot * S::kSlotBytes, left);
-        advance_copy(slot);
-        slot = slot + 1 == NB ? 0 : slot + 1;
-        --todo;
+    int slot = 0;
+    auto end = [&](int asked) {
+        const int after = FLUSH ? __builtin_amdgcn_readfirstlane(asked) : asked;
+        copy_item(after, slot);
+        now = next;
+        next = after;
+        slot ^= 1;
+    };
+    if constexpr (FLUSH) {
+        if (flushes) {
+            quantised(std::integral_constant<int, 1>{}, ring, 1);
+            now = __builtin_amdgcn_readfirstlane(ask());
+            copy_item(now, 0);
+            next = __builtin_amdgcn_readfirstlane(ask());
+            copy_item(next, 1);
+        }
     }
 #pragma unroll 1
-    for (int j = 0; j < len_a; ++j) {
-        wait_oldest(todo);
-        const int live = tiles - (at_a * S::kStepTiles + wave * PT);
-        if (live > 0) quantised(ring + slot * S::kSlotBytes, live);
-        if (++at_a == a1) at_a = a0;
-        advance_copy(slot);
-        slot = slot + 1 == NB ? 0 : slot + 1;
-        --todo;
+    while (now < n_row_items) {
+        begin();
+        const int asked = ask(), left = n_kr - row_of(now);
+        if (left > 0) fp16_rows(ring + slot * S::kSlotBytes, left);
+        end(asked);
+    }
+#pragma unroll 1
+    while (now < n_items) {
+        begin();
+        const int asked = ask(), live = tiles - tile_of(now);
+        if (live > 0) quantised(std::integral_constant<int, PT>{}, ring + slot * S::kSlotBytes, live);
+        end(asked);
     }
 
     // ---- merge the wavefronts (their rings are free) ----
     float* o_wave = reinterpret_cast<float*>(ring);
     {
-        const float l = wave_sum(l_lane * (own_i & 2 && BITS == 2 ? 2.f : 0.5f) + r_l * (1.f / 16));
+        const float l = wave_sum(l_lane * (own_i & 2 ? 0.5f * kValueFactor<BITS> : 0.5f) + r_l * (1.f / 16));
         if (lane == 0) {
             sm_ml[wave][0] = mref;
             sm_ml[wave][1] = l;
@@ -569,13 +659,13 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
         float zo[2];
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            float t = z_own[k] * (own_i & 2 && BITS == 2 ? 4.f : 1.f);
+            float t = z_own[k] * (own_i & 2 ? kValueFactor<BITS> : 1.f);
             t += dpp<kDppXor2>(t);
             t += dpp<kDppRor4>(t);
             t += dpp<kDppRor8>(t);
             zo[k] = add_rows(t);
         }
-        const float up = kValueUnscale * __uint_as_float((uint32_t)(127 + ks) << 23);
+        const float up = kValueUnscale<BITS> * __uint_as_float((uint32_t)(127 + ks) << 23);
 #pragma unroll
         for (int u8 = 0; u8 < 8; ++u8) {
             float4v o;
@@ -583,14 +673,16 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
             for (int i = 0; i < 4; ++i) o[i] = fmaf(acc[u8][i] + dpp<kDppRor8>(acc[u8][i]), up, zo[(u8 >> 1) & 1]);
             if (n < 4 && my_group == u8 >> 1) *reinterpret_cast<float4v*>(&o_wave[u8 * 16 + kb * 4]) = o;
         }
-        float r[8];
+        if (n_row_items > 0) {
+            float r[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) r[e] = add_rows(r_out[e]);
-        wave_lds_sync();
-        if (kb == 0) {
-            float4v* o = reinterpret_cast<float4v*>(&o_wave[n * 8]);
-            o[0] += float4v{r[0], r[1], r[2], r[3]};
-            o[1] += float4v{r[4], r[5], r[6], r[7]};
+            for (int e = 0; e < 8; ++e) r[e] = add_rows(r_out[e]);
+            wave_lds_sync();
+            if (kb == 0) {
+                float4v* o = reinterpret_cast<float4v*>(&o_wave[n * 8]);
+                o[0] += float4v{r[0], r[1], r[2], r[3]};
+                o[1] += float4v{r[4], r[5], r[6], r[7]};
+            }
         }
     }
     lds_barrier();
@@ -691,13 +783,13 @@ int compute_units() {
     return cus;
 }
 
-template <int BITS, int PT, int NB, int WV, int OCC, bool CS>
+template <int BITS, int PT, int NB, int WV, int OCC, bool CS, bool FLUSH>
 hipError_t launch(DecodeParams p, hipStream_t stream) {
     using S = Shape<BITS, PT, NB, WV>;
     static_assert(S::kLds <= 160 * 1024 / OCC / 1280 * 1280, "workgroups per compute unit (LDS is given out in pieces of 1280 bytes)");
-    static_assert(NB == 2 && PT <= 2, "waits and softmax of a slot");
+    static_assert(NB == 2 && PT <= 2, "two items in flight; masked tiles of a slot");
     const int64_t units = (int64_t)p.batch * p.n_kv_heads;
-    const int steps = (p.plan.tiles_a + S::kStepTiles - 1) / S::kStepTiles + (p.n_kr + S::kStepRows - 1) / S::kStepRows;
+    const int steps = (p.plan.tiles_a - FLUSH + S::kStepTiles - 1) / S::kStepTiles + (p.n_kr + S::kStepRows - 1) / S::kStepRows + (FLUSH ? S::kFlushSteps : 0);
     const int cus = compute_units();
     const int w = one_head_parts(units, steps, cus, std::min(p.part_stride, kOneHeadMaxParts), BITS == 2 ? 8 : 12);
     if (steps < 1 || units * w > 0x7fffffff) return hipErrorInvalidValue;
@@ -705,7 +797,7 @@ hipError_t launch(DecodeParams p, hipStream_t stream) {
     p.axis_len = steps / w;
     p.axis_rem = steps % w;
     p.one_round = units * w <= (int64_t)cus * OCC;
-    decode_one_kernel<BITS, PT, NB, WV, OCC, CS><<<(unsigned)(units * w), 64 * WV, 0, stream>>>(p);
+    decode_one_kernel<BITS, PT, NB, WV, OCC, CS, FLUSH><<<(unsigned)(units * w), 64 * WV, 0, stream>>>(p);
     return hipGetLastError();
 }
 
@@ -713,9 +805,18 @@ hipError_t launch(DecodeParams p, hipStream_t stream) {
 
 hipError_t launch_decode_one(const DecodeParams& p, hipStream_t stream) {
     if (p.n_q_heads != p.n_kv_heads || p.n_kq != p.n_vq || p.n_kr != p.n_vr || p.part_stride < 1) return hipErrorInvalidValue;
+    if (p.flush_k || p.flush_v) {
+        // the flushed tokens: one tile, the last quantised one, out of the rings right before the window
+        const QuantKeyParams* k = p.flush_k;
+        const QuantValueParams* v = p.flush_v;
+        if (!k || !v || p.kg_shift > 0 || k->n_tiles != 1 || v->n_tokens != kTileTokens || p.plan.tiles_a < 1 || p.n_kr < 1 ||
+            k->first_tile != p.plan.tiles_a - 1 || v->first_token != (p.plan.tiles_a - 1) * kTileTokens)
+            return hipErrorInvalidValue;
+        return p.bits == 2 ? launch<2, 2, 2, 4, 3, false, true>(p, stream) : launch<4, 1, 2, 4, 3, false, true>(p, stream);
+    }
     const bool cs = p.kg_shift > 0;
-    if (p.bits == 2) return cs ? launch<2, 2, 2, 4, 3, true>(p, stream) : launch<2, 2, 2, 4, 3, false>(p, stream);
-    return cs ? launch<4, 1, 2, 4, 3, true>(p, stream) : launch<4, 1, 2, 4, 3, false>(p, stream);
+    if (p.bits == 2) return cs ? launch<2, 2, 2, 4, 3, true, false>(p, stream) : launch<2, 2, 2, 4, 3, false, false>(p, stream);
+    return cs ? launch<4, 1, 2, 4, 3, true, false>(p, stream) : launch<4, 1, 2, 4, 3, false, false>(p, stream);
 }
 
 }  // namespace kivi

@@ -9,6 +9,7 @@
 // the two to differ.  This file is compiled with -ffp-contract=off, so the only fused operations
 // are the ones written as fmaf().
 #include "kivi_internal.h"
+#include "kivi_quantize_tile.h"
 #include "kivi_rows_block.h"
 
 #include <hip/hip_fp16.h>
@@ -19,20 +20,7 @@
 namespace kivi {
 namespace {
 
-typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-// packed fp16 minimum / maximum (v_pk_min_f16 / v_pk_max_f16): exact, no arithmetic.  Written as
-// instructions: the builtins make the compiler quiet signalling NaNs first (one more instruction per
-// operand), which finite inputs -- the precondition of the quantiser -- do not need.
-__device__ __forceinline__ half2v pk_min(half2v a, half2v b) {
-    half2v r;
-    asm("v_pk_min_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-__device__ __forceinline__ half2v pk_max(half2v a, half2v b) {
-    half2v r;
-    asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
+using namespace tile;
 
 // consecutive value tiles one workgroup walks, the next tile's rows prefetched (measured at the
 // 3968-token prefill of 512 units: 209 us with 1, 190 us with 4; the key kernel got slower with it)
@@ -47,33 +35,6 @@ __device__ __forceinline__ int64_t row_offset(const RowSource& s, int b, int h, 
         slot -= (slot >= s.ring_cap) ? s.ring_cap : 0;
     }
     return (int64_t)b * s.stride_b + (int64_t)h * s.stride_h + (int64_t)slot * s.stride_t;
-}
-
-__device__ __forceinline__ uint32_t encode(float x, float z, float s, float levels) {
-    float r = (x - z) / s;                 // IEEE fp32 division (correctly rounded)
-    r = __builtin_rintf(r);                // round half to even
-    r = fminf(fmaxf(r, 0.0f), levels);     // NaN (0/0) -> 0
-    return s == 0.0f ? 0u : (uint32_t)r;
-}
-
-// Group constants: zero-point and scale (for the exact path), and for the fast path y ~ 1/s,
-// c0 = fl(-z * y) and the tolerance below (y = c0 = 0 when the scale is 0, which makes every code
-// of the group 0).  The key kernel keeps them in LDS as one array per constant, so that the
-// constants of the consecutive channels a word covers are read as vectors (3 % on that kernel; the
-// same for the consecutive tokens of a value word gained 3 % at 4 bits and lost 4 % at 2 bits).
-struct GroupConst { float z, s, y, c0, tol; };
-
-__device__ __forceinline__ GroupConst group_const(float lo, float s) {
-    // y: the hardware reciprocal (1 ulp: relative error <= 2^-23), one instruction instead of a division
-    const float y = s == 0.0f ? 0.0f : __builtin_amdgcn_rcpf(s);
-    const float c0 = -lo * y;
-    // q' = fl(x * y + c0) against the contract's q = fl(fl(x - z) / s), with Q the exact quotient:
-    // |q - Q| <= Q * 2^-23 and |q' - Q| <= Q * 2^-22 + |z / s| * 2^-22 * 1.001 (error of y in both
-    // products, roundings of c0 and of the sum), so for Q <= 16.1:  |q' - q| < 5.8e-6 + |c0| * 2.4e-7.
-    // Twice that as tolerance.
-    // (scale below the smallest normal fp16 number: its rounding error is not relative, the quotient
-    // can pass `levels`: tolerance 1 = always the exact path)
-    return GroupConst{lo, s, y, c0, (s != 0.0f && s < 6.103515625e-05f) ? 1.0f : 1.2e-5f + fabsf(c0) * 4.8e-7f};
 }
 
 // The same code as encode() without a division per element: one fused multiply-add straight from
@@ -419,69 +380,13 @@ __device__ __forceinline__ void quantize_value_block(const QuantValueParams& p, 
 // maximum come from packed fp16 min / max in registers plus at most two cross-lane steps, the
 // partial words of the lanes that share a word are combined with DPP moves, and nothing goes
 // through LDS.  Same arithmetic contract as above (encode_fast with the exact redo).
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_u32(uint32_t x) {
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xF, 0xF, true);
-}
-template <int CTRL>
-__device__ __forceinline__ float dpp_f32(float x) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
-}
-constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E;      // quad_perm [1,0,3,2], [2,3,0,1]
-__device__ __forceinline__ uint32_t as_bits(half2v x) {
-    union { half2v h; uint32_t u; } a;
-    a.h = x;
-    return a.u;
-}
-__device__ __forceinline__ half2v as_half2(uint32_t x) {
-    union { half2v h; uint32_t u; } a;
-    a.u = x;
-    return a.h;
-}
-__device__ __forceinline__ float half_bits_to_float(uint32_t low16) { return (float)as_half2(low16).x; }
-// {a.x, b.x} and {a.y, b.y} (one byte-permute instruction each)
-__device__ __forceinline__ half2v low_halves(half2v a, half2v b) {
-    return as_half2(__builtin_amdgcn_perm(as_bits(b), as_bits(a), 0x05040100u));
-}
-__device__ __forceinline__ half2v high_halves(half2v a, half2v b) {
-    return as_half2(__builtin_amdgcn_perm(as_bits(b), as_bits(a), 0x07060302u));
-}
-template <int CTRL>
-__device__ __forceinline__ half2v dpp_h2(half2v x) {
-    union { half2v h; int i; } a, r;
-    a.h = x;
-    r.i = __builtin_amdgcn_mov_dpp(a.i, CTRL, 0xF, 0xF, true);
-    return r.h;
-}
-// A wavefront-uniform pointer pinned to scalar registers: keeps the compiler from folding a lane offset
-// into it early and then carrying every row address in vector registers (64-bit vector multiply-adds).
-typedef const half2v __attribute__((address_space(1)))* GlobalHalf2Ptr;       // keeps the loads global (not flat)
-__device__ __forceinline__ GlobalHalf2Ptr uniform_pointer(const void* p) {
-    const uint64_t v = reinterpret_cast<uint64_t>(p);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return reinterpret_cast<GlobalHalf2Ptr>(((uint64_t)hi << 32) | lo);
-}
-// mask ? a : b per bit (one bitfield-insert instruction)
-__device__ __forceinline__ uint32_t select_bits(uint32_t mask, uint32_t a, uint32_t b) { return (a & mask) | (b & ~mask); }
-
-__device__ __forceinline__ float encode_fast16(_Float16 x, float y, float c0, float& dev) {
-    const float q = fmaf((float)x, y, c0);
-    const float r = __builtin_rintf(q);
-    dev = fmaxf(dev, fabsf(q - r));
-    return r;
-}
-
-// Keys: lane l holds channels 2l, 2l + 1 of all 32 tokens (each row load of the wavefront is one
-// contiguous 256-byte row).  A channel's group is the lane's own column: no cross-lane step for
-// minimum and maximum.  A word of the packed tile (tokens t0 and t0 + 16, 8 or 4 consecutive
-// channels) is shared by 4 (B = 2) or 2 (B = 4) neighbouring lanes.
+// (quantize_key_tile, quantize_value_tile: kivi_quantize_tile.h.)
 template <int BITS>
 __device__ __forceinline__ void quantize_keys_stream_block(const QuantKeyParams& p, int bx, int h, int b) {
     const int lane = threadIdx.x & 63;
     const int g = bx * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // group = tile
     if (g >= p.n_tiles) return;                     // whole wavefronts leave; there is no barrier
-    const int64_t unit = (int64_t)b * p.n_kv_heads + h;
-    constexpr float levels = (float)((1 << BITS) - 1);
+    const int64_t at = ((int64_t)b * p.n_kv_heads + h) * p.cap_tiles + p.first_tile + g;
     // (the row address stays wavefront-uniform and the lane adds a 32-bit offset: scalar address arithmetic)
     const __half* src = p.src.base + (int64_t)b * p.src.stride_b + (int64_t)h * p.src.stride_h
                         + (int64_t)g * kTileTokens * p.src.stride_t;
@@ -489,254 +394,37 @@ __device__ __forceinline__ void quantize_keys_stream_block(const QuantKeyParams&
 #pragma unroll
     for (int t = 0; t < kTileTokens; ++t)
         x[t] = __builtin_nontemporal_load(uniform_pointer(src + t * p.src.stride_t) + (uint32_t)lane);
-
-    half2v mn[16], mx[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) { mn[i] = pk_min(x[i], x[i + 16]); mx[i] = pk_max(x[i], x[i + 16]); }
-#pragma unroll
-    for (int w = 8; w >= 1; w >>= 1)
-#pragma unroll
-        for (int i = 0; i < w; ++i) { mn[i] = pk_min(mn[i], mn[i + w]); mx[i] = pk_max(mx[i], mx[i + w]); }
-
-    float y[2], c0[2], zf[2], sf[2], tol = 0.f;
-    half2v s2, z2;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const float lo = (float)mn[0][i], hi = (float)mx[0][i];
-        const _Float16 s16 = (_Float16)((hi - lo) / levels);          // fp32 division, rounded to nearest even
-        const GroupConst gc = group_const(lo, (float)s16);
-        y[i] = gc.y; c0[i] = gc.c0; zf[i] = gc.z; sf[i] = gc.s;
-        tol = fmaxf(tol, gc.tol);
-        s2[i] = s16;
-        z2[i] = mn[0][i];
-    }
-    const int dst_tile = p.first_tile + g;
-    const int64_t o = (unit * p.cap_tiles + dst_tile) * kHeadDim + 2 * lane;
-    *reinterpret_cast<half2v*>(p.scale + o) = s2;
-    *reinterpret_cast<half2v*>(p.zero + o) = z2;
-
-    constexpr int kWords = kTileTokens * kHeadDim * BITS / 32;
-    uint32_t* dst = p.codes + (unit * p.cap_tiles + dst_tile) * kWords;
-    const int ks = lane >> 4, q = (lane >> 2) & 3, k = lane & 3;     // channel 2l = ks*32 + q*8 + 2k
-    const int shift = BITS == 2 ? 2 * k : 4 * (k & 1);
-    const uint32_t m0 = 0u - (uint32_t)(k & 1), m1 = 0u - (uint32_t)(k >> 1);
-    const float thr = 0.5f - tol;
-    // four tokens t0 (and their partners t0 + 16) at a time: byte i*2 + uo of the lane's partial word
-    // holds the code of (channel 2l + i, token t0 + 16 uo) -- bits (e&1)*16 + 8*uo of the layout --
-    // and the shift moves it to the lane's channel pair
-#pragma unroll
-    for (int blk = 0; blk < 4; ++blk) {
-        uint32_t pw[4];
-        float dev = 0.f;
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) {
-            const int t0 = blk * 4 + tt;
-            uint32_t w = 0;
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int uo = 0; uo < 2; ++uo)
-                    w = __builtin_amdgcn_cvt_pk_u8_f32(encode_fast16(x[t0 + 16 * uo][i], y[i], c0[i], dev), i * 2 + uo, w);
-            pw[tt] = w;
-        }
-        if (dev > thr) {      // rare: a quotient next to a rounding tie; redo the lane's 16 codes with true divisions
-#pragma unroll
-            for (int tt = 0; tt < 4; ++tt) {
-                const int t0 = blk * 4 + tt;
-                uint32_t w = 0;
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int uo = 0; uo < 2; ++uo)
-                        w |= encode((float)x[t0 + 16 * uo][i], zf[i], sf[i], levels) << (8 * (i * 2 + uo));
-                pw[tt] = w;
-            }
-        }
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) pw[tt] <<= shift;
-        // The lanes that share a word combine their partial words so that each ends up with a different
-        // token's complete word (a transpose over the lane group, 3 instructions per exchange): with the
-        // odd neighbour, the odd lane keeps the odd tokens and hands over the even ones, and vice versa;
-        // at 2 bits the same once more two lanes apart.
-        const uint32_t a = select_bits(m0, pw[1], pw[0]) | dpp_u32<kQuadXor1>(select_bits(m0, pw[0], pw[1]));   // token (k & 1)
-        const uint32_t c = select_bits(m0, pw[3], pw[2]) | dpp_u32<kQuadXor1>(select_bits(m0, pw[2], pw[3]));   // token 2 + (k & 1)
-        if (BITS == 2) {
-            const uint32_t w = select_bits(m1, c, a) | dpp_u32<kQuadXor2>(select_bits(m1, a, c));               // token k
-            dst[(q * 16 + blk * 4 + k) * 4 + ks] = w;
-        } else {
-            const int i = ks * 2 + (k >> 1);
-            dst[(i >> 2) * 256 + (q * 16 + blk * 4 + (k & 1)) * 4 + (i & 3)] = a;
-            dst[(i >> 2) * 256 + (q * 16 + blk * 4 + 2 + (k & 1)) * 4 + (i & 3)] = c;
-        }
-    }
+    const int64_t o = at * kHeadDim + 2 * lane;
+    uint32_t* dst = p.codes + at * (kTileTokens * kHeadDim * BITS / 32);
+    quantize_key_tile<BITS>(x, lane,
+        [&](half2v s2, half2v z2) {
+            *reinterpret_cast<half2v*>(p.scale + o) = s2;
+            *reinterpret_cast<half2v*>(p.zero + o) = z2;
+        },
+        [&](int i, uint32_t w) { dst[i] = w; });
 }
 
-// Values: lane (tl = l / 16, seg = l % 16) holds channels seg*8 .. seg*8 + 7 of tokens 8 tl .. 8 tl + 7
-// (a 16-byte load per token).  A group is 32 channels of a token = the 4 lanes of a quad; lane jj of
-// the quad derives the constants of tokens jj and jj + 4 and the others get them by quad broadcasts.
-// A word (8 tokens, channels c and c + 16) is shared by the lanes seg and seg ^ 2.
 template <int BITS>
 __device__ __forceinline__ void quantize_values_stream_block(const QuantValueParams& p, int bx, int h, int b) {
     const int lane = threadIdx.x & 63;
     const int ti = bx * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (ti >= p.n_tokens / kTileTokens) return;     // whole wavefronts leave; there is no barrier
-    const int64_t unit = (int64_t)b * p.n_kv_heads + h;
-    constexpr float levels = (float)((1 << BITS) - 1);
-    const int dst_tile = p.first_token / kTileTokens + ti;
-    const int tl = lane >> 4, seg = lane & 15, g = seg >> 2, jj = seg & 3, odd = (seg >> 1) & 1;
+    const int64_t at = ((int64_t)b * p.n_kv_heads + h) * p.cap_tiles + p.first_token / kTileTokens + ti;
+    const int tl = lane >> 4, seg = lane & 15;
     const __half* src = p.src.base + (int64_t)b * p.src.stride_b + (int64_t)h * p.src.stride_h
                         + ((int64_t)ti * kTileTokens + tl * 8) * p.src.stride_t + seg * 8;
-    typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
-    union Row { uint4v v4; half2v h2[4]; _Float16 h[8]; } x[8];
+    ValueRow x[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) x[i].v4 = __builtin_nontemporal_load(reinterpret_cast<const uint4v*>(src + i * p.src.stride_t));
-
-    // Group minimum / maximum of every token.  In the lane: packed fp16 min / max over its 8 channels
-    // (exact, no arithmetic); the halves of two tokens are then combined into one register
-    // (token i in the low half, token i + 1 in the high half), so that the two exchanges inside the quad
-    // serve two tokens at once.  Lane jj adopts the tokens jj and jj + 4.
-    half2v pmn[4], pmx[4];
-#pragma unroll
-    for (int i = 0; i < 8; i += 2) {
-        half2v lo2[2], hi2[2];
-#pragma unroll
-        for (int d = 0; d < 2; ++d) {
-            lo2[d] = pk_min(pk_min(x[i + d].h2[0], x[i + d].h2[1]), pk_min(x[i + d].h2[2], x[i + d].h2[3]));
-            hi2[d] = pk_max(pk_max(x[i + d].h2[0], x[i + d].h2[1]), pk_max(x[i + d].h2[2], x[i + d].h2[3]));
-        }
-        half2v mn = pk_min(low_halves(lo2[0], lo2[1]), high_halves(lo2[0], lo2[1]));
-        half2v mx = pk_max(low_halves(hi2[0], hi2[1]), high_halves(hi2[0], hi2[1]));
-        mn = pk_min(mn, dpp_h2<kQuadXor1>(mn)); mx = pk_max(mx, dpp_h2<kQuadXor1>(mx));
-        mn = pk_min(mn, dpp_h2<kQuadXor2>(mn)); mx = pk_max(mx, dpp_h2<kQuadXor2>(mx));
-        pmn[i >> 1] = mn;
-        pmx[i >> 1] = mx;
-    }
-    float my_lo[2], my_hi[2];
-    {
-        const uint32_t upper = 0u - (uint32_t)(jj >> 1);     // tokens 2, 3 (6, 7) are in the second register of a slot
-        const int sh = 16 * (jj & 1);
-#pragma unroll
-        for (int sl = 0; sl < 2; ++sl) {
-            my_lo[sl] = half_bits_to_float(select_bits(upper, as_bits(pmn[2 * sl + 1]), as_bits(pmn[2 * sl])) >> sh);
-            my_hi[sl] = half_bits_to_float(select_bits(upper, as_bits(pmx[2 * sl + 1]), as_bits(pmx[2 * sl])) >> sh);
-        }
-    }
-    float gy[2], gc0[2], gz[2], gs[2], tol = 0.f;
-#pragma unroll
-    for (int sl = 0; sl < 2; ++sl) {
-        const _Float16 s16 = (_Float16)((my_hi[sl] - my_lo[sl]) / levels);
-        const GroupConst gc = group_const(my_lo[sl], (float)s16);
-        gy[sl] = gc.y; gc0[sl] = gc.c0; gz[sl] = gc.z; gs[sl] = gc.s;
-        tol = fmaxf(tol, gc.tol);
-        const int64_t o = ((unit * p.cap_tiles + dst_tile) * kTileTokens + tl * 8 + jj + 4 * sl) * 4 + g;
-        reinterpret_cast<_Float16*>(p.scale)[o] = s16;
-        reinterpret_cast<_Float16*>(p.zero)[o] = (_Float16)my_lo[sl];
-    }
-    tol = fmaxf(tol, dpp_f32<kQuadXor1>(tol));
-    tol = fmaxf(tol, dpp_f32<kQuadXor2>(tol));
-    const float thr = 0.5f - tol;
-    // constants of token i for every lane of the quad: from lane i & 3, slot i >> 2
-    auto quad_bcast = [](float v, auto sel) {
-        constexpr int S = decltype(sel)::value;
-        return dpp_f32<S | (S << 2) | (S << 4) | (S << 6)>(v);
-    };
-    float yi[8], ci[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        auto pick = [&](const float (&a)[2]) {
-            const float v = a[i >> 2];
-            switch (i & 3) {
-                case 0: return quad_bcast(v, std::integral_constant<int, 0>{});
-                case 1: return quad_bcast(v, std::integral_constant<int, 1>{});
-                case 2: return quad_bcast(v, std::integral_constant<int, 2>{});
-                default: return quad_bcast(v, std::integral_constant<int, 3>{});
-            }
-        };
-        yi[i] = pick(gy);
-        ci[i] = pick(gc0);
-    }
-
-    constexpr int kWords = kTileTokens * kHeadDim * BITS / 32;
-    constexpr int WPC = BITS / 2;                    // words per channel: tokens 0-7 (B = 2) or 0-3, 4-7 (B = 4)
-    uint32_t* dst = p.codes + (unit * p.cap_tiles + dst_tile) * kWords;
-    uint32_t wq[8][WPC];
-    // two channels at a time; bit of token e inside its word: (e&1)*16 + B*((e>>1) & (8/B - 1)), plus 8 for
-    // the lanes whose channels are the upper 16 of their 32-channel group (odd)
-#pragma unroll
-    for (int jb = 0; jb < 4; ++jb) {
-        float dev = 0.f;
-#pragma unroll
-        for (int j = 2 * jb; j < 2 * jb + 2; ++j) {
-            // the codes of a word lie in bits 0-7 and 16-23: their sum is exact in one fp32 number
-            float acc[WPC];
-#pragma unroll
-            for (int a = 0; a < WPC; ++a) acc[a] = 0.f;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int bit = (e & 1) * 16 + BITS * ((e >> 1) & (8 / BITS - 1));
-                float& dstf = acc[BITS == 2 ? 0 : (e >> 2)];
-                dstf = fmaf(encode_fast16(x[e].h[j], yi[e], ci[e], dev), (float)(1u << bit), dstf);
-            }
-#pragma unroll
-            for (int a = 0; a < WPC; ++a) wq[j][a] = (uint32_t)acc[a];
-        }
-        // a quotient next to a rounding tie anywhere in the wavefront (rare): all lanes redo these two
-        // channels with true divisions (uniform branch: the quad broadcasts inside need every lane)
-        if (__builtin_amdgcn_ballot_w64(dev > thr) != 0) {
-            float zi[8], si[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                auto pick = [&](const float (&a)[2]) {
-                    const float v = a[i >> 2];
-                    switch (i & 3) {
-                        case 0: return quad_bcast(v, std::integral_constant<int, 0>{});
-                        case 1: return quad_bcast(v, std::integral_constant<int, 1>{});
-                        case 2: return quad_bcast(v, std::integral_constant<int, 2>{});
-                        default: return quad_bcast(v, std::integral_constant<int, 3>{});
-                    }
-                };
-                zi[i] = pick(gz);
-                si[i] = pick(gs);
-            }
-#pragma unroll
-            for (int j = 2 * jb; j < 2 * jb + 2; ++j) {
-                uint32_t w[WPC];
-#pragma unroll
-                for (int a = 0; a < WPC; ++a) w[a] = 0;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int bit = (e & 1) * 16 + BITS * ((e >> 1) & (8 / BITS - 1));
-                    w[BITS == 2 ? 0 : (e >> 2)] |= encode((float)x[e].h[j], zi[e], si[e], levels) << bit;
-                }
-#pragma unroll
-                for (int a = 0; a < WPC; ++a) wq[j][a] = w[a];
-            }
-        }
-    }
-    // combine with the lane that holds the other 16 channels of the group, then each of the two stores
-    // four of the eight channels' words
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-#pragma unroll
-        for (int a = 0; a < WPC; ++a) {
-            uint32_t w = wq[j][a] << (8 * odd);
-            w |= dpp_u32<kQuadXor2>(w);
-            wq[j][a] = w;
-        }
-    const uint32_t omask = 0u - (uint32_t)odd;
-#pragma unroll
-    for (int m = 0; m < 4; ++m)
-#pragma unroll
-        for (int a = 0; a < WPC; ++a) {
-            const uint32_t mine = (wq[m + 4][a] & omask) | (wq[m][a] & ~omask);     // a bitfield insert, not an indexed array
-            const int r = (seg & 1) * 8 + m + 4 * odd;             // channel % 16
-            if (BITS == 2) {
-                dst[(tl * 16 + r) * 4 + g] = mine;
-            } else {
-                const int i = g * 2 + a;
-                dst[(i >> 2) * 256 + (tl * 16 + r) * 4 + (i & 3)] = mine;
-            }
-        }
+    uint32_t* dst = p.codes + at * (kTileTokens * kHeadDim * BITS / 32);
+    _Float16* scale = reinterpret_cast<_Float16*>(p.scale) + at * (kTileTokens * 4);
+    _Float16* zero = reinterpret_cast<_Float16*>(p.zero) + at * (kTileTokens * 4);
+    quantize_value_tile<BITS>(x, lane,
+        [&](int i, _Float16 s, _Float16 z) {
+            scale[i] = s;
+            zero[i] = z;
+        },
+        [&](int i, uint32_t w) { dst[i] = w; });
 }
 
 template <int BITS>

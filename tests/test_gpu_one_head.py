@@ -21,7 +21,9 @@ CASES = [
     (4, 1, 2, 32, 32, 30000, 2, 1, 1),          # many parts
     (4, 1, 4, 32, 32, 30000, 2, 1, 1),
     (2, 1, 2, 32, 1024, 3000, 3, 1, 1),         # a large window: most steps are rows
-    (32, 9, 2, 32, 128, 1300, 2, 1, 1),         # one part a unit, not all compute units alike
+    (32, 9, 2, 32, 128, 1300, 14, 1, 1),        # one part a unit, not all compute units alike; a flush in the last step but two
+    (32, 9, 4, 32, 128, 1300, 14, 1, 1),
+    (2, 2, 2, 32, 64, 9599, 3, 1, 1),           # a flush beside parts of many steps
     (32, 26, 4, 32, 32, 900, 2, 1, 1),          # a few more units than fit at once
     (3, 2, 2, 64, 128, 2001, 3, 1, 1),
     (3, 2, 4, 128, 128, 2001, 3, 1, 1),
