@@ -139,7 +139,7 @@ typedef struct kivi_decode_plan {
     int32_t family;             /* KIVI_DECODE_VALU or KIVI_DECODE_MFMA                              */
     int32_t launches;           /* kernel launches of one attention call (a decoding step's flush is */
                                 /* not counted, see kivi_decode_step); with one query head per      */
-                                /* kv-head, K and V split alike, the most it takes                  */
+                                /* kv-head and n_kq >= n_vq, the most it takes                      */
     int32_t splits_quantised;   /* pieces of the all-quantised token range per (batch, kv-head); with */
                                 /* 3 or more query heads per kv-head a launch may cut finer         */
     int32_t splits_fp16;        /* pieces of the range that holds fp16 rows                         */
@@ -265,8 +265,8 @@ int kivi_decode_attention_static(const kivi_layout_t* layout, const kivi_cache_t
  * kivi_decode_plan) reads the new token's rows from k_new / v_new and writes them into the
  * residual rings itself.  A flush is a launch of its own before it, or, with up to four query heads per
  * kv-head and G = 32, part of the fp16-row launch of the two-launch form (which steps that flush take more often
- * than others with two heads: from 129 units on).  With one query head per kv-head, K and V split alike, G = 32 and 32
- * tokens to flush the whole step is one launch.
+ * than others with two heads: from 129 units on).  With one query head per kv-head and n_kq >= n_vq the whole
+ * step is one launch where 32 tokens leave a window with K and V split alike (G = 32), or one value token is quantised.
  *   k_new, v_new   device, fp16 [b][n_kv_heads][128]; they must stay valid until the launch has run
  *   other arguments as for kivi_decode_attention / kivi_flush_residual
  * Errors: INVALID_ARG (also: a ring is full, no capacity left for the flush), UNSUPPORTED,

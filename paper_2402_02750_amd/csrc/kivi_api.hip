@@ -372,8 +372,8 @@ int enqueue_attention(const kivi_layout_t* l, const kivi_cache_t* c, const void*
     p.two_launches = two ? 1 : 0;
     p.head_groups = wide_group_runs(l, path, two);
     // One query head per kv-head: a single launch whatever the plan, which its workspace rows always fit.
-    const bool one = path == KIVI_DECODE_MFMA && l->decode_path != KIVI_DECODE_MFMA_TWO && l->n_q_heads == l->n_kv_heads && c->n_kq == c->n_vq;
-    if ((flush_k || flush_v) && !((two || one) && flush_k && flush_v)) return KIVI_ERR_INVALID_ARG;
+    const bool one = path == KIVI_DECODE_MFMA && l->decode_path != KIVI_DECODE_MFMA_TWO && l->n_q_heads == l->n_kv_heads && c->n_kq >= c->n_vq;
+    if ((flush_k || flush_v) && !one && !(two && flush_k && flush_v)) return KIVI_ERR_INVALID_ARG;
     p.flush_k = flush_k;
     p.flush_v = flush_v;
     const size_t rows = (size_t)l->batch * l->n_q_heads * p.plan.n_splits();
@@ -972,17 +972,19 @@ int kivi_decode_step(const kivi_layout_t* l, kivi_cache_t* c, const void* k_new,
         // 1023 tokens, 51.1 -> 49.5 at 2175, 4 bits 42.2 -> 40.5; 5 to 8 heads would lose 5-6 us: residual_rows_kernel takes
         // longer than that kernel's own rows and a flush launch together.  Two heads: see wants_two_launches.)
         // One query head per kv-head: a flush of one tile, which is what every flushing step after the first has, rides in
-        // the attention's only launch (decode_one_kernel, which has both sides' figures).
+        // the attention's only launch, and so does one value token (decode_one_kernel, which has both sides' figures).
         const bool in_one = l->n_q_heads == l->n_kv_heads && l->decode_path != KIVI_DECODE_MFMA_TWO;
-        if ((nk > 0 || nv > 0) && l->group == kTileTokens &&
-            (in_one ? nk == kTileTokens && nv == kTileTokens && after.n_kq == after.n_vq
-                    : l->n_q_heads <= 4 * l->n_kv_heads && wants_two_launches(l, &after, KIVI_DECODE_MFMA, true))) {
+        const bool one_tile = l->group == kTileTokens && nk == kTileTokens && nv == kTileTokens && after.n_kq == after.n_vq;
+        const bool one_value = nk == 0 && nv == 1 && after.n_kq >= after.n_vq;
+        if ((nk > 0 || nv > 0) &&
+            (in_one ? one_tile || one_value
+                    : l->group == kTileTokens && l->n_q_heads <= 4 * l->n_kv_heads && wants_two_launches(l, &after, KIVI_DECODE_MFMA, true))) {
             const int64_t sh = (int64_t)l->cap_r_tokens * kHeadDim, sb = sh * l->n_kv_heads;
             const RowSource ksrc{static_cast<const __half*>(c->k_resid), sb, sh, kHeadDim, c->k_r_start, l->cap_r_tokens};
             const RowSource vsrc{static_cast<const __half*>(c->v_resid), sb, sh, kHeadDim, c->v_r_start, l->cap_r_tokens};
             const QuantKeyParams kp = key_quant_params(l, c, ksrc, nk);
             const QuantValueParams vp = value_quant_params(l, c, vsrc, nv);
-            if (int s = enqueue_attention(l, &after, q, softmax_scale, out, workspace, workspace_bytes, k_new, v_new, stream, &kp, &vp))
+            if (int s = enqueue_attention(l, &after, q, softmax_scale, out, workspace, workspace_bytes, k_new, v_new, stream, nk > 0 || !in_one ? &kp : nullptr, &vp))
                 return s;
             *c = after;
             return KIVI_OK;

@@ -1,5 +1,4 @@
-// Decode attention, matrix-core family, one query head per kv-head, K and V split at the same token (KIVI Equation 4 and
-// Algorithm 1 Decoding): fp16 rows and quantised tiles of a cache in ONE launch, every byte through asynchronous copies.
+// Decode attention, matrix-core family, one query head per kv-head (KIVI Equation 4 and Algorithm 1 Decoding): fp16 rows and quantised tiles of a cache in ONE launch, every byte through asynchronous copies.
 //
 // A unit is a (batch entry, kv-head).  Its work is a list of steps: first the fp16 rows of the window, then the
 // quantised tiles.  A step gives every wavefront of a workgroup one slot of its own LDS ring: PT tiles (codes, scales,
@@ -26,6 +25,15 @@
 // at 512 units x 4000, a fifth wavefront: two workgroups per compute unit instead of three).  Against a launch of its
 // own before the attention (4.5-5 us): 8 units x 512 tokens 13.6 -> 9.4 us, 256 x 4095 31.2 -> 25.6, 512 x 4095 49.0 -> 42.2; 4 bits, 256
 // x 4095 40.5 -> 34.3, 320 x 8191 78.3 -> 77.0.
+//
+// UNEVEN (n_kq >= n_vq, Algorithm 1's policy): the tokens between have quantised keys and fp16 value rows.  An item of those is
+// MT tokens: their key tile's codes, scales and zero-points and their value rows fill a slot with the same NI copies (the key tile is
+// read for every MT of its 32 tokens, from the L2 after the first); its logits go through LDS to the lanes that have the rows.  Values
+// that are not there in the last tile count as scale 0.  The value token that a step quantises lies in the first of these items;
+// its wavefront encodes the row that it has in LDS (a launch of its own before the attention took 4.7 us).  Items follow each
+// other without rounding to steps.  Whole steps, decode_mfma_kernel -> this one: 256 units x 4000 tokens, G = 64, 34.4 -> 22.3 us;
+// 32 x 500 13.9 -> 8.6, 256 x 1000 26.7 -> 13.0, 512 x 4000 46.9 -> 36.2, 2048 x 2000 118.9 -> 83.2; 4 bits 14.5 -> 8.2, 29.7 -> 15.0,
+// 65.8 -> 53.8, 146.0 -> 122.5; a window of 512 tokens, 256 x 4000 42.4 -> 31.1.
 //
 // Bound: HBM.  A launch that only copies what this one reads takes 29.7 us for 512 units of 124 tiles at 2 bits (6.6 TB/s), rows and
 // all 35; this kernel 39.5 (decode_mfma_kernel 46).  What is left is start (2 us to the first tile), the last step and the
@@ -77,7 +85,7 @@ template <int CTRL>
 __device__ __forceinline__ float dpp(float x) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
 }
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppRor4 = 0x124, kDppRor8 = 0x128;
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppRor4 = 0x124, kDppRor8 = 0x128, kDppRor12 = 0x12C;
 
 // sum / maximum over the lanes that differ in bits 4 and 5
 __device__ __forceinline__ float add_rows(float x) {
@@ -194,17 +202,20 @@ struct Shape {
     // what a flush weighs as a part's work: a step at 2 bits, two of half the tiles at 4 (320 units x 8191, 4 bits: 78.7 us with
     // one, 77.0 with two or three; 32 x 8191 at 2 bits: 24.4, 24.6, 25.2 us with one, two, three)
     static constexpr int kFlushSteps = 2 / PT;
+    // a slot of a key tile's codes, its scales and zero-points, and MT tokens' fp16 value rows
+    static constexpr int MT = 4 * (NI - kPlanes - 1), kMixedRows = kCodeBytes + 1024;
     // operands of a tile: key side hi (128 halves), 16 halves of skew, lo; value side 8 columns of 32 tokens
     static constexpr int kKeyColumn = 144, kOperandHalves = 272;
     static constexpr int kWaveBytes = NB * kSlotBytes + PT * kOperandHalves * 2;
     static constexpr int kLds = WV * kWaveBytes + WV * 8 + 16;
 };
 
-template <int BITS, int PT, int NB, int WV, int OCC, bool CS, bool FLUSH>
+template <int BITS, int PT, int NB, int WV, int OCC, bool CS, bool FLUSH, bool UNEVEN>
 __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(DecodeParams p) {
     using S = Shape<BITS, PT, NB, WV>;
     static_assert(!(CS && FLUSH), "a flush in this launch: G = 32");
-    constexpr int NI = S::NI, NT = S::NT, NR = (NT + 3) / 4;
+    static_assert(!(UNEVEN && FLUSH), "K and V split differently: a flush of one value token only");
+    constexpr int NI = S::NI, NT = S::NT, NR = (NT + 3) / 4, MT = S::MT;
     __shared__ __align__(16) unsigned char sm[S::kLds];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -223,8 +234,12 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
     const int u = blockIdx.x / p.unit_wgs, part = blockIdx.x % p.unit_wgs;
     // FLUSH: the last wavefront of a unit's last workgroup quantises the tokens that leave the window before it takes its share
     const bool flush_here = FLUSH && part == p.unit_wgs - 1, flushes = flush_here && wave == WV - 1;
-    const int tiles = p.plan.tiles_a - FLUSH;                                    // (the flushed tile is the last)
     const int n_kr = p.n_kr;
+    // UNEVEN: tokens below v_q have quantised values in the cache, the others rows in the ring from slot v_start on
+    const int v_q = p.n_vq - p.flushed_values;
+    const int v_start = !UNEVEN || p.v_r_start >= p.flushed_values ? p.v_r_start - (UNEVEN ? p.flushed_values : 0) : p.cap_r - 1;
+    const int v_skip = UNEVEN ? p.n_kq - v_q : 0;                                // value rows before the window's
+    const int tiles = UNEVEN ? (v_q + kTileTokens - 1) / kTileTokens : p.plan.tiles_a - FLUSH;      // (the flushed tile is the last)
     const StepAxis axis{p.axis_len, p.axis_rem};
     const int real = axis.start(p.unit_wgs) - (FLUSH ? S::kFlushSteps : 0);      // (the flush counts as the last steps)
     const int s0 = min(axis.start(part), real), s1 = min(axis.start(part + 1), real);
@@ -232,7 +247,11 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
     const int a0 = max(s0 - nr, 0), len_a = max(s1 - nr, 0) - a0;
     // An item is one wavefront's slot of a step.  A wavefront takes every WV-th, or -- a workgroup that flushes, whose last
     // wavefront comes late -- the next one that nobody has.
-    const int n_items = (s1 - s0) * WV, n_row_items = min(max(nr - s0, 0), s1 - s0) * WV;
+    // UNEVEN: all items one after the other: rows, MT tokens each whose keys only are quantised, tiles.
+    const int m0 = v_q & -MT, all_rows = (n_kr + NT - 1) / NT, all_fp16 = all_rows + (p.n_kq - m0) / MT;
+    const int n_items = UNEVEN ? min(s1 * WV, all_fp16 + (tiles + PT - 1) / PT) - s0 * WV : (s1 - s0) * WV;
+    const int n_row_items = UNEVEN ? min(max(all_rows - s0 * WV, 0), n_items) : min(max(nr - s0, 0), s1 - s0) * WV;
+    const int n_fp16_items = UNEVEN ? min(max(all_fp16 - s0 * WV, 0), n_items) : n_row_items;
     const int64_t unit = u;
 
     // ---- copies ----
@@ -269,24 +288,46 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
             const int r = 4 * j + kb;
             const bool is_v = r >= NT;
             const int t = min(t0 + (is_v ? r - NT : r), n_kr - 1);
-            const __half* src = (is_v ? p.v_resid : p.k_resid) + (unit * p.cap_r + ring_slot(is_v ? p.v_r_start : p.k_r_start, t, p.cap_r)) * kHeadDim;
+            const __half* src = (is_v ? p.v_resid : p.k_resid) + (unit * p.cap_r + ring_slot(is_v ? v_start : p.k_r_start, is_v ? t + v_skip : t, p.cap_r)) * kHeadDim;
             if (p.k_new && t == n_kr - 1) src = (is_v ? p.v_new : p.k_new) + unit * kHeadDim;
             copy_to_lds(src + n * 8, dst + j * 1024);
         }
+    };
+    // tokens t0 .. t0 + MT - 1 of a key tile, and their value rows (before the first: that one's again)
+    auto copy_mixed = [&](int t0, int slot) {
+        const uint32_t dst = ring_lds + slot * S::kSlotBytes;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        const int64_t tile = tile0 + t0 / kTileTokens;
+        const char* kc = reinterpret_cast<const char*>(p.k_codes) + tile * S::kCodeBytes;
+#pragma unroll
+        for (int pl = 0; pl < S::kPlanes; ++pl) copy_to_lds(kc + pl * 1024, lane16, dst + pl * 1024);
+        int64_t off = tile * 256;
+        if constexpr (CS) off = kb < 2 ? (tile >> kg) * 256 : (tile * 256) >> kg;
+        copy_to_lds(sc + off, dst + S::kCodeBytes);
+#pragma unroll
+        for (int j = 0; j < MT / 4; ++j)
+            copy_to_lds(p.v_resid + (unit * p.cap_r + ring_slot(v_start, max(t0 + 4 * j + kb - v_q, 0), p.cap_r)) * kHeadDim + n * 8, dst + S::kMixedRows + j * 1024);
     };
     // the query
     if (lane < 16) copy_to_lds(p.q + unit * kHeadDim + n * 8, (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)sm_query));
     // Tiles in an order rotated by the unit: workgroups in lockstep that all read the same relative offset of their units
     // would meet on few memory channels for unlucky strides (a copy alone: 32.3 -> 29.8 us at 512 units).
-    const int rot = len_a > 0 ? (int)((uint32_t)(u * 5) % (uint32_t)len_a) : 0;
+    const int turn = UNEVEN ? n_items - n_fp16_items : len_a, rot = turn > 0 ? (int)((uint32_t)(u * 5) % (uint32_t)turn) : 0;
     auto row_of = [&](int item) -> int { return (s0 + item / WV) * S::kStepRows + item % WV * NT; };      // first token in the window
+    auto mixed_of = [&](int item) -> int { return m0 + (s0 * WV + item - all_rows) * MT; };                // first token
     auto tile_of = [&](int item) -> int {
+        if constexpr (UNEVEN) {
+            int a = item - n_fp16_items + rot;
+            a -= a >= turn ? turn : 0;
+            return (s0 * WV + n_fp16_items - all_fp16 + a) * PT;
+        }
         int a = (item - n_row_items) / WV + rot;
         a -= a >= len_a ? len_a : 0;
         return (a0 + a) * S::kStepTiles + item % WV * PT;
     };
     auto copy_item = [&](int item, int slot) {
         if (item < n_row_items) copy_rows(row_of(item), slot);
+        else if (UNEVEN && item < n_fp16_items) copy_mixed(mixed_of(item), slot);
         else if (item < n_items) copy_tiles(tile_of(item), slot);
     };
     const int starters = flush_here ? WV - 1 : WV;
@@ -449,24 +490,12 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
             return *reinterpret_cast<const uint32_t*>(at + value_at);
         }
     };
-    // N tiles of a slot; live: those that are there
-    auto quantised = [&](auto count, const unsigned char* sl, int live) {
+    // logits (log2) of this lane's token of N tiles; s_raw: their scales, top: the largest
+    auto logits = [&](auto count, const auto& kw, const auto& s_raw, const auto& z, uint32_t top, auto& x) {
         constexpr int N = decltype(count)::value;
-        constexpr int kS = 2 * S::kCodeBytes;
-        uint32_t kw[N][2 * BITS], vw[N][2 * BITS], s_raw[N], v_raw[N], top = 0;
-        half2v s[N], z[N], vz[N];
+        half2v s[N];
 #pragma unroll
-        for (int t = 0; t < N; ++t) {
-            const unsigned char* at = sl + t * S::kTileBytes;
-            s_raw[t] = *reinterpret_cast<const uint32_t*>(at + kS + lane * 4);
-            z[t] = half2_of(*reinterpret_cast<const uint32_t*>(at + kS + 256 + lane * 4));
-            load_codes(at, kw[t]);
-            v_raw[t] = value_pair(at + kS + 512);
-            vz[t] = half2_of(value_pair(at + kS + 768));
-            load_codes(at + S::kCodeBytes, vw[t]);
-            s[t] = half2_of(s_raw[t]);
-            top = max_pairs(top, s_raw[t]);
-        }
+        for (int t = 0; t < N; ++t) s[t] = half2_of(s_raw[t]);
         float cx = c_code;
         if (any_above(top, kKeyScaleLimit)) {
             uint32_t a = 0;
@@ -506,13 +535,40 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
                 d[t][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(key_fragment<BITS>(kw[t], cb, 0), f[t][cb], d[t][0], 0, 0, 0);
                 d[t][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(key_fragment<BITS>(kw[t], cb, 1), f[t][cb], d[t][1], 0, 0, 0);
             }
-        // this lane's token of every tile: probability over the code's position factor
-        float x[N], pv[N], mx = -INFINITY;
 #pragma unroll
         for (int t = 0; t < N; ++t) {
             const float x0 = own_of(d[t][0]), x1 = own_of(d[t][1]);
             x[t] = fmaf((is_lo ? x1 : x0) + dpp<kDppRor8>(is_lo ? x0 : x1), cx, zk[t]);
-            if (t > 0 && t >= live) x[t] = -INFINITY;
+        }
+    };
+    // N tiles of a slot; live: those that are there (UNEVEN: tokens that are there)
+    auto quantised = [&](auto count, const unsigned char* sl, int live) {
+        constexpr int N = decltype(count)::value;
+        constexpr int kS = 2 * S::kCodeBytes;
+        auto there = [&](int t) -> bool { return UNEVEN ? t * kTileTokens + own_tok < live : t == 0 || t < live; };
+        uint32_t kw[N][2 * BITS], vw[N][2 * BITS], s_raw[N], v_raw[N], top = 0;
+        half2v z[N], vz[N];
+#pragma unroll
+        for (int t = 0; t < N; ++t) {
+            const unsigned char* at = sl + t * S::kTileBytes;
+            s_raw[t] = *reinterpret_cast<const uint32_t*>(at + kS + lane * 4);
+            z[t] = half2_of(*reinterpret_cast<const uint32_t*>(at + kS + 256 + lane * 4));
+            load_codes(at, kw[t]);
+            v_raw[t] = value_pair(at + kS + 512);
+            vz[t] = half2_of(value_pair(at + kS + 768));
+            load_codes(at + S::kCodeBytes, vw[t]);
+            if (UNEVEN && !there(t)) {                 // (never written)
+                v_raw[t] = 0;
+                vz[t] = half2v{0, 0};
+            }
+            top = max_pairs(top, s_raw[t]);
+        }
+        float x[N], pv[N], mx = -INFINITY;
+        logits(count, kw, s_raw, z, top, x);
+        // this lane's token of every tile: probability over the code's position factor
+#pragma unroll
+        for (int t = 0; t < N; ++t) {
+            if (!there(t)) x[t] = -INFINITY;
             mx = fmaxf(mx, x[t]);
         }
         if (__any(mx > mref + (float)kSlack)) raise_reference(mx);
@@ -522,7 +578,7 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
         for (int t = 0; t < N; ++t) {
             pv[t] = __builtin_amdgcn_exp2f(x[t] + off);
             l_lane += pv[t];
-            if (t == 0 || t < live) vtop = max_pairs(vtop, v_raw[t]);
+            if (UNEVEN || there(t)) vtop = max_pairs(vtop, v_raw[t]);
         }
         fit_value_exponent(vtop, [&]() {
             float m = 0.f;
@@ -590,9 +646,79 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
         }
         if (p.k_new && left <= NT && kb < 2) {                                    // the newest token's rows go to the rings
             const uint4v row = *reinterpret_cast<const uint4v*>(sl + (kb * NT + left - 1) * 256 + n * 16);
-            const int at = ring_slot(kb ? p.v_r_start : p.k_r_start, n_kr - 1, p.cap_r);
+            const int at = ring_slot(kb ? v_start : p.k_r_start, kb ? n_kr - 1 + v_skip : n_kr - 1, p.cap_r);
             *reinterpret_cast<uint4v*>(const_cast<__half*>(kb ? p.v_resid : p.k_resid) + (unit * p.cap_r + at) * kHeadDim + n * 8) = row;
         }
+    };
+    // The value token that is quantised in this step, its row in LDS: codes and group constants to the cache, the row
+    // becomes its codes.  A lane has channels 32 j + i and 16 on, j = lane % 4, i = lane / 4: one word of the tile, whose
+    // other codes stay.  Returns scale and zero-point of this lane's channels 8 n ..
+    auto flush_value = [&](_Float16* row) -> float2 {
+        constexpr float levels = (float)((1 << BITS) - 1);
+        const int j = lane & 3, i = lane >> 2, e = v_q & 7;
+        const float a = (float)row[32 * j + i], b = (float)row[32 * j + 16 + i];
+        float lo = -fminf(a, b), hi = fmaxf(a, b);
+        lo = max_rows(fmaxf(fmaxf(lo, dpp<kDppRor4>(lo)), fmaxf(dpp<kDppRor8>(lo), dpp<kDppRor12>(lo))));
+        hi = max_rows(fmaxf(fmaxf(hi, dpp<kDppRor4>(hi)), fmaxf(dpp<kDppRor8>(hi), dpp<kDppRor12>(hi))));
+        if (kg >= 1) {
+            lo = fmaxf(lo, dpp<kDppXor1>(lo));
+            hi = fmaxf(hi, dpp<kDppXor1>(hi));
+        }
+        if (kg >= 2) {
+            lo = fmaxf(lo, dpp<kDppXor2>(lo));
+            hi = fmaxf(hi, dpp<kDppXor2>(hi));
+        }
+        const __half s16 = __float2half_rn((hi + lo) / levels);
+        const float s = __half2float(s16), z = -lo;
+        const uint32_t ca = tile::encode(a, z, s, levels), cb = tile::encode(b, z, s, levels);
+        const int64_t at = tile0 + v_q / kTileTokens;
+        const int half_word = BITS == 2 ? j : 2 * j + (e >> 2);
+        uint32_t* word = const_cast<uint32_t*>(p.v_codes) + at * (S::kCodeBytes / 4) + (half_word >> 2) * 256 + ((v_q >> 3 & 3) * 16 + i) * 4 + (half_word & 3);
+        const int bit = (e & 1) * 16 + (BITS == 2 ? 2 * (e >> 1) : 4 * (e >> 1 & 1));
+        constexpr uint32_t mask = BITS == 2 ? 0x303u : 0xF0Fu;
+        *word = (*word & ~(mask << bit)) | (ca | cb << 8) << bit;
+        if (i == 0 && (j & ((1 << kg) - 1)) == 0) {
+            const int64_t o = (at * kTileTokens + (v_q & (kTileTokens - 1))) * (4 >> kg) + (j >> kg);
+            const_cast<__half*>(p.v_scale)[o] = s16;
+            const_cast<__half*>(p.v_zero)[o] = __float2half_rn(z);
+        }
+        row[32 * j + i] = (_Float16)(float)ca;
+        row[32 * j + 16 + i] = (_Float16)(float)cb;
+        wave_lds_sync();
+        return make_float2(__shfl(s, n >> 2), __shfl(z, n >> 2));
+    };
+    // MT tokens with quantised keys and fp16 value rows, the first is t0: one key tile's logits, the probabilities through
+    // LDS to the lanes that have the rows
+    auto mixed = [&](unsigned char* sl, int t0) {
+        uint32_t kw[1][2 * BITS], s_raw[1];
+        half2v z[1];
+        float x[1];
+        s_raw[0] = *reinterpret_cast<const uint32_t*>(sl + S::kCodeBytes + lane * 4);
+        z[0] = half2_of(*reinterpret_cast<const uint32_t*>(sl + S::kCodeBytes + 256 + lane * 4));
+        load_codes(sl, kw[0]);
+        logits(std::integral_constant<int, 1>{}, kw, s_raw, z, s_raw[0], x);
+        const int t = (t0 & -kTileTokens) + own_tok;
+        if (t < max(t0, v_q) || t >= t0 + MT) x[0] = -INFINITY;
+        if (__any(x[0] > mref + (float)kSlack)) raise_reference(x[0]);
+        float* pr_of = reinterpret_cast<float*>(operand);
+        wave_lds_sync();
+        pr_of[own_tok] = __builtin_amdgcn_exp2f(x[0] + ((float)kProbExp<BITS> - mref));
+        const int flushed = p.flushed_values && v_q >= t0 ? v_q - t0 : MT;        // (v_q is in the first of these items)
+        float2 sz = {1.f, 0.f};
+        if (flushed < MT) sz = flush_value(reinterpret_cast<_Float16*>(sl + S::kMixedRows + flushed * 256));
+        wave_lds_sync();
+#pragma unroll
+        for (int j = 0; j < MT / 4; ++j) {
+            const int r = 4 * j + kb;
+            const float pr = pr_of[(t0 & (kTileTokens - 1)) + r];
+            const bool coded = r == flushed;
+            const float by = coded ? pr * sz.x : pr, plus = coded ? pr * sz.y : 0.f;
+            r_l += pr;
+            const half8 v = *reinterpret_cast<const half8*>(sl + S::kMixedRows + r * 256 + n * 16);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) r_out[c] = fmaf(by, (float)v[c], r_out[c] + plus);
+        }
+        wave_lds_sync();
     };
     // The instruction arbiter favours the oldest wavefront of a SIMD.  Where all workgroups start at once the younger ones would
     // end late and alone (512 units: 28 against 36 us), so a wavefront's priority falls with the share of its work that is done (39.6 ->
@@ -640,10 +766,19 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
         if (left > 0) fp16_rows(ring + slot * S::kSlotBytes, left);
         end(asked);
     }
+    if constexpr (UNEVEN) {
+#pragma unroll 1
+        while (now < n_fp16_items) {
+            begin();
+            const int asked = ask();
+            mixed(ring + slot * S::kSlotBytes, mixed_of(now));
+            end(asked);
+        }
+    }
 #pragma unroll 1
     while (now < n_items) {
         begin();
-        const int asked = ask(), live = tiles - tile_of(now);
+        const int asked = ask(), live = UNEVEN ? v_q - tile_of(now) * kTileTokens : tiles - tile_of(now);
         if (live > 0) quantised(std::integral_constant<int, PT>{}, ring + slot * S::kSlotBytes, live);
         end(asked);
     }
@@ -673,7 +808,7 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
             for (int i = 0; i < 4; ++i) o[i] = fmaf(acc[u8][i] + dpp<kDppRor8>(acc[u8][i]), up, zo[(u8 >> 1) & 1]);
             if (n < 4 && my_group == u8 >> 1) *reinterpret_cast<float4v*>(&o_wave[u8 * 16 + kb * 4]) = o;
         }
-        if (n_row_items > 0) {
+        if (n_fp16_items > 0) {
             float r[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) r[e] = add_rows(r_out[e]);
@@ -783,13 +918,17 @@ int compute_units() {
     return cus;
 }
 
-template <int BITS, int PT, int NB, int WV, int OCC, bool CS, bool FLUSH>
+template <int BITS, int PT, int NB, int WV, int OCC, bool CS, bool FLUSH, bool UNEVEN>
 hipError_t launch(DecodeParams p, hipStream_t stream) {
     using S = Shape<BITS, PT, NB, WV>;
     static_assert(S::kLds <= 160 * 1024 / OCC / 1280 * 1280, "workgroups per compute unit (LDS is given out in pieces of 1280 bytes)");
     static_assert(NB == 2 && PT <= 2, "two items in flight; masked tiles of a slot");
     const int64_t units = (int64_t)p.batch * p.n_kv_heads;
-    const int steps = (p.plan.tiles_a - FLUSH + S::kStepTiles - 1) / S::kStepTiles + (p.n_kr + S::kStepRows - 1) / S::kStepRows + (FLUSH ? S::kFlushSteps : 0);
+    int steps = (p.plan.tiles_a - FLUSH + S::kStepTiles - 1) / S::kStepTiles + (p.n_kr + S::kStepRows - 1) / S::kStepRows + (FLUSH ? S::kFlushSteps : 0);
+    if (UNEVEN) {
+        const int v_q = p.n_vq - p.flushed_values, m0 = v_q & -S::MT, tiles = (v_q + kTileTokens - 1) / kTileTokens;
+        steps = ((p.n_kr + S::NT - 1) / S::NT + (p.n_kq - m0) / S::MT + (tiles + PT - 1) / PT + WV - 1) / WV;
+    }
     const int cus = compute_units();
     const int w = one_head_parts(units, steps, cus, std::min(p.part_stride, kOneHeadMaxParts), BITS == 2 ? 8 : 12);
     if (steps < 1 || units * w > 0x7fffffff) return hipErrorInvalidValue;
@@ -797,26 +936,38 @@ hipError_t launch(DecodeParams p, hipStream_t stream) {
     p.axis_len = steps / w;
     p.axis_rem = steps % w;
     p.one_round = units * w <= (int64_t)cus * OCC;
-    decode_one_kernel<BITS, PT, NB, WV, OCC, CS, FLUSH><<<(unsigned)(units * w), 64 * WV, 0, stream>>>(p);
+    decode_one_kernel<BITS, PT, NB, WV, OCC, CS, FLUSH, UNEVEN><<<(unsigned)(units * w), 64 * WV, 0, stream>>>(p);
     return hipGetLastError();
+}
+
+template <bool CS, bool FLUSH, bool UNEVEN>
+hipError_t launch_bits(const DecodeParams& p, hipStream_t stream) {
+    return p.bits == 2 ? launch<2, 2, 2, 4, 3, CS, FLUSH, UNEVEN>(p, stream) : launch<4, 1, 2, 4, 3, CS, FLUSH, UNEVEN>(p, stream);
 }
 
 }  // namespace
 
-hipError_t launch_decode_one(const DecodeParams& p, hipStream_t stream) {
-    if (p.n_q_heads != p.n_kv_heads || p.n_kq != p.n_vq || p.n_kr != p.n_vr || p.part_stride < 1) return hipErrorInvalidValue;
-    if (p.flush_k || p.flush_v) {
+hipError_t launch_decode_one(const DecodeParams& p_in, hipStream_t stream) {
+    DecodeParams p = p_in;
+    p.flushed_values = 0;
+    if (p.n_q_heads != p.n_kv_heads || p.n_kq + p.n_kr != p.n_vq + p.n_vr || p.n_kq < p.n_vq || p.part_stride < 1) return hipErrorInvalidValue;
+    const bool cs = p.kg_shift > 0;
+    const QuantKeyParams* k = p.flush_k;
+    const QuantValueParams* v = p.flush_v;
+    if (k) {
         // the flushed tokens: one tile, the last quantised one, out of the rings right before the window
-        const QuantKeyParams* k = p.flush_k;
-        const QuantValueParams* v = p.flush_v;
-        if (!k || !v || p.kg_shift > 0 || k->n_tiles != 1 || v->n_tokens != kTileTokens || p.plan.tiles_a < 1 || p.n_kr < 1 ||
+        if (!v || cs || p.n_kq != p.n_vq || k->n_tiles != 1 || v->n_tokens != kTileTokens || p.plan.tiles_a < 1 || p.n_kr < 1 ||
             k->first_tile != p.plan.tiles_a - 1 || v->first_token != (p.plan.tiles_a - 1) * kTileTokens)
             return hipErrorInvalidValue;
-        return p.bits == 2 ? launch<2, 2, 2, 4, 3, false, true>(p, stream) : launch<4, 1, 2, 4, 3, false, true>(p, stream);
+        return launch_bits<false, true, false>(p, stream);
     }
-    const bool cs = p.kg_shift > 0;
-    if (p.bits == 2) return cs ? launch<2, 2, 2, 4, 3, true, false>(p, stream) : launch<2, 2, 2, 4, 3, false, false>(p, stream);
-    return cs ? launch<4, 1, 2, 4, 3, true, false>(p, stream) : launch<4, 1, 2, 4, 3, false, false>(p, stream);
+    if (v) {
+        // ... or one value token, the last quantised one, out of the ring right before the others
+        if (v->n_tokens != 1 || v->first_token != p.n_vq - 1 || p.n_vr >= p.cap_r) return hipErrorInvalidValue;
+        p.flushed_values = 1;
+    }
+    if (v || p.n_kq != p.n_vq) return cs ? launch_bits<true, false, true>(p, stream) : launch_bits<false, false, true>(p, stream);
+    return cs ? launch_bits<true, false, false>(p, stream) : launch_bits<false, false, false>(p, stream);
 }
 
 }  // namespace kivi

@@ -131,6 +131,7 @@ struct DecodeParams {
     // steps, one more if g < axis_rem.  Batches of different lengths: wave_desc[4 g] = {first unit, first step in it,
     // steps, 0} of workgroup g, unit_parts[b] = steps before sequence b (kivi_tiles_plan.h)
     int32_t row_wgs, row_split, unit_wgs, axis_len, axis_rem;
+    int32_t flushed_values;     // decode_one_kernel: value tokens it quantises itself, the last of n_vq (0 or 1)
     int32_t one_round;          // decode_one_kernel: all its workgroups fit the device at once
     // the fp16-row launch that carries a flush, before decode_tiles_kernel: its part is the first of those that kernel merges
     // (maximum in the log2 domain, counted as finished)
@@ -154,7 +155,7 @@ hipError_t launch_decode_tiles(DecodeParams p, hipStream_t stream);
 // workgroups the device holds of it for a batch of different lengths
 int tiles_resident_ragged(int bits, int rep);
 int tiles_max_parts(int bits, int rep);       // parts of one unit that it merges, at most
-// decode_one_kernel (kivi_decode_one.hip): one query head per kv-head, K and V split at the same token, one launch
+// decode_one_kernel (kivi_decode_one.hip): one query head per kv-head, n_kq >= n_vq, one launch
 hipError_t launch_decode_one(const DecodeParams& p, hipStream_t stream);
 hipError_t launch_residual_rows(const DecodeParams& p, hipStream_t stream);
 // the same launch with extra workgroups that quantise the key group(s) and value tokens of a residual

@@ -39,30 +39,64 @@ def test_one_head(heads, batch, bits, group, residual, tokens, steps, kgain, vga
     """Decoding steps from a prompt, every step against the oracle; the cache's state after the last.  Tolerance as for
     decode_tiles_kernel, whose exponents and splits these are: probabilities and operands keep 21 bits, sums and
     logits in fp32: below 1e-4 of the largest value together."""
+    run_steps(heads, batch, bits, group, residual, tokens, steps, kgain, vgain, "window")
+
+
+# K and V split at different tokens: a value token quantised in most steps (every position in a tile, both halves of a
+# slot's tokens), values of a partly filled tile, key flushes (after which the window has no token with both rows)
+UNEVEN_CASES = [
+    (1, 1, 2, 32, 32, 1, 70, 1, 1),             # from nothing quantised to two tiles
+    (1, 1, 4, 32, 32, 20, 50, 1, 1),
+    (3, 2, 2, 64, 128, 2001, 40, 1, 1),         # rows, mixed slots and tiles in several parts
+    (3, 2, 4, 128, 128, 2001, 40, 1, 1),
+    (2, 2, 2, 32, 96, 959, 36, 1, 1),
+    (2, 2, 4, 64, 64, 1000, 36, 1, 1),
+    (2, 2, 2, 128, 128, 511, 34, 1, 1),
+    (2, 1, 2, 32, 1024, 3000, 3, 1, 1),         # a large window
+    (2, 1, 4, 32, 30016, 30100, 3, 1, 1),       # hardly anything but
+    (32, 9, 2, 64, 128, 1300, 3, 1, 1),         # one part a unit
+    (32, 9, 4, 32, 128, 1300, 3, 1, 1),
+    (32, 26, 4, 32, 32, 900, 2, 1, 1),          # a few more units than fit at once
+    (4, 1, 2, 32, 32, 30000, 2, 1, 1),
+    (2, 2, 2, 32, 64, 900, 2, 60, 1),
+    (2, 2, 4, 32, 64, 900, 2, 60, 500),
+    (2, 2, 2, 64, 64, 900, 2, 1, 2.0 ** -13),
+]
+
+
+@pytest.mark.parametrize("heads,batch,bits,group,residual,tokens,steps,kgain,vgain", UNEVEN_CASES)
+def test_one_head_uneven(heads, batch, bits, group, residual, tokens, steps, kgain, vgain):
+    """The same with the policy that flushes keys and values separately; tolerance as above (fp16 value rows are weighted with
+    fp32 probabilities)."""
+    run_steps(heads, batch, bits, group, residual, tokens, steps, kgain, vgain, "alg1")
+
+
+def run_steps(heads, batch, bits, group, residual, tokens, steps, kgain, vgain, policy):
     torch = gh.require_gpu()
     total = tokens + steps
+    flush = kivi.KIVI_FLUSH_ALG1 if policy == "alg1" else kivi.KIVI_FLUSH_WINDOW
     w = scaled(CONFIGS["llama7b"], name="onehead", batch=batch, n_q_heads=heads, n_kv_heads=heads, bits=bits, group=group,
                residual=residual, seed=17 * heads + bits + tokens)
-    print(f"case one head h={heads} b={batch} B={bits} G={group} R={residual} L={tokens}+{steps} gains {kgain} {vgain}", flush=True)
+    print(f"case one head {policy} h={heads} b={batch} B={bits} G={group} R={residual} L={tokens}+{steps} gains {kgain} {vgain}", flush=True)
     k = (workloads.keys(w, total).astype(np.float32) * kgain).astype(np.float16)
     v = (workloads.values(w, total).astype(np.float32) * vgain).astype(np.float16)
     scale = float(np.abs(v.astype(np.float32)).max())
     at = sorted({(0, 0), (batch - 1, heads - 1), (batch // 2, heads // 2)})
-    oc = gh.oracle_cache_for_heads(w, k[:, :, :tokens], v[:, :, :tokens], at, "window")
-    layout, cache = gh.gpu_prefill(w, k[:, :, :tokens], v[:, :, :tokens], kivi.KIVI_FLUSH_WINDOW, kivi.KIVI_DECODE_AUTO, extra_q_tokens=steps)
-    _, other = gh.gpu_prefill(w, k[:, :, :tokens], v[:, :, :tokens], kivi.KIVI_FLUSH_WINDOW, kivi.KIVI_DECODE_VALU, extra_q_tokens=steps)
+    oc = gh.oracle_cache_for_heads(w, k[:, :, :tokens], v[:, :, :tokens], at, policy)
+    layout, cache = gh.gpu_prefill(w, k[:, :, :tokens], v[:, :, :tokens], flush, kivi.KIVI_DECODE_AUTO, extra_q_tokens=steps)
+    _, other = gh.gpu_prefill(w, k[:, :, :tokens], v[:, :, :tokens], flush, kivi.KIVI_DECODE_VALU, extra_q_tokens=steps)
     for step in range(steps):
         q = (workloads.queries(w, step).astype(np.float32) / max(1, kgain)).astype(np.float16)
         new = [np.ascontiguousarray(x[:, :, tokens + step]) for x in (k, v)]
         kn, vn, qt = [torch.from_numpy(x).cuda() for x in (*new, q)]
         out = torch.full((batch, heads, 128), float("nan"), dtype=torch.float32, device="cuda")
-        kivi.kivi_decode_step(layout, cache, kn, vn, qt, w.softmax_scale, out)
+        kivi.kivi_decode_step(layout, cache, kn, vn, qt, w.softmax_scale, out, flush)
         oc.append(np.stack([k[b, h, tokens + step] for b, h in at])[:, None], np.stack([v[b, h, tokens + step] for b, h in at])[:, None])
         ref = gh.oracle_attention_for_heads(w, oc, q, at)
         got = out.cpu().numpy()
         err = np.abs(gh.pick_heads(got, w, at) - ref).max()
         assert err <= 1e-4 * scale, f"step {step}: {err:.3e} against {1e-4 * scale:.3e}"
         ref_all = torch.empty_like(out)        # all heads: the vector path on a cache of its own
-        kivi.kivi_decode_step(other.layout, other, kn, vn, qt, w.softmax_scale, ref_all)
+        kivi.kivi_decode_step(other.layout, other, kn, vn, qt, w.softmax_scale, ref_all, flush)
         gh.check_close(got / scale, ref_all.cpu().numpy() / scale, f"step {step}, all heads")
     gh.compare_quantized_state(cache, oc, at)
