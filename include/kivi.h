@@ -263,10 +263,10 @@ int kivi_decode_attention_static(const kivi_layout_t* layout, const kivi_cache_t
  * kivi_decode_attention.  On steps where nothing is flushed and the matrix-core family runs, the
  * append costs no launch of its own: the attention (one launch or two, see
  * kivi_decode_plan) reads the new token's rows from k_new / v_new and writes them into the
- * residual rings itself.  A flush is a launch of its own before it, or, with up to four query heads per
- * kv-head and G = 32, part of the fp16-row launch of the two-launch form (which steps that flush take more often
- * than others with two heads: from 129 units on).  With one query head per kv-head and n_kq >= n_vq the whole
- * step is one launch where 32 tokens leave a window with K and V split alike (G = 32), or one value token is quantised.
+ * residual rings itself.  A flush is a launch of its own before it, except:
+ * 32 tokens that leave a window with K and V split alike (G = 32) are quantised in the attention's launch where that is one
+ * launch, and with up to four query heads per kv-head in the first of two (which steps that flush take more often
+ * than others with two heads: from 129 units on); and with one query head per kv-head so is a single value token, n_kq >= n_vq.
  *   k_new, v_new   device, fp16 [b][n_kv_heads][128]; they must stay valid until the launch has run
  *   other arguments as for kivi_decode_attention / kivi_flush_residual
  * Errors: INVALID_ARG (also: a ring is full, no capacity left for the flush), UNSUPPORTED,

@@ -341,7 +341,7 @@ int part_rows(const kivi_layout_t* l, size_t bytes) {
 
 // Launch the attention of q over cache state `c` (already validated).  k_new / v_new non-null: the
 // rows of token length-1 are not in the rings yet and the (matrix-core) kernel puts them there.
-// flush_k / flush_v non-null (two-launch form, or one query head per kv-head): the residual flush that produced state `c` has
+// flush_k / flush_v non-null (two-launch form, decode_tiles_kernel, or one query head per kv-head): the residual flush that produced state `c` has
 // not been launched yet; the fp16-row launch carries it out with extra workgroups.
 int enqueue_attention(const kivi_layout_t* l, const kivi_cache_t* c, const void* q, float softmax_scale,
                       float* out, void* workspace, size_t workspace_bytes, const void* k_new, const void* v_new,
@@ -373,13 +373,13 @@ int enqueue_attention(const kivi_layout_t* l, const kivi_cache_t* c, const void*
     p.head_groups = wide_group_runs(l, path, two);
     // One query head per kv-head: a single launch whatever the plan, which its workspace rows always fit.
     const bool one = path == KIVI_DECODE_MFMA && l->decode_path != KIVI_DECODE_MFMA_TWO && l->n_q_heads == l->n_kv_heads && c->n_kq >= c->n_vq;
-    if ((flush_k || flush_v) && !one && !(two && flush_k && flush_v)) return KIVI_ERR_INVALID_ARG;
+    const bool tiles = path == KIVI_DECODE_MFMA && uses_tiles(l) && !(two && flush_k && l->n_q_heads <= 2 * l->n_kv_heads);
+    if ((flush_k || flush_v) && !one && !((two || tiles) && flush_k && flush_v)) return KIVI_ERR_INVALID_ARG;
     p.flush_k = flush_k;
     p.flush_v = flush_v;
     const size_t rows = (size_t)l->batch * l->n_q_heads * p.plan.n_splits();
     if (counter_bytes(l) + rows * (kHeadDim + 2) * sizeof(float) > workspace_bytes) return KIVI_ERR_WORKSPACE;
     p.counters = static_cast<int32_t*>(workspace);
-    const bool tiles = path == KIVI_DECODE_MFMA && uses_tiles(l) && !(flush_k && l->n_q_heads <= 2 * l->n_kv_heads);
     if (tiles && rows_launch_for_uneven_split(l, c, path)) p.two_launches = 1;
     p.part_stride = p.plan.n_splits();
     if (tiles || one) p.part_stride = part_rows(l, workspace_bytes - counter_bytes(l));
@@ -973,12 +973,14 @@ int kivi_decode_step(const kivi_layout_t* l, kivi_cache_t* c, const void* k_new,
         // longer than that kernel's own rows and a flush launch together.  Two heads: see wants_two_launches.)
         // One query head per kv-head: a flush of one tile, which is what every flushing step after the first has, rides in
         // the attention's only launch, and so does one value token (decode_one_kernel, which has both sides' figures).
+        // So does one tile in decode_tiles_kernel's single-launch form.
         const bool in_one = l->n_q_heads == l->n_kv_heads && l->decode_path != KIVI_DECODE_MFMA_TWO;
         const bool one_tile = l->group == kTileTokens && nk == kTileTokens && nv == kTileTokens && after.n_kq == after.n_vq;
+        const bool in_tiles = !in_one && one_tile && uses_tiles(l) && !wants_two_launches(l, &after, KIVI_DECODE_MFMA, true);
         const bool one_value = nk == 0 && nv == 1 && after.n_kq >= after.n_vq;
         if ((nk > 0 || nv > 0) &&
             (in_one ? one_tile || one_value
-                    : l->group == kTileTokens && l->n_q_heads <= 4 * l->n_kv_heads && wants_two_launches(l, &after, KIVI_DECODE_MFMA, true))) {
+                    : in_tiles || (l->group == kTileTokens && l->n_q_heads <= 4 * l->n_kv_heads && wants_two_launches(l, &after, KIVI_DECODE_MFMA, true)))) {
             const int64_t sh = (int64_t)l->cap_r_tokens * kHeadDim, sb = sh * l->n_kv_heads;
             const RowSource ksrc{static_cast<const __half*>(c->k_resid), sb, sh, kHeadDim, c->k_r_start, l->cap_r_tokens};
             const RowSource vsrc{static_cast<const __half*>(c->v_resid), sb, sh, kHeadDim, c->v_r_start, l->cap_r_tokens};

@@ -344,39 +344,7 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
     if constexpr (FLUSH) {
         if (flushes) {
             __builtin_amdgcn_s_setprio(3);             // (the longest chain of a short launch)
-            half2v x[kTileTokens];
-            tile::ValueRow y[8];
-            const int fk = p.k_r_start - kTileTokens, fv = p.v_r_start - kTileTokens;
-            const int k0 = fk < 0 ? fk + p.cap_r : fk, v0 = fv < 0 ? fv + p.cap_r : fv;
-            const char* kr = reinterpret_cast<const char*>(p.k_resid + unit * p.cap_r * kHeadDim);
-            const __half* vr = p.v_resid + unit * p.cap_r * kHeadDim + n * 8;
-#pragma unroll
-            for (int t = 0; t < kTileTokens; ++t) x[t] = *reinterpret_cast<const half2v*>(kr + (uint32_t)(ring_slot(k0, t, p.cap_r) * (kHeadDim * 2) + lane * 4));
-#pragma unroll
-            for (int i = 0; i < 8; ++i) y[i].v4 = *reinterpret_cast<const uint4v*>(vr + ring_slot(v0, kb * 8 + i, p.cap_r) * kHeadDim);
-            const int64_t at = tile0 + tiles;
-            uint32_t* kcodes = const_cast<uint32_t*>(p.k_codes) + at * (S::kCodeBytes / 4);
-            uint32_t* vcodes = const_cast<uint32_t*>(p.v_codes) + at * (S::kCodeBytes / 4);
-            uint32_t* lds = reinterpret_cast<uint32_t*>(ring);
-            _Float16* lds_scales = reinterpret_cast<_Float16*>(ring + 2 * S::kCodeBytes);      // k_scale, k_zero, v_scale, v_zero
-            auto put_pair = [&](const __half* array, int which, half2v v) {
-                *reinterpret_cast<half2v*>(const_cast<__half*>(array) + at * kHeadDim + 2 * lane) = v;
-                *reinterpret_cast<half2v*>(lds_scales + which * 128 + 2 * lane) = v;
-            };
-            tile::quantize_key_tile<BITS>(x, lane,
-                [&](half2v s2, half2v z2) {
-                    put_pair(p.k_scale, 0, s2);
-                    put_pair(p.k_zero, 1, z2);
-                },
-                [&](int i, uint32_t w) { kcodes[i] = lds[i] = w; });
-            tile::quantize_value_tile<BITS>(y, lane,
-                [&](int i, _Float16 s, _Float16 z) {
-                    reinterpret_cast<_Float16*>(const_cast<__half*>(p.v_scale))[at * 128 + i] = s;
-                    reinterpret_cast<_Float16*>(const_cast<__half*>(p.v_zero))[at * 128 + i] = z;
-                    lds_scales[256 + i] = s;
-                    lds_scales[384 + i] = z;
-                },
-                [&](int i, uint32_t w) { vcodes[i] = lds[S::kCodeBytes / 4 + i] = w; });
+            tile::flush_tile<BITS>(p, unit, tile0 + tiles, lane, ring, true);
             wave_lds_sync();
         }
     }

@@ -49,6 +49,12 @@
 // rows meet the fp32 probabilities in 16x16x4 fp32 products; packed parts go through a ring slot.  (Inside the pipelined workgroups that path cost 30 us:
 // its loads queue behind the copies in flight and its registers do not fit beside the loop's.)
 //
+// A step in which a tile leaves the window (K and V split alike, G = 32): the last wavefront of a unit's first row workgroup quantises it
+// out of the rings into the cache and a ring slot and attends to it there, the others take the rows.  (Of the units that
+// share a kv-head only the first stores it.)  Against a launch of its own before the attention (4.5-5 us), whole steps: 32 / 8
+// heads, batch 4, 32 767 tokens 35.3 -> 32.2 us; 71 / 1, batch 16, 4095 tokens 33.9 -> 30.3; 16 / 8, 32 / 8, 64 / 8 heads, batch 4, 2047
+// tokens 15.7 -> 13.6, 18.7 -> 15.9, 19.2 -> 16.5, 4 bits 16.0 -> 14.3, 15.8 -> 14.7, 19.2 -> 17.4.
+//
 // Work: every (batch, kv-head, run of query heads) unit has its steps (4 tiles, one per wavefront of a
 // workgroup) on an axis that is cut into one interval per resident workgroup (kivi_tiles_plan.h); a workgroup that
 // owns part of a unit leaves a part (m, l, o[128]) per head in the workspace, the last one merges.
@@ -61,6 +67,7 @@
 // output (there 1e-4: codes are placed high in the mantissa here, and the matrix unit aligns products by their nominal
 // exponent).
 #include "kivi_internal.h"
+#include "kivi_quantize_tile.h"
 #include "kivi_tiles_plan.h"
 
 #include <hip/hip_fp16.h>
@@ -141,15 +148,16 @@ __device__ __forceinline__ int table(const int32_t* base, int i) {
     return reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(base))[i];
 }
 
-// Asynchronous copy of 16 bytes per lane: lane l's bytes land at LDS offset lds + 16 l.  (m0 holds the offset; it is a reserved
+// Asynchronous copy of 16 bytes per lane: lane l's bytes land at LDS offset lds + 16 l.  (Five wait states between a vector
+// instruction that writes the scalar operand, a readlane out of a spill say, and this one: the compiler does not look into the block.  m0 holds the offset; it is a reserved
 // register, so the compiler warns that it will not keep a value in it across the statement: nor shall it.)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void copy_to_lds(const void* base, uint32_t lane_offset, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(lane_offset), "s"(base) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(lane_offset), "s"(base) : "memory", "m0");
 }
 __device__ __forceinline__ void copy_to_lds(const void* lane_ptr, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds), "v"(lane_ptr) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds), "v"(lane_ptr) : "memory", "m0");
 }
 #pragma clang diagnostic pop
 // Outputs (two channels at po, two 64 channels further) of the parts first, first + 1, ..., 0 past the last part: all
@@ -221,7 +229,8 @@ constexpr int max_parts_of(int bits, int hp) { return bits == 4 && hp == 8 ? kTi
 // kWhole: K and V split at the same token, so a tile is all quantised or all fp16; kMixed: any split.
 // kQuantisedRagged: the all-quantised tiles of a batch of sequences of different lengths (work cut by tables that
 // the host made); part 0 of every unit is what the fp16-row launch left.
-constexpr int kWhole = 0, kMixed = 1, kQuantisedRagged = 2;
+// kFlush: as kWhole, in a step in which a tile leaves the window (plan.tiles_a is without it, the first of the row workgroups' tiles).
+constexpr int kWhole = 0, kMixed = 1, kQuantisedRagged = 2, kFlush = 3;
 
 // HP: head slots of a unit (2, 4 or 8).  CS: G > 32 (scales stored once per group of G = 32 << kg_shift).
 template <int BITS, int HP, int MODE, bool CS>
@@ -1049,9 +1058,13 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
         }
     };
 
-    if constexpr (MODE == kWhole) {
+    if constexpr (MODE == kWhole || MODE == kFlush) {
         if (wg < 0) {                                  // ---- the fp16 rows of one unit (K and V split alike) ----
-            const int u = (int)blockIdx.x / p.row_split, tile0 = tiles_a_plan + (int)blockIdx.x % p.row_split * kWaves + wave;
+            constexpr int kFlushed = MODE == kFlush ? 1 : 0;
+            const int u = (int)blockIdx.x / p.row_split, cut = (int)blockIdx.x % p.row_split;
+            // kFlush: the first one's last wavefront quantises the tile that leaves the window and attends to it, the others have the rows
+            const bool flushes = kFlushed && cut == 0 && wave == kWaves - 1;
+            const int tile0 = flushes ? p.plan.tiles_total : tiles_a_plan + cut * kWaves + wave + (cut > 0 ? 0 : kFlushed);
             const int64_t unit = kv_unit(u);
             half8 raw[4], kr[2][4], vr[8];
             const int live = live_heads(u), last = p.length - 1;
@@ -1061,7 +1074,19 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
             for (int e = 0; e < 8; ++e) ro[e] = float4v{0.f, 0.f, 0.f, 0.f};
             mref = -INFINITY;
             l_lane = 0.f;
-            for (int tile = tile0; tile < p.plan.tiles_total; tile += kWaves * p.row_split) {
+            if constexpr (MODE == kFlush) {
+                if (flushes) {
+                    unsigned char* sl = &sm_ring[wave][0][0];
+                    tile::flush_tile<BITS>(p, unit, unit * p.cap_tiles + tiles_a_plan, lane, sl, u == kv_unit(u) * n_runs && p.q_head0 == 0);
+                    wave_lds_sync();
+#pragma unroll
+                    for (int cb = 0; cb < 4; ++cb) raw[cb] = *reinterpret_cast<const half8*>(src + cb * 32);
+                    reset_state();
+                    set_query(raw);
+                    quantised_tile(sl);
+                }
+            }
+            for (int tile = tile0; tile < p.plan.tiles_total; tile += kWaves * p.row_split - kFlushed) {
                 const int tt = tile * kTileTokens, tok = tok0 + (is_lo ? 16 : 0);
 #pragma unroll
                 for (int cb = 0; cb < 4; ++cb) raw[cb] = *reinterpret_cast<const half8*>(src + cb * 32);
@@ -1081,6 +1106,10 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
                 append_new_token(u, tile);
             }
             leave_unit(u, true, [&](int h0, float f) {
+                if (flushes) {
+                    write_acc(h0, f);
+                    return;
+                }
                 if (h0 == 0)
 #pragma unroll
                     for (int e = 0; e < 8; ++e) ro[e] *= f;
@@ -1235,7 +1264,9 @@ hipError_t launch_mode(DecodeParams p, hipStream_t stream) {
     }
     UniformCut cut;
     const bool two = p.two_launches > 0 && p.plan.tiles_total > p.plan.tiles_a && p.plan.tiles_a > 0;      // the fp16 rows in a launch of their own
-    if (!cut_uniform(units, p.plan.tiles_a, p.plan.tiles_total, resident_workgroups<BITS, HP, MODE, CS>(), p.part_stride, max_parts_of(BITS, HP), two, p.rows_for_tiles, cut))
+    // (kFlush: no further row workgroup for the flushed tile's sake -- one more part to merge: 32 units x 2047, 4 bits, 16.6 us with,
+    // 14.7 without)
+    if (!cut_uniform(units, p.plan.tiles_a, p.plan.tiles_total - (MODE == kFlush ? 1 : 0), resident_workgroups<BITS, HP, MODE, CS>(), p.part_stride, max_parts_of(BITS, HP), two, p.rows_for_tiles, cut))
         return hipErrorInvalidValue;
     p.row_split = cut.row_split;
     p.row_wgs = cut.row_wgs;
@@ -1266,7 +1297,14 @@ hipError_t launch_decode_tiles(DecodeParams p, hipStream_t stream) {
         if (hipError_t e = launch_residual_rows(p, stream); e != hipSuccess) return e;
         p.k_new = p.v_new = nullptr;
     }
-    if (p.flush_k && p.flush_v) {
+    const bool flush_inside = p.flush_k && p.flush_v && p.two_launches == 0;
+    if (flush_inside) {
+        // one tile, the last quantised one, out of the rings right before the window: the row workgroups' first
+        if (p.seq_state || p.kg_shift > 0 || p.n_kq != p.n_vq || p.n_kr < 1 || p.plan.tiles_a < 1 || p.flush_k->n_tiles != 1 || p.flush_v->n_tokens != kTileTokens ||
+            p.flush_k->first_tile != p.plan.tiles_a - 1 || p.flush_v->first_token != (p.plan.tiles_a - 1) * kTileTokens)
+            return hipErrorInvalidValue;
+        p.plan.tiles_a -= 1;
+    } else if (p.flush_k && p.flush_v) {
         // a step that flushes: one launch for the fp16 rows (which append the new token) and the tokens that leave the window
         if (p.seq_state || p.head_groups != 1 || p.two_launches == 0) return hipErrorInvalidValue;
         p.rows_for_tiles = 1;
@@ -1277,6 +1315,7 @@ hipError_t launch_decode_tiles(DecodeParams p, hipStream_t stream) {
         constexpr int B = decltype(b)::value, H = decltype(h)::value;
         const bool cs = p.kg_shift > 0;
         if (p.seq_state) e = cs ? hipErrorNotSupported : launch_mode<B, H, kQuantisedRagged, false>(p, stream);
+        else if (flush_inside) e = launch_mode<B, H, kFlush, false>(p, stream);
         else if (p.n_kq != p.n_vq) e = cs ? launch_mode<B, H, kMixed, true>(p, stream) : launch_mode<B, H, kMixed, false>(p, stream);
         else e = cs ? launch_mode<B, H, kWhole, true>(p, stream) : launch_mode<B, H, kWhole, false>(p, stream);
     });

@@ -6,8 +6,8 @@
 //
 // The value of a code is a bit contract: fp32 subtract, IEEE fp32 division, round-half-even, clamp (encode()).  The fast
 // path reaches the same code with one explicit fused multiply-add per element and falls back to encode() where a quotient
-// lies close enough to a rounding tie for the two to differ.  Files that include this are compiled with
-// -ffp-contract=off, so the only fused operations are the ones written as fmaf().
+// lies close enough to a rounding tie for the two to differ.  The only fused operations are the ones written as fmaf();
+// no other product is added to anything, but for the tolerance in group_const and sums of codes, which are exact.
 #pragma once
 
 #include "kivi_internal.h"
@@ -49,6 +49,7 @@ __device__ __forceinline__ uint32_t encode(float x, float z, float s, float leve
 struct GroupConst { float z, s, y, c0, tol; };
 
 __device__ __forceinline__ GroupConst group_const(float lo, float s) {
+#pragma clang fp contract(off)
     // y: the hardware reciprocal (1 ulp: relative error <= 2^-23), one instruction instead of a division
     const float y = s == 0.0f ? 0.0f : __builtin_amdgcn_rcpf(s);
     const float c0 = -lo * y;
@@ -354,6 +355,56 @@ __device__ __forceinline__ void quantize_value_tile(const ValueRow (&x)[8], int 
                 put_word((i >> 2) * 256 + (tl * 16 + r) * 4 + (i & 3), mine);
             }
         }
+}
+
+// The tile that leaves the window in a decoding step (K and V split alike, G = 32): the 32 tokens before the window, out of the rings
+// of `unit` into a slot in LDS (key codes, value codes, key scales, key zero-points, value scales, value zero-points) and, with
+// `store`, into tile `at` of the packed arrays.  One wavefront; wave_lds_sync() or the like has to follow.
+template <int BITS>
+__device__ __forceinline__ void flush_tile(const DecodeParams& p, int64_t unit, int64_t at, int lane, unsigned char* slot, bool store) {
+    constexpr int kCodeBytes = kTileTokens * kHeadDim * BITS / 8;
+    const int n = lane & 15, kb = lane >> 4;
+    half2v x[kTileTokens];
+    ValueRow y[8];
+    auto wrap = [&](int i) -> int { return i >= p.cap_r ? i - p.cap_r : i; };
+    const int fk = p.k_r_start - kTileTokens, fv = p.v_r_start - kTileTokens;
+    const int k0 = fk < 0 ? fk + p.cap_r : fk, v0 = fv < 0 ? fv + p.cap_r : fv;
+    const char* kr = reinterpret_cast<const char*>(p.k_resid + unit * p.cap_r * kHeadDim);
+    const __half* vr = p.v_resid + unit * p.cap_r * kHeadDim + n * 8;
+#pragma unroll
+    for (int t = 0; t < kTileTokens; ++t) x[t] = *reinterpret_cast<const half2v*>(kr + (uint32_t)(wrap(k0 + t) * (kHeadDim * 2) + lane * 4));
+#pragma unroll
+    for (int i = 0; i < 8; ++i) y[i].v4 = *reinterpret_cast<const uint4v*>(vr + wrap(v0 + kb * 8 + i) * kHeadDim);
+    uint32_t* kcodes = const_cast<uint32_t*>(p.k_codes) + at * (kCodeBytes / 4);
+    uint32_t* vcodes = const_cast<uint32_t*>(p.v_codes) + at * (kCodeBytes / 4);
+    uint32_t* lds = reinterpret_cast<uint32_t*>(slot);
+    _Float16* lds_scales = reinterpret_cast<_Float16*>(slot + 2 * kCodeBytes);
+    auto put_pair = [&](const __half* array, int which, half2v v) {
+        if (store) *reinterpret_cast<half2v*>(const_cast<__half*>(array) + at * kHeadDim + 2 * lane) = v;
+        *reinterpret_cast<half2v*>(lds_scales + which * 128 + 2 * lane) = v;
+    };
+    quantize_key_tile<BITS>(x, lane,
+        [&](half2v s2, half2v z2) {
+            put_pair(p.k_scale, 0, s2);
+            put_pair(p.k_zero, 1, z2);
+        },
+        [&](int i, uint32_t w) {
+            if (store) kcodes[i] = w;
+            lds[i] = w;
+        });
+    quantize_value_tile<BITS>(y, lane,
+        [&](int i, _Float16 s, _Float16 z) {
+            if (store) {
+                reinterpret_cast<_Float16*>(const_cast<__half*>(p.v_scale))[at * 128 + i] = s;
+                reinterpret_cast<_Float16*>(const_cast<__half*>(p.v_zero))[at * 128 + i] = z;
+            }
+            lds_scales[256 + i] = s;
+            lds_scales[384 + i] = z;
+        },
+        [&](int i, uint32_t w) {
+            if (store) vcodes[i] = w;
+            lds[kCodeBytes / 4 + i] = w;
+        });
 }
 
 }  // namespace tile

@@ -71,13 +71,13 @@ def test_one_head_uneven(heads, batch, bits, group, residual, tokens, steps, kga
     run_steps(heads, batch, bits, group, residual, tokens, steps, kgain, vgain, "alg1")
 
 
-def run_steps(heads, batch, bits, group, residual, tokens, steps, kgain, vgain, policy):
+def run_steps(heads, batch, bits, group, residual, tokens, steps, kgain, vgain, policy, rep=1):
     torch = gh.require_gpu()
     total = tokens + steps
     flush = kivi.KIVI_FLUSH_ALG1 if policy == "alg1" else kivi.KIVI_FLUSH_WINDOW
-    w = scaled(CONFIGS["llama7b"], name="onehead", batch=batch, n_q_heads=heads, n_kv_heads=heads, bits=bits, group=group,
+    w = scaled(CONFIGS["llama7b"], name="onehead", batch=batch, n_q_heads=heads * rep, n_kv_heads=heads, bits=bits, group=group,
                residual=residual, seed=17 * heads + bits + tokens)
-    print(f"case one head {policy} h={heads} b={batch} B={bits} G={group} R={residual} L={tokens}+{steps} gains {kgain} {vgain}", flush=True)
+    print(f"case one head {policy} h={heads}x{rep} b={batch} B={bits} G={group} R={residual} L={tokens}+{steps} gains {kgain} {vgain}", flush=True)
     k = (workloads.keys(w, total).astype(np.float32) * kgain).astype(np.float16)
     v = (workloads.values(w, total).astype(np.float32) * vgain).astype(np.float16)
     scale = float(np.abs(v.astype(np.float32)).max())
@@ -89,7 +89,7 @@ def run_steps(heads, batch, bits, group, residual, tokens, steps, kgain, vgain, 
         q = (workloads.queries(w, step).astype(np.float32) / max(1, kgain)).astype(np.float16)
         new = [np.ascontiguousarray(x[:, :, tokens + step]) for x in (k, v)]
         kn, vn, qt = [torch.from_numpy(x).cuda() for x in (*new, q)]
-        out = torch.full((batch, heads, 128), float("nan"), dtype=torch.float32, device="cuda")
+        out = torch.full((batch, heads * rep, 128), float("nan"), dtype=torch.float32, device="cuda")
         kivi.kivi_decode_step(layout, cache, kn, vn, qt, w.softmax_scale, out, flush)
         oc.append(np.stack([k[b, h, tokens + step] for b, h in at])[:, None], np.stack([v[b, h, tokens + step] for b, h in at])[:, None])
         ref = gh.oracle_attention_for_heads(w, oc, q, at)
