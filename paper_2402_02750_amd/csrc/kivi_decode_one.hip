@@ -21,10 +21,13 @@
 //
 // FLUSH (G = 32): the step in which the oldest 32 tokens leave the window takes this one launch too.  The last wavefront of a unit's
 // last workgroup quantises them out of the rings into the cache and into its own slot and attends to them there; the
-// others take its share of the rows and tiles meanwhile, the next item that nobody has (with fixed shares: 44.4 instead of 42.7 us
-// at 512 units x 4000, a fifth wavefront: two workgroups per compute unit instead of three).  Against a launch of its
-// own before the attention (4.5-5 us): 8 units x 512 tokens 13.6 -> 9.4 us, 256 x 4095 31.2 -> 25.6, 512 x 4095 49.0 -> 42.2; 4 bits, 256
-// x 4095 40.5 -> 34.3, 320 x 8191 78.3 -> 77.0.
+// others have the first items of rows and tiles to themselves meanwhile (kFlushLead).  The shares are fixed, so that a step repeats
+// itself bit by bit; with a counter that hands out items the order of the sums hung on timing (11 of 11 repetitions differed at 512
+// units).  Items follow each other without rounding to steps.  Counter -> fixed shares: 32 units x 4095 tokens 11.3 -> 10.7 us, 256
+// x 1023 13.7 -> 12.8, 512 x 1023 19.0 -> 18.4, 512 x 4095 41.8 -> 42.6, 2048 x 2175 99.6 -> 101.5; 4 bits 128 x 2047 16.2 -> 15.1, 320 x 8191
+// 77.5 -> 77.9.  (A fifth wavefront: two workgroups per compute unit instead of three.  The flushing wavefront's first item asked for
+// before the flush: no change.)  Against a launch of its own before the attention (4.5-5 us): 8 units x 512 tokens 13.5 -> 10.1 us,
+// 256 x 4095 31.2 -> 25.0, 512 x 4095 48.7 -> 42.6; 4 bits, 256 x 4095 40.5 -> 33.7, 320 x 8191 78.3 -> 77.9.
 //
 // UNEVEN (n_kq >= n_vq, Algorithm 1's policy): the tokens between have quantised keys and fp16 value rows.  An item of those is
 // MT tokens: their key tile's codes, scales and zero-points and their value rows fill a slot with the same NI copies (the key tile is
@@ -202,6 +205,11 @@ struct Shape {
     // what a flush weighs as a part's work: a step at 2 bits, two of half the tiles at 4 (320 units x 8191, 4 bits: 78.7 us with
     // one, 77.0 with two or three; 32 x 8191 at 2 bits: 24.4, 24.6, 25.2 us with one, two, three)
     static constexpr int kFlushSteps = 2 / PT;
+    // Items that each other wavefront of its workgroup takes before the flushing one takes its first: where all workgroups run at
+    // once, and where there are more than fit (the others of a compute unit use the time of a flush then).  2 bits, 256 units x 1023
+    // tokens 13.9 / 12.8 / 12.2 us with 4 / 5 / 6, 512 x 4095 43.2 / 42.6 / 43.1; 2048 x 1023 66.4 / 65.9 / 66.4 with 1 / 2 / 5; 4 bits, 256 x 4095 34.1 /
+    // 33.7 with 5 / 6, 320 x 8191 77.5 / 77.5 / 78.9 with 6 / 8 / 16.
+    static constexpr int kFlushLead = PT == 2 ? 5 : 6, kFlushLeadMany = PT == 2 ? 2 : 3;
     // a slot of a key tile's codes, its scales and zero-points, and MT tokens' fp16 value rows
     static constexpr int MT = 4 * (NI - kPlanes - 1), kMixedRows = kCodeBytes + 1024;
     // operands of a tile: key side hi (128 halves), 16 halves of skew, lo; value side 8 columns of 32 tokens
@@ -227,7 +235,6 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
     _Float16* operand = reinterpret_cast<_Float16*>(sm_query);
     float (*sm_ml)[2] = reinterpret_cast<float (*)[2]>(sm + WV * S::kWaveBytes);
     int& sm_last = *reinterpret_cast<int*>(sm + WV * S::kWaveBytes + WV * 8);
-    int& sm_next = *reinterpret_cast<int*>(sm + WV * S::kWaveBytes + WV * 8 + 4);
     const uint32_t ring_lds = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)ring);
 
     // ---- this workgroup's run of its unit's steps ----
@@ -245,12 +252,13 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
     const int s0 = min(axis.start(part), real), s1 = min(axis.start(part + 1), real);
     const int nr = (n_kr + S::kStepRows - 1) / S::kStepRows;
     const int a0 = max(s0 - nr, 0), len_a = max(s1 - nr, 0) - a0;
-    // An item is one wavefront's slot of a step.  A wavefront takes every WV-th, or -- a workgroup that flushes, whose last
-    // wavefront comes late -- the next one that nobody has.
-    // UNEVEN: all items one after the other: rows, MT tokens each whose keys only are quantised, tiles.
-    const int m0 = v_q & -MT, all_rows = (n_kr + NT - 1) / NT, all_fp16 = all_rows + (p.n_kq - m0) / MT;
-    const int n_items = UNEVEN ? min(s1 * WV, all_fp16 + (tiles + PT - 1) / PT) - s0 * WV : (s1 - s0) * WV;
-    const int n_row_items = UNEVEN ? min(max(all_rows - s0 * WV, 0), n_items) : min(max(nr - s0, 0), s1 - s0) * WV;
+    // An item is one wavefront's slot of a step.  A wavefront takes every WV-th; in a workgroup that flushes, whose last wavefront
+    // comes late, the others have the first `lead` items to themselves.  (The shares are fixed: sums in the same order every time.)
+    // FLAT: all items one after the other: rows, MT tokens each whose keys only are quantised (UNEVEN), tiles.
+    constexpr bool FLAT = UNEVEN || FLUSH;
+    const int m0 = v_q & -MT, all_rows = (n_kr + NT - 1) / NT, all_fp16 = all_rows + (UNEVEN ? (p.n_kq - m0) / MT : 0);
+    const int n_items = FLAT ? max(min(s1 * WV, all_fp16 + (tiles + PT - 1) / PT) - s0 * WV, 0) : (s1 - s0) * WV;
+    const int n_row_items = FLAT ? min(max(all_rows - s0 * WV, 0), n_items) : min(max(nr - s0, 0), s1 - s0) * WV;
     const int n_fp16_items = UNEVEN ? min(max(all_fp16 - s0 * WV, 0), n_items) : n_row_items;
     const int64_t unit = u;
 
@@ -312,11 +320,11 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
     if (lane < 16) copy_to_lds(p.q + unit * kHeadDim + n * 8, (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)sm_query));
     // Tiles in an order rotated by the unit: workgroups in lockstep that all read the same relative offset of their units
     // would meet on few memory channels for unlucky strides (a copy alone: 32.3 -> 29.8 us at 512 units).
-    const int turn = UNEVEN ? n_items - n_fp16_items : len_a, rot = turn > 0 ? (int)((uint32_t)(u * 5) % (uint32_t)turn) : 0;
+    const int turn = FLAT ? n_items - n_fp16_items : len_a, rot = turn > 0 ? (int)((uint32_t)(u * (FLUSH ? WV : 5)) % (uint32_t)turn) : 0;
     auto row_of = [&](int item) -> int { return (s0 + item / WV) * S::kStepRows + item % WV * NT; };      // first token in the window
     auto mixed_of = [&](int item) -> int { return m0 + (s0 * WV + item - all_rows) * MT; };                // first token
     auto tile_of = [&](int item) -> int {
-        if constexpr (UNEVEN) {
+        if constexpr (FLAT) {
             int a = item - n_fp16_items + rot;
             a -= a >= turn ? turn : 0;
             return (s0 * WV + n_fp16_items - all_fp16 + a) * PT;
@@ -330,14 +338,11 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
         else if (UNEVEN && item < n_fp16_items) copy_mixed(mixed_of(item), slot);
         else if (item < n_items) copy_tiles(tile_of(item), slot);
     };
-    const int starters = flush_here ? WV - 1 : WV;
-    int now = flushes ? n_items : wave, next = now + starters;
+    const int lead = flush_here ? (WV - 1) * (p.one_round ? S::kFlushLead : S::kFlushLeadMany) : 0;
+    auto after = [&](int item) -> int { return item + (item < lead ? WV - 1 : WV); };
+    int now = flushes ? n_items : wave, next = after(now);
     copy_item(now, 0);
     copy_item(next, 1);
-    if constexpr (FLUSH) {
-        if (tid == 0) sm_next = 2 * starters;
-        lds_barrier();
-    }
 
     // ---- the tokens that leave the window in this step: quantised out of the rings into the cache and into this
     // wavefront's slot, where it attends to them like to any tile ----
@@ -693,14 +698,6 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
     // 38.7 us); with more workgroups than fit at once the oldest ones' head start is what hides the others' starts (2048
     // units: 87 us as it is, 91 with falling priorities).
     const int quarter = p.one_round ? n_items >> 2 : 0x1fffffff;
-    // the item after `next`: asked for before an item's work is done, looked at after it
-    auto ask = [&]() -> int {
-        int v = next + WV;
-        if constexpr (FLUSH) {
-            if (lane == 0) v = __hip_atomic_fetch_add(&sm_next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-        return v;
-    };
     auto begin = [&]() {
         const int left = n_items - now;
         if (left > 3 * quarter) __builtin_amdgcn_s_setprio(3);
@@ -711,44 +708,42 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
         else wait_copies<0>();
     };
     int slot = 0;
-    auto end = [&](int asked) {
-        const int after = FLUSH ? __builtin_amdgcn_readfirstlane(asked) : asked;
-        copy_item(after, slot);
+    auto end = [&]() {
         now = next;
-        next = after;
+        next = after(next);
+        copy_item(next, slot);
         slot ^= 1;
     };
     if constexpr (FLUSH) {
         if (flushes) {
             quantised(std::integral_constant<int, 1>{}, ring, 1);
-            now = __builtin_amdgcn_readfirstlane(ask());
+            now = lead + wave;
             copy_item(now, 0);
-            next = __builtin_amdgcn_readfirstlane(ask());
+            next = after(now);
             copy_item(next, 1);
         }
     }
 #pragma unroll 1
     while (now < n_row_items) {
         begin();
-        const int asked = ask(), left = n_kr - row_of(now);
+        const int left = n_kr - row_of(now);
         if (left > 0) fp16_rows(ring + slot * S::kSlotBytes, left);
-        end(asked);
+        end();
     }
     if constexpr (UNEVEN) {
 #pragma unroll 1
         while (now < n_fp16_items) {
             begin();
-            const int asked = ask();
             mixed(ring + slot * S::kSlotBytes, mixed_of(now));
-            end(asked);
+            end();
         }
     }
 #pragma unroll 1
     while (now < n_items) {
         begin();
-        const int asked = ask(), live = UNEVEN ? v_q - tile_of(now) * kTileTokens : tiles - tile_of(now);
+        const int live = UNEVEN ? v_q - tile_of(now) * kTileTokens : tiles - tile_of(now);
         if (live > 0) quantised(std::integral_constant<int, PT>{}, ring + slot * S::kSlotBytes, live);
-        end(asked);
+        end();
     }
 
     // ---- merge the wavefronts (their rings are free) ----
@@ -892,10 +887,10 @@ hipError_t launch(DecodeParams p, hipStream_t stream) {
     static_assert(S::kLds <= 160 * 1024 / OCC / 1280 * 1280, "workgroups per compute unit (LDS is given out in pieces of 1280 bytes)");
     static_assert(NB == 2 && PT <= 2, "two items in flight; masked tiles of a slot");
     const int64_t units = (int64_t)p.batch * p.n_kv_heads;
-    int steps = (p.plan.tiles_a - FLUSH + S::kStepTiles - 1) / S::kStepTiles + (p.n_kr + S::kStepRows - 1) / S::kStepRows + (FLUSH ? S::kFlushSteps : 0);
-    if (UNEVEN) {
-        const int v_q = p.n_vq - p.flushed_values, m0 = v_q & -S::MT, tiles = (v_q + kTileTokens - 1) / kTileTokens;
-        steps = ((p.n_kr + S::NT - 1) / S::NT + (p.n_kq - m0) / S::MT + (tiles + PT - 1) / PT + WV - 1) / WV;
+    int steps = (p.plan.tiles_a + S::kStepTiles - 1) / S::kStepTiles + (p.n_kr + S::kStepRows - 1) / S::kStepRows;
+    if (UNEVEN || FLUSH) {
+        const int v_q = p.n_vq - (FLUSH ? kTileTokens : p.flushed_values), m0 = v_q & -S::MT, tiles = (v_q + kTileTokens - 1) / kTileTokens;
+        steps = ((p.n_kr + S::NT - 1) / S::NT + (UNEVEN ? (p.n_kq - m0) / S::MT : 0) + (tiles + PT - 1) / PT + WV - 1) / WV + (FLUSH ? S::kFlushSteps : 0);
     }
     const int cus = compute_units();
     const int w = one_head_parts(units, steps, cus, std::min(p.part_stride, kOneHeadMaxParts), BITS == 2 ? 8 : 12);

@@ -223,6 +223,47 @@ def test_run_twice_is_deterministic(path):
     assert np.array_equal(a, b)
 
 
+# (query heads, kv-heads, batch, bits, G, residual, policy, prompt tokens)
+STEP_CASES = [
+    (4, 4, 1, 2, 32, 32, kivi.KIVI_FLUSH_WINDOW, 1023),     # one query head per kv-head, a tile leaves the window; a few parts per unit
+    (32, 32, 4, 4, 32, 128, kivi.KIVI_FLUSH_WINDOW, 2047),
+    (32, 32, 16, 2, 32, 128, kivi.KIVI_FLUSH_WINDOW, 1023), # whole units
+    (32, 32, 32, 4, 32, 64, kivi.KIVI_FLUSH_WINDOW, 511),   # more units than fit at once
+    (8, 8, 2, 2, 64, 128, kivi.KIVI_FLUSH_ALG1, 4000),      # one value token leaves the window
+    (32, 32, 8, 4, 32, 64, kivi.KIVI_FLUSH_ALG1, 1001),
+    (32, 8, 4, 2, 32, 128, kivi.KIVI_FLUSH_WINDOW, 2047),   # grouped queries
+    (71, 1, 2, 2, 32, 128, kivi.KIVI_FLUSH_WINDOW, 1023),
+]
+
+
+@pytest.mark.parametrize("hq,hkv,batch,bits,group,residual,policy,tokens", STEP_CASES)
+def test_flushing_step_is_deterministic(hq, hkv, batch, bits, group, residual, policy, tokens):
+    """A whole decoding step that flushes, from equal states: the same bits every time, outputs and packed arrays."""
+    torch = gh.require_gpu()
+    print(f"case step twice {hq}/{hkv} b={batch} B={bits} G={group} R={residual} policy={policy} L={tokens}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(tokens + bits)
+    k, v = (torch.randn(batch, hkv, tokens + 1, 128, dtype=torch.float16, device="cuda", generator=gen) for _ in range(2))
+    q = torch.randn(batch, hq, 128, dtype=torch.float16, device="cuda", generator=gen)
+    new = [x[:, :, tokens].contiguous() for x in (k, v)]
+    layout = kivi.make_layout(batch, hq, hkv, bits, residual, gh.round_up(tokens + 1, 128), gh.round_up(residual + group, 32), group=group)
+    first = None
+    for _ in range(6):
+        cache = kivi.Cache(layout)
+        for buf in cache.buffers.values():
+            buf.zero_()
+        kivi.kivi_prefill(layout, k, v, tokens, cache, policy)
+        before = cache.c.n_vq
+        out = torch.empty(batch, hq, 128, dtype=torch.float32, device="cuda")
+        kivi.kivi_decode_step(layout, cache, *new, q, 128 ** -0.5, out, policy)
+        torch.cuda.synchronize()
+        assert cache.c.n_vq > before
+        got = [out] + list(cache.buffers.values())
+        if first is None:
+            first = [x.clone() for x in got]
+        else:
+            assert all(torch.equal(x, y) for x, y in zip(got, first))
+
+
 @pytest.mark.parametrize("path", PATHS, ids=PATH_IDS)
 @pytest.mark.parametrize("bits", [2, 4])
 def test_probability_accuracy_with_one_hot_values(path, bits):
