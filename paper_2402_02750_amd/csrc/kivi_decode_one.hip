@@ -11,8 +11,12 @@
 // inside an fp16 lane is the exact subnormal code * 4^r * 2^-24; the matrix instruction multiplies it with q_c s_c (keys) or
 // p_t s_t,g (values), split into fp16 hi + remainder in two matrix columns.  With one head 14 of 16 columns would be copies
 // if every lane made the eight elements of its own column.  Instead a lane makes two elements (two channels of the key
-// operand; one token, two groups of the value operand) with two or three packed instructions, and the columns are
+// operand; one token, two groups of the value operand) with six or seven instructions, and the columns are
 // filled through LDS; the value side's columns hold the four channel groups at once, so that a tile takes one operand.
+// Key operand: q_c s_c 4^-r is exact in fp32 and its remainder is magnified by 2^11, so that it keeps 22 bits also where hi is subnormal.
+// (Product and remainder in fp16, two packed instructions instead of six: launches 0.5 % shorter, but an error of 1.6e-4 of the output
+// instead of 4e-6 where one channel of the query is 2^16 times the others, and 1.2e-4 instead of 4e-6 with key scales of 2^-14.  All
+// factors smaller by 2^11, which saves one instruction: no faster, 1.2e-4 with key scales of 2^-14.)
 // Each lane's softmax work is one token (of 32, every token in two lanes), the one whose operand it makes.
 //
 // PT = 2 at 2 bits: the two tiles' chains (LDS, matrix unit, LDS, matrix unit: 0.9 us alone) overlap in one wavefront.  Three
@@ -75,8 +79,8 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kSlack = 4;                      // log2 headroom of the running softmax reference
 constexpr int kQueryExp = 8;                   // largest |q'| lies in [2^8, 2^9)
 constexpr uint32_t kKeyScaleLimit = 0x54005400u;       // two times fp16 64.0
-constexpr int kKeyScaleShift = 9;              // a slot with larger scales whose products pass kProductLimit takes s 2^-9
-constexpr uint32_t kProductLimit = 0x78007800u;        // two times fp16 2^15
+constexpr int kKeyScaleShift = 9;              // a slot with larger scales whose products pass kProductLimit takes q' 2^-9
+constexpr float kProductLimit = 32768.f;
 // Value side: p' = p 2^kProbExp, scales taken as s 2^-ks with s 2^-ks < 2^kValueTop; larger ones as they are while their
 // products with p' stay below kValueProductLimit; ks falls back when a slot's scales are 2^-kValueWindow of that
 template <int BITS> constexpr int kProbExp = BITS == 2 ? 8 : 11;
@@ -160,6 +164,16 @@ __device__ __forceinline__ void wait_copies() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// Products of two fp16 numbers with fp32 ones as x = hi + lo 2^-11: hi = fp16(x), and lo = fp16((x - hi) 2^11) keeps 11 bits more at any
+// magnitude of x.  a, b: the fp32 factors, a_up, b_up: 2^11 times those.
+constexpr float kLoMagnify = 2048.f, kLoShrink = 1.f / 2048.f;
+__device__ __forceinline__ void split_products(half2v s, float a, float b, float a_up, float b_up, half2v& hi, half2v& lo) {
+    // (fused operations with a zero, or with fp16 results: one mixed-precision instruction each)
+    hi = half2v{(_Float16)fmaf((float)s[0], a, 0.f), (_Float16)fmaf((float)s[1], b, 0.f)};
+    asm("" : "+v"(hi));                              // (or its upper half is made twice)
+    lo = half2v{(_Float16)fmaf((float)hi[0], -kLoMagnify, fmaf((float)s[0], a_up, 0.f)),
+                (_Float16)fmaf((float)hi[1], -kLoMagnify, fmaf((float)s[1], b_up, 0.f))};
+}
 __device__ __forceinline__ half2v pack_rtz(float a, float b) { return __builtin_bit_cast(half2v, __builtin_amdgcn_cvt_pkrtz(a, b)); }
 __device__ __forceinline__ half2v half2_of(uint32_t x) { return __builtin_bit_cast(half2v, x); }
 
@@ -377,8 +391,10 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
     else if (now < n_items) wait_copies<NI>();
     else if (!flushes) wait_copies<0>();               // (the rows of a flush have come after the query)
     asm volatile("" ::: "memory");
-    float c_code, c_zero;
-    half2v q_own, qk_own;
+    // c_own, c_other: factors of the key products of this lane's column and of its partner's (hi and lo, or lo and hi);
+    // qk, qk_up: this lane's two channels of q' over the codes' position factors, and 2^11 times those
+    float c_own, c_other, c_zero, qk[2], qk_up[2];
+    half2v q_own;
     const half8 q_row = *reinterpret_cast<const half8*>(sm_query + n * 16);
     {
         const half2v raw = *reinterpret_cast<const half2v*>(sm_query + lane * 4);
@@ -388,10 +404,16 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
         const _Float16 up1 = on ? (_Float16)__uint_as_float((uint32_t)(127 + ah) << 23) : (_Float16)0.f;
         const _Float16 up2 = (_Float16)__uint_as_float((uint32_t)(127 + a - ah) << 23);
         c_zero = p.softmax_scale * kLog2e * __uint_as_float((uint32_t)(127 - a) << 23);
-        c_code = c_zero * kKeyUnscale;
+        const float c_code = c_zero * kKeyUnscale;
+        c_own = is_lo ? c_code * kLoShrink : c_code;
+        c_other = is_lo ? c_code : c_code * kLoShrink;
         q_own = raw * half2v{up1, up1} * half2v{up2, up2};
-        const _Float16 pf = (_Float16)__uint_as_float((uint32_t)(127 - (BITS == 2 ? 2 * (lane & 3) : 4 * (lane & 1))) << 23);
-        qk_own = q_own * half2v{pf, pf};
+        const float f = on ? __uint_as_float((uint32_t)(127 + a - (BITS == 2 ? 2 * (lane & 3) : 4 * (lane & 1))) << 23) : 0.f;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            qk[i] = (float)raw[i] * f;
+            qk_up[i] = qk[i] * kLoMagnify;
+        }
     }
 
     auto rescale = [&](float f) {
@@ -466,28 +488,35 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
     // logits (log2) of this lane's token of N tiles; s_raw: their scales, top: the largest
     auto logits = [&](auto count, const auto& kw, const auto& s_raw, const auto& z, uint32_t top, auto& x) {
         constexpr int N = decltype(count)::value;
-        half2v s[N];
+        auto put_operands = [&](const uint32_t (&sr)[N], float f) {
 #pragma unroll
-        for (int t = 0; t < N; ++t) s[t] = half2_of(s_raw[t]);
-        float cx = c_code;
-        if (any_above(top, kKeyScaleLimit)) {
-            uint32_t a = 0;
+            for (int t = 0; t < N; ++t) {
+                half2v hi, lo;
+                split_products(half2_of(sr[t]), qk[0] * f, qk[1] * f, qk_up[0] * f, qk_up[1] * f, hi, lo);
+                _Float16* b = operand + t * S::kOperandHalves;
+                *reinterpret_cast<half2v*>(b + 2 * lane) = hi;
+                *reinterpret_cast<half2v*>(b + S::kKeyColumn + 2 * lane) = lo;
+            }
+        };
+        float f_own = c_own, f_other = c_other;
+        bool shift = false;
+        if (any_above(top, kKeyScaleLimit)) {          // (rare, and kept apart: nothing of it is to move into the ordinary path)
+            uint32_t sr[N];
+            float a = 0.f;
 #pragma unroll
-            for (int t = 0; t < N; ++t) a = max_pairs(a, __builtin_bit_cast(uint32_t, qk_own * s[t]) & 0x7FFF7FFFu);
-            if (any_above(a, kProductLimit)) {
-                const _Float16 f1 = (_Float16)(1.f / (1 << kKeyScaleShift));
-#pragma unroll
-                for (int t = 0; t < N; ++t) s[t] *= half2v{f1, f1};
-                cx = c_code * (float)(1 << kKeyScaleShift);
+            for (int t = 0; t < N; ++t) {
+                asm("" : "=v"(sr[t]) : "0"(s_raw[t]));
+                a = fmaxf(a, fmaxf(fabsf(qk[0] * (float)half2_of(sr[t])[0]), fabsf(qk[1] * (float)half2_of(sr[t])[1])));
+            }
+            shift = __any(a > kProductLimit);
+            if (shift) {
+                put_operands(sr, 1.f / (1 << kKeyScaleShift));
+                f_own *= (float)(1 << kKeyScaleShift);
+                f_other *= (float)(1 << kKeyScaleShift);
+                asm volatile("" ::: "memory");
             }
         }
-#pragma unroll
-        for (int t = 0; t < N; ++t) {
-            const half2v hi = qk_own * s[t], lo = __builtin_elementwise_fma(qk_own, s[t], -hi);
-            _Float16* b = operand + t * S::kOperandHalves;
-            *reinterpret_cast<half2v*>(b + 2 * lane) = hi;
-            *reinterpret_cast<half2v*>(b + S::kKeyColumn + 2 * lane) = lo;
-        }
+        if (!shift) put_operands(s_raw, 1.f);
         wave_lds_sync();
         half8 f[N][4];
 #pragma unroll
@@ -511,7 +540,7 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
 #pragma unroll
         for (int t = 0; t < N; ++t) {
             const float x0 = own_of(d[t][0]), x1 = own_of(d[t][1]);
-            x[t] = fmaf((is_lo ? x1 : x0) + dpp<kDppRor8>(is_lo ? x0 : x1), cx, zk[t]);
+            x[t] = fmaf(is_lo ? x1 : x0, f_own, fmaf(dpp<kDppRor8>(is_lo ? x0 : x1), f_other, zk[t]));
         }
     };
     // N tiles of a slot; live: those that are there (UNEVEN: tokens that are there)

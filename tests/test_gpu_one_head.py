@@ -31,6 +31,8 @@ CASES = [
     (2, 2, 4, 32, 64, 900, 2, 60, 500),         # large value scales
     (2, 2, 2, 32, 64, 900, 2, 1, 2.0 ** -13),   # value scales among fp16's subnormals
     (2, 2, 4, 32, 64, 900, 2, 2.0 ** -10, 1),   # small key scales
+    (2, 2, 2, 32, 64, 900, 2, 2.0 ** -12, 1),
+    (2, 2, 4, 64, 64, 900, 2, 2.0 ** -14, 1),   # ... next to fp16's subnormals
 ]
 
 
@@ -71,6 +73,55 @@ def test_one_head_uneven(heads, batch, bits, group, residual, tokens, steps, kga
     run_steps(heads, batch, bits, group, residual, tokens, steps, kgain, vgain, "alg1")
 
 
+
+# (bits, G, policy)
+FORMS = [(2, 32, "window"), (4, 32, "window"), (2, 64, "alg1"), (4, 32, "alg1"), (4, 128, "window")]
+
+
+@pytest.mark.parametrize("ratio,size", [(2.0 ** 12, 2.0 ** -8), (2.0 ** 16, 2.0 ** -8), (2.0 ** 18, 2.0 ** -8)])
+@pytest.mark.parametrize("bits,group,policy", FORMS)
+def test_one_head_query_outliers(bits, group, policy, ratio, size):
+    """A channel at which the query looks with `ratio` times the weight, and whose keys are smaller by as much, takes no bits
+    from the others.  Tolerance as in test_key_outliers (test_gpu_tiles.py): 2^-20 of the largest value."""
+    rng = np.random.default_rng(bits + group)
+    tokens = 1500
+    k = rng.standard_normal((1, 3, tokens, 128)) / size
+    q = rng.standard_normal((1, 3, 128)) * size
+    k[..., 5] /= ratio
+    q[..., 5] = np.sign(q[..., 5]) * size * ratio
+    check_outliers(bits, group, policy, k, rng.standard_normal((1, 3, tokens, 128)), q, 2.0 ** -20)
+
+
+@pytest.mark.parametrize("large,small", [(1000, 2.0 ** -5), (4000, 2.0 ** -3), (30000, 2.0 ** -3)])
+@pytest.mark.parametrize("bits,group,policy", FORMS)
+def test_one_head_key_outliers(bits, group, policy, large, small):
+    """A key channel 2^15 and more times larger than the others, at which the query hardly looks, takes no bits from them.
+    Tolerance as above."""
+    rng = np.random.default_rng(bits + group)
+    tokens = 1500
+    k = rng.standard_normal((1, 3, tokens, 128)) * small
+    k[..., 5] = rng.uniform(-1, 1, (1, 3, tokens)) * large
+    q = rng.standard_normal((1, 3, 128)) / small
+    q[..., 5] *= small / large
+    check_outliers(bits, group, policy, k, rng.standard_normal((1, 3, tokens, 128)), q, 2.0 ** -20)
+
+
+def check_outliers(bits, group, policy, k, v, q, bound):
+    """An attention call against the oracle; `bound` is in units of the largest value."""
+    gh.require_gpu()
+    k, v, q = (x.astype(np.float16) for x in (k, v, q))
+    heads = k.shape[1]
+    w = scaled(CONFIGS["llama7b"], name="oneoutliers", batch=1, n_q_heads=heads, n_kv_heads=heads, bits=bits, group=group, residual=128, seed=1)
+    print(f"case one head outliers B={bits} G={group} {policy}", flush=True)
+    at = [(0, h) for h in range(heads)]
+    ref = gh.oracle_attention_for_heads(w, gh.oracle_cache_for_heads(w, k, v, at, policy), q, at)
+    flush = kivi.KIVI_FLUSH_ALG1 if policy == "alg1" else kivi.KIVI_FLUSH_WINDOW
+    layout, cache = gh.gpu_prefill(w, k, v, flush, kivi.KIVI_DECODE_AUTO)
+    err = np.abs(gh.pick_heads(gh.gpu_attention(layout, cache, q, w.softmax_scale), w, at) - ref).max()
+    bound *= float(np.abs(v.astype(np.float32)).max())
+    assert err <= bound, f"{err:.3e} against {bound:.3e}"
+
+
 def run_steps(heads, batch, bits, group, residual, tokens, steps, kgain, vgain, policy, rep=1):
     torch = gh.require_gpu()
     total = tokens + steps
@@ -86,7 +137,7 @@ def run_steps(heads, batch, bits, group, residual, tokens, steps, kgain, vgain, 
     layout, cache = gh.gpu_prefill(w, k[:, :, :tokens], v[:, :, :tokens], flush, kivi.KIVI_DECODE_AUTO, extra_q_tokens=steps)
     _, other = gh.gpu_prefill(w, k[:, :, :tokens], v[:, :, :tokens], flush, kivi.KIVI_DECODE_VALU, extra_q_tokens=steps)
     for step in range(steps):
-        q = (workloads.queries(w, step).astype(np.float32) / max(1, kgain)).astype(np.float16)
+        q = (workloads.queries(w, step).astype(np.float32) / kgain).clip(-60000, 60000).astype(np.float16)     # logits of ordinary size
         new = [np.ascontiguousarray(x[:, :, tokens + step]) for x in (k, v)]
         kn, vn, qt = [torch.from_numpy(x).cuda() for x in (*new, q)]
         out = torch.full((batch, heads * rep, 128), float("nan"), dtype=torch.float32, device="cuda")
