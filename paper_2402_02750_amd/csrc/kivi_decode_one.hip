@@ -17,6 +17,8 @@
 // (Product and remainder in fp16, two packed instructions instead of six: launches 0.5 % shorter, but an error of 1.6e-4 of the output
 // instead of 4e-6 where one channel of the query is 2^16 times the others, and 1.2e-4 instead of 4e-6 with key scales of 2^-14.  All
 // factors smaller by 2^11, which saves one instruction: no faster, 1.2e-4 with key scales of 2^-14.)
+// Value operand the same way, p_t 4^-r in fp32.  (p_t as two fp16 numbers and products in fp16: as many instructions, but a channel group
+// whose values are 2^16 times smaller than another's had an error of 6e-4 (2 bits) and 4e-3 (4 bits) of its outputs.)
 // Each lane's softmax work is one token (of 32, every token in two lanes), the one whose operand it makes.
 //
 // PT = 2 at 2 bits: the two tiles' chains (LDS, matrix unit, LDS, matrix unit: 0.9 us alone) overlap in one wavefront.  Three
@@ -47,7 +49,7 @@
 // merge (3 us).  Whole steps, 2 bits, decode_mfma_kernel -> this one: 32 units x 3000 tokens 12.8 -> 9.5 us, 128 x 4000 22.8 ->
 // 16.2, 256 x 1000 22.7 -> 11.2, 256 x 4000 31.1 -> 24.7, 512 x 1000 23.7 -> 17.7, 512 x 4000 46.3 -> 39.6, 768 x 4000 69.6 -> 58.7,
 // 2048 x 2000 92.4 -> 86.0; 4 bits: 256 x 4000 40.7 -> 33.2, 320 x 8000 75.5 -> 72.6, 1024 x 4000 112.3 -> 111.3.
-// Error against 64 bits: 3e-6 to 1.2e-5 of the output (decode_mfma_kernel 5e-5 to 2.5e-4).
+// Error against 64 bits: 7e-7 to 5e-6 of the output (decode_mfma_kernel 2e-5 to 2.5e-4).
 #include "kivi_internal.h"
 #include "kivi_quantize_tile.h"
 #include "kivi_tiles_plan.h"
@@ -174,7 +176,6 @@ __device__ __forceinline__ void split_products(half2v s, float a, float b, float
     lo = half2v{(_Float16)fmaf((float)hi[0], -kLoMagnify, fmaf((float)s[0], a_up, 0.f)),
                 (_Float16)fmaf((float)hi[1], -kLoMagnify, fmaf((float)s[1], b_up, 0.f))};
 }
-__device__ __forceinline__ half2v pack_rtz(float a, float b) { return __builtin_bit_cast(half2v, __builtin_amdgcn_cvt_pkrtz(a, b)); }
 __device__ __forceinline__ half2v half2_of(uint32_t x) { return __builtin_bit_cast(half2v, x); }
 
 // Code fragments of tile coordinate u = 2 pair + odd: codes as high in the mantissa as they go (keys at bits 2, 4, 6, 8 or 2, 6;
@@ -588,20 +589,12 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
             for (int t = 0; t < N; ++t) m = fmaxf(m, pv[t] * fmaxf((float)half2_of(v_raw[t])[0], (float)half2_of(v_raw[t])[1]));
             return m;
         });
-        _Float16 k1 = (_Float16)1.f, k2 = (_Float16)1.f;
-        if (ks != 0) {          // 2^-ks as two factors: each is a normal fp16 number for every ks in [-24, 16]
-            k1 = (_Float16)__uint_as_float((uint32_t)(127 - ks / 2) << 23);
-            k2 = (_Float16)__uint_as_float((uint32_t)(127 - ks + ks / 2) << 23);
-#pragma unroll
-            for (int t = 0; t < N; ++t) v_raw[t] = __builtin_bit_cast(uint32_t, half2_of(v_raw[t]) * half2v{k1, k1} * half2v{k2, k2});
-        }
+        const float pk = __uint_as_float((uint32_t)(127 - ks) << 23), pk_up = pk * kLoMagnify;
 #pragma unroll
         for (int t = 0; t < N; ++t) {
-            const half2v ph = pack_rtz(pv[t], pv[t]);
-            float rest;
-            asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(rest) : "v"(ph), "v"(pv[t]));
-            const half2v pl = pack_rtz(rest, rest), sv = half2_of(v_raw[t]);
-            const half2v hi = ph * sv, lo = __builtin_elementwise_fma(pl, sv, __builtin_elementwise_fma(ph, sv, -hi));
+            half2v hi, lo;
+            const float ps = pv[t] * pk, ps_up = pv[t] * pk_up;
+            split_products(half2_of(v_raw[t]), ps, ps, ps_up, ps_up, hi, lo);
             z_own[0] = fmaf(pv[t], (float)vz[t][0], z_own[0]);
             z_own[1] = fmaf(pv[t], (float)vz[t][1], z_own[1]);
             _Float16* col = operand + t * S::kOperandHalves + own_pair * 4 * 32 + own_tok;         // columns (group, hi / lo)
@@ -797,7 +790,7 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
         for (int u8 = 0; u8 < 8; ++u8) {
             float4v o;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = fmaf(acc[u8][i] + dpp<kDppRor8>(acc[u8][i]), up, zo[(u8 >> 1) & 1]);
+            for (int i = 0; i < 4; ++i) o[i] = fmaf(fmaf(dpp<kDppRor8>(acc[u8][i]), kLoShrink, acc[u8][i]), up, zo[(u8 >> 1) & 1]);     // (of use in the lanes of hi)
             if (n < 4 && my_group == u8 >> 1) *reinterpret_cast<float4v*>(&o_wave[u8 * 16 + kb * 4]) = o;
         }
         if (n_fp16_items > 0) {

@@ -106,8 +106,36 @@ def test_one_head_key_outliers(bits, group, policy, large, small):
     check_outliers(bits, group, policy, k, rng.standard_normal((1, 3, tokens, 128)), q, 2.0 ** -20)
 
 
-def check_outliers(bits, group, policy, k, v, q, bound):
-    """An attention call against the oracle; `bound` is in units of the largest value."""
+@pytest.mark.parametrize("ratio", [2.0 ** 12, 2.0 ** 16, 2.0 ** 18])
+@pytest.mark.parametrize("bits,group,policy", [f for f in FORMS if f[1] < 128])
+def test_one_head_value_groups(bits, group, policy, ratio):
+    """A channel group whose values are `ratio` times smaller than the others' keeps its bits: the bound, as in test_value_outliers
+    (test_gpu_tiles.py) 2^-20 of the largest value, holds for every group with its own largest value."""
+    rng = np.random.default_rng(bits + group)
+    k, v = (rng.standard_normal((1, 3, 1500, 128)) for _ in range(2))
+    v *= 64
+    v[..., :group] /= ratio
+    check_outliers(bits, group, policy, k, v, rng.standard_normal((1, 3, 128)), 2.0 ** -20)
+
+
+@pytest.mark.parametrize("outlier,size,every", [(40000, 2.0 ** -4, 5000), (1000, 2.0 ** -8, 5000), (40000, 2.0 ** -4, 32), (1000, 2.0 ** -8, 320)])
+@pytest.mark.parametrize("bits,group,policy", FORMS)
+def test_one_head_value_outliers(bits, group, policy, outlier, size, every):
+    """Tokens with very large values and no probability take no bits from the others: 2^-20 of the largest ordinary value."""
+    rng = np.random.default_rng(bits + group)
+    tokens = 1500
+    k, v = (rng.standard_normal((1, 3, tokens, 128)) for _ in range(2))
+    q = np.repeat(rng.standard_normal((1, 1, 128)) * 0.3, 3, axis=1)
+    v *= size
+    ordinary = float(np.abs(v).max())
+    for t in range(7, tokens - 128, every):
+        k[:, :, t] = -40 * np.sign(q[0, 0])
+        v[:, :, t] = outlier * np.sign(v[:, :, t])
+    check_outliers(bits, group, policy, k, v, q, 2.0 ** -20, ordinary)
+
+
+def check_outliers(bits, group, policy, k, v, q, bound, largest=None):
+    """An attention call against the oracle; `bound` is in units of `largest`, by default of every channel group's largest value."""
     gh.require_gpu()
     k, v, q = (x.astype(np.float16) for x in (k, v, q))
     heads = k.shape[1]
@@ -117,9 +145,10 @@ def check_outliers(bits, group, policy, k, v, q, bound):
     ref = gh.oracle_attention_for_heads(w, gh.oracle_cache_for_heads(w, k, v, at, policy), q, at)
     flush = kivi.KIVI_FLUSH_ALG1 if policy == "alg1" else kivi.KIVI_FLUSH_WINDOW
     layout, cache = gh.gpu_prefill(w, k, v, flush, kivi.KIVI_DECODE_AUTO)
-    err = np.abs(gh.pick_heads(gh.gpu_attention(layout, cache, q, w.softmax_scale), w, at) - ref).max()
-    bound *= float(np.abs(v.astype(np.float32)).max())
-    assert err <= bound, f"{err:.3e} against {bound:.3e}"
+    err = np.abs(gh.pick_heads(gh.gpu_attention(layout, cache, q, w.softmax_scale), w, at) - ref)
+    err = err.reshape(-1, 128 // group, group).max((0, 2))
+    bounds = bound * (np.abs(v.astype(np.float32)).reshape(-1, 128 // group, group).max((0, 2)) if largest is None else largest)
+    assert (err <= bounds).all(), f"{err} against {bounds}"
 
 
 def run_steps(heads, batch, bits, group, residual, tokens, steps, kgain, vgain, policy, rep=1):
