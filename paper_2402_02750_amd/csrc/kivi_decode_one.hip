@@ -401,14 +401,12 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
         const half2v raw = *reinterpret_cast<const half2v*>(sm_query + lane * 4);
         const float mx = wave_max(fmaxf(fabsf((float)raw[0]), fabsf((float)raw[1])));
         const bool on = mx > 0.f;
-        const int a = on ? min(kQueryExp + 127 - (int)(__float_as_uint(mx) >> 23), 28) : 0, ah = a / 2;
-        const _Float16 up1 = on ? (_Float16)__uint_as_float((uint32_t)(127 + ah) << 23) : (_Float16)0.f;
-        const _Float16 up2 = (_Float16)__uint_as_float((uint32_t)(127 + a - ah) << 23);
-        c_zero = p.softmax_scale * kLog2e * __uint_as_float((uint32_t)(127 - a) << 23);
-        const float c_code = c_zero * kKeyUnscale;
+        const int a = on ? min(kQueryExp + 127 - (int)(__float_as_uint(mx) >> 23), 28) : 0;
+        c_zero = p.softmax_scale * kLog2e;
+        const float c_code = c_zero * kKeyUnscale * __uint_as_float((uint32_t)(127 - a) << 23);
         c_own = is_lo ? c_code * kLoShrink : c_code;
         c_other = is_lo ? c_code : c_code * kLoShrink;
-        q_own = raw * half2v{up1, up1} * half2v{up2, up2};
+        q_own = raw;                                   // (zero-points meet the query as it is: exact products, sums in fp32)
         const float f = on ? __uint_as_float((uint32_t)(127 + a - (BITS == 2 ? 2 * (lane & 3) : 4 * (lane & 1))) << 23) : 0.f;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {

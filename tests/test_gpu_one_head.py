@@ -78,7 +78,7 @@ def test_one_head_uneven(heads, batch, bits, group, residual, tokens, steps, kga
 FORMS = [(2, 32, "window"), (4, 32, "window"), (2, 64, "alg1"), (4, 32, "alg1"), (4, 128, "window")]
 
 
-@pytest.mark.parametrize("ratio,size", [(2.0 ** 12, 2.0 ** -8), (2.0 ** 16, 2.0 ** -8), (2.0 ** 18, 2.0 ** -8)])
+@pytest.mark.parametrize("ratio,size", [(2.0 ** 12, 2.0 ** -8), (2.0 ** 16, 2.0 ** -8), (2.0 ** 18, 2.0 ** -8), (2.0 ** 23, 2.0 ** -8)])
 @pytest.mark.parametrize("bits,group,policy", FORMS)
 def test_one_head_query_outliers(bits, group, policy, ratio, size):
     """A channel at which the query looks with `ratio` times the weight, and whose keys are smaller by as much, takes no bits
