@@ -155,7 +155,9 @@ inline bool cut_uniform(int64_t units, int tiles_a, int tiles_total, int residen
 // leave compute units with fewer workgroups than others -- are faster (2 bits, best number / one per compute unit: 32 units x
 // 32 000 tokens 23 / 25 us, 64 x 32 000 39 / 42, 192 x 16 000 57 / 76, 320 x 8000 53 / 59; but 256 x 1000 11.2 against 13.1).
 // A few more units than fit at once: halves, if they are long, so that the last ones do not run alone for as long (800 units x 4000
-// tokens, 4 bits, 101 -> 96 us, 2 bits 70 -> 69; 2000 tokens 41.6 -> 45.8).
+// tokens, 4 bits, 101 -> 96 us, 2 bits 70 -> 69; 2000 tokens 41.6 -> 45.8).  With more units beside them the last ones are alone for
+// less long, and the line moves to longer units (896 units, whole / halves: 4 bits, 4127 tokens 118.0 / 113.3 us, 3000
+// tokens 82.0 / 84.0; 2 bits 80.9 / 79.4 and 59.5 / 61.3), until whole units are the faster ones (960 units x 4000 tokens, 4 bits 107.1 / 111.1).
 constexpr int kOneHeadMaxParts = 128;
 inline int one_head_parts(int64_t units, int steps, int compute_units, int room, int many) {
     const int64_t cus = compute_units;
@@ -163,7 +165,8 @@ inline int one_head_parts(int64_t units, int steps, int compute_units, int room,
     if (steps > many * w) {
         w = std::max<int64_t>(1, 2 * cus / units);
         if (units * w * 16 < 2 * cus * 15) w = std::max<int64_t>(1, 3 * cus / units);
-        if (units > 3 * cus && units * 8 <= 27 * cus && steps > 2 * many) w = 2;
+        const bool halves = units * 8 <= 27 * cus ? steps > 2 * many : units * 2 <= 7 * cus && steps * 4 > 9 * many;
+        if (units > 3 * cus && halves) w = 2;
     }
     return (int)std::max<int64_t>(1, std::min({w, (int64_t)steps, (int64_t)room}));
 }

@@ -32,7 +32,7 @@ static int check(int64_t units, int items, int flush, int cus, int room, int man
     return done == items ? 0 : 6;
 }
 extern "C" int check_all(int items_max, int flush, int many, int* at) {
-    const int units[] = {1, 2, 3, 8, 31, 32, 85, 86, 128, 255, 256, 257, 320, 512, 767, 768, 769, 800, 864, 865, 2048};
+    const int units[] = {1, 2, 3, 8, 31, 32, 85, 86, 128, 255, 256, 257, 320, 512, 767, 768, 769, 800, 864, 865, 896, 897, 2048};
     const int rooms[] = {1, 2, 3, 8, 31, 128};
     for (int items = flush ? 0 : 1; items <= items_max; ++items)
         for (int u : units)
