@@ -138,10 +138,11 @@ int kivi_cache_sizes(const kivi_layout_t* layout, kivi_cache_sizes_t* sizes);
 typedef struct kivi_decode_plan {
     int32_t family;             /* KIVI_DECODE_VALU or KIVI_DECODE_MFMA                              */
     int32_t launches;           /* kernel launches of one attention call (a decoding step's flush is */
-                                /* not counted, see kivi_decode_step); with one query head per      */
-                                /* kv-head and n_kq >= n_vq, the most it takes                      */
-    int32_t splits_quantised;   /* pieces of the all-quantised token range per (batch, kv-head); with */
-                                /* 3 or more query heads per kv-head a launch may cut finer         */
+                                /* not counted, see kivi_decode_step)                               */
+    int32_t splits_quantised;   /* pieces of the all-quantised token range per (batch, kv-head); they */
+                                /* and splits_fp16 give the workspace that the call needs.  A launch */
+                                /* may cut otherwise with one query head per kv-head and n_kq >= n_vq, */
+                                /* and finer with 3 or more heads                                   */
     int32_t splits_fp16;        /* pieces of the range that holds fp16 rows                         */
     int32_t tiles_per_split_quantised, tiles_per_split_fp16;   /* in 32-token tiles                */
     int32_t units_per_kv_head;  /* 1; 2 or 4 when the query heads of every kv-head are served as    */

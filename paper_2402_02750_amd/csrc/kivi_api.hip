@@ -251,8 +251,9 @@ int decode_family(const kivi_layout_t* l) {
 //  (0) Two heads: a flush has to end before the launch that reads its tiles, so the single-launch form takes
 //      two launches as well, the first of them nearly empty.  Riding with the fp16 rows it costs nothing of its own.
 //      Not while decode_tiles_kernel serves them well (8 units, 1055 tokens, 4 bits: 13.7 / 17.2 us; 64 units 17.1 / 17.7;
-//      even at 128; 256 units, 4095 tokens 40.7 / 35.7).  (One head: decode_one_kernel, a single launch whatever this says
-//      unless the caller asks for two.)
+//      even at 128; 256 units, 4095 tokens 40.7 / 35.7).
+// One head: decode_one_kernel, a single launch unless the caller asks for two (one_launch); (1) and (2) only decide the plan's
+// pieces, and with them the workspace that the call asks for.
 bool wants_two_launches(const kivi_layout_t* l, const kivi_cache_t* c, int path, bool flush = false) {
     if (path != KIVI_DECODE_MFMA || l->decode_path == KIVI_DECODE_MFMA_ONE) return false;
     const int rep_launch = std::min(l->n_q_heads / l->n_kv_heads, kMaxRep);
@@ -324,9 +325,16 @@ bool rows_launch_for_uneven_split(const kivi_layout_t* l, const kivi_cache_t* c,
            ceil_div(c->n_kq + c->n_kr, kTileTokens) > 20;
 }
 
+// One query head per kv-head and no value token quantised before its key: decode_one_kernel, a single launch (unless the caller
+// asks for two), whatever wants_two_launches says; the plan's pieces are its need of workspace then.
+bool one_launch(const kivi_layout_t* l, const kivi_cache_t* c, int path) {
+    return path == KIVI_DECODE_MFMA && l->decode_path != KIVI_DECODE_MFMA_TWO && l->n_q_heads == l->n_kv_heads && c->n_kq >= c->n_vq;
+}
+
 // Launches of one attention call: a group wider than kMaxRep heads takes one pass per kMaxRep heads, except in the
 // matrix-core family's single-launch form, where the runs are units of one launch.
 int attention_launches(const kivi_layout_t* l, const kivi_cache_t* c, int path, bool two_launches) {
+    if (one_launch(l, c, path)) return 1;
     if (rows_launch_for_uneven_split(l, c, path)) return 2;
     const int passes = wide_group_runs(l, path, two_launches) > 1 ? 1 : ceil_div(l->n_q_heads / l->n_kv_heads, kMaxRep);
     return path == KIVI_DECODE_MFMA ? (two_launches ? 2 : 1) * passes : passes + 1;      // vector-ALU family: decodes + merge
@@ -341,8 +349,8 @@ int part_rows(const kivi_layout_t* l, size_t bytes) {
 
 // Launch the attention of q over cache state `c` (already validated).  k_new / v_new non-null: the
 // rows of token length-1 are not in the rings yet and the (matrix-core) kernel puts them there.
-// flush_k / flush_v non-null (two-launch form, decode_tiles_kernel, or one query head per kv-head): the residual flush that produced state `c` has
-// not been launched yet; the fp16-row launch carries it out with extra workgroups.
+// flush_k / flush_v non-null (two-launch form, decode_tiles_kernel, or one query head per kv-head): the residual flush that produced
+// state `c` has not been launched yet.  A single launch quantises the tokens itself, of two the first with extra workgroups.
 int enqueue_attention(const kivi_layout_t* l, const kivi_cache_t* c, const void* q, float softmax_scale,
                       float* out, void* workspace, size_t workspace_bytes, const void* k_new, const void* v_new,
                       void* stream, const QuantKeyParams* flush_k = nullptr, const QuantValueParams* flush_v = nullptr) {
@@ -371,8 +379,7 @@ int enqueue_attention(const kivi_layout_t* l, const kivi_cache_t* c, const void*
     p.plan = plan_splits(l, c, path == KIVI_DECODE_MFMA, two);
     p.two_launches = two ? 1 : 0;
     p.head_groups = wide_group_runs(l, path, two);
-    // One query head per kv-head: a single launch whatever the plan, which its workspace rows always fit.
-    const bool one = path == KIVI_DECODE_MFMA && l->decode_path != KIVI_DECODE_MFMA_TWO && l->n_q_heads == l->n_kv_heads && c->n_kq >= c->n_vq;
+    const bool one = one_launch(l, c, path);
     const bool tiles = path == KIVI_DECODE_MFMA && uses_tiles(l) && !(two && flush_k && l->n_q_heads <= 2 * l->n_kv_heads);
     if ((flush_k || flush_v) && !one && !((two || tiles) && flush_k && flush_v)) return KIVI_ERR_INVALID_ARG;
     p.flush_k = flush_k;
@@ -974,10 +981,10 @@ int kivi_decode_step(const kivi_layout_t* l, kivi_cache_t* c, const void* k_new,
         // One query head per kv-head: a flush of one tile, which is what every flushing step after the first has, rides in
         // the attention's only launch, and so does one value token (decode_one_kernel, which has both sides' figures).
         // So does one tile in decode_tiles_kernel's single-launch form.
-        const bool in_one = l->n_q_heads == l->n_kv_heads && l->decode_path != KIVI_DECODE_MFMA_TWO;
+        const bool in_one = one_launch(l, &after, KIVI_DECODE_MFMA);
         const bool one_tile = l->group == kTileTokens && nk == kTileTokens && nv == kTileTokens && after.n_kq == after.n_vq;
         const bool in_tiles = !in_one && one_tile && uses_tiles(l) && !wants_two_launches(l, &after, KIVI_DECODE_MFMA, true);
-        const bool one_value = nk == 0 && nv == 1 && after.n_kq >= after.n_vq;
+        const bool one_value = nk == 0 && nv == 1;
         if ((nk > 0 || nv > 0) &&
             (in_one ? one_tile || one_value
                     : in_tiles || (l->group == kTileTokens && l->n_q_heads <= 4 * l->n_kv_heads && wants_two_launches(l, &after, KIVI_DECODE_MFMA, true)))) {

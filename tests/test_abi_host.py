@@ -229,10 +229,17 @@ def test_decode_plan(lib):
     p = plan(16, 32, 32, 2, 3968, 128)
     assert (p.family, p.launches) == (kivi.KIVI_DECODE_MFMA, 1)
     assert (p.splits_quantised, p.tiles_per_split_quantised, p.splits_fp16, p.tiles_per_split_fp16) == (8, 16, 1, 4)
-    # four units per workgroup: fp16 rows in a launch of their own, one part per unit
-    p = plan(64, 32, 32, 2, 1920, 150)
+    # four units per workgroup, two heads: fp16 rows in a launch of their own, one part per unit
+    p = plan(64, 64, 32, 2, 1920, 150)
     assert (p.family, p.launches, p.splits_fp16, p.tiles_per_split_fp16) == (kivi.KIVI_DECODE_MFMA, 2, 1, 5)
-    assert plan(64, 32, 32, 2, 1920, 150, path=kivi.KIVI_DECODE_MFMA_ONE).launches == 1
+    assert plan(64, 64, 32, 2, 1920, 150, path=kivi.KIVI_DECODE_MFMA_ONE).launches == 1
+    # one head: a single launch at any size (320 units at 4 bits x 8192, 2048 units x 2048, ...) unless two are asked for; the pieces,
+    # which give the workspace, are still those of two
+    for shape in ((64, 32, 32, 2, 1920, 150), (8, 40, 40, 4, 8064, 128), (64, 32, 32, 2, 1920, 128), (48, 8, 8, 2, 3968, 128)):
+        assert plan(*shape).launches == 1
+        assert plan(*shape, path=kivi.KIVI_DECODE_MFMA_TWO).launches == 2
+    p = plan(64, 32, 32, 2, 1920, 150)
+    assert (p.splits_fp16, p.tiles_per_split_fp16) == (1, 5)
     assert plan(16, 32, 32, 2, 3968, 128, path=kivi.KIVI_DECODE_MFMA_TWO).launches == 2
     # 6 or 8 query heads per kv-head and few chunks per workgroup: the halves of every group as units of their own
     assert plan(1, 64, 8, 2, 3968, 128).units_per_kv_head == 4      # 8 units x 12 chunks, 2 bits: quarters
@@ -261,11 +268,11 @@ def test_decode_plan(lib):
     assert plan(32, 64, 8, 2, 4064, 32).launches == 1        # a single tile of fp16 rows
     assert plan(8, 32, 8, 2, 3968, 128).launches == 1        # 2-bit, 4 heads: 64 units x 128 tiles is little work
     assert plan(48, 32, 8, 2, 3968, 128).launches == 2
-    # 1 head per kv-head: only by units per workgroup -- more than one, or between a half and one
+    # 2 heads per kv-head: only by units per workgroup -- more than one, or between a half and one
     # (workgroups straddle two units) in a launch long enough to carry a second one
-    assert plan(32, 8, 8, 2, 3968, 128).launches == 1        # 256 units: two workgroups per unit
-    assert plan(48, 8, 8, 2, 3968, 128).launches == 2        # 384 units x 128 tiles
-    assert plan(48, 8, 8, 2, 992, 128).launches == 1         # 384 units x 35 tiles: too short
+    assert plan(32, 16, 8, 2, 3968, 128).launches == 1       # 256 units: two workgroups per unit
+    assert plan(48, 16, 8, 2, 3968, 128).launches == 2       # 384 units x 128 tiles
+    assert plan(48, 16, 8, 2, 992, 128).launches == 1        # 384 units x 35 tiles: too short
     assert plan(2, 64, 8, 2, 4096, 128).launches == 1
     # vector-ALU family: decode + merge
     p = plan(16, 32, 32, 2, 3968, 128, path=kivi.KIVI_DECODE_VALU)
@@ -297,6 +304,12 @@ def test_decode_launches_ragged(lib):
     # 16 query heads per kv-head: two groups of 8, a pair of launches each
     l16 = kivi.make_layout(4, 32, 2, 2, 128, 4096, 192)
     assert kivi.kivi_decode_launches_ragged(l16, st) == 4
+    # K and V split differently, one head: a launch per run of equal states, whatever its size
+    l1 = kivi.make_layout(96, 32, 32, 2, 128, 4096, 192)
+    st1 = kivi.make_states(96)
+    for b in range(96):
+        st1[b] = kivi.kivi_seq_state_t(2048, 2048, 0, 130, 0, 130) if b < 95 else kivi.kivi_seq_state_t(128, 100, 0, 10, 0, 38)
+    assert kivi.kivi_decode_launches_ragged(l1, st1) == 2
     # an empty slot, or K and V split differently (Algorithm 1's policy): run by run
     st[0] = kivi.kivi_seq_state_t()
     assert kivi.kivi_decode_launches_ragged(l, st) >= 3
