@@ -58,6 +58,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 namespace kivi {
 namespace {
@@ -216,7 +217,6 @@ struct Shape {
     static constexpr int kPlanes = BITS / 2;
     static constexpr int NI = PT * (2 * kPlanes + 1);          // copy instructions per slot
     static constexpr int NT = 2 * NI;                          // tokens whose fp16 rows (K and V) fill a slot
-    static constexpr int kStepTiles = WV * PT, kStepRows = WV * NT;
     // what a flush weighs as a part's work: a step at 2 bits, two of half the tiles at 4 (320 units x 8191, 4 bits: 78.7 us with
     // one, 77.0 with two or three; 32 x 8191 at 2 bits: 24.4, 24.6, 25.2 us with one, two, three)
     static constexpr int kFlushSteps = 2 / PT;
@@ -254,27 +254,18 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
 
     // ---- this workgroup's run of its unit's steps ----
     const int u = blockIdx.x / p.unit_wgs, part = blockIdx.x % p.unit_wgs;
-    // FLUSH: the last wavefront of a unit's last workgroup quantises the tokens that leave the window before it takes its share
-    const bool flush_here = FLUSH && part == p.unit_wgs - 1, flushes = flush_here && wave == WV - 1;
     const int n_kr = p.n_kr;
     // UNEVEN: tokens below v_q have quantised values in the cache, the others rows in the ring from slot v_start on
     const int v_q = p.n_vq - p.flushed_values;
     const int v_start = !UNEVEN || p.v_r_start >= p.flushed_values ? p.v_r_start - (UNEVEN ? p.flushed_values : 0) : p.cap_r - 1;
     const int v_skip = UNEVEN ? p.n_kq - v_q : 0;                                // value rows before the window's
     const int tiles = UNEVEN ? (v_q + kTileTokens - 1) / kTileTokens : p.plan.tiles_a - FLUSH;      // (the flushed tile is the last)
-    const StepAxis axis{p.axis_len, p.axis_rem};
-    const int real = axis.start(p.unit_wgs) - (FLUSH ? S::kFlushSteps : 0);      // (the flush counts as the last steps)
-    const int s0 = min(axis.start(part), real), s1 = min(axis.start(part + 1), real);
-    const int nr = (n_kr + S::kStepRows - 1) / S::kStepRows;
-    const int a0 = max(s0 - nr, 0), len_a = max(s1 - nr, 0) - a0;
-    // An item is one wavefront's slot of a step.  A wavefront takes every WV-th; in a workgroup that flushes, whose last wavefront
-    // comes late, the others have the first `lead` items to themselves.  (The shares are fixed: sums in the same order every time.)
-    // FLAT: all items one after the other: rows, MT tokens each whose keys only are quantised (UNEVEN), tiles.
-    constexpr bool FLAT = UNEVEN || FLUSH;
-    const int m0 = v_q & -MT, all_rows = (n_kr + NT - 1) / NT, all_fp16 = all_rows + (UNEVEN ? (p.n_kq - m0) / MT : 0);
-    const int n_items = FLAT ? max(min(s1 * WV, all_fp16 + (tiles + PT - 1) / PT) - s0 * WV, 0) : (s1 - s0) * WV;
-    const int n_row_items = FLAT ? min(max(all_rows - s0 * WV, 0), n_items) : min(max(nr - s0, 0), s1 - s0) * WV;
-    const int n_fp16_items = UNEVEN ? min(max(all_fp16 - s0 * WV, 0), n_items) : n_row_items;
+    using Work = OneHeadItems<BITS, FLUSH, UNEVEN>;
+    static_assert(std::is_same_v<Work, OneHeadWork<WV, PT, S::NT, S::MT, S::kFlushSteps, FLUSH, UNEVEN>>);
+    Work work(StepAxis{p.axis_len, p.axis_rem}, part, p.unit_wgs, tiles, p.n_kq, v_q, n_kr);
+    // the last wavefront of a unit's last workgroup quantises the tokens that leave the window before it takes its share
+    const bool flushes = FLUSH && part == p.unit_wgs - 1 && wave == WV - 1;
+    const int n_items = work.n_items, n_row_items = work.n_row_items, n_fp16_items = work.n_fp16_items;
     const int64_t unit = u;
 
     // ---- copies ----
@@ -333,29 +324,13 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
     };
     // the query
     if (lane < 16) copy_to_lds(p.q + unit * kHeadDim + n * 8, (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)sm_query));
-    // Tiles in an order rotated by the unit: workgroups in lockstep that all read the same relative offset of their units
-    // would meet on few memory channels for unlucky strides (a copy alone: 32.3 -> 29.8 us at 512 units).
-    const int turn = FLAT ? n_items - n_fp16_items : len_a, rot = turn > 0 ? (int)((uint32_t)(u * (FLUSH ? WV : 5)) % (uint32_t)turn) : 0;
-    auto row_of = [&](int item) -> int { return (s0 + item / WV) * S::kStepRows + item % WV * NT; };      // first token in the window
-    auto mixed_of = [&](int item) -> int { return m0 + (s0 * WV + item - all_rows) * MT; };                // first token
-    auto tile_of = [&](int item) -> int {
-        if constexpr (FLAT) {
-            int a = item - n_fp16_items + rot;
-            a -= a >= turn ? turn : 0;
-            return (s0 * WV + n_fp16_items - all_fp16 + a) * PT;
-        }
-        int a = (item - n_row_items) / WV + rot;
-        a -= a >= len_a ? len_a : 0;
-        return (a0 + a) * S::kStepTiles + item % WV * PT;
-    };
+    work.order(part, p.unit_wgs, u, p.one_round ? S::kFlushLead : S::kFlushLeadMany);
     auto copy_item = [&](int item, int slot) {
-        if (item < n_row_items) copy_rows(row_of(item), slot);
-        else if (UNEVEN && item < n_fp16_items) copy_mixed(mixed_of(item), slot);
-        else if (item < n_items) copy_tiles(tile_of(item), slot);
+        if (item < n_row_items) copy_rows(work.row_of(item), slot);
+        else if (UNEVEN && item < n_fp16_items) copy_mixed(work.mixed_of(item), slot);
+        else if (item < n_items) copy_tiles(work.tile_of(item), slot);
     };
-    const int lead = flush_here ? (WV - 1) * (p.one_round ? S::kFlushLead : S::kFlushLeadMany) : 0;
-    auto after = [&](int item) -> int { return item + (item < lead ? WV - 1 : WV); };
-    int now = flushes ? n_items : wave, next = after(now);
+    int now = flushes ? n_items : work.first(wave, false), next = work.after(now);
     copy_item(now, 0);
     copy_item(next, 1);
 
@@ -730,23 +705,23 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
     int slot = 0;
     auto end = [&]() {
         now = next;
-        next = after(next);
+        next = work.after(next);
         copy_item(next, slot);
         slot ^= 1;
     };
     if constexpr (FLUSH) {
         if (flushes) {
             quantised(std::integral_constant<int, 1>{}, ring, 1);
-            now = lead + wave;
+            now = work.first(wave, true);
             copy_item(now, 0);
-            next = after(now);
+            next = work.after(now);
             copy_item(next, 1);
         }
     }
 #pragma unroll 1
     while (now < n_row_items) {
         begin();
-        const int left = n_kr - row_of(now);
+        const int left = n_kr - work.row_of(now);
         if (left > 0) fp16_rows(ring + slot * S::kSlotBytes, left);
         end();
     }
@@ -754,14 +729,14 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
 #pragma unroll 1
         while (now < n_fp16_items) {
             begin();
-            mixed(ring + slot * S::kSlotBytes, mixed_of(now));
+            mixed(ring + slot * S::kSlotBytes, work.mixed_of(now));
             end();
         }
     }
 #pragma unroll 1
     while (now < n_items) {
         begin();
-        const int live = UNEVEN ? v_q - tile_of(now) * kTileTokens : tiles - tile_of(now);
+        const int live = UNEVEN ? v_q - work.tile_of(now) * kTileTokens : tiles - work.tile_of(now);
         if (live > 0) quantised(std::integral_constant<int, PT>{}, ring + slot * S::kSlotBytes, live);
         end();
     }
@@ -907,11 +882,8 @@ hipError_t launch(DecodeParams p, hipStream_t stream) {
     static_assert(S::kLds <= 160 * 1024 / OCC / 1280 * 1280, "workgroups per compute unit (LDS is given out in pieces of 1280 bytes)");
     static_assert(NB == 2 && PT <= 2, "two items in flight; masked tiles of a slot");
     const int64_t units = (int64_t)p.batch * p.n_kv_heads;
-    int steps = (p.plan.tiles_a + S::kStepTiles - 1) / S::kStepTiles + (p.n_kr + S::kStepRows - 1) / S::kStepRows;
-    if (UNEVEN || FLUSH) {
-        const int v_q = p.n_vq - (FLUSH ? kTileTokens : p.flushed_values), m0 = v_q & -S::MT, tiles = (v_q + kTileTokens - 1) / kTileTokens;
-        steps = ((p.n_kr + S::NT - 1) / S::NT + (UNEVEN ? (p.n_kq - m0) / S::MT : 0) + (tiles + PT - 1) / PT + WV - 1) / WV + (FLUSH ? S::kFlushSteps : 0);
-    }
+    const int v_q = p.n_vq - (FLUSH ? kTileTokens : p.flushed_values);
+    const int steps = OneHeadItems<BITS, FLUSH, UNEVEN>::steps((v_q + kTileTokens - 1) / kTileTokens, p.n_kq, v_q, p.n_kr);
     const int cus = compute_units();
     const int w = one_head_parts(units, steps, cus, std::min(p.part_stride, kOneHeadMaxParts), BITS == 2 ? 8 : 12);
     if (steps < 1 || units * w > 0x7fffffff) return hipErrorInvalidValue;

@@ -171,4 +171,72 @@ inline int one_head_parts(int64_t units, int steps, int compute_units, int room,
     return (int)std::max<int64_t>(1, std::min({w, (int64_t)steps, (int64_t)room}));
 }
 
+// What decode_one_kernel's wavefronts take of a unit: the kernel's own arithmetic, here so that it can be walked without a device.
+// A unit is n_kr tokens of fp16 rows, with UNEVEN the tokens from v_q (values in the cache) to n_kq, whose keys only are quantised, and
+// `tiles` tiles.  An item is one wavefront's slot of a step: NT tokens' rows, MT tokens' key tile and value rows, or PT tiles.
+// FLAT: items one after the other; otherwise rows are rounded to steps, then tiles.
+template <int WV, int PT, int NT, int MT, int FLUSH_STEPS, bool FLUSH, bool UNEVEN>
+struct OneHeadWork {
+    static constexpr bool FLAT = FLUSH || UNEVEN;
+    static constexpr int kTiles = WV * PT, kRows = WV * NT;        // of a step
+    int s0, m0, a0, len_a, all_rows, all_fp16, turn, rot, lead;
+    int n_row_items, n_fp16_items, n_items;                        // of this part: rows; and those of MT tokens; and tiles
+
+    // steps of a unit; with FLUSH the last FLUSH_STEPS are the flush, which no item stands for
+    static KIVI_HOST_DEVICE int steps(int tiles, int n_kq, int v_q, int n_kr) {
+        if (!FLAT) return (tiles + kTiles - 1) / kTiles + (n_kr + kRows - 1) / kRows;
+        const int fp16 = (n_kr + NT - 1) / NT + (UNEVEN ? (n_kq - (v_q & -MT)) / MT : 0);
+        return (fp16 + (tiles + PT - 1) / PT + WV - 1) / WV + (FLUSH ? FLUSH_STEPS : 0);
+    }
+    // part `part` of `parts`; order() completes it (apart, so that the kernel computes that where it needs it: in one, steps that flush
+    // took 0.8 % more)
+    KIVI_HOST_DEVICE OneHeadWork(StepAxis axis, int part, int parts, int tiles, int n_kq, int v_q, int n_kr) {
+        const int real = axis.start(parts) - (FLUSH ? FLUSH_STEPS : 0), s1 = least(axis.start(part + 1), real);
+        s0 = least(axis.start(part), real);
+        const int nr = (n_kr + kRows - 1) / kRows;
+        a0 = most(s0 - nr, 0);
+        len_a = most(s1 - nr, 0) - a0;
+        m0 = v_q & -MT;
+        all_rows = (n_kr + NT - 1) / NT;
+        all_fp16 = all_rows + (UNEVEN ? (n_kq - m0) / MT : 0);
+        n_items = FLAT ? most(least(s1 * WV, all_fp16 + (tiles + PT - 1) / PT) - s0 * WV, 0) : (s1 - s0) * WV;
+        n_row_items = FLAT ? least(most(all_rows - s0 * WV, 0), n_items) : least(most(nr - s0, 0), s1 - s0) * WV;
+        n_fp16_items = UNEVEN ? least(most(all_fp16 - s0 * WV, 0), n_items) : n_row_items;
+    }
+    // u: the unit; flush_lead: items that each other wavefront takes before the one that flushes (the last one of the last part)
+    // takes its first
+    KIVI_HOST_DEVICE void order(int part, int parts, int u, int flush_lead) {
+        // Tiles in an order rotated by the unit: workgroups in lockstep that all read the same relative offset of their units
+        // would meet on few memory channels for unlucky strides (a copy alone: 32.3 -> 29.8 us at 512 units).
+        turn = FLAT ? n_items - n_fp16_items : len_a;
+        rot = turn > 0 ? (int)((uint32_t)(u * (FLUSH ? WV : 5)) % (uint32_t)turn) : 0;
+        lead = FLUSH && part == parts - 1 ? (WV - 1) * flush_lead : 0;
+    }
+    // A wavefront takes every WV-th item; in the workgroup that flushes, whose last wavefront comes late, the others have the first
+    // `lead` items to themselves.  (The shares are fixed: sums in the same order every time.)
+    KIVI_HOST_DEVICE int first(int wave, bool flushes) const { return flushes ? lead + wave : wave; }
+    KIVI_HOST_DEVICE int after(int item) const { return item + (item < lead ? WV - 1 : WV); }
+    // an item's first token of the window, token, and tile
+    KIVI_HOST_DEVICE int row_of(int item) const { return (s0 + item / WV) * kRows + item % WV * NT; }
+    KIVI_HOST_DEVICE int mixed_of(int item) const { return m0 + (s0 * WV + item - all_rows) * MT; }
+    KIVI_HOST_DEVICE int tile_of(int item) const {
+        if (FLAT) {
+            int a = item - n_fp16_items + rot;
+            a -= a >= turn ? turn : 0;
+            return (s0 * WV + n_fp16_items - all_fp16 + a) * PT;
+        }
+        int a = (item - n_row_items) / WV + rot;
+        a -= a >= len_a ? len_a : 0;
+        return (a0 + a) * kTiles + item % WV * PT;
+    }
+
+private:
+    static KIVI_HOST_DEVICE int least(int a, int b) { return a < b ? a : b; }
+    static KIVI_HOST_DEVICE int most(int a, int b) { return a > b ? a : b; }
+};
+
+// the two bit widths' slots (decode_one_kernel checks that they are its own)
+template <int BITS, bool FLUSH, bool UNEVEN>
+using OneHeadItems = OneHeadWork<4, BITS == 2 ? 2 : 1, BITS == 2 ? 12 : 10, BITS == 2 ? 16 : 8, BITS == 2 ? 1 : 2, FLUSH, UNEVEN>;
+
 }  // namespace kivi
