@@ -22,15 +22,19 @@ def round_up(x, m):
     return (x + m - 1) // m * m
 
 
-def gpu_prefill(w, k_np, v_np, policy, decode_path, extra_q_tokens=0):
-    """Upload K, V ([b, h, l, 128] fp16 numpy) and run kivi_prefill.  Returns (layout, cache)."""
+def gpu_prefill(w, k_np, v_np, policy, decode_path, extra_q_tokens=0, ring=None, zero=False):
+    """Upload K, V ([b, h, l, 128] fp16 numpy) and run kivi_prefill.  Returns (layout, cache).  `ring`: slots of the residual
+    rings (None: 32 more than they need); `zero`: arrays that no call has written hold zeros."""
     import torch
     l = k_np.shape[2]
     cap_q = max(round_up(l + extra_q_tokens, w.group), w.group)
-    cap_r = round_up(w.residual + w.group, 32) + 32
+    cap_r = round_up(w.residual + w.group, 32) + 32 if ring is None else ring
     layout = kivi.make_layout(w.batch, w.n_q_heads, w.n_kv_heads, w.bits, w.residual, cap_q, cap_r,
                               decode_path=decode_path, group=w.group)
     cache = kivi.Cache(layout)
+    if zero:
+        for buf in cache.buffers.values():
+            buf.zero_()
     kt = torch.from_numpy(k_np).cuda()
     vt = torch.from_numpy(v_np).cuda()
     kivi.kivi_prefill(layout, kt, vt, l, cache, policy)

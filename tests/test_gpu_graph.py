@@ -45,3 +45,51 @@ def test_replayed_launch_matches_eager(path):
         torch.cuda.synchronize()
         assert np.array_equal(got, out_eager.cpu().numpy()), f"replay {trial} differs from the eager launch"
         gh.check_close(gh.pick_heads(got, w, heads), gh.oracle_attention_for_heads(w, oc, q, heads), f"replay {trial}")
+
+
+@pytest.mark.parametrize("bits,group,policy,tokens", [
+    (2, 32, kivi.KIVI_FLUSH_WINDOW, 2047),      # one query head per kv-head: a tile leaves the window in the captured step
+    (4, 32, kivi.KIVI_FLUSH_WINDOW, 2047),
+    (2, 64, kivi.KIVI_FLUSH_ALG1, 2000),        # ... a value token
+])
+def test_replayed_flushing_step_matches_eager(bits, group, policy, tokens):
+    """A whole step that flushes, captured with one query head per kv-head (one launch with several workgroups per unit): every replay
+    gives the eager step's bits, with attention calls on the same workspace in between."""
+    torch = gh.require_gpu()
+    print(f"case graph flushing step bits={bits} G={group} policy={policy}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(bits + tokens)
+    heads, residual = 4, 128
+    k, v = (torch.randn(2, heads, tokens + 1, 128, dtype=torch.float16, device="cuda", generator=gen) for _ in range(2))
+    q = torch.randn(2, heads, 128, dtype=torch.float16, device="cuda", generator=gen)
+    new = [x[:, :, tokens].contiguous() for x in (k, v)]
+    layout = kivi.make_layout(2, heads, heads, bits, residual, gh.round_up(tokens + 1, 128), gh.round_up(residual + group, 32), group=group)
+    fields = ("n_kq", "n_vq", "k_r_start", "n_kr", "v_r_start", "n_vr")
+
+    def start():
+        cache = kivi.Cache(layout)
+        for buf in cache.buffers.values():
+            buf.zero_()
+        kivi.kivi_prefill(layout, k, v, tokens, cache, policy)
+        return cache, [getattr(cache.c, f) for f in fields]
+
+    cache, _ = start()
+    expected, again, out = (torch.empty(2, heads, 128, dtype=torch.float32, device="cuda") for _ in range(3))
+    kivi.kivi_decode_step(layout, cache, *new, q, 128 ** -0.5, expected, policy)        # eager
+    torch.cuda.synchronize()
+    arrays = {name: buf.clone() for name, buf in cache.buffers.items()}
+
+    cache, before = start()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        kivi.kivi_decode_step(layout, cache, *new, q, 128 ** -0.5, out, policy, stream=torch.cuda.current_stream())
+    assert cache.c.n_vq > before[1]
+    for replay in range(4):
+        out.fill_(float("nan"))
+        graph.replay()                                 # (the rings still hold what left the window: a replay flushes it again)
+        torch.cuda.synchronize()
+        assert torch.equal(out, expected), f"replay {replay}"
+        assert all(torch.equal(buf, arrays[name]) for name, buf in cache.buffers.items()), f"replay {replay}"
+        kivi.kivi_decode_attention(layout, cache, q, 128 ** -0.5, again)
+        torch.cuda.synchronize()
+        gh.check_close(again.cpu().numpy(), expected.cpu().numpy(), f"attention after replay {replay}")

@@ -94,23 +94,30 @@ def test_flush(batch, heads, group, bits):
     (64, 24, 8, 1023, 96, 4),       # two tiles
 ])
 def test_flush_step(batch, hq, hkv, tokens, residual, bits):
-    """A step that flushes: the automatic choice carries the flush out in the fp16-row launch, the single-launch form
-    before it.  Cache arrays equal byte for byte; outputs as far apart as two launch forms of one attention."""
+    """A step that flushes, by the automatic choice and in the single-launch form, against append, flush and attention as calls of
+    their own.  Cache arrays equal byte for byte; outputs as far apart as two launch forms of one attention."""
     torch = gh.require_gpu()
     print(f"case flush step B={batch} heads {hq}/{hkv} L={tokens} R={residual} bits={bits}", flush=True)
     gen = torch.Generator(device="cuda").manual_seed(tokens + bits)
     k, v = (torch.randn(batch, hkv, tokens + 1, 128, dtype=torch.float16, device="cuda", generator=gen) for _ in range(2))
     q = torch.randn(batch, hq, 128, dtype=torch.float16, device="cuda", generator=gen)
+    new = [x[:, :, tokens].contiguous() for x in (k, v)]
     caches, outs = [], []
-    for path in (kivi.KIVI_DECODE_AUTO, kivi.KIVI_DECODE_MFMA_ONE):
+    for apart, path in ((True, kivi.KIVI_DECODE_AUTO), (False, kivi.KIVI_DECODE_AUTO), (False, kivi.KIVI_DECODE_MFMA_ONE)):
         layout = kivi.make_layout(batch, hq, hkv, bits, residual, gh.round_up(tokens + 1, 32), gh.round_up(residual + 32, 32), decode_path=path)
         cache, out = _zeroed(layout), torch.empty(batch, hq, 128, dtype=torch.float32, device="cuda")
         kivi.kivi_prefill(layout, k, v, tokens, cache, W)
         before = cache.c.n_kq
-        kivi.kivi_decode_step(layout, cache, k[:, :, tokens].contiguous(), v[:, :, tokens].contiguous(), q, 128 ** -0.5, out, W)
+        if apart:
+            kivi.kivi_append_residual(layout, cache, *new)
+            kivi.kivi_flush_residual(layout, cache, W)
+            kivi.kivi_decode_attention(layout, cache, q, 128 ** -0.5, out)
+        else:
+            kivi.kivi_decode_step(layout, cache, *new, q, 128 ** -0.5, out, W)
         torch.cuda.synchronize()
         assert cache.c.n_kq == before + 32
         caches.append(cache)
         outs.append(out.cpu().numpy())
-    assert _bytes(caches[0], PACKED + ("k_resid", "v_resid")) == _bytes(caches[1], PACKED + ("k_resid", "v_resid"))
-    gh.check_close(outs[0], outs[1], "two launches against one")
+    for cache, out, what in zip(caches[1:], outs[1:], ("automatic", "one launch")):
+        assert _bytes(cache, PACKED + ("k_resid", "v_resid")) == _bytes(caches[0], PACKED + ("k_resid", "v_resid")), what
+        gh.check_close(out, outs[0], what)

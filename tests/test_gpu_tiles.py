@@ -255,7 +255,7 @@ def test_key_outliers(hq, hkv, bits, group, policy, large, small, looks):
 
 
 @pytest.mark.parametrize("group", [32, 64, 128])
-@pytest.mark.parametrize("hq,bits", [(2, 2), (4, 4), (7, 2), (8, 4)])
+@pytest.mark.parametrize("hq,bits", [(1, 2), (1, 4), (2, 2), (4, 4), (7, 2), (8, 4)])
 def test_unwritten_scales(hq, bits, group):
     """Values that end inside a tile (Algorithm 1's policy): what the packed arrays hold past them does not count, be it
     zeros or NaN.  Same bytes out."""
