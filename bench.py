@@ -196,7 +196,7 @@ def run_stream(args, w, path_name, path):
                    "step": "kivi_decode_step: append newest token + flush (every 32nd step) + decode attention"},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic(w.name, path_name),
-                     "kernel": "whole steps (attention kernel plus, on flush steps, the copy and quantise kernels): "
+                     "kernel": "whole steps (one launch each, which on flush steps quantises the group too): "
                                "sum of the attention's algorithmic bytes over the steps / time of all steps",
                      "algorithmic_bytes_per_launch": bytes_total / w.decode_steps},
         "extra": {"flush_steps": flushes,

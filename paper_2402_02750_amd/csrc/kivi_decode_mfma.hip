@@ -1,5 +1,6 @@
-// Decode attention, matrix-core family for gfx950 (KIVI Equation 4 + Algorithm 1 Decoding), one or two query heads
-// per kv-head (kivi_decode_tiles.hip serves wider groups and smaller batches of two).
+// Decode attention, matrix-core family for gfx950 (KIVI Equation 4 + Algorithm 1 Decoding): two query heads per kv-head in large
+// batches, and one where value tokens are quantised before their keys, in batches of different lengths, and where the caller asks for two
+// launches (kivi_decode_one.hip serves one head otherwise, kivi_decode_tiles.hip wider groups and smaller batches of two).
 //
 // Why matrix cores for a bandwidth-bound scan: at 2 bits a cached element is 3/8 of a byte, so at
 // HBM speed a compute unit sees ~28 elements per clock while its vector ALUs retire 64 lane-ops

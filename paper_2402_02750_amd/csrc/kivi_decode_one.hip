@@ -32,24 +32,26 @@
 // units).  Items follow each other without rounding to steps.  Counter -> fixed shares: 32 units x 4095 tokens 11.3 -> 10.7 us, 256
 // x 1023 13.7 -> 12.8, 512 x 1023 19.0 -> 18.4, 512 x 4095 41.8 -> 42.6, 2048 x 2175 99.6 -> 101.5; 4 bits 128 x 2047 16.2 -> 15.1, 320 x 8191
 // 77.5 -> 77.9.  (A fifth wavefront: two workgroups per compute unit instead of three.  The flushing wavefront's first item asked for
-// before the flush: no change.)  Against a launch of its own before the attention (4.5-5 us): 8 units x 512 tokens 13.5 -> 10.1 us,
-// 256 x 4095 31.2 -> 25.0, 512 x 4095 48.7 -> 42.6; 4 bits, 256 x 4095 40.5 -> 33.7, 320 x 8191 78.3 -> 77.9.
+// before the flush: no change.)  Against a launch of its own before the attention: 8 units x 511 tokens 10.8 -> 9.6 us, 256 x 4095
+// 28.1 -> 23.5, 512 x 4095 45.9 -> 41.4, 2048 x 2175 105.7 -> 103.1; 4 bits, 256 x 4095 36.4 -> 32.5, 320 x 8191 78.6 -> 77.7.  (With
+// 4 bits, 800 units and more and 2000 tokens and more, steps that flush are up to 3 % longer than decode_mfma_kernel's two launches.)
 //
 // UNEVEN (n_kq >= n_vq, Algorithm 1's policy): the tokens between have quantised keys and fp16 value rows.  An item of those is
 // MT tokens: their key tile's codes, scales and zero-points and their value rows fill a slot with the same NI copies (the key tile is
 // read for every MT of its 32 tokens, from the L2 after the first); its logits go through LDS to the lanes that have the rows.  Values
 // that are not there in the last tile count as scale 0.  The value token that a step quantises lies in the first of these items;
 // its wavefront encodes the row that it has in LDS (a launch of its own before the attention took 4.7 us).  Items follow each
-// other without rounding to steps.  Whole steps, decode_mfma_kernel -> this one: 256 units x 4000 tokens, G = 64, 34.4 -> 22.3 us;
-// 32 x 500 13.9 -> 8.6, 256 x 1000 26.7 -> 13.0, 512 x 4000 46.9 -> 36.2, 2048 x 2000 118.9 -> 83.2; 4 bits 14.5 -> 8.2, 29.7 -> 15.0,
-// 65.8 -> 53.8, 146.0 -> 122.5; a window of 512 tokens, 256 x 4000 42.4 -> 31.1.
+// other without rounding to steps.  Whole steps, G = 64, decode_mfma_kernel -> this one: 256 units x 4000 tokens 34.0 -> 22.7 us;
+// 32 x 500 13.9 -> 8.1, 256 x 1000 26.3 -> 12.5, 512 x 4000 48.3 -> 40.0, 2048 x 2000 114.9 -> 82.7; 4 bits 32 x 500 14.7 -> 8.3, 256 x 1000
+// 29.1 -> 14.8, 512 x 4000 67.4 -> 54.8, 2048 x 2000 134.8 -> 113.5; a window of 512 tokens, 256 x 4000 38.6 -> 28.0.
 //
 // Bound: HBM.  A launch that only copies what this one reads takes 29.7 us for 512 units of 124 tiles at 2 bits (6.6 TB/s), rows and
-// all 35; this kernel 39.5 (decode_mfma_kernel 46).  What is left is start (2 us to the first tile), the last step and the
-// merge (3 us).  Whole steps, 2 bits, decode_mfma_kernel -> this one: 32 units x 3000 tokens 12.8 -> 9.5 us, 128 x 4000 22.8 ->
-// 16.2, 256 x 1000 22.7 -> 11.2, 256 x 4000 31.1 -> 24.7, 512 x 1000 23.7 -> 17.7, 512 x 4000 46.3 -> 39.6, 768 x 4000 69.6 -> 58.7,
-// 2048 x 2000 92.4 -> 86.0; 4 bits: 256 x 4000 40.7 -> 33.2, 320 x 8000 75.5 -> 72.6, 1024 x 4000 112.3 -> 111.3.
-// Error against 64 bits: 7e-7 to 5e-6 of the output (decode_mfma_kernel 2e-5 to 2.5e-4).
+// all 35; this kernel 39.4 (decode_mfma_kernel 45.5).  From 1000 to 8000 tokens at 512 units a token more costs what its bytes take at 6.1 TB/s
+// (4 bits 6.6); beyond that a step has 2.5 us.  Whole steps, 2 bits, decode_mfma_kernel -> this one: 32 units x 3000 tokens 12.6 -> 9.1 us,
+// 128 x 4000 22.4 -> 15.6, 256 x 1000 22.6 -> 11.3, 256 x 4000 30.0 -> 23.1, 512 x 1000 22.3 -> 15.1, 512 x 4000 45.5 -> 39.4, 768 x 4000 67.4 ->
+// 56.9, 2048 x 2000 98.7 -> 87.3; 4 bits: 256 x 4000 38.6 -> 30.7, 320 x 8000 74.6 -> 72.0, 1024 x 4000 112.4 -> 111.6.
+// Error against 64 bits: 7e-7 to 2e-6 of the output on plain normal data, 4e-6 to 1.6e-5 with key channels of large magnitude
+// (decode_mfma_kernel 2e-5 to 2.5e-4).
 #include "kivi_internal.h"
 #include "kivi_quantize_tile.h"
 #include "kivi_tiles_plan.h"
