@@ -226,6 +226,12 @@ constexpr int kLdsBytes = 160 * 1024 / 3 / 1280 * 1280;    // three workgroups p
 // parts of one unit, at most (their statistics meet in LDS)
 constexpr int max_parts_of(int bits, int hp) { return bits == 4 && hp == 8 ? kTilesMaxParts / 2 : kTilesMaxParts; }
 
+// The kernel's scalar divisions by numbers that the launch fixes (by_steps: of a unit).  Not in DecodeParams: 56 bytes more cost a
+// launch of the other kernels 0.1 us.
+struct TilesParams : DecodeParams {
+    FastDiv by_runs, by_kv_heads, by_unit_wgs, by_row_split, by_steps, by_axis_longer, by_axis_len;
+};
+
 // kWhole: K and V split at the same token, so a tile is all quantised or all fp16; kMixed: any split.
 // kQuantisedRagged: the all-quantised tiles of a batch of sequences of different lengths (work cut by tables that
 // the host made); part 0 of every unit is what the fp16-row launch left.
@@ -234,7 +240,7 @@ constexpr int kWhole = 0, kMixed = 1, kQuantisedRagged = 2, kFlush = 3;
 
 // HP: head slots of a unit (2, 4 or 8).  CS: G > 32 (scales stored once per group of G = 32 << kg_shift).
 template <int BITS, int HP, int MODE, bool CS>
-__global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodeParams p) {
+__global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParams p) {
     constexpr bool kRagged = MODE == kQuantisedRagged;
     constexpr int kCodeBytes = kTileTokens * kHeadDim * BITS / 8;      // one tile of K or V codes
     constexpr int kPlanes = BITS / 2;
@@ -266,12 +272,14 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
     const int tok0 = (kb & 1) * 8 + (kb >> 1) * 4;
 
     const int rep_total = p.n_q_heads / p.n_kv_heads, run = p.rep_here, n_runs = p.head_groups;
-    auto kv_unit = [&](int u) -> int { return u / n_runs; };
+    auto kv_unit = [&](int u) -> int { return p.by_runs.of(u); };
+    auto batch_of_kv = [&](int unit) -> int { return p.by_kv_heads.of(unit); };
     auto first_head = [&](int u) -> int {       // query head of head slot 0
-        return (kv_unit(u) % p.n_kv_heads) * rep_total + p.q_head0 + (u - kv_unit(u) * n_runs) * run;
+        const int unit = kv_unit(u);
+        return (unit - batch_of_kv(unit) * p.n_kv_heads) * rep_total + p.q_head0 + (u - unit * n_runs) * run;
     };
     auto live_heads = [&](int u) -> int { return min(run, rep_total - p.q_head0 - (u - kv_unit(u) * n_runs) * run); };
-    auto batch_of = [&](int u) -> int { return kv_unit(u) / p.n_kv_heads; };
+    auto batch_of = [&](int u) -> int { return batch_of_kv(kv_unit(u)); };
 
     // ---- this workgroup's interval of the axis of all-quantised steps ----
     const int tiles_a_plan = p.plan.tiles_a;
@@ -289,25 +297,22 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
         else return n_a;                                               // (a sequence without quantised tiles has one empty step)
     };
     auto axis_start = [&](int u) -> int {
-        if constexpr (kRagged) return table(p.unit_parts, batch_of(u)) + u % p.n_kv_heads * steps_of(u);
+        if constexpr (kRagged) return table(p.unit_parts, batch_of(u)) + (u - batch_of(u) * p.n_kv_heads) * steps_of(u);
         else return u * n_a;
     };
     // the workgroup's steps [j0, j1) in unit u, visited in an order rotated by the unit, so that workgroups in
     // lockstep do not all read the same relative offset of their units (which meets on few memory channels
     // for unlucky strides); `left`: steps of the interval not done yet
-    struct Range { int j0, j1, rot, tiles; };
+    struct Range { int j0, j1, at, tiles; };           // at: the step visited first
     auto range_of = [&](int u, int first, int left) -> Range {
         Range r;
         r.tiles = tiles_a_plan;
         if constexpr (kRagged) r.tiles = table(p.seq_state, 4 * batch_of(u)) / kTileTokens;
         r.j0 = first;
         r.j1 = min(steps_of(u), first + left);
-        r.rot = (int)((uint32_t)(u * 5) % (uint32_t)max(r.j1 - r.j0, 1));
+        // (multiples of the golden ratio: neighbouring units start far apart)
+        r.at = r.j0 + (int)(((uint64_t)((uint32_t)u * 0x9E3779B9u) * (uint32_t)(r.j1 - r.j0)) >> 32);
         return r;
-    };
-    auto step_at = [&](const Range& r, int j) -> int {
-        const int x = j + r.rot;
-        return x >= r.j1 ? x - (r.j1 - r.j0) : x;
     };
 
     // ---- copies of packed tiles into this wavefront's ring ----
@@ -316,8 +321,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
     // lanes 0-15 k_scale, 16-31 k_zero, 32-47 v_scale, 48-63 v_zero
     const __half* scale_base = kb == 0 ? p.k_scale : kb == 1 ? p.k_zero : kb == 2 ? p.v_scale : p.v_zero;
     const char* scale_lane = reinterpret_cast<const char*>(scale_base) + (CS && kb >= 2 ? min(n * 16, (256 >> kg) - 16) : n * 16);
-    auto copy_tile = [&](int64_t tile, int slot) {
-        const uint32_t dst = ring_lds + slot * kSlotBytes;
+    auto copy_tile = [&](int64_t tile, uint32_t dst) {
         const char* kc = reinterpret_cast<const char*>(p.k_codes) + tile * kCodeBytes;
         const char* vc = reinterpret_cast<const char*>(p.v_codes) + tile * kCodeBytes;
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");             // the slot's last readers have their data
@@ -807,7 +811,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
         const int tok = tok0 + (is_lo ? 16 : 0);                       // this lane's tokens: tok + i
         const int n_vq_here = min(max(p.n_vq - tt, 0), kTileTokens);
         if (tt < p.n_kq || n_vq_here > 0) {                             // (the tile lies within the packed arrays' capacity)
-            copy_tile(unit * p.cap_tiles + tile, 0);
+            copy_tile(unit * p.cap_tiles + tile, ring_lds);
             wait_copies<0>();
         }
         if (tt < p.n_kq) {
@@ -878,13 +882,13 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
             parts = unit_wgs;
             mine = wg - u * unit_wgs;
         } else if (steps > 0) {
-            const int at = axis_start(u), g0 = axis.owner(at);
-            parts = axis.owner(at + steps - 1) - g0 + 1;
+            const int at = axis_start(u), g0 = axis.owner(at, p.by_axis_longer, p.by_axis_len);
+            parts = axis.owner(at + steps - 1, p.by_axis_longer, p.by_axis_len) - g0 + 1;
             mine = wg - g0;
         }
         if (tiles_b > 0) {
             parts += p.row_split;
-            mine = rows ? (int)blockIdx.x % p.row_split : mine + p.row_split;
+            mine = rows ? (int)blockIdx.x - p.by_row_split.of(blockIdx.x) * p.row_split : mine + p.row_split;
         }
         const int stride = p.part_stride, base = kRagged ? 1 : 0;           // part 0: the fp16-row launch's
         // the wavefronts' statistics, then their outputs relative to the common maximum
@@ -1061,7 +1065,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
     if constexpr (MODE == kWhole || MODE == kFlush) {
         if (wg < 0) {                                  // ---- the fp16 rows of one unit (K and V split alike) ----
             constexpr int kFlushed = MODE == kFlush ? 1 : 0;
-            const int u = (int)blockIdx.x / p.row_split, cut = (int)blockIdx.x % p.row_split;
+            const int u = p.by_row_split.of(blockIdx.x), cut = (int)blockIdx.x - u * p.row_split;
             // kFlush: the first one's last wavefront quantises the tile that leaves the window and attends to it, the others have the rows
             const bool flushes = kFlushed && cut == 0 && wave == kWaves - 1;
             const int tile0 = flushes ? p.plan.tiles_total : tiles_a_plan + cut * kWaves + wave + (cut > 0 ? 0 : kFlushed);
@@ -1120,7 +1124,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
     }
     if constexpr (MODE == kMixed) {
         if (wg < 0) {                                  // ---- the tiles of one unit that hold fp16 rows or are split differently ----
-            const int u = (int)blockIdx.x / p.row_split, tile0 = tiles_a_plan + (int)blockIdx.x % p.row_split * kWaves + wave;
+            const int u = p.by_row_split.of(blockIdx.x), tile0 = tiles_a_plan + ((int)blockIdx.x - u * p.row_split) * kWaves + wave;
             half8 raw[4];
             const int live = live_heads(u);
             const __half* src = p.q + ((int64_t)batch_of(u) * p.n_q_heads + first_head(u) + min(head, live - 1)) * kHeadDim + kb * 8;
@@ -1141,28 +1145,34 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
         first = table(p.wave_desc, 4 * wg + 1);
         left = table(p.wave_desc, 4 * wg + 2);
     } else if (unit_wgs > 0) {
-        u = wg / unit_wgs;
+        u = p.by_unit_wgs.of(wg);
         const int g = wg - u * unit_wgs;
         first = axis.start(g);
         left = axis.start(g + 1) - first;
     } else {
         const int pos0 = axis.start(wg);
-        u = pos0 / n_a;
+        u = p.by_steps.of(pos0);
         first = pos0 - u * n_a;
         left = axis.start(wg + 1) - pos0;
     }
     copy_query(u, 0);
     // cursor of the next tile to copy: the interval's steps, unit by unit
+    // (No divisions after a copy: 130 scalar instructions a tile then, 40 now; launches 0.7-1 us shorter.)
     Range nx = range_of(u, first, left);
-    int nx_u = u, nx_j = nx.j0, nx_left = left;
-    auto advance_copy = [&](int slot) {
+    int nx_u = u, nx_here = nx.j1 - nx.j0, nx_left = left;            // steps left in this unit, and in all
+    int64_t nx_tile0 = (int64_t)kv_unit(u) * p.cap_tiles;
+    uint32_t nx_dst = ring_lds;
+    auto advance_copy = [&]() {
         if (nx_left <= 0) return;
-        const int t = max(min(step_at(nx, nx_j) * kWaves + wave, nx.tiles - 1), 0);
-        copy_tile((int64_t)kv_unit(nx_u) * p.cap_tiles + t, slot);
-        if (--nx_left > 0 && ++nx_j == nx.j1) {
+        copy_tile(nx_tile0 + max(min(nx.at * kWaves + wave, nx.tiles - 1), 0), nx_dst);
+        nx_dst = nx_dst == ring_lds + (NB - 1) * kSlotBytes ? ring_lds : nx_dst + kSlotBytes;
+        nx.at = nx.at + 1 == nx.j1 ? nx.j0 : nx.at + 1;
+        --nx_left;
+        if (--nx_here == 0 && nx_left > 0) {
             ++nx_u;
             nx = range_of(nx_u, 0, nx_left);
-            nx_j = nx.j0;
+            nx_here = nx.j1 - nx.j0;
+            nx_tile0 = (int64_t)kv_unit(nx_u) * p.cap_tiles;
         }
     };
     // waits for the oldest of the tiles in flight: `todo` steps are left, so min(todo, NB) tiles are in flight
@@ -1171,27 +1181,34 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
         else if (NB > 2 && todo == 2) wait_copies<NI>();
         else wait_copies<0>();
     };
-#pragma unroll 1
-    for (int i = 0; i < NB; ++i) advance_copy(i);
-    const int in_flight = min(left, NB);
-    if (in_flight == NB) wait_copies<NB * NI>();       // the query has arrived, the tiles are on their way
-    else if (in_flight == 2) wait_copies<2 * NI>();
-    else wait_copies<NI>();
+    // One tile at first, the others when the query is ready: the first NB tiles of all wavefronts together keep the memory busy for
+    // 4-5 us, and with all of them asked for at once the first ones came that late (after 7.1 us, now 5.3: 64 / 8 heads, batch 4,
+    // 16 377 tokens 30.1 -> 29.5 us, 32 / 8 heads, 32 767 tokens 31.2 -> 30.2, 71 / 1 heads 29.4 -> 28.2).
+    advance_copy();
+    wait_copies<NI>();                                 // the query has arrived, the tile is on its way
     lds_barrier();
-    int slot = 0, q_buf = 0;
+    int slot = 0, q_buf = 0, ahead = 1;
     // The instruction arbiter favours the oldest wavefront of a SIMD, so the workgroups of a compute unit
     // would finish one after the other, the last one alone and latency-bound: a wavefront's priority falls with
     // the share of its interval that is done.
     const int quarter = left >> 2;
+    int priority = 3, drop_at = 3 * quarter;
+    __builtin_amdgcn_s_setprio(3);
     auto set_progress_priority = [&](int remaining) {
-        if (remaining > 3 * quarter) __builtin_amdgcn_s_setprio(3);
-        else if (remaining > 2 * quarter) __builtin_amdgcn_s_setprio(2);
-        else if (remaining > quarter) __builtin_amdgcn_s_setprio(1);
-        else __builtin_amdgcn_s_setprio(0);
+        if (remaining > drop_at) return;
+        --priority;
+        drop_at -= quarter;
+        if (priority == 2) __builtin_amdgcn_s_setprio(2);
+        else if (priority == 1) __builtin_amdgcn_s_setprio(1);
+        else {
+            __builtin_amdgcn_s_setprio(0);
+            drop_at = 0;
+        }
     };
 #pragma unroll 1
     while (true) {
         const Range r = range_of(u, first, left);
+        int at = r.at;
         left -= r.j1 - r.j0;
         {
             half8 raw[4];
@@ -1200,14 +1217,17 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(DecodePara
             reset_state();
             set_query(raw);
         }
+#pragma unroll 1
+        for (; ahead < NB; ++ahead) advance_copy();
         if (left > 0) copy_query(u + 1, q_buf ^ 1);
         if constexpr (kRagged) copy_rows_part(u);
         for (int j = r.j0; j < r.j1; ++j) {
             const int todo = left + r.j1 - j;          // steps of the interval that are not done
             set_progress_priority(todo);
             wait_oldest(todo);
-            if (step_at(r, j) * kWaves + wave < r.tiles) quantised_tile(&sm_ring[wave][slot][0]);
-            advance_copy(slot);
+            if (at * kWaves + wave < r.tiles) quantised_tile(&sm_ring[wave][slot][0]);
+            advance_copy();
+            at = at + 1 == r.j1 ? r.j0 : at + 1;
             slot = slot + 1 == NB ? 0 : slot + 1;
         }
         // the next query and the rows' part: there already if a tile requested after them was waited for
@@ -1254,9 +1274,18 @@ bool with_tiles_variant(int bits, int rep, F&& fn) {
 }
 
 template <int BITS, int HP, int MODE, bool CS>
-hipError_t launch_mode(DecodeParams p, hipStream_t stream) {
+hipError_t launch_mode(const DecodeParams& params, hipStream_t stream) {
+    TilesParams p{};
+    static_cast<DecodeParams&>(p) = params;
     const int64_t units = (int64_t)p.batch * p.n_kv_heads * p.head_groups;
+    p.by_runs = FastDiv::by(p.head_groups);
+    p.by_kv_heads = FastDiv::by(p.n_kv_heads);
+    auto set_axis = [&]() {
+        p.by_axis_len = FastDiv::by(p.axis_len);
+        p.by_axis_longer = FastDiv::by(p.axis_len + 1);
+    };
     if constexpr (MODE == kQuantisedRagged) {
+        set_axis();
         if (p.n_slices < 1 || !p.wave_desc || !p.unit_parts || !p.seq_state) return hipErrorInvalidValue;
         p.row_wgs = 0;
         decode_tiles_kernel<BITS, HP, MODE, CS><<<p.n_slices, 64 * kWaves, 0, stream>>>(p);
@@ -1273,6 +1302,10 @@ hipError_t launch_mode(DecodeParams p, hipStream_t stream) {
     p.unit_wgs = cut.unit_wgs;
     p.axis_len = cut.axis.len;
     p.axis_rem = cut.axis.rem;
+    set_axis();
+    p.by_row_split = FastDiv::by(cut.row_split);
+    p.by_unit_wgs = FastDiv::by(std::max(cut.unit_wgs, 1));
+    p.by_steps = FastDiv::by(std::max((p.plan.tiles_a + kWaves - 1) / kWaves, 1));
     if (p.rows_for_tiles) {
         if (!two) return hipErrorInvalidValue;
         p.row_wgs = 0;

@@ -54,6 +54,20 @@ extern "C" int check_equal(int n, int sequences, int heads, int max_wgs, int row
 extern "C" int check_steps(const int32_t* steps, int sequences, int heads, int max_wgs, int rows, int* most) {
     return check(std::vector<int32_t>(steps, steps + sequences), heads, max_wgs, rows, most);
 }
+// quotients by d around every k-th multiple, and the owners of an axis: 0, or a dividend for which they differ from the operators'
+extern "C" int check_division(int d, int k) {
+    const FastDiv by = FastDiv::by(d);
+    for (int64_t m = 0; m <= 0x7fffffff; m += (int64_t)d * k)
+        for (int64_t n = m - 1; n <= m + 1; ++n)
+            if (n >= 0 && n <= 0x7fffffff && by.of((int)n) != (int)(n / d)) return (int)n;
+    if (by.of(0x7fffffff) != 0x7fffffff / d) return 0x7fffffff;
+    for (int rem = 0; d < 1000 && rem < 7; rem += 3) {
+        const StepAxis axis{d, rem};
+        for (int pos = 1; pos < 20 * d; ++pos)
+            if (axis.owner(pos) != axis.owner(pos, FastDiv::by(d + 1), FastDiv::by(d))) return pos;
+    }
+    return 0;
+}
 // the same for a batch of one length: tiles_a quantised tiles, row_tiles with fp16 rows
 extern "C" int check_uniform(int units, int tiles_a, int row_tiles, int resident, int stride, int limit, int own_launch, int* out) {
     UniformCut cut;
@@ -117,6 +131,12 @@ def plan(tmp_path_factory):
 
 # workgroups at once: a device with a few compute units, two or three workgroups on each of 256, the table's limit
 RESIDENT = (5, 64, 256, 512, 768, 4096)
+
+
+@pytest.mark.parametrize("d", [1, 2, 3, 5, 7, 31, 32, 33, 640, 641, 6700417, (1 << 30) - 1, 1 << 30, (1 << 30) + 1, (1 << 31) - 1])
+def test_division(plan, d):
+    """Every kind of divisor: powers of two and their neighbours, factors of 2^32 + 1, the largest."""
+    assert plan.check_division(d, max(1, 200003 // d)) == 0
 
 
 @pytest.mark.parametrize("rows", [2, 4, 6, 38, 64, 128])
