@@ -304,22 +304,23 @@ int kivi_batch_slice(const kivi_layout_t* layout, const kivi_cache_t* cache, int
  *   One pair of launches for the whole batch, whatever the lengths: when the matrix-core family
  * serves the layout (decode_path AUTO, MFMA or MFMA_TWO), every sequence has K and V split alike
  * (the WINDOW policy) with 1 to 512 fp16 rows (at most 16 tiles; fewer with many query heads per
- * kv-head), and at least one sequence has quantised tokens.  The fp16 rows of all sequences run in
- * one launch (which also appends the step's new tokens), the all-quantised parts in a second; both
- * read each sequence's counters from a copy in the workspace, and the shorter sequences' share of
- * the work partition is skipped (where that share is large, or the batch holds as many (batch,
- * kv-head) units as the chip holds wavefronts, and with 3 or more query heads per kv-head, the second launch
- * divides the tokens that are there evenly instead).  A step adds one launch per run of equal sequences that flush
- * in it (a sequence flushes every G-th step).
+ * kv-head), at least one sequence has quantised tokens, and the group size is 32 or there are two or
+ * more query heads per kv-head.  (A pair per 8 query heads per kv-head for 9 to 16 of them.)  The fp16
+ * rows of all sequences run in one launch (which also appends the step's new tokens), the
+ * all-quantised parts in a second, which divides the tokens that are there evenly (with one and
+ * two query heads per kv-head: where the sequences differ much, or the batch holds as many (batch, kv-head)
+ * units as the chip holds wavefronts).  With three or more query heads per kv-head (two with G > 32) and up to
+ * 192 sequences their counters travel in the first launch's arguments, and 32 tokens of a sequence that leave its window
+ * (G = 32) are quantised in that launch; otherwise a step adds one launch per run of equal sequences that
+ * flush in it (a sequence flushes every G-th step).
  *   Otherwise (another policy or family, empty slots, sequences without fp16 rows) the batch is
  * walked in runs of consecutive entries with equal state and each run is one call of the uniform
  * entry point on that part of the batch (same stream, same workspace): B different lengths take B
  * calls.  Entries without any token (all counts 0) are skipped by kivi_decode_attention_ragged and
  * their `out` rows are left untouched.  kivi_decode_launches_ragged tells which applies.
- *   The one-pair form copies the sequences' counters from host memory into the workspace with an
- * asynchronous copy on `stream` at every call (16 bytes per sequence): do not record these two entry
- * points into a HIP graph -- a replay would copy from host memory that is gone, and the counters
- * change from step to step anyway.
+ *   The counters are of the call: in the launch's arguments, or (more sequences, one or two query heads) in a copy from
+ * host memory into the workspace on `stream`.  Do not record these two entry points into a HIP graph:
+ * a replay would see the counters of the recorded step, or copy from host memory that is gone.
  *   k_new, v_new, q, out   the whole batch's tensors, as for the uniform entry points
  * Errors: as for the uniform entry points; entries before the failing run have been processed.
  */
@@ -332,8 +333,8 @@ int kivi_decode_attention_ragged(const kivi_layout_t* layout, const kivi_cache_t
 
 /*
  * Host helper: the number of kernel launches kivi_decode_attention_ragged enqueues for these
- * sequence states (no launch).  Two per group of up to 8 query heads per kv-head when the whole batch
- * goes through one pair of launches (see above); otherwise the sum over the runs of equal state.
+ * sequence states (no launch).  Two when the whole batch goes through one pair of launches (four with 9 to 16 query
+ * heads per kv-head, see above); otherwise the sum over the runs of equal state.
  * Errors: INVALID_ARG, UNSUPPORTED.
  */
 int kivi_decode_launches_ragged(const kivi_layout_t* layout, const kivi_seq_state_t* states, int32_t* launches);

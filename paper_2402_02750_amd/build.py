@@ -13,7 +13,8 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libkivi_hip.so")
 
 SOURCES = ["kivi_api.hip", "kivi_quantize.hip", "kivi_decode_valu.hip", "kivi_decode_mfma.hip",
-           "kivi_decode_tiles.hip", "kivi_decode_one.hip", "kivi_decode_rows.hip"]
+           "kivi_decode_tiles.hip", "kivi_decode_one.hip", "kivi_decode_rows.hip",
+           "kivi_ragged_rows.hip"]
 
 COMMON_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wextra",
@@ -27,6 +28,7 @@ PER_FILE_FLAGS = {
     # the quantiser's (x - z) / s must stay a subtract followed by a division
     "kivi_quantize.hip": ["-ffp-contract=off"],
     "kivi_decode_one.hip": ["-ffp-contract=off"],       # quantises the tokens of a flush
+    "kivi_ragged_rows.hip": ["-ffp-contract=off"],      # the same
 }
 
 

@@ -480,7 +480,10 @@ constexpr int kNotApplicable = 1;       // (internal) the fast path does not ser
 // ragged_launch then carries the plan out.
 struct RaggedPlan {
     DecodeParams p;             // all but the addresses and the query
-    bool tiles;                 // decode_tiles_kernel
+    bool tiles;                 // decode_tiles_kernel, and launch_ragged_rows before it
+    bool in_arguments;          // ... which takes the counters as arguments and writes the tables itself
+    int max_row_tiles;          // of any sequence
+    int units_per_sequence;     // decode_tiles_kernel
     size_t parts_offset;        // of the parts in the workspace
     // what the kernels read per call, int32: the sequences' counters (state_ints with the padding), then the work
     // tables, if any: the workgroups' (or slices') from state_ints on, the sequences' (units') from unit_table on
@@ -489,9 +492,23 @@ struct RaggedPlan {
     std::vector<int32_t> steps;
 };
 
+// decode_tiles_kernel serves the packed tiles: from three heads per kv-head on, and two with G > 32 (which the other kernels have no form
+// for); one pair of launches for up to 8 heads, a pair per 8 for up to 16, and from 17 on one pair with runs of 8 heads as units of
+// their own, as in a batch of one length.
+bool ragged_on_tiles(const kivi_layout_t* l) {
+    const int rep = l->n_q_heads / l->n_kv_heads;
+    return rep >= 3 || (rep == 2 && l->group > kTileTokens);
+}
+int ragged_runs(const kivi_layout_t* l) {
+    const int rep = l->n_q_heads / l->n_kv_heads;
+    return rep > 2 * kMaxRep ? ceil_div(rep, kMaxRep) : 1;
+}
+// whether batches of different lengths have one pair of launches for this group size and number of heads
+bool ragged_pair_serves(const kivi_layout_t* l) { return l->group == kTileTokens || ragged_on_tiles(l); }
+
 int ragged_plan(const kivi_layout_t* l, const kivi_seq_state_t* st, size_t workspace_bytes, RaggedPlan& plan) {
     if (decode_family(l) != KIVI_DECODE_MFMA || l->decode_path == KIVI_DECODE_MFMA_ONE) return kNotApplicable;
-    if (l->cap_q_tokens < kTileTokens || l->group != kTileTokens) return kNotApplicable;
+    if (l->cap_q_tokens < kTileTokens || !ragged_pair_serves(l)) return kNotApplicable;
     const int rep_total = l->n_q_heads / l->n_kv_heads;
     const int rep_launch = std::min(rep_total, kMaxRep);
     const int rep_variant = rep_launch <= 2 ? rep_launch : (rep_launch <= 4 ? 4 : 8);
@@ -552,22 +569,29 @@ int ragged_plan(const kivi_layout_t* l, const kivi_seq_state_t* st, size_t works
     // heads per kv-head, length spreads from +-12 % to 1 : 80: 0.70-0.96 of the padded plan's time above the
     // threshold, 1.05-1.7 below it).
     const int64_t wasted = units * ceil_div(max_tiles_a, 4) - total;
-    const bool tiles = plan.tiles = rep_total >= 3;
+    const bool tiles = plan.tiles = ragged_on_tiles(l);
+    plan.in_arguments = false;
+    plan.max_row_tiles = max_tiles_b;
+    p.head_groups = tiles ? ragged_runs(l) : 1;
     if (tiles) {
         // decode_tiles_kernel: the unit-major axis of four-tile steps (at least one per unit) in equal
         // intervals, one per resident workgroup, as far as the units' parts fit (kivi_tiles_plan.h).  (The table fits
         // where the slices' would: at most kMaxSlices entries, and 4 bytes per sequence instead of 8 per unit.)
         std::vector<int32_t>& steps = plan.steps;
         steps.resize((size_t)l->batch);
+        const int units_per_sequence = plan.units_per_sequence = l->n_kv_heads * p.head_groups;
         int64_t all = 0;
         for (int b = 0; b < l->batch; ++b) {
-            steps[(size_t)b] = std::max(1, ceil_div(st[b].n_kq / kTileTokens, kStepTiles));
-            all += (int64_t)steps[(size_t)b] * l->n_kv_heads;
+            steps[(size_t)b] = ragged_steps(st[b].n_kq);
+            all += (int64_t)steps[(size_t)b] * units_per_sequence;
         }
         if (all > 0x3fffffff) return kNotApplicable;
         const int stride = std::min(part_rows(l, workspace_bytes > parts_offset ? workspace_bytes - parts_offset : 0), tiles_max_parts(l->bits, rep_launch));
         if (stride < 2) return KIVI_ERR_WORKSPACE;
-        const RaggedCut cut = cut_ragged(steps, l->n_kv_heads, std::min(tiles_resident_ragged(l->bits, rep_launch), kMaxSlices), stride, tables);
+        const int resident = std::min(tiles_resident_ragged(l->bits, rep_launch, l->group > kTileTokens), kMaxSlices);
+        RaggedCut cut = ragged_axis(steps, units_per_sequence, resident, stride);
+        plan.in_arguments = l->batch <= kInlineSequences && !cut.whole_units;
+        if (!plan.in_arguments) cut = cut_ragged(steps, units_per_sequence, resident, stride, tables);
         p.axis_len = cut.axis.len;
         p.axis_rem = cut.axis.rem;
         plan.unit_table = state_ints + (size_t)cut.workgroups * RaggedCut::kWords;
@@ -620,12 +644,12 @@ int ragged_plan(const kivi_layout_t* l, const kivi_seq_state_t* st, size_t works
     if (parts_offset + rows * (kHeadDim + 2) * sizeof(float) > workspace_bytes) return KIVI_ERR_WORKSPACE;
     p.ragged_min_tiles = min_tiles_a;
     p.rep_variant = rep_launch;
-    p.head_groups = 1;
     return KIVI_OK;
 }
 
+// flush: the n_flush sequences whose last quantised tile is still in the rings (only with plan.in_arguments).
 int ragged_launch(const kivi_layout_t* l, const kivi_cache_t* c, const RaggedPlan& plan, const void* q, float softmax_scale, float* out,
-                  void* workspace, const void* k_new, const void* v_new, void* stream) {
+                  void* workspace, const void* k_new, const void* v_new, void* stream, const uint8_t* flush = nullptr, int n_flush = 0) {
     DecodeParams p = plan.p;
     p.k_codes = static_cast<const uint32_t*>(c->k_codes);
     p.k_scale = static_cast<const __half*>(c->k_scale);
@@ -649,17 +673,28 @@ int ragged_launch(const kivi_layout_t* l, const kivi_cache_t* c, const RaggedPla
     }
     p.part_o = reinterpret_cast<float*>(ws + plan.parts_offset);
     p.part_ml = p.part_o + (size_t)l->batch * l->n_q_heads * p.part_stride * kHeadDim;
-    if (hipMemcpyAsync(dev_state, plan.tables.data(), (plan.unit_table ? plan.tables.size() : (size_t)l->batch * 4) * sizeof(int32_t),
+    const RaggedTables device_tables{dev_state, dev_state + plan.unit_table, dev_state + plan.state_ints, p.n_slices, p.axis_len, p.axis_rem, plan.units_per_sequence};
+    if (!plan.in_arguments && hipMemcpyAsync(dev_state, plan.tables.data(), (plan.unit_table ? plan.tables.size() : (size_t)l->batch * 4) * sizeof(int32_t),
                        hipMemcpyHostToDevice, hs) != hipSuccess)
         return KIVI_ERR_HIP;
     const int rep_total = l->n_q_heads / l->n_kv_heads;
-    for (int h0 = 0; h0 < rep_total; h0 += kMaxRep) {
+    for (int h0 = 0; h0 < rep_total; h0 += p.head_groups > 1 ? rep_total : kMaxRep) {
         p.q_head0 = h0;
         p.rep_here = std::min(kMaxRep, rep_total - h0);
-        const hipError_t e = plan.tiles ? launch_decode_tiles(p, hs) : launch_decode_mfma(p, hs);
+        hipError_t e = hipSuccess;
+        if (plan.tiles) {
+            DecodeParams rows = p;
+            if (p.head_groups > 1) rows.rep_here = rep_total;
+            e = launch_ragged_rows(rows, plan.max_row_tiles, plan.in_arguments ? plan.tables.data() : nullptr, flush, h0 == 0 ? n_flush : 0,
+                                   plan.in_arguments ? &device_tables : nullptr, hs);
+            p.k_new = p.v_new = nullptr;
+            if (e == hipSuccess) e = launch_decode_tiles(p, hs);
+        } else {
+            e = launch_decode_mfma(p, hs);
+            p.k_new = p.v_new = nullptr;
+        }
         if (e == hipErrorNotSupported) return KIVI_ERR_UNSUPPORTED;
         if (int s2 = hip_status(e)) return s2;
-        p.k_new = p.v_new = nullptr;
     }
     return KIVI_OK;
 }
@@ -706,19 +741,25 @@ int ragged_step_fast(const kivi_layout_t* l, const kivi_cache_t* c, kivi_seq_sta
     // (a step has always asked for room for the longest sequence's splits, also where the plan makes do with less)
     const size_t rows = (size_t)l->batch * l->n_q_heads * (ceil_div(plan.p.plan.tiles_a, plan.p.plan.tiles_per_split_a) + 1);
     if (plan.parts_offset + rows * (kHeadDim + 2) * sizeof(float) > workspace_bytes) return KIVI_ERR_WORKSPACE;
-    // pass 2: the flushes, one launch per run of consecutive sequences with equal state that flush
+    // pass 2: the flushes.  One tile of a sequence (G = 32), which is what every flush after the first is, rides with the fp16 rows
+    // where those have the counters as arguments; others take a launch per run of consecutive sequences with equal state.
     hipStream_t hs = static_cast<hipStream_t>(stream);
+    const bool ride = plan.in_arguments && l->group == kTileTokens;
+    uint8_t riding[kInlineSequences];
+    int n_riding = 0;
     for (int b0 = 0; b0 < l->batch;) {
         int b1 = b0 + 1;
         while (b1 < l->batch && same_state(states[b0], states[b1])) ++b1;
-        if (nks[b0] > 0 || nvs[b0] > 0) {
+        if (ride && nks[b0] == kTileTokens && nvs[b0] == kTileTokens) {
+            for (int b = b0; b < b1; ++b) riding[n_riding++] = (uint8_t)b;
+        } else if (nks[b0] > 0 || nvs[b0] > 0) {
             kivi_layout_t sl; kivi_cache_t sc;
             if (int s = kivi_batch_slice(l, c, b0, b1 - b0, &states[b0], &sl, &sc)) return s;
             if (int s = enqueue_flush(&sl, &sc, nks[b0], nvs[b0], hs)) return s;
         }
         b0 = b1;
     }
-    if (int s = ragged_launch(l, c, plan, q, softmax_scale, out, workspace, k_new, v_new, stream)) return s;
+    if (int s = ragged_launch(l, c, plan, q, softmax_scale, out, workspace, k_new, v_new, stream, riding, n_riding)) return s;
     for (int b = 0; b < l->batch; ++b) states[b] = after[b];
     return KIVI_OK;
 }
@@ -1054,10 +1095,9 @@ int kivi_decode_launches_ragged(const kivi_layout_t* l, const kivi_seq_state_t* 
     if (!states || !launches) return KIVI_ERR_INVALID_ARG;
     const int path = decode_family(l);
     const int rep_total = l->n_q_heads / l->n_kv_heads;
-    const int head_groups = ceil_div(rep_total, kMaxRep);
+    const int head_groups = ragged_runs(l) > 1 ? 1 : ceil_div(rep_total, kMaxRep);
     // the conditions of ragged_plan
-    bool fast = path == KIVI_DECODE_MFMA && l->decode_path != KIVI_DECODE_MFMA_ONE && l->cap_q_tokens >= kTileTokens &&
-                l->group == kTileTokens;
+    bool fast = path == KIVI_DECODE_MFMA && l->decode_path != KIVI_DECODE_MFMA_ONE && l->cap_q_tokens >= kTileTokens && ragged_pair_serves(l);
     int max_tiles_a = 0, max_tiles_b = 0;
     for (int b = 0; b < l->batch; ++b) {
         const kivi_seq_state_t& x = states[b];

@@ -142,7 +142,7 @@ __device__ __forceinline__ void device_store(float* p, float2 v) {
     __hip_atomic_store(reinterpret_cast<uint64_t*>(p), __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Wave-uniform read of a table the host made, through the scalar cache: a vector load would return
+// Wave-uniform read of a table that an earlier launch made, through the scalar cache: a vector load would return
 // behind all copies in flight.
 __device__ __forceinline__ int table(const int32_t* base, int i) {
     return reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(base))[i];
@@ -234,7 +234,7 @@ struct TilesParams : DecodeParams {
 
 // kWhole: K and V split at the same token, so a tile is all quantised or all fp16; kMixed: any split.
 // kQuantisedRagged: the all-quantised tiles of a batch of sequences of different lengths (work cut by tables that
-// the host made); part 0 of every unit is what the fp16-row launch left.
+// launch_ragged_rows made or the host did); part 0 of every unit is what the fp16-row launch left.
 // kFlush: as kWhole, in a step in which a tile leaves the window (plan.tiles_a is without it, the first of the row workgroups' tiles).
 constexpr int kWhole = 0, kMixed = 1, kQuantisedRagged = 2, kFlush = 3;
 
@@ -293,11 +293,11 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
     const int unit_wgs = p.unit_wgs;
     // steps of a unit, and where they begin on the axis
     auto steps_of = [&](int u) -> int {
-        if constexpr (kRagged) return max((table(p.seq_state, 4 * batch_of(u)) / kTileTokens + kWaves - 1) / kWaves, 1);
+        if constexpr (kRagged) return ragged_steps(table(p.seq_state, 4 * batch_of(u)));
         else return n_a;                                               // (a sequence without quantised tiles has one empty step)
     };
     auto axis_start = [&](int u) -> int {
-        if constexpr (kRagged) return table(p.unit_parts, batch_of(u)) + (u - batch_of(u) * p.n_kv_heads) * steps_of(u);
+        if constexpr (kRagged) return table(p.unit_parts, batch_of(u)) + (u - batch_of(u) * p.n_kv_heads * n_runs) * steps_of(u);
         else return u * n_a;
     };
     // the workgroup's steps [j0, j1) in unit u, visited in an order rotated by the unit, so that workgroups in
@@ -931,7 +931,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
                 const int64_t prow = (row0 + hh) * stride;
                 if (parts == 1) {
                     if constexpr (kRagged) {
-                        const float mr = sm_part_ml[hh][0] * kLog2e, mn = fmaxf(m, mr);        // the fp16-row launch's part
+                        const float mr = sm_part_ml[hh][0], mn = fmaxf(m, mr);        // the fp16-row launch's part
                         const float f0 = __builtin_amdgcn_exp2f(m - mn), f1 = __builtin_amdgcn_exp2f(mr - mn);
                         oo.x = fmaf(oo.x, f0, sm_part[hh][c] * f1);
                         oo.y = fmaf(oo.y, f0, sm_part[hh][c + 1] * f1);
@@ -980,7 +980,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
                         if (32 * k < parts)
                             v[k] = __builtin_bit_cast(float2, __hip_atomic_load(reinterpret_cast<const uint64_t*>(ml + 2 * min(sp + 32 * k, parts - 1)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
                     }
-                    float m = kRagged ? sm_part_ml[min(sh, live - 1)][0] * kLog2e : -INFINITY;
+                    float m = kRagged ? sm_part_ml[min(sh, live - 1)][0] : -INFINITY;
 #pragma unroll
                     for (int k = 0; k < kStat; ++k) m = fmaxf(m, v[k].x);
 #pragma unroll
@@ -999,7 +999,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
                     for (int d = 1; d < 32; d <<= 1) lsum += __shfl_xor(lsum, d);
                     if (sp == 0) {
                         if constexpr (kRagged) {
-                            const float w = __builtin_amdgcn_exp2f(sm_part_ml[min(sh, live - 1)][0] * kLog2e - m);
+                            const float w = __builtin_amdgcn_exp2f(sm_part_ml[min(sh, live - 1)][0] - m);
                             lsum = fmaf(sm_part_ml[min(sh, live - 1)][1], w, lsum);
                             sm_ml[1][sh][0] = w;
                         }
@@ -1325,10 +1325,7 @@ hipError_t launch_decode_tiles(DecodeParams p, hipStream_t stream) {
     if (p.head_groups < 1 || p.rep_here < 1 || (p.head_groups > 1 && (p.q_head0 != 0 || p.head_groups * p.rep_here < rep_total || (p.head_groups - 1) * p.rep_here >= rep_total)))
         return hipErrorInvalidValue;
     if (p.seq_state) {
-        // sequences of different lengths: residual_rows_kernel takes each one's fp16 rows (and appends the new tokens)
-        if (p.head_groups != 1 || p.two_launches == 0) return hipErrorInvalidValue;
-        if (hipError_t e = launch_residual_rows(p, stream); e != hipSuccess) return e;
-        p.k_new = p.v_new = nullptr;
+        if (p.k_new || p.flush_k || p.two_launches == 0) return hipErrorInvalidValue;      // (launch_ragged_rows goes before)
     }
     const bool flush_inside = p.flush_k && p.flush_v && p.two_launches == 0;
     if (flush_inside) {
@@ -1347,7 +1344,7 @@ hipError_t launch_decode_tiles(DecodeParams p, hipStream_t stream) {
     with_tiles_variant(p.bits, p.rep_here, [&](auto b, auto h) {
         constexpr int B = decltype(b)::value, H = decltype(h)::value;
         const bool cs = p.kg_shift > 0;
-        if (p.seq_state) e = cs ? hipErrorNotSupported : launch_mode<B, H, kQuantisedRagged, false>(p, stream);
+        if (p.seq_state) e = cs ? launch_mode<B, H, kQuantisedRagged, true>(p, stream) : launch_mode<B, H, kQuantisedRagged, false>(p, stream);
         else if (flush_inside) e = launch_mode<B, H, kFlush, false>(p, stream);
         else if (p.n_kq != p.n_vq) e = cs ? launch_mode<B, H, kMixed, true>(p, stream) : launch_mode<B, H, kMixed, false>(p, stream);
         else e = cs ? launch_mode<B, H, kWhole, true>(p, stream) : launch_mode<B, H, kWhole, false>(p, stream);
@@ -1361,9 +1358,12 @@ int tiles_max_parts(int bits, int rep) {
     return n;
 }
 
-int tiles_resident_ragged(int bits, int rep) {
+int tiles_resident_ragged(int bits, int rep, bool large_groups) {
     int n = 0;
-    with_tiles_variant(bits, rep, [&](auto b, auto h) { n = resident_workgroups<decltype(b)::value, decltype(h)::value, kQuantisedRagged, false>(); });
+    with_tiles_variant(bits, rep, [&](auto b, auto h) {
+        constexpr int B = decltype(b)::value, H = decltype(h)::value;
+        n = large_groups ? resident_workgroups<B, H, kQuantisedRagged, true>() : resident_workgroups<B, H, kQuantisedRagged, false>();
+    });
     return n;
 }
 

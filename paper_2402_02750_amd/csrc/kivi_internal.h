@@ -153,11 +153,24 @@ constexpr int kTilesMaxParts = 128;    // decode_tiles_kernel: parts of one (bat
 // decode_tiles_kernel (kivi_decode_tiles.hip); with two_launches > 0 the fp16-row launch goes before it
 hipError_t launch_decode_tiles(DecodeParams p, hipStream_t stream);
 // workgroups the device holds of it for a batch of different lengths
-int tiles_resident_ragged(int bits, int rep);
+int tiles_resident_ragged(int bits, int rep, bool large_groups);
 int tiles_max_parts(int bits, int rep);       // parts of one unit that it merges, at most
 // decode_one_kernel (kivi_decode_one.hip): one query head per kv-head, n_kq >= n_vq, one launch
 hipError_t launch_decode_one(const DecodeParams& p, hipStream_t stream);
 hipError_t launch_residual_rows(const DecodeParams& p, hipStream_t stream);
+// Batches of different lengths before decode_tiles_kernel: fp16 rows, append, flush and tables (kivi_ragged_rows.hip).
+// What the kernel writes for the second launch, in device memory: every sequence's counters (as seq_state), the steps before it, and the
+// intervals of the axis of steps.
+struct RaggedTables {
+    int32_t *seq_state, *before, *intervals;
+    int32_t n_intervals, axis_len, axis_rem, units_per_sequence;
+};
+constexpr int kInlineSequences = 192;  // sequences whose counters fit the kernel's arguments (4096 bytes)
+// seq: the counters in host memory, at most kInlineSequences of them, `flush` the n_flush sequences whose last quantised tile (G = 32) is still in
+// the rings; null: the counters are in p.seq_state already, nothing is flushed and no table is written.  max_tiles: of fp16 rows, of
+// any sequence.
+hipError_t launch_ragged_rows(const DecodeParams& p, int max_tiles, const int32_t* seq, const uint8_t* flush, int n_flush, const RaggedTables* tables,
+                              hipStream_t stream);
 // the same launch with extra workgroups that quantise the key group(s) and value tokens of a residual
 // flush (G = 32 only: hipErrorNotSupported otherwise, nothing launched)
 hipError_t launch_rows_and_flush(const DecodeParams& p, const QuantKeyParams& kp, const QuantValueParams& vp, hipStream_t stream);

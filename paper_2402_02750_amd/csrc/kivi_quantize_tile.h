@@ -357,24 +357,38 @@ __device__ __forceinline__ void quantize_value_tile(const ValueRow (&x)[8], int 
         }
 }
 
+// The 32 rows before ring slot `start` (the first one after them), channels 2 lane, 2 lane + 1
+template <class Row>
+__device__ __forceinline__ void load_key_rows_before(const DecodeParams& p, int64_t unit, int start, int lane, Row (&x)[kTileTokens]) {
+    const int first = start - kTileTokens, k0 = first < 0 ? first + p.cap_r : first;
+    const char* kr = reinterpret_cast<const char*>(p.k_resid + unit * p.cap_r * kHeadDim);
+#pragma unroll
+    for (int t = 0; t < kTileTokens; ++t) {
+        const int i = k0 + t;
+        x[t] = *reinterpret_cast<const half2v*>(kr + (uint32_t)((i >= p.cap_r ? i - p.cap_r : i) * (kHeadDim * 2) + lane * 4));
+    }
+}
+// ... rows 8 (lane / 16) + i, channels 8 (lane % 16) ..
+__device__ __forceinline__ void load_value_rows_before(const DecodeParams& p, int64_t unit, int start, int lane, ValueRow (&y)[8]) {
+    const int first = start - kTileTokens, v0 = first < 0 ? first + p.cap_r : first;
+    const __half* vr = p.v_resid + unit * p.cap_r * kHeadDim + (lane & 15) * 8;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int at = v0 + (lane >> 4) * 8 + i;
+        y[i].v4 = *reinterpret_cast<const uint4v*>(vr + (at >= p.cap_r ? at - p.cap_r : at) * kHeadDim);
+    }
+}
+
 // The tile that leaves the window in a decoding step (K and V split alike, G = 32): the 32 tokens before the window, out of the rings
 // of `unit` into a slot in LDS (key codes, value codes, key scales, key zero-points, value scales, value zero-points) and, with
 // `store`, into tile `at` of the packed arrays.  One wavefront; wave_lds_sync() or the like has to follow.
 template <int BITS>
 __device__ __forceinline__ void flush_tile(const DecodeParams& p, int64_t unit, int64_t at, int lane, unsigned char* slot, bool store) {
     constexpr int kCodeBytes = kTileTokens * kHeadDim * BITS / 8;
-    const int n = lane & 15, kb = lane >> 4;
     half2v x[kTileTokens];
     ValueRow y[8];
-    auto wrap = [&](int i) -> int { return i >= p.cap_r ? i - p.cap_r : i; };
-    const int fk = p.k_r_start - kTileTokens, fv = p.v_r_start - kTileTokens;
-    const int k0 = fk < 0 ? fk + p.cap_r : fk, v0 = fv < 0 ? fv + p.cap_r : fv;
-    const char* kr = reinterpret_cast<const char*>(p.k_resid + unit * p.cap_r * kHeadDim);
-    const __half* vr = p.v_resid + unit * p.cap_r * kHeadDim + n * 8;
-#pragma unroll
-    for (int t = 0; t < kTileTokens; ++t) x[t] = *reinterpret_cast<const half2v*>(kr + (uint32_t)(wrap(k0 + t) * (kHeadDim * 2) + lane * 4));
-#pragma unroll
-    for (int i = 0; i < 8; ++i) y[i].v4 = *reinterpret_cast<const uint4v*>(vr + wrap(v0 + kb * 8 + i) * kHeadDim);
+    load_key_rows_before(p, unit, p.k_r_start, lane, x);
+    load_value_rows_before(p, unit, p.v_r_start, lane, y);
     uint32_t* kcodes = const_cast<uint32_t*>(p.k_codes) + at * (kCodeBytes / 4);
     uint32_t* vcodes = const_cast<uint32_t*>(p.v_codes) + at * (kCodeBytes / 4);
     uint32_t* lds = reinterpret_cast<uint32_t*>(slot);
@@ -405,6 +419,32 @@ __device__ __forceinline__ void flush_tile(const DecodeParams& p, int64_t unit, 
             if (store) vcodes[i] = w;
             lds[kCodeBytes / 4 + i] = w;
         });
+}
+
+// Keys and values of such a tile into the packed arrays alone, one wavefront each; start: the rings' first slots after the flush
+template <int BITS>
+__device__ __forceinline__ void flush_keys(const DecodeParams& p, int64_t unit, int64_t at, int start, int lane) {
+    half2v x[kTileTokens];
+    load_key_rows_before(p, unit, start, lane, x);
+    uint32_t* codes = const_cast<uint32_t*>(p.k_codes) + at * (kTileTokens * kHeadDim * BITS / 32);
+    quantize_key_tile<BITS>(x, lane,
+        [&](half2v s2, half2v z2) {
+            *reinterpret_cast<half2v*>(const_cast<__half*>(p.k_scale) + at * kHeadDim + 2 * lane) = s2;
+            *reinterpret_cast<half2v*>(const_cast<__half*>(p.k_zero) + at * kHeadDim + 2 * lane) = z2;
+        },
+        [&](int i, uint32_t w) { codes[i] = w; });
+}
+template <int BITS>
+__device__ __forceinline__ void flush_values(const DecodeParams& p, int64_t unit, int64_t at, int start, int lane) {
+    ValueRow y[8];
+    load_value_rows_before(p, unit, start, lane, y);
+    uint32_t* codes = const_cast<uint32_t*>(p.v_codes) + at * (kTileTokens * kHeadDim * BITS / 32);
+    quantize_value_tile<BITS>(y, lane,
+        [&](int i, _Float16 s, _Float16 z) {
+            reinterpret_cast<_Float16*>(const_cast<__half*>(p.v_scale))[at * 128 + i] = s;
+            reinterpret_cast<_Float16*>(const_cast<__half*>(p.v_zero))[at * 128 + i] = z;
+        },
+        [&](int i, uint32_t w) { codes[i] = w; });
 }
 
 }  // namespace tile

@@ -62,9 +62,13 @@ struct RaggedCut {
     static constexpr int kWords = 4;
 };
 
-// steps[b]: steps of each of the n_kv_heads units of sequence b (at least 1); rows: parts per head that fit, row 0
-// included (at least 2).  Appends the table to `out`.
-inline RaggedCut cut_ragged(const std::vector<int32_t>& steps, int n_kv_heads, int64_t max_workgroups, int rows, std::vector<int32_t>& out) {
+// a unit's steps, of a sequence with n_q quantised tokens (with none: one empty step)
+KIVI_HOST_DEVICE int ragged_steps(int n_q) {
+    const int tiles = n_q / 32, steps = (tiles + kStepTiles - 1) / kStepTiles;
+    return steps < 1 ? 1 : steps;
+}
+// The intervals' workgroups and axis (no table): see cut_ragged.
+inline RaggedCut ragged_axis(const std::vector<int32_t>& steps, int n_kv_heads, int64_t max_workgroups, int rows) {
     RaggedCut cut;
     const int max_parts = rows - 1;
     int64_t total = 0, max_steps = 1;
@@ -80,6 +84,28 @@ inline RaggedCut cut_ragged(const std::vector<int32_t>& steps, int n_kv_heads, i
     if (!cut.whole_units && cut.workgroups > max_parts)
         cut.workgroups = std::max<int64_t>(max_parts, std::min(cut.workgroups, total / shortest_interval(max_steps, max_parts)));
     cut.axis = cut.whole_units ? StepAxis{0x3fffffff, 0} : StepAxis{(int32_t)(total / cut.workgroups), (int32_t)(total % cut.workgroups)};
+    return cut;
+}
+// Interval g of a cut that is not of whole units, from each sequence's steps and the steps before it (units_per_sequence times the
+// former, added up): {first unit, first step in it, steps, 0}.
+struct RaggedInterval { int32_t unit, first, steps, none; };
+KIVI_HOST_DEVICE RaggedInterval ragged_interval(const int32_t* before, const int32_t* steps, int sequences, int units_per_sequence, StepAxis axis, int g) {
+    const int start = axis.start(g);
+    int lo = 0, hi = sequences;                        // before[lo] <= start < before[hi]
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) / 2;
+        if (before[mid] <= start) lo = mid;
+        else hi = mid;
+    }
+    const int into = start - before[lo], unit = into / steps[lo];
+    return RaggedInterval{lo * units_per_sequence + unit, into - unit * steps[lo], axis.start(g + 1) - start, 0};
+}
+
+// steps[b]: steps of each of the n_kv_heads units of sequence b (at least 1); rows: parts per head that fit, row 0
+// included (at least 2).  Appends the table to `out`.
+inline RaggedCut cut_ragged(const std::vector<int32_t>& steps, int n_kv_heads, int64_t max_workgroups, int rows, std::vector<int32_t>& out) {
+    const RaggedCut cut = ragged_axis(steps, n_kv_heads, max_workgroups, rows);
+    const int64_t units = (int64_t)steps.size() * n_kv_heads;
 
     const size_t base = out.size();
     out.resize(base + (size_t)cut.workgroups * RaggedCut::kWords + steps.size(), 0);

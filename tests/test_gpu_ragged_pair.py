@@ -1,0 +1,89 @@
+"""Batches of different lengths with two and more query heads per kv-head: the first launch (fp16 rows, flush, tables)
+and the second against the run-by-run vector path, which has kernels of its own for all of it."""
+import pytest
+
+import gpu_harness as gh
+from paper_2402_02750_amd import kivi
+
+pytestmark = pytest.mark.gpu
+
+# (query heads, kv-heads, bits, G, R, tokens of every sequence, steps, launches)
+LONG = [31, 64, 95, 96, 127, 128, 159, 222, 223, 1000, 4127]
+CASES = [
+    (8, 2, 2, 32, 64, LONG, 70, 2),                     # every sequence flushes twice, the rings (96 slots) wrap
+    (24, 4, 4, 32, 64, LONG, 70, 2),                    # six heads, 4 bits
+    (3, 1, 2, 32, 0, [40, 33, 500], 3, None),           # no window: the flush takes the new token itself
+    (4, 2, 2, 64, 128, [191, 500, 64, 1900], 66, 2),    # two heads, G = 64
+    (12, 2, 4, 128, 128, [300, 255, 1, 2500], 3, 2),    # six heads, G = 128; a sequence without quantised tokens
+    (8, 1, 2, 64, 192, [333, 3000], 3, 2),              # eight heads, seven tiles of rows
+    (10, 1, 2, 32, 96, [127, 700], 3, 4),               # ten heads: a pair of launches per eight
+    (17, 1, 4, 32, 96, [127, 700, 64], 34, 2),          # seventeen: runs of eight as units, the rows in two
+    (71, 1, 2, 64, 128, [900, 191], 3, 2),
+    (128, 1, 2, 32, 64, [400, 95], 2, 2),
+    (9, 3, 2, 32, 480, [520, 600, 2000], 3, 2),         # a window of sixteen tiles
+    (6, 2, 4, 32, 32, [63 + i for i in range(192)], 2, 2),      # as many sequences as the arguments hold: flushes among them
+    (6, 2, 2, 32, 32, [63 + i for i in range(193)], 2, 2),      # one more
+]
+
+
+@pytest.mark.parametrize("hq,hkv,bits,group,residual,tokens,steps,launches", CASES)
+def test_pair(hq, hkv, bits, group, residual, tokens, steps, launches):
+    """Outputs within the repository's tolerance, every byte of the cache the same."""
+    torch = gh.require_gpu()
+    print(f"case ragged pair hq={hq} hkv={hkv} bits={bits} G={group} R={residual} {len(tokens)} sequences", flush=True)
+    batch, total = len(tokens), max(tokens) + steps
+    gen = torch.Generator(device="cuda").manual_seed(hq + bits)
+    k, v = (torch.randn(batch, hkv, total, 128, dtype=torch.float16, device="cuda", generator=gen) for _ in range(2))
+    k[..., 7] *= 9
+    at = {}
+    for path in (kivi.KIVI_DECODE_AUTO, kivi.KIVI_DECODE_VALU):
+        layout = kivi.make_layout(batch, hq, hkv, bits, residual, gh.round_up(total, group), gh.round_up(residual + group, 32), group=group,
+                                  decode_path=path)
+        cache = kivi.Cache(layout)
+        for buf in cache.buffers.values():
+            buf.zero_()
+        states = kivi.make_states(batch)
+        for b, n in enumerate(tokens):
+            part = kivi.CacheSlice(cache, b, 1)
+            kivi.kivi_prefill(part.layout, k[b:b + 1], v[b:b + 1], n, part)
+            states[b] = part.state()
+        at[path] = layout, cache, states
+    for step in range(steps):
+        rows = torch.tensor([n + step for n in tokens], device="cuda")
+        new = [x[torch.arange(batch, device="cuda"), :, rows].contiguous() for x in (k, v)]
+        q = torch.randn(batch, hq, 128, dtype=torch.float16, device="cuda", generator=gen)
+        outs = []
+        for layout, cache, states in at.values():
+            out = torch.full((batch, hq, 128), float("nan"), dtype=torch.float32, device="cuda")
+            kivi.kivi_decode_step_ragged(layout, cache, states, *new, q, 128 ** -0.5, out)
+            outs.append(out)
+        torch.cuda.synchronize()
+        gh.check_close(outs[0].cpu().numpy(), outs[1].cpu().numpy(), f"step {step}")
+        (l0, c0, s0), (_, c1, s1) = at.values()
+        assert bytes(s0) == bytes(s1), f"step {step}"
+        for name in c0.buffers:
+            assert torch.equal(c0.buffers[name], c1.buffers[name]), f"step {step}: {name}"
+        if launches:
+            assert kivi.kivi_decode_launches_ragged(l0, s0) == launches
+
+
+def test_pair_is_deterministic():
+    """The same step on copies of one cache: the same bytes (sums in the same order, whichever workgroup comes last)."""
+    torch = gh.require_gpu()
+    print("case ragged pair: repetitions", flush=True)
+    tokens, hq, hkv = [95, 700, 223, 3000, 5000], 16, 4
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    k, v = (torch.randn(5, hkv, max(tokens) + 1, 128, dtype=torch.float16, device="cuda", generator=gen) for _ in range(2))
+    q, kn, vn = (torch.randn(5, h, 128, dtype=torch.float16, device="cuda", generator=gen) for h in (hq, hkv, hkv))
+    layout = kivi.make_layout(5, hq, hkv, 2, 64, 5024, 96)
+    outs = []
+    for _ in range(6):
+        cache, states = kivi.Cache(layout), kivi.make_states(5)
+        for b, n in enumerate(tokens):
+            part = kivi.CacheSlice(cache, b, 1)
+            kivi.kivi_prefill(part.layout, k[b:b + 1], v[b:b + 1], n, part)
+            states[b] = part.state()
+        outs.append(torch.empty(5, hq, 128, dtype=torch.float32, device="cuda"))
+        kivi.kivi_decode_step_ragged(layout, cache, states, kn, vn, q, 128 ** -0.5, outs[-1])
+    torch.cuda.synchronize()
+    assert all(torch.equal(outs[0], o) for o in outs[1:])

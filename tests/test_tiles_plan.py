@@ -54,6 +54,23 @@ extern "C" int check_equal(int n, int sequences, int heads, int max_wgs, int row
 extern "C" int check_steps(const int32_t* steps, int sequences, int heads, int max_wgs, int rows, int* most) {
     return check(std::vector<int32_t>(steps, steps + sequences), heads, max_wgs, rows, most);
 }
+// the device's way to an interval of a ragged cut against the host's table: 0, or the interval + 1
+extern "C" int check_intervals(const int32_t* steps, int sequences, int units, int max_wgs, int rows) {
+    const std::vector<int32_t> all(steps, steps + sequences);
+    std::vector<int32_t> out, before(sequences);
+    const RaggedCut cut = cut_ragged(all, units, max_wgs, rows, out), axis = ragged_axis(all, units, max_wgs, rows);
+    if (cut.whole_units || axis.workgroups != cut.workgroups || axis.axis.len != cut.axis.len || axis.axis.rem != cut.axis.rem) return -1;
+    for (int b = 1; b < sequences; ++b) before[b] = before[b - 1] + all[b - 1] * units;
+    for (int b = 0; b < sequences; ++b)
+        if (out[cut.workgroups * 4 + b] != before[b]) return -2;
+    for (int g = 0; g < cut.workgroups; ++g) {
+        const RaggedInterval x = ragged_interval(before.data(), steps, sequences, units, cut.axis, g);
+        if (x.unit != out[4 * g] || x.first != out[4 * g + 1] || x.steps != out[4 * g + 2]) return g + 1;
+    }
+    for (int n = 0; n < 1000; ++n)
+        if (ragged_steps(n) != std::max(1, (n / 32 + 3) / 4)) return -3;
+    return 0;
+}
 // quotients by d around every k-th multiple, and the owners of an axis: 0, or a dividend for which they differ from the operators'
 extern "C" int check_division(int d, int k) {
     const FastDiv by = FastDiv::by(d);
@@ -131,6 +148,15 @@ def plan(tmp_path_factory):
 
 # workgroups at once: a device with a few compute units, two or three workgroups on each of 256, the table's limit
 RESIDENT = (5, 64, 256, 512, 768, 4096)
+
+
+@pytest.mark.parametrize("steps", [[1], [20, 20, 20, 99], [1, 300, 1, 1], [2047] * 3, [1] * 192, list(range(1, 193)), list(range(192, 0, -1))])
+def test_intervals(plan, steps):
+    arr = (ctypes.c_int32 * len(steps))(*steps)
+    for units in (1, 2, 9, 40):
+        for rows in (3, 4, 38, 128):
+            for wgs in RESIDENT:
+                assert plan.check_intervals(arr, len(steps), units, wgs, rows) == 0, f"{units} units, {wgs} workgroups, {rows} rows"
 
 
 @pytest.mark.parametrize("d", [1, 2, 3, 5, 7, 31, 32, 33, 640, 641, 6700417, (1 << 30) - 1, 1 << 30, (1 << 30) + 1, (1 << 31) - 1])
