@@ -304,22 +304,21 @@ int kivi_batch_slice(const kivi_layout_t* layout, const kivi_cache_t* cache, int
  *   One pair of launches for the whole batch, whatever the lengths: when the matrix-core family
  * serves the layout (decode_path AUTO, MFMA or MFMA_TWO), every sequence has K and V split alike
  * (the WINDOW policy) with 1 to 512 fp16 rows (at most 16 tiles; fewer with many query heads per
- * kv-head), at least one sequence has quantised tokens, and the group size is 32 or there are two or
- * more query heads per kv-head.  (A pair per 8 query heads per kv-head for 9 to 16 of them.)  The fp16
- * rows of all sequences run in one launch (which also appends the step's new tokens), the
- * all-quantised parts in a second, which divides the tokens that are there evenly (with one and
- * two query heads per kv-head: where the sequences differ much, or the batch holds as many (batch, kv-head)
- * units as the chip holds wavefronts).  With three or more query heads per kv-head (two with G > 32) and up to
- * 192 sequences their counters travel in the first launch's arguments, and 32 tokens of a sequence that leave its window
- * (G = 32) are quantised in that launch; otherwise a step adds one launch per run of equal sequences that
- * flush in it (a sequence flushes every G-th step).
+ * kv-head), and at least one sequence has quantised tokens.  (A pair per 8 query heads per kv-head for 9 to 16
+ * of them.)  Up to 192 sequences' counters travel in the first launch's arguments, and it quantises the 32
+ * tokens that leave a sequence's window (G = 32).  With two and more query heads per kv-head it also
+ * attends to the fp16 rows of all sequences and appends the step's new tokens; the second launch has the packed
+ * tokens, divided evenly.  With one query head per kv-head the second launch has the rows, the packed tokens and the
+ * append.  More sequences' counters are copied into the workspace (one query head per kv-head: the second launch
+ * alone then), and what is not quantised in the first launch adds one launch per run of equal sequences that flush in the
+ * step (a sequence flushes every G-th step).
  *   Otherwise (another policy or family, empty slots, sequences without fp16 rows) the batch is
  * walked in runs of consecutive entries with equal state and each run is one call of the uniform
  * entry point on that part of the batch (same stream, same workspace): B different lengths take B
  * calls.  Entries without any token (all counts 0) are skipped by kivi_decode_attention_ragged and
  * their `out` rows are left untouched.  kivi_decode_launches_ragged tells which applies.
- *   The counters are of the call: in the launch's arguments, or (more sequences, one or two query heads) in a copy from
- * host memory into the workspace on `stream`.  Do not record these two entry points into a HIP graph:
+ *   The counters are of the call: in the launch's arguments, or (more sequences) in a copy from host memory into the
+ * workspace on `stream`.  Do not record these two entry points into a HIP graph:
  * a replay would see the counters of the recorded step, or copy from host memory that is gone.
  *   k_new, v_new, q, out   the whole batch's tensors, as for the uniform entry points
  * Errors: as for the uniform entry points; entries before the failing run have been processed.
@@ -334,7 +333,7 @@ int kivi_decode_attention_ragged(const kivi_layout_t* layout, const kivi_cache_t
 /*
  * Host helper: the number of kernel launches kivi_decode_attention_ragged enqueues for these
  * sequence states (no launch).  Two when the whole batch goes through one pair of launches (four with 9 to 16 query
- * heads per kv-head, see above); otherwise the sum over the runs of equal state.
+ * heads per kv-head, one with one query head per kv-head and more than 192 sequences, see above); otherwise the sum over the runs of equal state.
  * Errors: INVALID_ARG, UNSUPPORTED.
  */
 int kivi_decode_launches_ragged(const kivi_layout_t* layout, const kivi_seq_state_t* states, int32_t* launches);

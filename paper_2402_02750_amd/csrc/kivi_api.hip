@@ -67,13 +67,14 @@ size_t counter_bytes(const kivi_layout_t* l) {
 
 // Room for the per-sequence counters of a batch of different lengths (16 bytes per sequence, padded
 // to 256 bytes); the ragged entry points keep them behind the split counters.
-// Room for the tables of the sliced second launch of a batch of different lengths: 16 bytes per slice
-// (at most kMaxSlices) and 8 bytes per (batch, kv-head) unit, behind the per-sequence counters.
+// Room for the tables of the second launch of such a batch, behind the counters: 16 bytes per workgroup (at most kMaxSlices) and 8
+// bytes per (batch, kv-head) unit, of which 4 bytes per sequence are used.
 constexpr int kMaxSlices = 4096;
 constexpr int64_t kMaxSliceUnits = 65536;
 size_t slice_table_bytes(const kivi_layout_t* l) {
     const int64_t units = std::min<int64_t>((int64_t)l->batch * l->n_kv_heads, kMaxSliceUnits);
-    return ((size_t)kMaxSlices * 16 + (size_t)units * 8 + 255) / 256 * 256;
+    const size_t many = l->batch > 4096 ? (size_t)l->batch * 24 : 0;       // (decode_one_kernel's 36 bytes per sequence)
+    return ((size_t)kMaxSlices * 16 + (size_t)units * 8 + many + 255) / 256 * 256;
 }
 
 size_t seq_state_bytes(const kivi_layout_t* l) {
@@ -484,46 +485,46 @@ struct RaggedPlan {
     bool in_arguments;          // ... which takes the counters as arguments and writes the tables itself
     int max_row_tiles;          // of any sequence
     int units_per_sequence;     // decode_tiles_kernel
+    std::vector<OneHeadSequence> sequences;     // decode_one_kernel, longest first
     size_t parts_offset;        // of the parts in the workspace
-    // what the kernels read per call, int32: the sequences' counters (state_ints with the padding), then the work
-    // tables, if any: the workgroups' (or slices') from state_ints on, the sequences' (units') from unit_table on
+    // what the kernels read per call, int32: the sequences' counters (state_ints with the padding), the workgroups' table
+    // from state_ints on and the sequences' from unit_table on; one head per kv-head: the sequences' table, and their first
+    // workgroups from unit_table on (the two tables are left to the first launch with in_arguments)
     std::vector<int32_t> tables;
     size_t state_ints, unit_table;
     std::vector<int32_t> steps;
 };
 
-// decode_tiles_kernel serves the packed tiles: from three heads per kv-head on, and two with G > 32 (which the other kernels have no form
-// for); one pair of launches for up to 8 heads, a pair per 8 for up to 16, and from 17 on one pair with runs of 8 heads as units of
+// The second launch: decode_tiles_kernel from two heads per kv-head on, decode_one_kernel for one.  (Two heads, decode_mfma_kernel's forms for
+// such batches before, whole steps: 32 units 29.1 -> 25.8 us, 128 of 500-8000 tokens 44.6 -> 28.5, 512 of 2000-2200 43.4 -> 41.5, of
+// 500-8000 96 -> 64, 1024 of 500-4000 134 -> 72, 2048 of 1000-1100 89 -> 85; the least gain, none, at 512 of 4000-4200 and 4 bits.)
+// One pair of launches for up to 8 heads, a pair per 8 for up to 16, and from 17 on one pair with runs of 8 heads as units of
 // their own, as in a batch of one length.
-bool ragged_on_tiles(const kivi_layout_t* l) {
-    const int rep = l->n_q_heads / l->n_kv_heads;
-    return rep >= 3 || (rep == 2 && l->group > kTileTokens);
-}
+bool ragged_on_tiles(const kivi_layout_t* l) { return l->n_q_heads >= 2 * l->n_kv_heads; }
 int ragged_runs(const kivi_layout_t* l) {
     const int rep = l->n_q_heads / l->n_kv_heads;
     return rep > 2 * kMaxRep ? ceil_div(rep, kMaxRep) : 1;
 }
-// whether batches of different lengths have one pair of launches for this group size and number of heads
-bool ragged_pair_serves(const kivi_layout_t* l) { return l->group == kTileTokens || ragged_on_tiles(l); }
-
 int ragged_plan(const kivi_layout_t* l, const kivi_seq_state_t* st, size_t workspace_bytes, RaggedPlan& plan) {
     if (decode_family(l) != KIVI_DECODE_MFMA || l->decode_path == KIVI_DECODE_MFMA_ONE) return kNotApplicable;
-    if (l->cap_q_tokens < kTileTokens || !ragged_pair_serves(l)) return kNotApplicable;
+    if (l->cap_q_tokens < kTileTokens) return kNotApplicable;
     const int rep_total = l->n_q_heads / l->n_kv_heads;
     const int rep_launch = std::min(rep_total, kMaxRep);
     const int rep_variant = rep_launch <= 2 ? rep_launch : (rep_launch <= 4 ? 4 : 8);
-    int max_tiles_a = 0, max_tiles_b = 0, min_tiles_a = INT32_MAX;
+    int max_tiles_a = 0, max_tiles_b = 0;
     for (int b = 0; b < l->batch; ++b) {
         const kivi_seq_state_t& x = st[b];
         if (x.n_kq != x.n_vq || x.n_kr != x.n_vr || x.n_kr < 1 || x.n_kq % kTileTokens != 0) return kNotApplicable;
         const int tiles_a = x.n_kq / kTileTokens;
         max_tiles_a = std::max(max_tiles_a, tiles_a);
-        min_tiles_a = std::min(min_tiles_a, tiles_a);
         max_tiles_b = std::max(max_tiles_b, ceil_div(x.n_kq + x.n_kr, kTileTokens) - tiles_a);
     }
     if (max_tiles_a < 1 || !residual_rows_possible(max_tiles_b, rep_variant)) return kNotApplicable;
     const MfmaGeometry g = mfma_geometry(l->bits, rep_launch);
     if (g.chunk_tiles == 0) return kNotApplicable;
+    // (G > 32: with less workspace than documented the batch goes run by run, which asks for no more than each run's)
+    size_t documented = 0;
+    if (kivi_decode_workspace_bytes(l, &documented) != KIVI_OK || (l->group > kTileTokens && workspace_bytes < documented)) return kNotApplicable;
 
     DecodeParams& p = plan.p;
     p = DecodeParams{};
@@ -542,41 +543,28 @@ int ragged_plan(const kivi_layout_t* l, const kivi_seq_state_t* st, size_t works
     p.plan.n_splits_b = 1;
     p.two_launches = 1;
     const size_t parts_offset = plan.parts_offset = counter_bytes(l) + seq_state_bytes(l) + slice_table_bytes(l);
+    // up to two heads per kv-head have always asked for room for the longest sequence's splits, also where the plan makes do with less
+    const size_t asked = (size_t)l->batch * l->n_q_heads * p.plan.n_splits() * (kHeadDim + 2) * sizeof(float);
+    if (rep_total <= 2 && parts_offset + asked > workspace_bytes) return KIVI_ERR_WORKSPACE;
 
-    // Fewer units than the chip holds wavefronts, every sequence with quantised tokens, at most 4 heads
-    // per launch: the second launch runs as equally long slices of the unit-major axis of four-tile
-    // groups, one per wavefront, so that no wavefront idles through a shorter sequence's share (with
-    // more units than wavefronts every wavefront takes whole units instead, which balances by itself).
-    const int64_t units = (int64_t)l->batch * l->n_kv_heads;
-    const int slice_waves = (min_tiles_a >= 1 && rep_total <= 4) ? wave_slices_resident(l->bits, rep_launch) : 0;
-    // Everything the kernels read per call goes to the device in ONE copy (a copy is an operation of its
-    // own on the stream): the sequences' counters, then -- if used -- the slice table and the unit table.
-    // (An asynchronous copy out of pageable memory has taken its source when the call returns.)
+    // What the kernels read per call goes to the device as arguments of the first launch, or (many sequences) in ONE copy, which is
+    // an operation of its own on the stream.  (An asynchronous copy out of pageable memory has taken its source when the call
+    // returns.)
     std::vector<int32_t>& tables = plan.tables;
-    const size_t state_ints = plan.state_ints = seq_state_bytes(l) / sizeof(int32_t);
-    plan.unit_table = 0;
-    tables.assign(state_ints, 0);
-    for (int b = 0; b < l->batch; ++b) {
-        const kivi_seq_state_t& x = st[b];
-        tables[4 * (size_t)b + 0] = x.n_kq; tables[4 * (size_t)b + 1] = x.n_kr;
-        tables[4 * (size_t)b + 2] = x.k_r_start; tables[4 * (size_t)b + 3] = x.v_r_start;
-    }
-    int64_t total = 0;                                      // groups of four tiles over all units
-    for (int b = 0; b < l->batch; ++b) total += (int64_t)ceil_div(st[b].n_kq / kTileTokens, 4) * l->n_kv_heads;
-    // The slices cost a fixed ~18 us more than the padded plan (short slices, parts through memory for
-    // every shared unit) and save the group steps the padded plan wastes on shorter sequences, ~3.7 us per
-    // 2048 of them: they pay from about 14 000 wasted group steps on (sweep of 128-1600 units, 1, 2 and 4
-    // heads per kv-head, length spreads from +-12 % to 1 : 80: 0.70-0.96 of the padded plan's time above the
-    // threshold, 1.05-1.7 below it).
-    const int64_t wasted = units * ceil_div(max_tiles_a, 4) - total;
     const bool tiles = plan.tiles = ragged_on_tiles(l);
     plan.in_arguments = false;
     plan.max_row_tiles = max_tiles_b;
     p.head_groups = tiles ? ragged_runs(l) : 1;
     if (tiles) {
-        // decode_tiles_kernel: the unit-major axis of four-tile steps (at least one per unit) in equal
-        // intervals, one per resident workgroup, as far as the units' parts fit (kivi_tiles_plan.h).  (The table fits
-        // where the slices' would: at most kMaxSlices entries, and 4 bytes per sequence instead of 8 per unit.)
+        plan.state_ints = seq_state_bytes(l) / sizeof(int32_t);
+        tables.assign(plan.state_ints, 0);
+        for (int b = 0; b < l->batch; ++b) {
+            const kivi_seq_state_t& x = st[b];
+            tables[4 * (size_t)b + 0] = x.n_kq; tables[4 * (size_t)b + 1] = x.n_kr;
+            tables[4 * (size_t)b + 2] = x.k_r_start; tables[4 * (size_t)b + 3] = x.v_r_start;
+        }
+        // the unit-major axis of four-tile steps (at least one per unit) in equal intervals, one per resident workgroup, as far
+        // as the units' parts fit (kivi_tiles_plan.h)
         std::vector<int32_t>& steps = plan.steps;
         steps.resize((size_t)l->batch);
         const int units_per_sequence = plan.units_per_sequence = l->n_kv_heads * p.head_groups;
@@ -594,55 +582,48 @@ int ragged_plan(const kivi_layout_t* l, const kivi_seq_state_t* st, size_t works
         if (!plan.in_arguments) cut = cut_ragged(steps, units_per_sequence, resident, stride, tables);
         p.axis_len = cut.axis.len;
         p.axis_rem = cut.axis.rem;
-        plan.unit_table = state_ints + (size_t)cut.workgroups * RaggedCut::kWords;
+        plan.unit_table = plan.state_ints + (size_t)cut.workgroups * RaggedCut::kWords;
         p.n_slices = (int32_t)cut.workgroups;
         p.part_stride = stride;
-    } else if (slice_waves > 0 && units < slice_waves && units <= kMaxSliceUnits && wasted >= 14000) {
-        const int n_slices = (int)std::min<int64_t>(std::min(slice_waves, kMaxSlices), total);
-        tables.resize(state_ints + (size_t)n_slices * 4 + (size_t)units * 2, 0);
-        int32_t* desc = tables.data() + state_ints;
-        int32_t* parts = desc + (size_t)n_slices * 4;
-        // slice s covers the groups [s * total / n_slices, (s + 1) * total / n_slices) of the unit-major axis
-        auto groups_of = [&](int64_t u) { return (int64_t)ceil_div(st[u / l->n_kv_heads].n_kq / kTileTokens, 4); };
-        {
-            int64_t u = 0, g_before = 0;                    // groups of the units before u
-            for (int si = 0; si < n_slices; ++si) {
-                const int64_t begin = (int64_t)si * total / n_slices, end = (int64_t)(si + 1) * total / n_slices;
-                while (g_before + groups_of(u) <= begin) g_before += groups_of(u++);
-                desc[4 * (size_t)si + 0] = (int32_t)u;
-                desc[4 * (size_t)si + 1] = (int32_t)(begin - g_before);
-                desc[4 * (size_t)si + 2] = (int32_t)(end - begin);
-                desc[4 * (size_t)si + 3] = 0;
+    } else {
+        // workgroups in the order of the sequences' lengths: the longest would end last, and alone, otherwise
+        std::vector<OneHeadSequence>& sequences = plan.sequences;
+        sequences.resize((size_t)l->batch);
+        int64_t all = 0;
+        for (int b = 0; b < l->batch; ++b) {
+            const kivi_seq_state_t& x = st[b];
+            const int tiles_a = x.n_kq / kTileTokens;
+            const int n = l->bits == 2 ? OneHeadItems<2, false, false>::steps(tiles_a, x.n_kq, x.n_kq, x.n_kr)
+                                       : OneHeadItems<4, false, false>::steps(tiles_a, x.n_kq, x.n_kq, x.n_kr);
+            sequences[(size_t)b] = OneHeadSequence{0, b, 1, x.n_kq, x.n_kr, x.k_r_start, x.v_r_start, n};
+            all += (int64_t)n * l->n_kv_heads;
+        }
+        std::stable_sort(sequences.begin(), sequences.end(), [](const OneHeadSequence& a, const OneHeadSequence& b) { return a.steps > b.steps; });
+        const int stride = std::min(part_rows(l, workspace_bytes > parts_offset ? workspace_bytes - parts_offset : 0), kOneHeadMaxParts);
+        if (stride < 1) return KIVI_ERR_WORKSPACE;
+        const int cus = one_head_compute_units();
+        int64_t wgs = 0;
+        for (OneHeadSequence& s : sequences) {
+            s.parts = one_head_ragged_parts(all, s.steps, cus, stride, l->bits == 2 ? 8 : 12);
+            s.first_wg = (int32_t)wgs;
+            wgs += (int64_t)s.parts * l->n_kv_heads;
+            if (wgs > 0x3fffffff) return kNotApplicable;
+        }
+        p.n_slices = (int32_t)wgs;
+        p.part_stride = stride;
+        plan.in_arguments = l->batch <= kInlineSequences;
+        const size_t entry = sizeof(OneHeadSequence) / sizeof(int32_t);
+        plan.state_ints = 0;
+        plan.unit_table = (size_t)l->batch * entry;
+        tables.resize((size_t)l->batch * (entry + 1));
+        if (!plan.in_arguments)
+            for (size_t i = 0; i < sequences.size(); ++i) {
+                *reinterpret_cast<OneHeadSequence*>(tables.data() + entry * i) = sequences[i];
+                tables[plan.unit_table + i] = sequences[i].first_wg;
             }
-        }
-        // slices touching a unit: from the one that holds its first group to the one that holds its last
-        // (group x lies in slice ((x + 1) * n_slices - 1) / total)
-        int max_parts = 1;
-        {
-            int64_t g_before = 0;
-            for (int64_t u = 0; u < units; ++u) {
-                const int64_t groups = groups_of(u);
-                const int first = (int)(((g_before + 1) * n_slices - 1) / total);
-                const int last = (int)(((g_before + groups) * n_slices - 1) / total);
-                parts[2 * (size_t)u + 0] = first;
-                parts[2 * (size_t)u + 1] = last - first + 1;
-                max_parts = std::max(max_parts, last - first + 1);
-                g_before += groups;
-            }
-        }
-        const size_t rows_s = (size_t)l->batch * l->n_q_heads * (max_parts + 1);
-        if (parts_offset + rows_s * (kHeadDim + 2) * sizeof(float) <= workspace_bytes) {
-            plan.unit_table = state_ints + (size_t)n_slices * 4;
-            p.n_slices = n_slices;
-            p.plan.n_splits_a = max_parts;              // workspace rows per (batch, query head): the fp16-row part + one per slice
-        } else {
-            tables.resize(state_ints);
-        }
     }
-    if (!tiles) p.part_stride = p.plan.n_splits();
     const size_t rows = (size_t)l->batch * l->n_q_heads * p.part_stride;
     if (parts_offset + rows * (kHeadDim + 2) * sizeof(float) > workspace_bytes) return KIVI_ERR_WORKSPACE;
-    p.ragged_min_tiles = min_tiles_a;
     p.rep_variant = rep_launch;
     return KIVI_OK;
 }
@@ -666,33 +647,36 @@ int ragged_launch(const kivi_layout_t* l, const kivi_cache_t* c, const RaggedPla
     hipStream_t hs = static_cast<hipStream_t>(stream);
     int32_t* dev_state = reinterpret_cast<int32_t*>(ws + counter_bytes(l));
     p.counters = reinterpret_cast<int32_t*>(ws);
-    p.seq_state = dev_state;
-    if (plan.unit_table) {
-        p.wave_desc = dev_state + plan.state_ints;
-        p.unit_parts = dev_state + plan.unit_table;
-    }
+    if (plan.tiles) p.seq_state = dev_state;
+    p.wave_desc = dev_state + plan.state_ints;
+    p.unit_parts = dev_state + plan.unit_table;
     p.part_o = reinterpret_cast<float*>(ws + plan.parts_offset);
     p.part_ml = p.part_o + (size_t)l->batch * l->n_q_heads * p.part_stride * kHeadDim;
-    const RaggedTables device_tables{dev_state, dev_state + plan.unit_table, dev_state + plan.state_ints, p.n_slices, p.axis_len, p.axis_rem, plan.units_per_sequence};
-    if (!plan.in_arguments && hipMemcpyAsync(dev_state, plan.tables.data(), (plan.unit_table ? plan.tables.size() : (size_t)l->batch * 4) * sizeof(int32_t),
-                       hipMemcpyHostToDevice, hs) != hipSuccess)
+    if (!plan.in_arguments && hipMemcpyAsync(dev_state, plan.tables.data(), plan.tables.size() * sizeof(int32_t), hipMemcpyHostToDevice, hs) != hipSuccess)
         return KIVI_ERR_HIP;
+    if (!plan.tiles) {
+        const RaggedTables tables{nullptr, nullptr, nullptr, 0, 0, 0, 0, dev_state, dev_state + plan.unit_table};
+        if (plan.in_arguments) {
+            uint8_t places[kInlineSequences];           // of the sequences that flush, in the table's order
+            int n = 0;
+            for (size_t i = 0; i < plan.sequences.size(); ++i)
+                if (std::find(flush, flush + n_flush, plan.sequences[i].sequence) != flush + n_flush) places[n++] = (uint8_t)i;
+            if (int s = hip_status(launch_ragged_one_head(p, plan.sequences.data(), places, n, tables, hs))) return s;
+        }
+        return hip_status(launch_decode_one(p, hs));
+    }
+    const RaggedTables device_tables{dev_state, dev_state + plan.unit_table, dev_state + plan.state_ints, p.n_slices, p.axis_len, p.axis_rem,
+                                     plan.units_per_sequence, nullptr, nullptr};
     const int rep_total = l->n_q_heads / l->n_kv_heads;
     for (int h0 = 0; h0 < rep_total; h0 += p.head_groups > 1 ? rep_total : kMaxRep) {
         p.q_head0 = h0;
         p.rep_here = std::min(kMaxRep, rep_total - h0);
-        hipError_t e = hipSuccess;
-        if (plan.tiles) {
-            DecodeParams rows = p;
-            if (p.head_groups > 1) rows.rep_here = rep_total;
-            e = launch_ragged_rows(rows, plan.max_row_tiles, plan.in_arguments ? plan.tables.data() : nullptr, flush, h0 == 0 ? n_flush : 0,
-                                   plan.in_arguments ? &device_tables : nullptr, hs);
-            p.k_new = p.v_new = nullptr;
-            if (e == hipSuccess) e = launch_decode_tiles(p, hs);
-        } else {
-            e = launch_decode_mfma(p, hs);
-            p.k_new = p.v_new = nullptr;
-        }
+        DecodeParams rows = p;
+        if (p.head_groups > 1) rows.rep_here = rep_total;
+        hipError_t e = launch_ragged_rows(rows, plan.max_row_tiles, plan.in_arguments ? plan.tables.data() : nullptr, flush, h0 == 0 ? n_flush : 0,
+                                          plan.in_arguments ? &device_tables : nullptr, hs);
+        p.k_new = p.v_new = nullptr;
+        if (e == hipSuccess) e = launch_decode_tiles(p, hs);
         if (e == hipErrorNotSupported) return KIVI_ERR_UNSUPPORTED;
         if (int s2 = hip_status(e)) return s2;
     }
@@ -1097,7 +1081,7 @@ int kivi_decode_launches_ragged(const kivi_layout_t* l, const kivi_seq_state_t* 
     const int rep_total = l->n_q_heads / l->n_kv_heads;
     const int head_groups = ragged_runs(l) > 1 ? 1 : ceil_div(rep_total, kMaxRep);
     // the conditions of ragged_plan
-    bool fast = path == KIVI_DECODE_MFMA && l->decode_path != KIVI_DECODE_MFMA_ONE && l->cap_q_tokens >= kTileTokens && ragged_pair_serves(l);
+    bool fast = path == KIVI_DECODE_MFMA && l->decode_path != KIVI_DECODE_MFMA_ONE && l->cap_q_tokens >= kTileTokens;
     int max_tiles_a = 0, max_tiles_b = 0;
     for (int b = 0; b < l->batch; ++b) {
         const kivi_seq_state_t& x = states[b];
@@ -1108,7 +1092,7 @@ int kivi_decode_launches_ragged(const kivi_layout_t* l, const kivi_seq_state_t* 
     }
     const int rep_launch = std::min(rep_total, kMaxRep);
     if (fast && max_tiles_a >= 1 && residual_rows_possible(max_tiles_b, rep_launch <= 2 ? rep_launch : (rep_launch <= 4 ? 4 : 8))) {
-        *launches = 2 * head_groups;
+        *launches = rep_total == 1 && l->batch > kInlineSequences ? 1 : 2 * head_groups;
         return KIVI_OK;
     }
     // run by run

@@ -45,6 +45,12 @@
 // 32 x 500 13.9 -> 8.1, 256 x 1000 26.3 -> 12.5, 512 x 4000 48.3 -> 40.0, 2048 x 2000 114.9 -> 82.7; 4 bits 32 x 500 14.7 -> 8.3, 256 x 1000
 // 29.1 -> 14.8, 512 x 4000 67.4 -> 54.8, 2048 x 2000 134.8 -> 113.5; a window of 512 tokens, 256 x 4000 38.6 -> 28.0.
 //
+// RAGGED (sequences of different lengths, K and V split alike): a workgroup looks up its sequence -- sixty-four candidates a step -- in a table that
+// the launch before made (launch_ragged_one_head, which also quantises what leaves the windows); sequences go by length, the
+// longest first, and the workgroups of a unit by one_head_ragged_parts.  Whole steps, residual_rows_kernel and decode_mfma_kernel's forms for
+// such batches -> this: 16 x 32 heads, 500-8000 tokens 81.4 -> 52.3 us, 4 bits 99.4 -> 73.5; 64 x 32, 500-2000 94.0 -> 70.5, 1900-2200 112.8 ->
+// 93.1; 4 x 32, 100-1000 18.2 -> 14.1; 128 x 4, 50-16 000 124.6 -> 93; G = 64, 16 x 32, 500-8000 (run by run before) 160 -> 48.
+//
 // Bound: HBM.  A launch that only copies what this one reads takes 29.7 us for 512 units of 124 tiles at 2 bits (6.6 TB/s), rows and
 // all 35; this kernel 39.4 (decode_mfma_kernel 45.5).  From 1000 to 8000 tokens at 512 units a token more costs what its bytes take at 6.1 TB/s
 // (4 bits 6.6); beyond that a step has 2.5 us.  Whole steps, 2 bits, decode_mfma_kernel -> this one: 32 units x 3000 tokens 12.6 -> 9.1 us,
@@ -235,11 +241,28 @@ struct Shape {
     static constexpr int kLds = WV * kWaveBytes + WV * 8 + 16;
 };
 
-template <int BITS, int PT, int NB, int WV, int OCC, bool CS, bool FLUSH, bool UNEVEN>
+// The sequence of workgroup wg: the last whose first workgroup is not after it.  Sixty-four candidates at a time.
+__device__ __forceinline__ OneHeadSequence find_sequence(const DecodeParams& p, int wg, int lane) {
+    int lo = 0, n = p.batch;                           // among [lo, lo + n)
+    while (n > 1) {
+        const int stride = (n + 63) / 64, i = lane * stride;
+        const bool not_after = i < n && p.unit_parts[lo + i] <= wg;
+        const int at = (__popcll(__builtin_amdgcn_ballot_w64(not_after)) - 1) * stride;
+        lo += at;
+        n = min(stride, n - at);
+    }
+    // (through the scalar cache)
+    const auto* e = reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(p.wave_desc)) + 8 * lo;
+    return OneHeadSequence{e[0], e[1], e[2], e[3], e[4], e[5], e[6], e[7]};
+}
+
+// RAGGED: sequences of different lengths.
+template <int BITS, int PT, int NB, int WV, int OCC, bool CS, bool FLUSH, bool UNEVEN, bool RAGGED>
 __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(DecodeParams p) {
     using S = Shape<BITS, PT, NB, WV>;
     static_assert(!(CS && FLUSH), "a flush in this launch: G = 32");
     static_assert(!(UNEVEN && FLUSH), "K and V split differently: a flush of one value token only");
+    static_assert(!(RAGGED && (UNEVEN || FLUSH)), "different lengths: K and V split alike, flushed before");
     constexpr int NI = S::NI, NT = S::NT, NR = (NT + 3) / 4, MT = S::MT;
     __shared__ __align__(16) unsigned char sm[S::kLds];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -255,7 +278,24 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
     const uint32_t ring_lds = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)ring);
 
     // ---- this workgroup's run of its unit's steps ----
-    const int u = blockIdx.x / p.unit_wgs, part = blockIdx.x % p.unit_wgs;
+    int u, part;
+    if constexpr (RAGGED) {
+        const OneHeadSequence s = find_sequence(p, blockIdx.x, lane);
+        const int at = (int)blockIdx.x - s.first_wg, head = at / s.parts;
+        u = s.sequence * p.n_kv_heads + head;
+        part = at - head * s.parts;
+        p.n_kq = p.n_vq = s.n_q;
+        p.n_kr = p.n_vr = s.n_r;
+        p.k_r_start = s.k_start;
+        p.v_r_start = s.v_start;
+        p.plan.tiles_a = s.n_q / kTileTokens;
+        p.unit_wgs = s.parts;
+        p.axis_len = s.steps / s.parts;
+        p.axis_rem = s.steps - p.axis_len * s.parts;
+    } else {
+        u = blockIdx.x / p.unit_wgs;
+        part = blockIdx.x % p.unit_wgs;
+    }
     const int n_kr = p.n_kr;
     // UNEVEN: tokens below v_q have quantised values in the cache, the others rows in the ring from slot v_start on
     const int v_q = p.n_vq - p.flushed_values;
@@ -878,11 +918,17 @@ int compute_units() {
     return cus;
 }
 
-template <int BITS, int PT, int NB, int WV, int OCC, bool CS, bool FLUSH, bool UNEVEN>
+template <int BITS, int PT, int NB, int WV, int OCC, bool CS, bool FLUSH, bool UNEVEN, bool RAGGED>
 hipError_t launch(DecodeParams p, hipStream_t stream) {
     using S = Shape<BITS, PT, NB, WV>;
     static_assert(S::kLds <= 160 * 1024 / OCC / 1280 * 1280, "workgroups per compute unit (LDS is given out in pieces of 1280 bytes)");
     static_assert(NB == 2 && PT <= 2, "two items in flight; masked tiles of a slot");
+    if constexpr (RAGGED) {
+        if (p.n_slices < 1) return hipErrorInvalidValue;
+        p.one_round = p.n_slices <= (int64_t)compute_units() * OCC;
+        decode_one_kernel<BITS, PT, NB, WV, OCC, CS, FLUSH, UNEVEN, RAGGED><<<(unsigned)p.n_slices, 64 * WV, 0, stream>>>(p);
+        return hipGetLastError();
+    }
     const int64_t units = (int64_t)p.batch * p.n_kv_heads;
     const int v_q = p.n_vq - (FLUSH ? kTileTokens : p.flushed_values);
     const int steps = OneHeadItems<BITS, FLUSH, UNEVEN>::steps((v_q + kTileTokens - 1) / kTileTokens, p.n_kq, v_q, p.n_kr);
@@ -893,20 +939,26 @@ hipError_t launch(DecodeParams p, hipStream_t stream) {
     p.axis_len = steps / w;
     p.axis_rem = steps % w;
     p.one_round = units * w <= (int64_t)cus * OCC;
-    decode_one_kernel<BITS, PT, NB, WV, OCC, CS, FLUSH, UNEVEN><<<(unsigned)(units * w), 64 * WV, 0, stream>>>(p);
+    decode_one_kernel<BITS, PT, NB, WV, OCC, CS, FLUSH, UNEVEN, RAGGED><<<(unsigned)(units * w), 64 * WV, 0, stream>>>(p);
     return hipGetLastError();
 }
 
-template <bool CS, bool FLUSH, bool UNEVEN>
+template <bool CS, bool FLUSH, bool UNEVEN, bool RAGGED = false>
 hipError_t launch_bits(const DecodeParams& p, hipStream_t stream) {
-    return p.bits == 2 ? launch<2, 2, 2, 4, 3, CS, FLUSH, UNEVEN>(p, stream) : launch<4, 1, 2, 4, 3, CS, FLUSH, UNEVEN>(p, stream);
+    return p.bits == 2 ? launch<2, 2, 2, 4, 3, CS, FLUSH, UNEVEN, RAGGED>(p, stream) : launch<4, 1, 2, 4, 3, CS, FLUSH, UNEVEN, RAGGED>(p, stream);
 }
 
 }  // namespace
 
+int one_head_compute_units() { return compute_units(); }
+
 hipError_t launch_decode_one(const DecodeParams& p_in, hipStream_t stream) {
     DecodeParams p = p_in;
     p.flushed_values = 0;
+    if (p.wave_desc) {
+        if (p.n_q_heads != p.n_kv_heads || !p.unit_parts || p.flush_k || p.part_stride < 1) return hipErrorInvalidValue;
+        return p.kg_shift > 0 ? launch_bits<true, false, false, true>(p, stream) : launch_bits<false, false, false, true>(p, stream);
+    }
     if (p.n_q_heads != p.n_kv_heads || p.n_kq + p.n_kr != p.n_vq + p.n_vr || p.n_kq < p.n_vq || p.part_stride < 1) return hipErrorInvalidValue;
     const bool cs = p.kg_shift > 0;
     const QuantKeyParams* k = p.flush_k;

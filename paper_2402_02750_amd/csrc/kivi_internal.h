@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "kivi.h"
+#include "kivi_tiles_plan.h"
 
 namespace kivi {
 
@@ -106,21 +107,18 @@ struct DecodeParams {
     // > 0: the matrix-core family runs as two launches (fp16 rows, then the all-quantised chunks); the
     // plan then has a single fp16-row split per unit (n_splits_b == 1).
     int32_t two_launches;
-    // Batches whose sequences differ in length (two-launch form only; null otherwise): per batch entry
-    // {n_q, n_r, k_r_start, v_r_start} in device memory (K and V split alike).  The scalar counters
-    // and the plan above then describe the LONGEST sequence: every unit gets that many chunks on the
-    // cost axis, and a shorter sequence's surplus chunks and tiles are masked.
+    // Batches whose sequences differ in length (null otherwise): per batch entry {n_q, n_r, k_r_start, v_r_start} in device memory (K
+    // and V split alike).  The scalar counters and the plan above then describe the LONGEST sequence.
     const int32_t* seq_state;
     int32_t kg_shift;           // log2(G / 32): scales and zero-points are stored once per group (keys: row tile >> kg_shift;
                                 // values: 4 >> kg_shift entries per token); > 0 runs on instantiations of its own
     int32_t head_groups;        // decode_tiles_kernel: runs of rep_here query heads per kv-head, each a unit of its own (the last may be shorter)
-    // Two-launch form, second launch as equally long slices of the unit-major axis of four-tile groups
-    // (device arrays made by the host; null: not used): wave_desc[4 s] = {first unit, first group in it,
-    // groups, 0} of slice s; unit_parts[2 u] = {first slice touching unit u, slices touching it}.
+    // ... and the tables of such a batch: decode_tiles_kernel, wave_desc[4 g] = {first unit, first step in it, steps, 0} of workgroup g,
+    // unit_parts[b] = steps before sequence b (kivi_tiles_plan.h); decode_one_kernel, an OneHeadSequence per sequence, and their
+    // first workgroups.  n_slices: workgroups.
     const int32_t* wave_desc;
     const int32_t* unit_parts;
     int32_t n_slices;
-    int32_t ragged_min_tiles;   // with seq_state: the fewest all-quantised tiles any sequence has (host knowledge)
     // Host side only (two-launch form): the residual flush of this decode step, to be carried out by
     // extra workgroups of the fp16-row launch instead of a launch of its own; null otherwise.
     const QuantKeyParams* flush_k;
@@ -128,8 +126,7 @@ struct DecodeParams {
     int32_t part_stride;        // workspace rows (parts) per (batch, query head)
     // decode_tiles_kernel: its first row_wgs workgroups hold the units' fp16 rows, row_split per unit; interval g of the axis of
     // all-quantised steps (of one unit, cut into unit_wgs intervals; unit_wgs = 0: of all units) has axis_len
-    // steps, one more if g < axis_rem.  Batches of different lengths: wave_desc[4 g] = {first unit, first step in it,
-    // steps, 0} of workgroup g, unit_parts[b] = steps before sequence b (kivi_tiles_plan.h)
+    // steps, one more if g < axis_rem.
     int32_t row_wgs, row_split, unit_wgs, axis_len, axis_rem;
     int32_t flushed_values;     // decode_one_kernel: value tokens it quantises itself, the last of n_vq (0 or 1)
     int32_t one_round;          // decode_one_kernel: all its workgroups fit the device at once
@@ -156,7 +153,10 @@ hipError_t launch_decode_tiles(DecodeParams p, hipStream_t stream);
 int tiles_resident_ragged(int bits, int rep, bool large_groups);
 int tiles_max_parts(int bits, int rep);       // parts of one unit that it merges, at most
 // decode_one_kernel (kivi_decode_one.hip): one query head per kv-head, n_kq >= n_vq, one launch
+// (with p.wave_desc: a batch of different lengths, G as one likes; wave_desc and unit_parts are the two tables of RaggedTables,
+// n_slices all workgroups)
 hipError_t launch_decode_one(const DecodeParams& p, hipStream_t stream);
+int one_head_compute_units();
 hipError_t launch_residual_rows(const DecodeParams& p, hipStream_t stream);
 // Batches of different lengths before decode_tiles_kernel: fp16 rows, append, flush and tables (kivi_ragged_rows.hip).
 // What the kernel writes for the second launch, in device memory: every sequence's counters (as seq_state), the steps before it, and the
@@ -164,11 +164,16 @@ hipError_t launch_residual_rows(const DecodeParams& p, hipStream_t stream);
 struct RaggedTables {
     int32_t *seq_state, *before, *intervals;
     int32_t n_intervals, axis_len, axis_rem, units_per_sequence;
+    // decode_one_kernel instead: an OneHeadSequence per sequence, longest first, and the first workgroups once more on their own
+    int32_t *one_head, *first_wg;
 };
 constexpr int kInlineSequences = 192;  // sequences whose counters fit the kernel's arguments (4096 bytes)
 // seq: the counters in host memory, at most kInlineSequences of them, `flush` the n_flush sequences whose last quantised tile (G = 32) is still in
 // the rings; null: the counters are in p.seq_state already, nothing is flushed and no table is written.  max_tiles: of fp16 rows, of
 // any sequence.
+// one_head (tables->one_head): no fp16 rows; `sequences` in the order of the table, seq and flush in that order too.
+hipError_t launch_ragged_one_head(const DecodeParams& p, const OneHeadSequence* sequences, const uint8_t* flush, int n_flush, const RaggedTables& tables,
+                                  hipStream_t stream);
 hipError_t launch_ragged_rows(const DecodeParams& p, int max_tiles, const int32_t* seq, const uint8_t* flush, int n_flush, const RaggedTables* tables,
                               hipStream_t stream);
 // the same launch with extra workgroups that quantise the key group(s) and value tokens of a residual
@@ -183,7 +188,5 @@ hipError_t launch_stream_read(const void* src, size_t bytes, uint32_t* sink, hip
 // that serves (bits, query heads per kv-head); the split planner and the kernel must agree on both.
 struct MfmaGeometry { int chunk_tiles, resident_workgroups; };
 MfmaGeometry mfma_geometry(int bits, int rep);
-// wavefronts the device holds of the sliced form of decode_wave_units_kernel (0: no instantiation for the shape)
-int wave_slices_resident(int bits, int rep);
 
 }  // namespace kivi

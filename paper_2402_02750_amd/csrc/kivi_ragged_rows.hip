@@ -51,7 +51,8 @@ struct RaggedRowsParams : DecodeParams {
     int32_t n_flush;                           // flush workgroups
     RaggedTables tables;
     int4 seq[kInlineSequences];                // n_q, n_r, k_r_start, v_r_start after the step
-    uint8_t flush[kInlineSequences];           // the sequences that flush
+    uint8_t flush[kInlineSequences];           // which of them flush
+    uint8_t sequence[kInlineSequences];        // one head: the batch entries that `seq` is of (n_r | parts << 16 there)
 };
 static_assert(sizeof(RaggedRowsParams) <= 4096, "kernel arguments");
 
@@ -72,9 +73,9 @@ __global__ __launch_bounds__(1024) void ragged_rows_kernel(RaggedRowsParams p) {
     int at = blockIdx.x;
     if constexpr (INLINE) {
         if (at < p.n_flush) {
-            const int f = p.by_kv_heads.of(at), b = p.flush[f];
+            const int f = p.by_kv_heads.of(at), i = p.flush[f], b = p.tables.one_head ? p.sequence[i] : i;
             const int64_t unit = (int64_t)b * p.n_kv_heads + (at - f * p.n_kv_heads);
-            const int4 st = p.seq[b];
+            const int4 st = p.seq[i];
             const int64_t tile = unit * p.cap_tiles + st.x / kTileTokens - 1;
             if (wave == 0) tile::flush_keys<BITS>(p, unit, tile, st.z, lane);
             if (wave == min(1, n_waves - 1)) tile::flush_values<BITS>(p, unit, tile, st.w, lane);
@@ -85,6 +86,7 @@ __global__ __launch_bounds__(1024) void ragged_rows_kernel(RaggedRowsParams p) {
             const RaggedTables& t = p.tables;
             int* before = reinterpret_cast<int*>(sm_dyn);               // [kInlineSequences]
             int* steps = before + kInlineSequences;
+            const bool one_head = t.one_head != nullptr;
             if (wave == 0) {
                 int sum = 0;
                 for (int b0 = 0; b0 < p.batch; b0 += 64) {
@@ -92,9 +94,13 @@ __global__ __launch_bounds__(1024) void ragged_rows_kernel(RaggedRowsParams p) {
                     int mine = 0;
                     if (b < p.batch) {
                         const int4 st = p.seq[b];
-                        reinterpret_cast<int4*>(t.seq_state)[b] = st;
-                        steps[b] = ragged_steps(st.x);
-                        mine = steps[b] * t.units_per_sequence;
+                        if (one_head) {
+                            mine = (st.y >> 16) * p.n_kv_heads;         // (of the workgroups' axis)
+                        } else {
+                            reinterpret_cast<int4*>(t.seq_state)[b] = st;
+                            steps[b] = ragged_steps(st.x);
+                            mine = steps[b] * t.units_per_sequence;
+                        }
                     }
                     int upto = mine;                                     // of this and the lanes before
 #pragma unroll
@@ -104,11 +110,20 @@ __global__ __launch_bounds__(1024) void ragged_rows_kernel(RaggedRowsParams p) {
                     }
                     if (b < p.batch) {
                         before[b] = sum + upto - mine;
-                        t.before[b] = before[b];
+                        if (one_head) {
+                            const int4 st = p.seq[b];
+                            const int n_r = st.y & 0xffff;
+                            t.first_wg[b] = before[b];
+                            reinterpret_cast<OneHeadSequence*>(t.one_head)[b] = OneHeadSequence{before[b], p.sequence[b], st.y >> 16, st.x, n_r, st.z, st.w,
+                                                                                                OneHeadItems<BITS, false, false>::steps(st.x / kTileTokens, st.x, st.x, n_r)};
+                        } else {
+                            t.before[b] = before[b];
+                        }
                     }
                     sum += __shfl(upto, 63);
                 }
             }
+            if (one_head) return;
             __syncthreads();
             const StepAxis axis{t.axis_len, t.axis_rem};
             for (int g = tid; g < t.n_intervals; g += blockDim.x)
@@ -241,12 +256,33 @@ __global__ __launch_bounds__(1024) void ragged_rows_kernel(RaggedRowsParams p) {
 
 }  // namespace
 
+hipError_t launch_ragged_one_head(const DecodeParams& params, const OneHeadSequence* sequences, const uint8_t* flush, int n_flush, const RaggedTables& tables,
+                                  hipStream_t stream) {
+    if (params.batch > kInlineSequences || !tables.one_head || !tables.first_wg) return hipErrorInvalidValue;
+    RaggedRowsParams p{};
+    static_cast<DecodeParams&>(p) = params;
+    p.by_kv_heads = FastDiv::by(p.n_kv_heads);
+    p.n_flush = n_flush * p.n_kv_heads;
+    p.tables = tables;
+    for (int i = 0; i < p.batch; ++i) {
+        const OneHeadSequence& s = sequences[i];
+        if (s.n_r > 0xffff || s.parts > 0x7fff) return hipErrorInvalidValue;
+        p.seq[i] = make_int4(s.n_q, s.n_r | s.parts << 16, s.k_start, s.v_start);
+        p.sequence[i] = (uint8_t)s.sequence;
+    }
+    std::copy(flush, flush + n_flush, p.flush);
+    const unsigned grid = (unsigned)(p.n_flush + 1), lds = sizeof(int) * 2 * kInlineSequences;
+    if (p.bits == 2) ragged_rows_kernel<2, true><<<grid, 128, lds, stream>>>(p);
+    else ragged_rows_kernel<4, true><<<grid, 128, lds, stream>>>(p);
+    return hipGetLastError();
+}
+
 hipError_t launch_ragged_rows(const DecodeParams& params, int max_tiles, const int32_t* seq, const uint8_t* flush, int n_flush, const RaggedTables* tables,
                               hipStream_t stream) {
     const int rep_total = params.n_q_heads / params.n_kv_heads, heads = std::min(params.rep_here, rep_total - params.q_head0);
     const int64_t units = (int64_t)params.batch * params.n_kv_heads;
     const bool in_arguments = seq != nullptr;
-    if (max_tiles < 1 || max_tiles > 16 || heads < 1 || params.part_stride < 1 || (in_arguments ? params.batch > kInlineSequences || !tables : !params.seq_state || n_flush > 0))
+    if ((tables && tables->one_head) || max_tiles < 1 || max_tiles > 16 || heads < 1 || params.part_stride < 1 || (in_arguments ? params.batch > kInlineSequences || !tables : !params.seq_state || n_flush > 0))
         return hipErrorInvalidValue;
     RaggedRowsParams p{};
     static_cast<DecodeParams&>(p) = params;

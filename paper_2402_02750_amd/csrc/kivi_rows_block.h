@@ -73,13 +73,8 @@ __device__ __forceinline__ void residual_rows_block(const DecodeParams& p, float
     float* sm_part = sm_dyn + tiles_b * REP * kTileTokens;                                          // [tiles_b][REP][130]
     const int64_t unit = unit_index;
     const int b = (int)(unit / p.n_kv_heads), h = (int)(unit % p.n_kv_heads);
-    // the sequence's counters: the launch's, or (batches of different lengths) its entry of seq_state
-    int n_q = p.n_kq, length = p.length, k_start = p.k_r_start, v_start = p.v_r_start;
-    if (p.seq_state) {
-        const int4 st = reinterpret_cast<const int4*>(p.seq_state)[b];      // n_q, n_r, k_r_start, v_r_start
-        n_q = st.x; length = st.x + st.y; k_start = st.z; v_start = st.w;
-    }
-    const int tt = (n_q / kTileTokens + wave) * kTileTokens;  // first token of the tile (past the end for a shorter sequence's surplus wavefronts)
+    const int n_q = p.n_kq, length = p.length, k_start = p.k_r_start, v_start = p.v_r_start;
+    const int tt = (n_q / kTileTokens + wave) * kTileTokens;  // first token of the tile
     const int rep = p.rep_here, rep_total = p.n_q_heads / p.n_kv_heads;
     const int64_t q_row0 = (int64_t)b * p.n_q_heads + (int64_t)h * rep_total + p.q_head0;
     const bool fused_append = p.k_new != nullptr;
@@ -135,8 +130,8 @@ __device__ __forceinline__ void residual_rows_block(const DecodeParams& p, float
 #pragma unroll
     for (int hh = 0; hh < REP; ++hh) {
         const float a = lane < kTileTokens ? sm_p[hh][lane] : -INFINITY;
-        m[hh] = wave_max32(a);                             // -inf only for a tile past the end of a shorter sequence
-        const float pt = lane < kTileTokens ? __expf(a - (m[hh] == -INFINITY ? 0.f : m[hh])) : 0.f;
+        m[hh] = wave_max32(a);                             // finite: the tile has a token
+        const float pt = lane < kTileTokens ? __expf(a - m[hh]) : 0.f;
         l[hh] = wave_sum32(pt);
         if (lane < kTileTokens) sm_p[hh][lane] = pt;
     }

@@ -214,6 +214,20 @@ inline int one_head_parts(int64_t units, int steps, int compute_units, int room,
     return (int)std::max<int64_t>(1, std::min({w, (int64_t)steps, (int64_t)room}));
 }
 
+// Batches of different lengths: a sequence's units get as many workgroups as their steps ask for.  `total`: the steps of all units.  One
+// workgroup per compute unit while none of them has more than `many` steps, as above; else one per two thirds of a compute unit's
+// share of the steps, so that 256 units of one length are cut into halves and from 384 on such units are whole.  (Half of that share:
+// 512 units of 3900-4100 tokens 52.3 us in place of 47.7, 4 bits 79.7 / 64.0, 320 of 2000 30.0 / 25.1..27.8; a third 56.0, 71.5, 29.0.  Three
+// fifths and three quarters: 128 units of 500-16 000 tokens 30.8 and 33.9 us, 256 of 500-8000 35.8 and 31.5.)
+inline int one_head_ragged_parts(int64_t total, int steps, int compute_units, int room, int many) {
+    const int64_t cus = compute_units;
+    const int64_t w = total <= many * cus ? (steps * cus + total - 1) / total : (3 * steps * cus + 2 * total - 1) / (2 * total);
+    return (int)std::max<int64_t>(1, std::min({w, (int64_t)steps, (int64_t)room}));
+}
+// What a workgroup of such a batch reads: its sequence's first workgroup (of all units, head by head), the sequence, workgroups per unit, counters
+// after the step, steps of a unit.
+struct OneHeadSequence { int32_t first_wg, sequence, parts, n_q, n_r, k_start, v_start, steps; };
+
 // What decode_one_kernel's wavefronts take of a unit: the kernel's own arithmetic, here so that it can be walked without a device.
 // A unit is n_kr tokens of fp16 rows, with UNEVEN the tokens from v_q (values in the cache) to n_kq, whose keys only are quantised, and
 // `tiles` tiles.  An item is one wavefront's slot of a step: NT tokens' rows, MT tokens' key tile and value rows, or PT tiles.

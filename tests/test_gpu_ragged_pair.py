@@ -1,4 +1,4 @@
-"""Batches of different lengths with two and more query heads per kv-head: the first launch (fp16 rows, flush, tables)
+"""Batches of different lengths: the first launch (fp16 rows, flush, tables; one query head per kv-head: flush and tables)
 and the second against the run-by-run vector path, which has kernels of its own for all of it."""
 import pytest
 
@@ -23,6 +23,16 @@ CASES = [
     (9, 3, 2, 32, 480, [520, 600, 2000], 3, 2),         # a window of sixteen tiles
     (6, 2, 4, 32, 32, [63 + i for i in range(192)], 2, 2),      # as many sequences as the arguments hold: flushes among them
     (6, 2, 2, 32, 32, [63 + i for i in range(193)], 2, 2),      # one more
+    (4, 2, 2, 32, 64, LONG, 70, 2),                     # two heads
+    (2, 2, 2, 32, 64, LONG, 70, 2),                     # one head: several workgroups per unit
+    (3, 3, 4, 32, 64, LONG, 70, 2),
+    (40, 40, 2, 32, 64, [64 + 67 * i for i in range(24)], 33, 2),       # ... whole units, the longest in parts
+    (40, 40, 4, 32, 64, [4100, 64, 95, 100, 3000] + [200] * 20, 33, 2),
+    (2, 2, 2, 64, 128, [191, 500, 64, 1900], 66, 2),
+    (1, 1, 4, 128, 128, [300, 255, 1, 2500, 20000], 3, 2),
+    (2, 2, 2, 32, 480, [520, 600, 2000], 3, 2),         # a window of sixteen tiles
+    (1, 1, 2, 32, 32, [63 + i for i in range(192)], 2, 2),
+    (1, 1, 4, 32, 32, [63 + i for i in range(193)], 2, 1),      # counters copied, no first launch; two levels of the search
 ]
 
 
@@ -67,11 +77,12 @@ def test_pair(hq, hkv, bits, group, residual, tokens, steps, launches):
             assert kivi.kivi_decode_launches_ragged(l0, s0) == launches
 
 
-def test_pair_is_deterministic():
+@pytest.mark.parametrize("hq,hkv", [(16, 4), (4, 4)])
+def test_pair_is_deterministic(hq, hkv):
     """The same step on copies of one cache: the same bytes (sums in the same order, whichever workgroup comes last)."""
     torch = gh.require_gpu()
-    print("case ragged pair: repetitions", flush=True)
-    tokens, hq, hkv = [95, 700, 223, 3000, 5000], 16, 4
+    print(f"case ragged pair: repetitions hq={hq} hkv={hkv}", flush=True)
+    tokens = [95, 700, 223, 3000, 5000]
     gen = torch.Generator(device="cuda").manual_seed(5)
     k, v = (torch.randn(5, hkv, max(tokens) + 1, 128, dtype=torch.float16, device="cuda", generator=gen) for _ in range(2))
     q, kn, vn = (torch.randn(5, h, 128, dtype=torch.float16, device="cuda", generator=gen) for h in (hq, hkv, hkv))

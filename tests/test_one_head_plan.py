@@ -70,6 +70,22 @@ int check_form(int form, int64_t units, int u, int n_kq, int v_q, int n_kr, int 
                        : check<BITS, false, true>(units, u, n_kq, v_q, n_kr, cus, room, flush_lead);
 }
 }
+// batches of different lengths: steps -> workgroups per unit; 0, or what is wrong
+extern "C" int check_ragged(const int* steps, int sequences, int heads, int cus, int room, int many) {
+    int64_t total = 0, wgs = 0, longest = 0;
+    for (int b = 0; b < sequences; ++b) total += (int64_t)steps[b] * heads;
+    for (int b = 0; b < sequences; ++b) {
+        const int parts = one_head_ragged_parts(total, steps[b], cus, room, many);
+        if (parts < 1 || parts > room || parts > steps[b]) return 1;
+        const StepAxis axis{steps[b] / parts, steps[b] % parts};
+        if (axis.len < 1 || axis.start(parts) != steps[b]) return 2;
+        if (parts < room) longest = std::max<int64_t>(longest, axis.len + (axis.rem > 0));
+        wgs += (int64_t)parts * heads;
+    }
+    if (longest * (total <= (int64_t)many * cus ? cus : 3 * cus / 2) > total + longest * 3 * cus / 2) return 3;      // longer than its share, rounded up
+    if (wgs > (int64_t)sequences * heads + 2 * (int64_t)cus) return 4;
+    return 0;
+}
 // form 0: K and V split alike, 1: with a flush, 2: split differently
 extern "C" int check_all(int bits, int form, int n_kq, int v_q, int n_kr, int* at) {
     const int units[] = {1, 2, 3, 8, 31, 32, 85, 86, 128, 255, 256, 257, 320, 512, 767, 768, 769, 800, 864, 865, 896, 897, 2048};
@@ -94,6 +110,16 @@ def plan(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-include", "algorithm", "-include", "vector", "-include", "cstdint",
                     "-I", os.path.join(ROOT, "paper_2402_02750_amd", "csrc"), str(d / "plan.cpp"), "-o", str(d / "plan.so")], check=True)
     return ctypes.CDLL(str(d / "plan.so"))
+
+
+@pytest.mark.parametrize("heads", [1, 4, 40])
+@pytest.mark.parametrize("steps", [[1], [300], [1, 1, 300], [16] * 64, list(range(1, 193)), [5000, 1, 2, 3], [7] * 4000])
+def test_ragged_parts(plan, steps, heads):
+    arr = (ctypes.c_int * len(steps))(*steps)
+    for cus in (256, 7):
+        for room in (1, 2, 128):
+            for many in (8, 12):
+                assert plan.check_ragged(arr, len(steps), heads, cus, room, many) == 0, f"{cus} compute units, {room} rows, {many}"
 
 
 TILES = list(range(0, 12)) + [15, 16, 17, 31, 63, 64, 65, 128, 1000]
