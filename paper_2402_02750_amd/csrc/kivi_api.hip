@@ -999,10 +999,8 @@ int kivi_decode_step(const kivi_layout_t* l, kivi_cache_t* c, const void* k_new,
         after = flushed;
         after.n_kr += 1;
         after.n_vr += 1;
-        // In the two-launch form (G = 32) of up to four query heads per kv-head the fp16-row launch quantises the flushed
-        // tokens with extra workgroups: a flush step takes two launches in all.  (3 and 4 heads, 512 units: 40.5 -> 38.7 us at
-        // 1023 tokens, 51.1 -> 49.5 at 2175, 4 bits 42.2 -> 40.5; 5 to 8 heads would lose 5-6 us: residual_rows_kernel takes
-        // longer than that kernel's own rows and a flush launch together.  Two heads: see wants_two_launches.)
+        // In the two-launch form (G = 32) the launch of the fp16 rows quantises the flushed tokens (three and more query heads per
+        // kv-head: one tile; two heads: see wants_two_launches).
         // One query head per kv-head: a flush of one tile, which is what every flushing step after the first has, rides in
         // the attention's only launch, and so does one value token (decode_one_kernel, which has both sides' figures).
         // So does one tile in decode_tiles_kernel's single-launch form.
@@ -1012,7 +1010,8 @@ int kivi_decode_step(const kivi_layout_t* l, kivi_cache_t* c, const void* k_new,
         const bool one_value = nk == 0 && nv == 1;
         if ((nk > 0 || nv > 0) &&
             (in_one ? one_tile || one_value
-                    : in_tiles || (l->group == kTileTokens && l->n_q_heads <= 4 * l->n_kv_heads && wants_two_launches(l, &after, KIVI_DECODE_MFMA, true)))) {
+                    : in_tiles || (wants_two_launches(l, &after, KIVI_DECODE_MFMA, true) &&
+                                   (l->n_q_heads > 2 * l->n_kv_heads ? one_tile : l->group == kTileTokens)))) {
             const int64_t sh = (int64_t)l->cap_r_tokens * kHeadDim, sb = sh * l->n_kv_heads;
             const RowSource ksrc{static_cast<const __half*>(c->k_resid), sb, sh, kHeadDim, c->k_r_start, l->cap_r_tokens};
             const RowSource vsrc{static_cast<const __half*>(c->v_resid), sb, sh, kHeadDim, c->v_r_start, l->cap_r_tokens};

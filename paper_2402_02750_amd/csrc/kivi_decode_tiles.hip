@@ -1334,11 +1334,13 @@ hipError_t launch_decode_tiles(DecodeParams p, hipStream_t stream) {
             p.flush_k->first_tile != p.plan.tiles_a - 1 || p.flush_v->first_token != (p.plan.tiles_a - 1) * kTileTokens)
             return hipErrorInvalidValue;
         p.plan.tiles_a -= 1;
-    } else if (p.flush_k && p.flush_v) {
-        // a step that flushes: one launch for the fp16 rows (which append the new token) and the tokens that leave the window
-        if (p.seq_state || p.head_groups != 1 || p.two_launches == 0) return hipErrorInvalidValue;
+    } else if (!p.seq_state && p.two_launches > 0 && p.n_kq == p.n_vq && p.plan.tiles_total > p.plan.tiles_a && p.plan.tiles_a > 0) {
+        // two launches: the fp16 rows (which append the new token), and the tile that leaves the window in the step
+        if (p.head_groups != 1) return hipErrorInvalidValue;
         p.rows_for_tiles = 1;
-        if (hipError_t e = launch_rows_and_flush(p, *p.flush_k, *p.flush_v, stream); e != hipSuccess) return e;
+        if (hipError_t e = launch_ragged_rows(p, p.plan.tiles_total - p.plan.tiles_a, nullptr, nullptr, p.flush_k ? p.batch : 0, nullptr, stream); e != hipSuccess) return e;
+    } else if (p.flush_k) {
+        return hipErrorInvalidValue;
     }
     hipError_t e = hipErrorNotSupported;
     with_tiles_variant(p.bits, p.rep_here, [&](auto b, auto h) {

@@ -130,8 +130,8 @@ struct DecodeParams {
     int32_t row_wgs, row_split, unit_wgs, axis_len, axis_rem;
     int32_t flushed_values;     // decode_one_kernel: value tokens it quantises itself, the last of n_vq (0 or 1)
     int32_t one_round;          // decode_one_kernel: all its workgroups fit the device at once
-    // the fp16-row launch that carries a flush, before decode_tiles_kernel: its part is the first of those that kernel merges
-    // (maximum in the log2 domain, counted as finished)
+    // a launch of the fp16 rows goes before decode_tiles_kernel (launch_ragged_rows): its part is the first of those that kernel
+    // merges (maximum in the log2 domain, counted as finished)
     int32_t rows_for_tiles;
 };
 
@@ -168,6 +168,7 @@ struct RaggedTables {
     int32_t *one_head, *first_wg;
 };
 constexpr int kInlineSequences = 192;  // sequences whose counters fit the kernel's arguments (4096 bytes)
+// p.rows_for_tiles: a batch of one length, no tables; seq and flush null, n_flush the batch, if it flushes a tile, or 0.  Otherwise
 // seq: the counters in host memory, at most kInlineSequences of them, `flush` the n_flush sequences whose last quantised tile (G = 32) is still in
 // the rings; null: the counters are in p.seq_state already, nothing is flushed and no table is written.  max_tiles: of fp16 rows, of
 // any sequence.

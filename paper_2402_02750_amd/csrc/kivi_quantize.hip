@@ -622,6 +622,26 @@ hipError_t launch_prefill(const QuantKeyParams& kp, const QuantValueParams& vp, 
     return launch_quantize_values(values_after(vp, vp.n_tokens / kTileTokens * kTileTokens), stream);
 }
 
+// One tile (G = 32) of every unit out of the rings, in registers: a wavefront for its keys, one for its values.  (A launch before the
+// attention costs a step 4.0 us with it, 4.5-5 with the forms that stage tiles in LDS; in the attention's own launch, where there is
+// such a form, less: 64 x 32 heads, 2175 tokens 101.8 us in one launch, 105.3 in two.)
+struct FlushTilesParams {
+    const __half *k_resid, *v_resid;
+    const uint32_t* k_codes; const __half* k_scale; const __half* k_zero;
+    const uint32_t* v_codes; const __half* v_scale; const __half* v_zero;
+    int32_t cap_r, cap_tiles, k_start, v_start;        // start: the slot after the flushed rows
+    int32_t tile, units;
+};
+template <int BITS>
+__global__ __launch_bounds__(256) void flush_tiles_kernel(FlushTilesParams p) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int unit = (int)blockIdx.x * 2 + (wave >> 1);
+    if (unit >= p.units) return;
+    const int64_t at = (int64_t)unit * p.cap_tiles + p.tile;
+    if (wave & 1) tile::flush_values<BITS>(p, unit, at, p.v_start, lane);
+    else tile::flush_keys<BITS>(p, unit, at, p.k_start, lane);
+}
+
 template <int BITS>
 hipError_t launch_flush_bits(const QuantKeyParams& kp, const QuantValueParams& vp, hipStream_t stream) {
     const int tg = kp.tiles_per_group;
@@ -638,6 +658,24 @@ hipError_t launch_flush_bits(const QuantKeyParams& kp, const QuantValueParams& v
 }
 
 hipError_t launch_flush_quantize(const QuantKeyParams& kp, const QuantValueParams& vp, hipStream_t stream) {
+    if (kp.tiles_per_group == 1 && vp.group_blocks == 1 && kp.n_tiles == 1 && vp.n_tokens == kTileTokens && kp.src.ring_cap >= kTileTokens &&
+        vp.first_token == kp.first_tile * kTileTokens && kp.src.ring_cap == vp.src.ring_cap && kp.bits == vp.bits) {
+        FlushTilesParams p{};
+        p.k_resid = kp.src.base;
+        p.v_resid = vp.src.base;
+        p.k_codes = kp.codes; p.k_scale = kp.scale; p.k_zero = kp.zero;
+        p.v_codes = vp.codes; p.v_scale = vp.scale; p.v_zero = vp.zero;
+        p.cap_r = kp.src.ring_cap;
+        p.cap_tiles = kp.cap_tiles;
+        p.k_start = (kp.src.ring_start + kTileTokens) % p.cap_r;
+        p.v_start = (vp.src.ring_start + kTileTokens) % p.cap_r;
+        p.tile = kp.first_tile;
+        p.units = kp.batch * kp.n_kv_heads;
+        const unsigned grid = (unsigned)((p.units + 1) / 2);
+        if (kp.bits == 2) flush_tiles_kernel<2><<<grid, 256, 0, stream>>>(p);
+        else flush_tiles_kernel<4><<<grid, 256, 0, stream>>>(p);
+        return hipGetLastError();
+    }
     if (kp.n_tiles <= 0) return launch_quantize_values(vp, stream);
     if (vp.n_tokens <= 0) return launch_quantize_keys(kp, stream);
     return kp.bits == 2 ? launch_flush_bits<2>(kp, vp, stream) : launch_flush_bits<4>(kp, vp, stream);
@@ -647,8 +685,8 @@ hipError_t launch_rows_and_flush(const DecodeParams& p, const QuantKeyParams& kp
                                  hipStream_t stream) {
     const int tiles_b = p.plan.tiles_total - p.plan.tiles_a;
     const int64_t units = (int64_t)p.batch * p.n_kv_heads;
-    const int rep = p.rep_variant <= 2 ? p.rep_variant : (p.rep_variant <= 4 ? 4 : 8);
-    if (kp.tiles_per_group != 1 || vp.group_blocks != 1 || rep > 4) return hipErrorNotSupported;
+    const int rep = p.rep_variant;
+    if (kp.tiles_per_group != 1 || vp.group_blocks != 1 || rep > 2) return hipErrorNotSupported;
     if (!residual_rows_possible(tiles_b, rep) || p.plan.n_splits_b != 1 || p.n_kq != p.n_vq) return hipErrorInvalidValue;
     if (kp.bits != vp.bits || kp.n_tiles < 0 || vp.n_tokens < 0 || kp.n_tiles + vp.n_tokens <= 0) return hipErrorInvalidValue;
     const int n_key_blocks = kp.n_tiles;
@@ -667,8 +705,7 @@ hipError_t launch_rows_and_flush(const DecodeParams& p, const QuantKeyParams& kp
         else rows_flush_kernel<R, 4><<<grid, block, lds, stream>>>(p, kp, vp, tiles_b, n_key_blocks, n_value_blocks);
     };
     if (rep == 1) go(std::integral_constant<int, 1>{});
-    else if (rep == 2) go(std::integral_constant<int, 2>{});
-    else go(std::integral_constant<int, 4>{});
+    else go(std::integral_constant<int, 2>{});
     return hipGetLastError();
 }
 

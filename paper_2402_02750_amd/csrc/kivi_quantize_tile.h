@@ -358,8 +358,8 @@ __device__ __forceinline__ void quantize_value_tile(const ValueRow (&x)[8], int 
 }
 
 // The 32 rows before ring slot `start` (the first one after them), channels 2 lane, 2 lane + 1
-template <class Row>
-__device__ __forceinline__ void load_key_rows_before(const DecodeParams& p, int64_t unit, int start, int lane, Row (&x)[kTileTokens]) {
+template <class Params>
+__device__ __forceinline__ void load_key_rows_before(const Params& p, int64_t unit, int start, int lane, half2v (&x)[kTileTokens]) {
     const int first = start - kTileTokens, k0 = first < 0 ? first + p.cap_r : first;
     const char* kr = reinterpret_cast<const char*>(p.k_resid + unit * p.cap_r * kHeadDim);
 #pragma unroll
@@ -369,7 +369,8 @@ __device__ __forceinline__ void load_key_rows_before(const DecodeParams& p, int6
     }
 }
 // ... rows 8 (lane / 16) + i, channels 8 (lane % 16) ..
-__device__ __forceinline__ void load_value_rows_before(const DecodeParams& p, int64_t unit, int start, int lane, ValueRow (&y)[8]) {
+template <class Params>
+__device__ __forceinline__ void load_value_rows_before(const Params& p, int64_t unit, int start, int lane, ValueRow (&y)[8]) {
     const int first = start - kTileTokens, v0 = first < 0 ? first + p.cap_r : first;
     const __half* vr = p.v_resid + unit * p.cap_r * kHeadDim + (lane & 15) * 8;
 #pragma unroll
@@ -422,8 +423,8 @@ __device__ __forceinline__ void flush_tile(const DecodeParams& p, int64_t unit, 
 }
 
 // Keys and values of such a tile into the packed arrays alone, one wavefront each; start: the rings' first slots after the flush
-template <int BITS>
-__device__ __forceinline__ void flush_keys(const DecodeParams& p, int64_t unit, int64_t at, int start, int lane) {
+template <int BITS, class Params>
+__device__ __forceinline__ void flush_keys(const Params& p, int64_t unit, int64_t at, int start, int lane) {
     half2v x[kTileTokens];
     load_key_rows_before(p, unit, start, lane, x);
     uint32_t* codes = const_cast<uint32_t*>(p.k_codes) + at * (kTileTokens * kHeadDim * BITS / 32);
@@ -434,8 +435,8 @@ __device__ __forceinline__ void flush_keys(const DecodeParams& p, int64_t unit, 
         },
         [&](int i, uint32_t w) { codes[i] = w; });
 }
-template <int BITS>
-__device__ __forceinline__ void flush_values(const DecodeParams& p, int64_t unit, int64_t at, int start, int lane) {
+template <int BITS, class Params>
+__device__ __forceinline__ void flush_values(const Params& p, int64_t unit, int64_t at, int start, int lane) {
     ValueRow y[8];
     load_value_rows_before(p, unit, start, lane, y);
     uint32_t* codes = const_cast<uint32_t*>(p.v_codes) + at * (kTileTokens * kHeadDim * BITS / 32);

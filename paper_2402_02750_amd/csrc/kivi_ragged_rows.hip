@@ -1,4 +1,4 @@
-// Batches of sequences of different lengths: the first of a step's two launches (KIVI Equation 4, the X_R terms, and Algorithm 1
+// Two and more query heads per kv-head, and batches of sequences of different lengths: the first of a step's two launches (KIVI Equation 4, the X_R terms, and Algorithm 1
 // Decoding).  Its workgroups have one of three roles:
 //   flush   (G = 32) one per unit of a sequence whose oldest 32 tokens leave the window: one wavefront quantises the keys, one the values
 //   tables  one: the sequences' counters and the second launch's intervals into the workspace, out of the kernel's arguments
@@ -17,6 +17,9 @@
 // Bound: latency -- launch, counters, rows, matrix unit, merge of the tiles in LDS, a chain that all wavefronts run at once.
 // Whole steps, before / with this launch: 64 sequences of 500-8000 tokens, 32 / 8 heads 81.6 / 69.5 us; 8 of them 37.1 / 24.6; 4 of 100-300
 // tokens 19.7 / 12.1; 64 / 8 heads, 4 of 4000-16 000 53.0 / 35.2, 28 / 4, 4 bits, 32 of 400-5000 68.5 / 49.2; 200 sequences, counters copied, 155 / 112.
+// Batches of one length, three and more heads, the two-launch form (kOneLength; before: the rows by decode_tiles_kernel, 53 KB of LDS a workgroup, or by
+// rows_flush_kernel, and with five and more heads a launch for the flush): 64 x 32 / 8 heads, 2000 tokens 43.9 -> 39.7 us, with a flush 45.2 ->
+// 40.3, 4096 tokens 64.6 -> 58.8; 32 x 64 / 8, 2047 39.6 -> 33.5; 16 x 64 / 8, 4095, 4 bits 50.2 -> 43.0; 32 x 28 / 4, 3000, 4 bits 34.9 -> 29.3.
 // Forms that went run by run before: G = 64, 64 x 32 / 8 heads 787 / 71 us; 71 / 1 heads, 16 sequences 399 / 41.
 #include "kivi_internal.h"
 #include "kivi_quantize_tile.h"
@@ -63,25 +66,31 @@ __device__ __forceinline__ int ring_slot(int start, int i, int cap) {
 }
 __device__ __forceinline__ half2v pack_rtz(float a, float b) { return __builtin_bit_cast(half2v, __builtin_amdgcn_cvt_pkrtz(a, b)); }
 
-// INLINE: the sequences' counters are among the arguments (otherwise in p.seq_state, and nothing is flushed here)
-template <int BITS, bool INLINE>
+// Where a sequence's counters are: among the arguments, in p.seq_state (then nothing is flushed here), or p's own for all of them
+// (a batch of one length; then there are no tables)
+constexpr int kInArguments = 0, kInMemory = 1, kOneLength = 2;
+
+template <int BITS, int SOURCE>
 __global__ __launch_bounds__(1024) void ragged_rows_kernel(RaggedRowsParams p) {
     extern __shared__ __align__(16) float sm_dyn[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_waves = blockDim.x >> 6;
     const int n = lane & 15, kb = lane >> 4;
     int at = blockIdx.x;
-    if constexpr (INLINE) {
+    const int4 all = make_int4(p.n_kq, p.n_kr, p.k_r_start, p.v_r_start);       // kOneLength
+    if constexpr (SOURCE != kInMemory) {
         if (at < p.n_flush) {
-            const int f = p.by_kv_heads.of(at), i = p.flush[f], b = p.tables.one_head ? p.sequence[i] : i;
+            const int f = p.by_kv_heads.of(at), i = SOURCE == kOneLength ? f : p.flush[f], b = SOURCE != kOneLength && p.tables.one_head ? p.sequence[i] : i;
             const int64_t unit = (int64_t)b * p.n_kv_heads + (at - f * p.n_kv_heads);
-            const int4 st = p.seq[i];
+            const int4 st = SOURCE == kOneLength ? all : p.seq[i];
             const int64_t tile = unit * p.cap_tiles + st.x / kTileTokens - 1;
             if (wave == 0) tile::flush_keys<BITS>(p, unit, tile, st.z, lane);
             if (wave == min(1, n_waves - 1)) tile::flush_values<BITS>(p, unit, tile, st.w, lane);
             return;
         }
         at -= p.n_flush;
+    }
+    if constexpr (SOURCE == kInArguments) {
         if (at == 0) {
             const RaggedTables& t = p.tables;
             int* before = reinterpret_cast<int*>(sm_dyn);               // [kInlineSequences]
@@ -139,7 +148,8 @@ __global__ __launch_bounds__(1024) void ragged_rows_kernel(RaggedRowsParams p) {
     const int rep_total = p.n_q_heads / p.n_kv_heads, h0 = p.q_head0 + chunk * p.chunk_heads;
     const int heads = min(p.chunk_heads, min(rep_total, p.q_head0 + p.rep_here) - h0);
     int4 st;
-    if constexpr (INLINE) st = p.seq[b];
+    if constexpr (SOURCE == kInArguments) st = p.seq[b];
+    else if constexpr (SOURCE == kOneLength) st = all;
     else st = reinterpret_cast<const int4*>(p.seq_state)[b];
     const int n_q = st.x, last = st.x + st.y - 1, tt = n_q + wave * kTileTokens;
     const int64_t q_row0 = (int64_t)b * p.n_q_heads + (int64_t)kvh * rep_total + h0;
@@ -252,6 +262,7 @@ __global__ __launch_bounds__(1024) void ragged_rows_kernel(RaggedRowsParams p) {
         *reinterpret_cast<float4v*>(p.part_o + row * kHeadDim + c) = o;
         if (c == 0) *reinterpret_cast<float2*>(p.part_ml + row * 2) = make_float2(m, l);
     }
+    if (SOURCE == kOneLength && tid == 0) __hip_atomic_fetch_add(p.counters + unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // (one of the parts that decode_tiles_kernel counts)
 }
 
 }  // namespace
@@ -272,8 +283,8 @@ hipError_t launch_ragged_one_head(const DecodeParams& params, const OneHeadSeque
     }
     std::copy(flush, flush + n_flush, p.flush);
     const unsigned grid = (unsigned)(p.n_flush + 1), lds = sizeof(int) * 2 * kInlineSequences;
-    if (p.bits == 2) ragged_rows_kernel<2, true><<<grid, 128, lds, stream>>>(p);
-    else ragged_rows_kernel<4, true><<<grid, 128, lds, stream>>>(p);
+    if (p.bits == 2) ragged_rows_kernel<2, kInArguments><<<grid, 128, lds, stream>>>(p);
+    else ragged_rows_kernel<4, kInArguments><<<grid, 128, lds, stream>>>(p);
     return hipGetLastError();
 }
 
@@ -281,8 +292,10 @@ hipError_t launch_ragged_rows(const DecodeParams& params, int max_tiles, const i
                               hipStream_t stream) {
     const int rep_total = params.n_q_heads / params.n_kv_heads, heads = std::min(params.rep_here, rep_total - params.q_head0);
     const int64_t units = (int64_t)params.batch * params.n_kv_heads;
-    const bool in_arguments = seq != nullptr;
-    if ((tables && tables->one_head) || max_tiles < 1 || max_tiles > 16 || heads < 1 || params.part_stride < 1 || (in_arguments ? params.batch > kInlineSequences || !tables : !params.seq_state || n_flush > 0))
+    const bool one_length = params.rows_for_tiles > 0, in_arguments = !one_length && seq != nullptr;
+    if ((tables && tables->one_head) || max_tiles < 1 || max_tiles > 16 || heads < 1 || params.part_stride < 1) return hipErrorInvalidValue;
+    if (one_length ? seq || tables || heads > 8 || (n_flush != 0 && n_flush != params.batch) || params.n_kq != params.n_vq || params.n_kr < 1
+                   : in_arguments ? params.batch > kInlineSequences || !tables : !params.seq_state || n_flush > 0)
         return hipErrorInvalidValue;
     RaggedRowsParams p{};
     static_cast<DecodeParams&>(p) = params;
@@ -293,7 +306,7 @@ hipError_t launch_ragged_rows(const DecodeParams& params, int max_tiles, const i
     p.by_kv_heads = FastDiv::by(p.n_kv_heads);
     p.by_chunks = FastDiv::by(p.n_chunks);
     p.n_flush = n_flush * p.n_kv_heads;
-    const int64_t grid = units * p.n_chunks + (in_arguments ? p.n_flush + 1 : 0);
+    const int64_t grid = units * p.n_chunks + (in_arguments ? 1 : 0) + p.n_flush;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
     size_t lds = (size_t)max_tiles * p.chunk_heads * kPartFloats * sizeof(float);
     const unsigned threads = 64 * max_tiles;
@@ -302,10 +315,13 @@ hipError_t launch_ragged_rows(const DecodeParams& params, int max_tiles, const i
         for (int b = 0; b < p.batch; ++b) p.seq[b] = make_int4(seq[4 * b], seq[4 * b + 1], seq[4 * b + 2], seq[4 * b + 3]);
         std::copy(flush, flush + n_flush, p.flush);
         lds = std::max(lds, sizeof(int) * 2 * kInlineSequences);
-        if (p.bits == 2) ragged_rows_kernel<2, true><<<(unsigned)grid, threads, lds, stream>>>(p);
-        else ragged_rows_kernel<4, true><<<(unsigned)grid, threads, lds, stream>>>(p);
+        if (p.bits == 2) ragged_rows_kernel<2, kInArguments><<<(unsigned)grid, threads, lds, stream>>>(p);
+        else ragged_rows_kernel<4, kInArguments><<<(unsigned)grid, threads, lds, stream>>>(p);
+    } else if (one_length) {
+        if (p.bits == 2) ragged_rows_kernel<2, kOneLength><<<(unsigned)grid, threads, lds, stream>>>(p);
+        else ragged_rows_kernel<4, kOneLength><<<(unsigned)grid, threads, lds, stream>>>(p);
     } else {
-        ragged_rows_kernel<2, false><<<(unsigned)grid, threads, lds, stream>>>(p);      // (the bits are the flush's)
+        ragged_rows_kernel<2, kInMemory><<<(unsigned)grid, threads, lds, stream>>>(p);      // (the bits are the flush's)
     }
     return hipGetLastError();
 }

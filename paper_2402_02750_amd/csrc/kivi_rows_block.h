@@ -181,11 +181,10 @@ __device__ __forceinline__ void residual_rows_block(const DecodeParams& p, float
         const int64_t prow = (q_row0 + hh) * row_stride;
         p.part_o[prow * kHeadDim + c] = oo;
         if (c == 0) {
-            p.part_ml[prow * 2 + 0] = p.rows_for_tiles ? mm * 1.4426950408889634f : mm;
+            p.part_ml[prow * 2 + 0] = mm;
             p.part_ml[prow * 2 + 1] = ll;
         }
     }
-    if (p.rows_for_tiles && tid == 0) __hip_atomic_fetch_add(p.counters + unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 

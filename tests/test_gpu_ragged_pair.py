@@ -98,3 +98,40 @@ def test_pair_is_deterministic(hq, hkv):
         kivi.kivi_decode_step_ragged(layout, cache, states, kn, vn, q, 128 ** -0.5, outs[-1])
     torch.cuda.synchronize()
     assert all(torch.equal(outs[0], o) for o in outs[1:])
+
+
+@pytest.mark.parametrize("hq,hkv,batch,bits,group,residual,tokens", [
+    (3, 1, 3, 2, 32, 32, 95),           # one tile quantised in the first step; windows of one and two tiles
+    (8, 2, 2, 4, 32, 128, 700),         # four heads
+    (40, 8, 5, 2, 32, 64, 1055),        # five: the flush rides too
+    (16, 2, 2, 4, 32, 160, 2000),       # eight heads, six tiles of rows
+    (24, 2, 2, 2, 32, 64, 300),         # twelve: two pairs of launches, the first flushes and appends
+    (10, 2, 2, 2, 64, 128, 800),        # G = 64: a launch for the flush
+])
+def test_one_length_in_two_launches(hq, hkv, batch, bits, group, residual, tokens):
+    """A batch of one length whose fp16 rows (and flush) have a launch of their own: 40 steps against the vector path; outputs within
+    the repository's tolerance, every byte of the cache the same."""
+    torch = gh.require_gpu()
+    print(f"case one length, two launches hq={hq} hkv={hkv} bits={bits} G={group} R={residual} L={tokens}", flush=True)
+    steps = 40
+    gen = torch.Generator(device="cuda").manual_seed(hq)
+    k, v = (torch.randn(batch, hkv, tokens + steps, 128, dtype=torch.float16, device="cuda", generator=gen) for _ in range(2))
+    caches = []
+    for path in (kivi.KIVI_DECODE_MFMA_TWO, kivi.KIVI_DECODE_VALU):
+        layout = kivi.make_layout(batch, hq, hkv, bits, residual, gh.round_up(tokens + steps, group), gh.round_up(residual + group, 32), group=group,
+                                  decode_path=path)
+        cache = kivi.Cache(layout)
+        for buf in cache.buffers.values():
+            buf.zero_()
+        kivi.kivi_prefill(layout, k, v, tokens, cache)
+        caches.append((layout, cache))
+    for step in range(steps):
+        q = torch.randn(batch, hq, 128, dtype=torch.float16, device="cuda", generator=gen)
+        new = [x[:, :, tokens + step].contiguous() for x in (k, v)]
+        outs = [torch.full((batch, hq, 128), float("nan"), dtype=torch.float32, device="cuda") for _ in caches]
+        for (layout, cache), out in zip(caches, outs):
+            kivi.kivi_decode_step(layout, cache, *new, q, 128 ** -0.5, out)
+        torch.cuda.synchronize()
+        gh.check_close(outs[0].cpu().numpy(), outs[1].cpu().numpy(), f"step {step}")
+        for name in caches[0][1].buffers:
+            assert torch.equal(caches[0][1].buffers[name], caches[1][1].buffers[name]), f"step {step}: {name}"
