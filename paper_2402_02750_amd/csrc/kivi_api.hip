@@ -249,12 +249,13 @@ int decode_family(const kivi_layout_t* l) {
 //      against two: 3 heads 28.3 / 30.0 us (4 bits 29.4 / 31.4), 8 heads 35.0 / 37.1 (4 bits 46.3 / 51.9); with 31 tiles
 //      38.5 / 35.1 and 62.4 / 58.2, and at 1024 units and 15 tiles 48.3 / 44.7 and 78.3 / 70.0.
 // `flush`: the step also flushes and the fp16-row launch could carry that out (G = 32).
-//  (0) Two heads: a flush has to end before the launch that reads its tiles, so the single-launch form takes
-//      two launches as well, the first of them nearly empty.  Riding with the fp16 rows it costs nothing of its own.
-//      Not while decode_tiles_kernel serves them well (8 units, 1055 tokens, 4 bits: 13.7 / 17.2 us; 64 units 17.1 / 17.7;
-//      even at 128; 256 units, 4095 tokens 40.7 / 35.7).
+//  (0) Two heads: a flush has to end before the launch that reads its tiles, so the single-launch form of decode_mfma_kernel takes
+//      two launches as well, the first of them nearly empty: then it rides with the fp16 rows at no cost of its own.  Up to 384
+//      units and units x tiles of 40 000 decode_tiles_kernel carries it in its only launch (136 units x 8191 tokens 41.2 -> 35.0 us, 192 x
+//      4095 32.7 -> 26.7, 256 x 4095 35.2 -> 34.2, 384 x 2047 35.4 -> 30.4; beyond: 384 x 4095 48.3 / 49.8, 256 x 16 383 91.2 / 96.8).
 // One head: decode_one_kernel, a single launch unless the caller asks for two (one_launch); (1) and (2) only decide the plan's
 // pieces, and with them the workspace that the call asks for.
+constexpr int kTwoHeadTilesUnits = 384;
 bool wants_two_launches(const kivi_layout_t* l, const kivi_cache_t* c, int path, bool flush = false) {
     if (path != KIVI_DECODE_MFMA || l->decode_path == KIVI_DECODE_MFMA_ONE) return false;
     const int rep_launch = std::min(l->n_q_heads / l->n_kv_heads, kMaxRep);
@@ -266,8 +267,8 @@ bool wants_two_launches(const kivi_layout_t* l, const kivi_cache_t* c, int path,
     if (!possible) return false;
     if (l->decode_path == KIVI_DECODE_MFMA_TWO) return true;
     const int64_t units = (int64_t)l->batch * l->n_kv_heads;
-    if (flush && rep_variant == 2 && units > 128) return true;                                       // (0)
     const int64_t work = units * tiles_total, row_work = units * tiles_b;
+    if (flush && rep_variant == 2 && units > 128) return units > kTwoHeadTilesUnits || work > 40000; // (0)
     if (rep_variant >= 4 && units < 768 && tiles_total <= 20) return false;                          // (5)
     if (rep_variant == 8) return tiles_b >= 2 && work >= 4000 && row_work >= 384;                    // (3)
     if (rep_variant == 4) return units >= 512 || (units >= 384 && work >= 40000);                    // (4)
@@ -310,18 +311,22 @@ int wide_group_runs(const kivi_layout_t* l, int path, bool two_launches) {
 // Which kernel of the matrix-core family serves the layout: decode_tiles_kernel from three query heads per
 // kv-head on (sweeps over 8-1024 units, contexts 200-30 000, 2 and 4 bits, G = 32 to 128, both policies: 1.0-2.7 times as
 // fast as decode_mfma_kernel was; slower only at 512 units: 0.93-0.96 on steps that flush with 5 to 8 heads at 4 bits, up to
-// 1055 tokens, and 0.88-0.97 with K and V split differently, mostly with 4 heads), and with two heads up to 256 units (1.03-1.19; at
-// 512 units 0.70, that kernel's cheaper tiles win).  With one head per kv-head most of its matrix columns would idle.
-bool uses_tiles(const kivi_layout_t* l) {
+// 1055 tokens, and 0.88-0.97 with K and V split differently, mostly with 4 heads), and with two heads up to 384 units where that is one
+// launch (320 units x 2047 tokens with a flush 35.1 -> 28.9 us, 384 x 1000 28.8 -> 20.0, split differently 288 x 2000 35.0 -> 28.1; from
+// 512 units on that kernel's cheaper tiles win: 512 x 1000 28.4 / 29.5 us, 4 bits, 512 x 4000 69.0 / 77.3).  With one head per kv-head most of its matrix columns would idle.
+bool uses_tiles(const kivi_layout_t* l, const kivi_cache_t* c) {
     const int rep = l->n_q_heads / l->n_kv_heads;
-    return rep >= 3 || (rep == 2 && (int64_t)l->batch * l->n_kv_heads <= 256 && l->decode_path != KIVI_DECODE_MFMA_TWO);
+    if (rep != 2) return rep >= 3;
+    // (K and V split differently, 384 units x 8000 tokens: 88.9 us here, 81.1 there; x 4000, 4 bits 59.0 / 65.7)
+    const int64_t units = (int64_t)l->batch * l->n_kv_heads, work = units * ceil_div(c->n_kq + c->n_kr, kTileTokens);
+    return (units <= 256 || (units <= kTwoHeadTilesUnits && work <= 64000)) && l->decode_path != KIVI_DECODE_MFMA_TWO;
 }
 // K and V split at different tokens (Algorithm 1's policy), decode_tiles_kernel: the tiles that are not all quantised in a
 // launch of their own, as in the two-launch form, where they would take the residency of the others in one.  From 512 units
 // on and not for short contexts (1500 tokens, 4 heads, 512 / 1024 units: 55.7 -> 46.8, 93.0 -> 82.3 us; 8 heads, 512 units
 // 66.9 -> 56.6; 500 tokens 36.7 / 37.5 and 58.6 / 60.9; 256 units, 1500 tokens 26.7 / 34.5).
 bool rows_launch_for_uneven_split(const kivi_layout_t* l, const kivi_cache_t* c, int path) {
-    return path == KIVI_DECODE_MFMA && l->decode_path != KIVI_DECODE_MFMA_ONE && uses_tiles(l) && l->n_q_heads <= kMaxRep * l->n_kv_heads &&
+    return path == KIVI_DECODE_MFMA && l->decode_path != KIVI_DECODE_MFMA_ONE && uses_tiles(l, c) && l->n_q_heads <= kMaxRep * l->n_kv_heads &&
            c->n_kq != c->n_vq && std::min(c->n_kq, c->n_vq) >= kTileTokens && (int64_t)l->batch * l->n_kv_heads >= 512 &&
            ceil_div(c->n_kq + c->n_kr, kTileTokens) > 20;
 }
@@ -381,7 +386,7 @@ int enqueue_attention(const kivi_layout_t* l, const kivi_cache_t* c, const void*
     p.two_launches = two ? 1 : 0;
     p.head_groups = wide_group_runs(l, path, two);
     const bool one = one_launch(l, c, path);
-    const bool tiles = path == KIVI_DECODE_MFMA && uses_tiles(l) && !(two && flush_k && l->n_q_heads <= 2 * l->n_kv_heads);
+    const bool tiles = path == KIVI_DECODE_MFMA && uses_tiles(l, c) && !(two && l->n_q_heads <= 2 * l->n_kv_heads);
     if ((flush_k || flush_v) && !one && !((two || tiles) && flush_k && flush_v)) return KIVI_ERR_INVALID_ARG;
     p.flush_k = flush_k;
     p.flush_v = flush_v;
@@ -1006,7 +1011,7 @@ int kivi_decode_step(const kivi_layout_t* l, kivi_cache_t* c, const void* k_new,
         // So does one tile in decode_tiles_kernel's single-launch form.
         const bool in_one = one_launch(l, &after, KIVI_DECODE_MFMA);
         const bool one_tile = l->group == kTileTokens && nk == kTileTokens && nv == kTileTokens && after.n_kq == after.n_vq;
-        const bool in_tiles = !in_one && one_tile && uses_tiles(l) && !wants_two_launches(l, &after, KIVI_DECODE_MFMA, true);
+        const bool in_tiles = !in_one && one_tile && uses_tiles(l, &after) && !wants_two_launches(l, &after, KIVI_DECODE_MFMA, true);
         const bool one_value = nk == 0 && nv == 1;
         if ((nk > 0 || nv > 0) &&
             (in_one ? one_tile || one_value
