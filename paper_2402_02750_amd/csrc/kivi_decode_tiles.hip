@@ -872,8 +872,9 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
 
     // ---- leave a unit: merge the four wavefronts; write the output or this workgroup's part ----
     // rows: this workgroup holds fp16 rows of the unit (the first parts), otherwise some of its all-quantised steps
-    // write_o(h0, f): this wavefront's outputs of the heads [h0, h0 + HR), times f, into its rows of sm_o
-    auto leave_unit = [&](int u, bool rows, auto&& write_o) {
+    // last: of the workgroup, so that no copies are in flight and all heads' outputs fit the rings; otherwise HR heads at a time
+    // write_o(o, h0, count, f): this wavefront's outputs of the heads [h0, h0 + count), times f, as rows from o on
+    auto leave_unit = [&](int u, bool rows, bool last, auto&& write_o) {
         const int64_t row0 = (int64_t)batch_of(u) * p.n_q_heads + first_head(u);
         const int live = live_heads(u);
         int parts = 0, mine = 0;
@@ -906,12 +907,17 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) m_all = fmaxf(m_all, sm_ml[w][head][0]);
         const float f_own = mref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mref - m_all);
-#pragma unroll
-        for (int h0 = 0; h0 < HP; h0 += HR) {
-            write_o(h0, f_own);
+        static_assert(HP * kHeadDim * sizeof(float) <= sizeof(sm_ring[0]), "all heads' outputs");
+        const int at_once = last ? HP : HR;
+        const uint32_t o_stride = last ? sizeof(sm_ring[0]) / sizeof(float) : HR * kHeadDim;      // from wavefront to wavefront
+        float* o_base = last ? reinterpret_cast<float*>(&sm_ring[0][0][0]) : &sm_o[0][0][0];
+#pragma unroll 1
+        for (int h0 = 0; h0 < HP; h0 += at_once) {
+            write_o(o_base + wave * o_stride, h0, at_once, f_own);
             lds_barrier();
-            const int hh = h0 + tid / (kHeadDim / 2), c = tid % (kHeadDim / 2) * 2;     // two channels of one head
-            if (hh < h0 + HR && hh < live) {
+            const int c = tid % (kHeadDim / 2) * 2;                                     // two channels of one head
+#pragma unroll 1
+            for (int hh = h0 + tid / (kHeadDim / 2); hh < min(h0 + at_once, live); hh += kWaves) {
                 float m = -INFINITY, ll = 0.f;
 #pragma unroll
                 for (int w = 0; w < kWaves; ++w) m = fmaxf(m, sm_ml[w][hh][0]);
@@ -924,7 +930,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
                 float2 oo = {0.f, 0.f};
 #pragma unroll
                 for (int w = 0; w < kWaves; ++w) {
-                    const float2 x = *reinterpret_cast<const float2*>(&sm_o[w][hh - h0][c]);
+                    const float2 x = *reinterpret_cast<const float2*>(o_base + w * o_stride + (hh - h0) * kHeadDim + c);
                     oo.x += x.x;
                     oo.y += x.y;
                 }
@@ -944,7 +950,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
                     if (c == 0) device_store(p.part_ml + at * 2, make_float2(m, ll));
                 }
             }
-            if (h0 + HR < HP || parts == 1) lds_barrier();                 // LDS is written again
+            if (h0 + at_once < HP || parts == 1) lds_barrier();            // LDS is written again
         }
         if (parts > 1) {
             // published as in decode_mfma_kernel: device-scope stores, the wait for their acknowledgement,
@@ -1046,7 +1052,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
         }
     };
 
-    auto write_acc = [&](int h0, float f) {
+    auto write_acc = [&](float* rows, int h0, int count, float f) {
         float zz[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) zz[g] = (zsum[g] + dpp<kDppRor8>(zsum[g])) * f;
@@ -1058,7 +1064,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
 #pragma unroll
             for (int i = 0; i < 4; ++i) o[i] = fmaf(acc[u8][i] + dpp<kDppRor8>(acc[u8][i]), up, zz[g]);
             const bool valid = !is_lo && (HP == 8 || (HP == 4 ? my_group == (g & 1) : my_group == g));
-            if (valid && head >= h0 && head < h0 + HR) *reinterpret_cast<float4v*>(&sm_o[wave][head - h0][u8 * 16 + kb * 4]) = o;
+            if (valid && head >= h0 && head < h0 + count) *reinterpret_cast<float4v*>(rows + (head - h0) * kHeadDim + u8 * 16 + kb * 4) = o;
         }
     };
 
@@ -1109,15 +1115,14 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
                 row_outputs(vr, pv, ro);
                 append_new_token(u, tile);
             }
-            leave_unit(u, true, [&](int h0, float f) {
+            leave_unit(u, true, true, [&](float* to, int h0, int count, float f) {
                 if (flushes) {
-                    write_acc(h0, f);
+                    write_acc(to, h0, count, f);
                     return;
                 }
-                if (h0 == 0)
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) ro[e] *= f;
-                store_rows(ro, sm_o[wave], h0, HR);
+                for (int e = 0; e < 8; ++e) ro[e] *= f;
+                store_rows(ro, reinterpret_cast<float (*)[kHeadDim]>(to), h0, count);
             });
             return;
         }
@@ -1133,7 +1138,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
             reset_state();
             set_query(raw);
             for (int tile = tile0; tile < p.plan.tiles_total; tile += kWaves * p.row_split) general_tile(u, tile);
-            leave_unit(u, true, write_acc);
+            leave_unit(u, true, true, write_acc);
             return;
         }
     }
@@ -1232,7 +1237,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
         }
         // the next query and the rows' part: there already if a tile requested after them was waited for
         if ((kRagged || left > 0) && r.j1 - r.j0 <= NB) wait_copies<0>();
-        leave_unit(u, false, write_acc);                          // (its barriers make the query visible to all wavefronts)
+        leave_unit(u, false, left <= 0, write_acc);                          // (its barriers make the query visible to all wavefronts)
         if (left <= 0) break;
         ++u;
         first = 0;
