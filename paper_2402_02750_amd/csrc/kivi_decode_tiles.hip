@@ -11,8 +11,8 @@
 // instructions as one and nothing goes through LDS:
 //   column n -> head n % HP, hi part (n < 8) or lo part (n >= 8); with HP < 8 the spare column
 //   bits select among the channel groups (below).
-//   keys  : x = q' s by packed fp16 arithmetic.  t = RN(A s), operand = RN(q' s - t) with A = 0 in the
-//           hi columns (operand = RN(q' s)) and A = q' in the lo columns (operand = the remainder,
+//   keys  : x = q' s by packed fp16 arithmetic.  operand = RN(q' s - t) with t = 0 in the hi columns (operand = RN(q' s)) and
+//           t = RN(q' s) in the lo columns (operand = the remainder,
 //           which is exact unless it leaves fp16's range).  q' is the query times a power of two
 //           that puts its largest element into [2^8, 2^9): with s < 64 nothing overflows and the
 //           remainder keeps 2^-33 of the largest product.  In a tile with a larger scale (wave-uniform
@@ -27,8 +27,10 @@
 //           i.e. four operands per tile with HP = 8; with HP = 4 the columns of a head hold two groups
 //           at once and with HP = 2 all four, so that the tile takes two operands or one (a matrix
 //           instruction of group g fills the columns of the other groups with sums that nobody reads).
-//   zero-points: keys by a 16x16x128 product (all rows alike, so every lane gets its head's sum),
-//           values by one with the rows = channel groups.
+//   zero-points: keys by a 16x16x128 product (all rows alike, so every lane gets its head's sum), or, with HP < 8, by dot products of eight
+//           channels in each of the four columns that share a head and kb, and six exchanges: 12 vector instructions in place of four
+//           of the matrix unit's, which take as long as 25 (the two units hardly overlap: 16 matrix instructions and 64 others of
+//           three wavefronts take nine tenths of the sum of their times).  Values by one product with the rows = channel groups.
 //   Both exponents hold for ordinary data at no cost per tile.  Larger key scales and value scales are looked at
 //   together with what they meet -- the query's channel, the probabilities -- and scaled down only if the products need
 //   it; the value exponent falls back when large scales are past.  (Error against 64 bits with a key channel 2^15
@@ -113,6 +115,14 @@ __device__ __forceinline__ float dpp(float x) {
 }
 constexpr int kDppRor8 = 0x128;                // rotate by 8 within 16: the hi and lo column of a head
 constexpr int kHiLanes = 0x3, kLoLanes = 0xC;  // bank masks: columns 0-7, columns 8-15
+constexpr int kDppRor4 = 0x124;
+// sum over the lanes that differ in bits 4 and 5
+__device__ __forceinline__ float add_rows(float x) {
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(x), false, false);
+    x = __int_as_float(a[0]) + __int_as_float(a[1]);
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
+    return __int_as_float(b[0]) + __int_as_float(b[1]);
+}
 // `x` of the partner column in the lanes of BANKS, `own` in the others
 template <int BANKS>
 __device__ __forceinline__ half2v from_partner(half2v own, half2v x) {
@@ -365,7 +375,10 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
     int ks;                            // value scales enter as s 2^-ks
     bool ks_set;
     uint32_t value_limit;              // fp16 pair: tiles with larger scales go to fit_value_exponent; below 2^(ks + kValueTop), or 0 with ks > 0
-    half2v qz[4][4], qk[4][4], qa[4][4];   // query: q 2^a; times 1 / position factor; the same, 0 in the hi columns
+    half2v qz[4][4], qk[4][4];         // query: q 2^a; times 1 / position factor
+    half2v rounded[4] = {};            // keys' products in the lo columns, 0 in the hi columns
+    constexpr uint64_t kLoColumns = 0xFF00FF00FF00FF00ull;
+    half2v q_zero[4];                  // HP < 8: q 2^a of channel block n / 4
     float c_code, c_zero;              // logit (log2 domain) = code sum * c_code + zero sum * c_zero
 
     auto reset_state = [&]() {
@@ -410,7 +423,13 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
                 const _Float16 pf = BITS == 2 ? (_Float16)(1.f / (float)(1 << (2 * r))) : (_Float16)((r & 1) ? 1.f / 16.f : 1.f);
                 qz[cb][r] = f.p[r] * half2v{up1, up1} * half2v{up2, up2};
                 qk[cb][r] = qz[cb][r] * half2v{pf, pf};
-                qa[cb][r] = is_lo ? qk[cb][r] : half2v{(_Float16)0.f, (_Float16)0.f};
+            }
+        }
+        if constexpr (HP < 8) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const half2v even = is_lo ? qz[2][r] : qz[0][r], odd = is_lo ? qz[3][r] : qz[1][r];
+                q_zero[r] = n & 4 ? odd : even;
             }
         }
     };
@@ -612,11 +631,15 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) {
             Frag f;
+            // In the lo columns alone; the hi columns' zeros stay.  (A second query with zeros there took sixteen registers, or was made
+            // anew with twelve instructions a tile: 64 sequences of 500-8000 tokens, 32 / 8 heads 71.1 -> 70.1 us, 16 / 8 69.0 -> 67.1.)
+            uint64_t active;
+            asm("s_and_saveexec_b64 %4, %13\n\tv_pk_mul_f16 %0, %5, %9\n\tv_pk_mul_f16 %1, %6, %10\n\tv_pk_mul_f16 %2, %7, %11\n\tv_pk_mul_f16 %3, %8, %12\n\ts_mov_b64 exec, %4"
+                : "+v"(rounded[0]), "+v"(rounded[1]), "+v"(rounded[2]), "+v"(rounded[3]), "=&s"(active)
+                : "v"(qk[cb][0]), "v"(qk[cb][1]), "v"(qk[cb][2]), "v"(qk[cb][3]), "v"(s[cb].p[0]), "v"(s[cb].p[1]), "v"(s[cb].p[2]), "v"(s[cb].p[3]), "s"(kLoColumns)
+                : "scc");
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const half2v t = qa[cb][r] * s[cb].p[r];
-                f.p[r] = __builtin_elementwise_fma(qk[cb][r], s[cb].p[r], -t);
-            }
+            for (int r = 0; r < 4; ++r) f.p[r] = __builtin_elementwise_fma(qk[cb][r], s[cb].p[r], -rounded[r]);
             d0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(key_fragment<BITS>(w, cb, 0), f.h, d0, 0, 0, 0);
             d1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(key_fragment<BITS>(w, cb, 1), f.h, d1, 0, 0, 0);
         }
@@ -693,8 +716,20 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) {
             s[cb].h = *reinterpret_cast<const half8*>(sl + kScaleOff + cb * 64 + kb * 16);
-            const half8 z = *reinterpret_cast<const half8*>(sl + kScaleOff + 256 + cb * 64 + kb * 16);
-            dz = __builtin_amdgcn_mfma_f32_16x16x32_f16(z, query_frag(cb), dz, 0, 0, 0);
+            if constexpr (HP >= 8) {
+                const half8 z = *reinterpret_cast<const half8*>(sl + kScaleOff + 256 + cb * 64 + kb * 16);
+                dz = __builtin_amdgcn_mfma_f32_16x16x32_f16(z, query_frag(cb), dz, 0, 0, 0);
+            }
+        }
+        if constexpr (HP < 8) {
+            Frag z;
+            z.h = *reinterpret_cast<const half8*>(sl + kScaleOff + 256 + (n >> 2) * 64 + kb * 16);
+            float sum = 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sum = __builtin_amdgcn_fdot2(q_zero[r], z.p[r], sum, false);
+            sum += dpp<kDppRor8>(sum);
+            sum += dpp<kDppRor4>(sum);
+            dz[0] = add_rows(sum);
         }
         const float cx = key_products(w, s, big, x);
         zk = dz[0] * c_zero;
