@@ -123,6 +123,37 @@ __device__ __forceinline__ float add_rows(float x) {
     auto b = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
     return __int_as_float(b[0]) + __int_as_float(b[1]);
 }
+__device__ __forceinline__ float max_rows(float x) {
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(x), false, false);
+    x = fmaxf(__int_as_float(a[0]), __int_as_float(a[1]));
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
+    return fmaxf(__int_as_float(b[0]), __int_as_float(b[1]));
+}
+// over the 16 lanes of a row
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141;
+__device__ __forceinline__ float row_max(float x) {
+    x = fmaxf(x, dpp<kDppXor1>(x));
+    x = fmaxf(x, dpp<kDppXor2>(x));
+    x = fmaxf(x, dpp<kDppHalfMirror>(x));
+    return fmaxf(x, dpp<kDppRor8>(x));
+}
+__device__ __forceinline__ float row_sum(float x) {
+    x += dpp<kDppXor1>(x);
+    x += dpp<kDppXor2>(x);
+    x += dpp<kDppHalfMirror>(x);
+    return x + dpp<kDppRor8>(x);
+}
+// over the 32 lanes of a half of the wavefront
+__device__ __forceinline__ float half_max(float x) {
+    x = row_max(x);
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(x), false, false);
+    return fmaxf(__int_as_float(a[0]), __int_as_float(a[1]));
+}
+__device__ __forceinline__ float half_sum(float x) {
+    x = row_sum(x);
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(x), false, false);
+    return __int_as_float(a[0]) + __int_as_float(a[1]);
+}
 // `x` of the partner column in the lanes of BANKS, `own` in the others
 template <int BANKS>
 __device__ __forceinline__ half2v from_partner(half2v own, half2v x) {
@@ -404,8 +435,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
                 top = __builtin_elementwise_max(top, __builtin_bit_cast(ushort2v, f.r[r] & 0x7FFF7FFFu));
             }
         float mx = (float)__builtin_bit_cast(_Float16, (unsigned short)max(top[0], top[1]));
-        mx = fmaxf(mx, __shfl_xor(mx, 16));
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        mx = max_rows(mx);
         const bool on = mx > 0.f;
         // 2^a mx in [2^8, 2^9) (a query below 2^-20 stays smaller), as two factors that fp16 holds
         const int a = on ? min(kQueryExp + 127 - (int)(__float_as_uint(mx) >> 23), 28) : 0, a1 = a / 2;
@@ -458,13 +488,12 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
         };
         const float mx = logits(zk - (mref - kProbExp<BITS>));
         if (__any(mx > (float)(kProbExp<BITS> + kSlack))) {
+            const bool started = __any(mref != -INFINITY);
             float t = logits(zk);
-            t = fmaxf(t, dpp<kDppRor8>(t));
-            t = fmaxf(t, __shfl_xor(t, 16));
-            t = fmaxf(t, __shfl_xor(t, 32));
+            t = max_rows(fmaxf(t, dpp<kDppRor8>(t)));
             const float mnew = fmaxf(mref, t);
             const float f = mref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mref - mnew);
-            rescale(f);
+            if (started) rescale(f);                   // (before, there is nothing to rescale)
             l_lane *= f;
             mref = mnew;
             logits(zk - (mref - kProbExp<BITS>));
@@ -533,8 +562,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
     // Exponent ks of the value scales (wave-uniform) that puts the largest of a tile's below 2^kValueTop; s2: two of them per lane
     auto wanted_exponent = [&](uint32_t s2) -> int {
         float mx = fmaxf((float)half2_of(s2)[0], (float)half2_of(s2)[1]);
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) mx = fmaxf(mx, __shfl_xor(mx, d));
+        mx = max_rows(row_max(mx));
         const int e = (int)(__float_as_uint(mx) >> 23) - 126;              // mx < 2^e (mx = 0: e = -126)
         return __builtin_amdgcn_readfirstlane(max(e - kValueTop<BITS>, -24));
     };
@@ -929,9 +957,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
         const int stride = p.part_stride, base = kRagged ? 1 : 0;           // part 0: the fp16-row launch's
         // the wavefronts' statistics, then their outputs relative to the common maximum
         {
-            float l = l_lane + dpp<kDppRor8>(l_lane);
-            l += __shfl_xor(l, 16);
-            l += __shfl_xor(l, 32);
+            const float l = add_rows(l_lane + dpp<kDppRor8>(l_lane));
             if (lane < HP) {
                 sm_ml[wave][lane][0] = mref;
                 sm_ml[wave][lane][1] = l;
@@ -1024,8 +1050,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
                     float m = kRagged ? sm_part_ml[min(sh, live - 1)][0] : -INFINITY;
 #pragma unroll
                     for (int k = 0; k < kStat; ++k) m = fmaxf(m, v[k].x);
-#pragma unroll
-                    for (int d = 1; d < 32; d <<= 1) m = fmaxf(m, __shfl_xor(m, d));
+                    m = half_max(m);
                     float lsum = 0.f;
 #pragma unroll
                     for (int k = 0; k < kStat; ++k) {
@@ -1036,8 +1061,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
                     }
 #pragma unroll
                     for (int i = sp + 32 * kStat; i < kPad; i += 32) sm_w[sh][i] = 0.f;
-#pragma unroll
-                    for (int d = 1; d < 32; d <<= 1) lsum += __shfl_xor(lsum, d);
+                    lsum = half_sum(lsum);
                     if (sp == 0) {
                         if constexpr (kRagged) {
                             const float w = __builtin_amdgcn_exp2f(sm_part_ml[min(sh, live - 1)][0] - m);

@@ -64,6 +64,19 @@ __device__ __forceinline__ int ring_slot(int start, int i, int cap) {
     s -= (s >= cap) ? cap : 0;
     return s;
 }
+// sum / maximum over the lanes that differ in bits 4 and 5
+__device__ __forceinline__ float add_rows(float x) {
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(x), false, false);
+    x = __int_as_float(a[0]) + __int_as_float(a[1]);
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
+    return __int_as_float(b[0]) + __int_as_float(b[1]);
+}
+__device__ __forceinline__ float max_rows(float x) {
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(x), false, false);
+    x = fmaxf(__int_as_float(a[0]), __int_as_float(a[1]));
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
+    return fmaxf(__int_as_float(b[0]), __int_as_float(b[1]));
+}
 __device__ __forceinline__ half2v pack_rtz(float a, float b) { return __builtin_bit_cast(half2v, __builtin_amdgcn_cvt_pkrtz(a, b)); }
 
 // Where a sequence's counters are: among the arguments, in p.seq_state (then nothing is flushed here), or p's own for all of them
@@ -196,8 +209,7 @@ __global__ __launch_bounds__(1024) void ragged_rows_kernel(RaggedRowsParams p) {
                 mx = fmaxf(mx, x[4 * half + i]);
             }
         }
-        mx = fmaxf(mx, __shfl_xor(mx, 16));
-        mx = fmaxf(mx, __shfl_xor(mx, 32));            // finite: the tile has a token
+        mx = max_rows(mx);                             // finite: the tile has a token
         float l = 0.f;
         Frag hi, mid, lo;
 #pragma unroll
@@ -214,8 +226,7 @@ __global__ __launch_bounds__(1024) void ragged_rows_kernel(RaggedRowsParams p) {
             pr[0] -= (float)mid.p[r][0]; pr[1] -= (float)mid.p[r][1];
             lo.p[r] = pack_rtz(pr[0], pr[1]);
         }
-        l += __shfl_xor(l, 16);
-        l += __shfl_xor(l, 32);
+        l = add_rows(l);
         float4v o[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
