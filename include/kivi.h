@@ -266,8 +266,8 @@ int kivi_decode_attention_static(const kivi_layout_t* layout, const kivi_cache_t
  * kivi_decode_plan) reads the new token's rows from k_new / v_new and writes them into the
  * residual rings itself.  A flush is a launch of its own before it, except:
  * 32 tokens that leave a window with K and V split alike (G = 32) are quantised in the attention's launch where that is one
- * launch, and with up to four query heads per kv-head in the first of two (which steps that flush take more often
- * than others with two heads: from 129 units on); and with one query head per kv-head so is a single value token, n_kq >= n_vq.
+ * launch, and in the first of two (which steps that flush take more often than others with two heads and more than 128 units: beyond 384 units or
+ * units x tiles of 40 000); and with one query head per kv-head so is a single value token, n_kq >= n_vq.
  *   k_new, v_new   device, fp16 [b][n_kv_heads][128]; they must stay valid until the launch has run
  *   other arguments as for kivi_decode_attention / kivi_flush_residual
  * Errors: INVALID_ARG (also: a ring is full, no capacity left for the flush), UNSUPPORTED,

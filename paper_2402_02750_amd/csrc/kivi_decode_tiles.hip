@@ -35,8 +35,8 @@
 //   together with what they meet -- the query's channel, the probabilities -- and scaled down only if the products need
 //   it; the value exponent falls back when large scales are past.  (Error against 64 bits with a key channel 2^15
 //   times larger than the others, or values of 40 000 among values of 1/16: 1e-6 to 5e-6 of the output.)
-// Counted over whole launches (2 bits, G = 32; rows, merges and all): 328 vector instructions per tile at HP = 4 for four
-// heads, 455 at HP = 8 for eight, 443 for runs of eight of 71.
+// Counted over whole launches (2 bits, G = 32; rows, merges and all): 323 vector and 17 matrix instructions per tile at HP = 4
+// for four heads, 415 and 22 at HP = 8 for eight, 427 and 23 for runs of eight of 71.
 //
 // Packed data: `global_load_lds` copies a tile (codes, and the four scale / zero-point rows with one
 // instruction) straight into the wavefront's own ring of LDS slots, NB tiles ahead, across unit
@@ -61,11 +61,12 @@
 // workgroup) on an axis that is cut into one interval per resident workgroup (kivi_tiles_plan.h); a workgroup that
 // owns part of a unit leaves a part (m, l, o[128]) per head in the workspace, the last one merges.
 //
-// Bound: about half by issue of vector instructions (three wavefronts per SIMD; by the counters 18 us of the 31-35 us
-// launch at 32 query / 8 kv heads, batch 4, 32 767 tokens, 2 bits; 12 of 30 at 64 / 8; the copies alone would stream twice as
-// fast), for the rest by what each launch pays once: ~5 us until the first tile is there, ~3 us to leave a unit, the merge.
-// Measured against decode_mfma_kernel, whole steps: 32 / 8 heads 47.2 -> 35.1 us (2.9 TB/s); 64 / 8 heads, batch 4, 16 377
-// tokens 48.4 -> 30.3 us; 71 / 1 heads, batch 16, 4095 tokens 70.6 -> 33.9 us.  Error against 64 bits 5e-6 to 1e-5 of the
+// Bound: issue (three wavefronts per SIMD; a tile costs its SIMD ~1060 cycles at HP = 4, 1190 at HP = 8: 2.6 for a vector
+// instruction, 16 for a matrix one, hardly overlapped; waits for data are 2 %; the copies alone would stream twice as fast),
+// and what each launch pays once: 4.4-5 us until the first tile is done with, 1.3-2.1 us to leave a unit, 1 us to be counted,
+// 2.2-3.5 us for the merge.
+// Whole steps at 2 bits, decode_mfma_kernel / this kernel at first / now: 32 / 8 heads, batch 4, 32 767 tokens 47.2 / 32.1 / 30.4 us
+// (3.4 TB/s); 64 / 8 heads, batch 4, 16 377 tokens 48.4 / 30.2 / 25.9; 71 / 1 heads, batch 16, 4095 tokens 70.6 / 30.4 / 25.4.  Error against 64 bits 5e-6 to 1e-5 of the
 // output (there 1e-4: codes are placed high in the mantissa here, and the matrix unit aligns products by their nominal
 // exponent).
 #include "kivi_internal.h"
