@@ -31,8 +31,9 @@
 // itself bit by bit; with a counter that hands out items the order of the sums hung on timing (11 of 11 repetitions differed at 512
 // units).  Items follow each other without rounding to steps.  Counter -> fixed shares: 32 units x 4095 tokens 11.3 -> 10.7 us, 256
 // x 1023 13.7 -> 12.8, 512 x 1023 19.0 -> 18.4, 512 x 4095 41.8 -> 42.6, 2048 x 2175 99.6 -> 101.5; 4 bits 128 x 2047 16.2 -> 15.1, 320 x 8191
-// 77.5 -> 77.9.  (A fifth wavefront: two workgroups per compute unit instead of three.  The flushing wavefront's first item asked for
-// before the flush: no change.)  Against a launch of its own before the attention: 8 units x 511 tokens 10.8 -> 9.6 us, 256 x 4095
+// 77.5 -> 77.9.  (A fifth wavefront: two workgroups per compute unit instead of three.  Keys and values by a wavefront
+// each, whose items go to the others: faster where compute units are idle, 128 units x 1023 tokens 11.8 -> 11.2 us, but 256 units 13.0 ->
+// 13.7, 2048 units 67.0 -> 68.3.  The flushing wavefront's first item asked for before the flush: no change.)  Against a launch of its own before the attention: 8 units x 511 tokens 10.8 -> 9.6 us, 256 x 4095
 // 28.1 -> 23.5, 512 x 4095 45.9 -> 41.4, 2048 x 2175 105.7 -> 103.1; 4 bits, 256 x 4095 36.4 -> 32.5, 320 x 8191 78.6 -> 77.7.  (With
 // 4 bits, 800 units and more and 2000 tokens and more, steps that flush are up to 3 % longer than decode_mfma_kernel's two launches.)
 //
