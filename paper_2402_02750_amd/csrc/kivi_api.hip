@@ -510,6 +510,12 @@ int ragged_runs(const kivi_layout_t* l) {
     const int rep = l->n_q_heads / l->n_kv_heads;
     return rep > 2 * kMaxRep ? ceil_div(rep, kMaxRep) : 1;
 }
+// G > 32 and all sequences alike: one run, which is one call of the uniform entry point, and the pair is the slower form of it (1
+// sequence of 8000 tokens, G = 64, one call / the pair: 32 / 32 heads 12.0 / 15.0 us, 16 / 8 13.0 / 21.3, 64 / 8 18.3 / 29.2; 16 of 4000, 32 / 8
+// 22.9 / 25.8, 71 / 1 33.3 / 34.9).  From two runs on the pair is the faster one (1000 and 3000 tokens, 4 bits, 32 / 8 heads 23.1 / 17.4 us).
+bool one_run_of_large_groups(const kivi_layout_t* l, const kivi_seq_state_t* st) {
+    return l->group > kTileTokens && std::all_of(st, st + l->batch, [&](const kivi_seq_state_t& x) { return same_state(x, st[0]); });
+}
 int ragged_plan(const kivi_layout_t* l, const kivi_seq_state_t* st, size_t workspace_bytes, RaggedPlan& plan) {
     if (decode_family(l) != KIVI_DECODE_MFMA || l->decode_path == KIVI_DECODE_MFMA_ONE) return kNotApplicable;
     if (l->cap_q_tokens < kTileTokens) return kNotApplicable;
@@ -524,7 +530,7 @@ int ragged_plan(const kivi_layout_t* l, const kivi_seq_state_t* st, size_t works
         max_tiles_a = std::max(max_tiles_a, tiles_a);
         max_tiles_b = std::max(max_tiles_b, ceil_div(x.n_kq + x.n_kr, kTileTokens) - tiles_a);
     }
-    if (max_tiles_a < 1 || !residual_rows_possible(max_tiles_b, rep_variant)) return kNotApplicable;
+    if (max_tiles_a < 1 || !residual_rows_possible(max_tiles_b, rep_variant) || one_run_of_large_groups(l, st)) return kNotApplicable;
     const MfmaGeometry g = mfma_geometry(l->bits, rep_launch);
     if (g.chunk_tiles == 0) return kNotApplicable;
     // (G > 32: with less workspace than documented the batch goes run by run, which asks for no more than each run's)
@@ -1095,7 +1101,8 @@ int kivi_decode_launches_ragged(const kivi_layout_t* l, const kivi_seq_state_t* 
         max_tiles_b = std::max(max_tiles_b, ceil_div(x.n_kq + x.n_kr, kTileTokens) - x.n_kq / kTileTokens);
     }
     const int rep_launch = std::min(rep_total, kMaxRep);
-    if (fast && max_tiles_a >= 1 && residual_rows_possible(max_tiles_b, rep_launch <= 2 ? rep_launch : (rep_launch <= 4 ? 4 : 8))) {
+    if (fast && max_tiles_a >= 1 && residual_rows_possible(max_tiles_b, rep_launch <= 2 ? rep_launch : (rep_launch <= 4 ? 4 : 8)) &&
+        !one_run_of_large_groups(l, states)) {
         *launches = rep_total == 1 && l->batch > kInlineSequences ? 1 : 2 * head_groups;
         return KIVI_OK;
     }

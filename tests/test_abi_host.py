@@ -343,3 +343,19 @@ def test_decode_launches_run_by_run(lib, hq, hkv, group, path):
     assert kivi.kivi_decode_launches_ragged(l, st) == expected
     if path != kivi.KIVI_DECODE_VALU:
         assert expected == 2
+
+
+@pytest.mark.parametrize("hq,hkv", [(4, 4), (16, 8), (32, 8), (64, 8), (16, 1), (71, 1)])
+def test_decode_launches_ragged_large_groups(lib, hq, hkv):
+    """G > 32: sequences all alike are one call of the uniform entry point, with the launches that it makes; any other batch takes the
+    pair that G = 32 takes for both."""
+    pair = 4 if hq == 16 * hkv else 2
+    for group in (32, 64, 128):
+        l = kivi.make_layout(3, hq, hkv, 2, 128, 4096, 256, group=group)
+        st = kivi.make_states(3)
+        for b in range(3):
+            st[b] = kivi.kivi_seq_state_t(1024, 1024, 7, 130, 7, 130)
+        alike = kivi.kivi_decode_plan(l, _fake_cache(n_kq=1024, n_vq=1024, n_kr=130, n_vr=130)).launches
+        assert kivi.kivi_decode_launches_ragged(l, st) == (alike if group > 32 else pair)
+        st[1] = kivi.kivi_seq_state_t(1024, 1024, 8, 130, 8, 130)           # the ring starts elsewhere: not alike
+        assert kivi.kivi_decode_launches_ragged(l, st) == pair

@@ -77,6 +77,35 @@ def test_pair(hq, hkv, bits, group, residual, tokens, steps, launches):
             assert kivi.kivi_decode_launches_ragged(l0, s0) == launches
 
 
+@pytest.mark.parametrize("hq,hkv,bits,group", [(2, 2, 2, 64), (4, 2, 4, 128), (8, 1, 2, 64), (17, 1, 4, 64)])
+def test_large_groups_alike(hq, hkv, bits, group):
+    """G > 32, sequences all alike: kivi_decode_step's own outputs and bytes, over steps with and without a flush."""
+    torch = gh.require_gpu()
+    print(f"case ragged, all alike hq={hq} hkv={hkv} bits={bits} G={group}", flush=True)
+    batch, tokens, steps = 3, 128 + 3 * group - 2, 5
+    gen = torch.Generator(device="cuda").manual_seed(hq)
+    k, v = (torch.randn(batch, hkv, tokens + steps, 128, dtype=torch.float16, device="cuda", generator=gen) for _ in range(2))
+    layout = kivi.make_layout(batch, hq, hkv, bits, 128, gh.round_up(tokens + steps, group), 128 + group, group=group)
+    uniform, ragged, states = kivi.Cache(layout), kivi.Cache(layout), kivi.make_states(batch)
+    for cache in (uniform, ragged):
+        for buf in cache.buffers.values():
+            buf.zero_()
+        kivi.kivi_prefill(layout, k, v, tokens, cache)
+    for b in range(batch):
+        states[b] = kivi.CacheSlice(ragged, b, 1).state()
+    for step in range(steps):
+        new = [x[:, :, tokens + step].contiguous() for x in (k, v)]
+        q = torch.randn(batch, hq, 128, dtype=torch.float16, device="cuda", generator=gen)
+        outs = [torch.full((batch, hq, 128), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2)]
+        kivi.kivi_decode_step(layout, uniform, *new, q, 128 ** -0.5, outs[0])
+        kivi.kivi_decode_step_ragged(layout, ragged, states, *new, q, 128 ** -0.5, outs[1])
+        torch.cuda.synchronize()
+        assert torch.isfinite(outs[0]).all() and torch.equal(outs[0], outs[1]), f"step {step}"
+        for name in uniform.buffers:
+            assert torch.equal(uniform.buffers[name], ragged.buffers[name]), f"step {step}: {name}"
+    assert all(s.n_kq == uniform.c.n_kq for s in states) and uniform.c.n_kq > 2 * group
+
+
 @pytest.mark.parametrize("hq,hkv", [(16, 4), (4, 4)])
 def test_pair_is_deterministic(hq, hkv):
     """The same step on copies of one cache: the same bytes (sums in the same order, whichever workgroup comes last)."""
