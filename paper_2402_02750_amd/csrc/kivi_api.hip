@@ -487,14 +487,15 @@ constexpr int kNotApplicable = 1;       // (internal) the fast path does not ser
 struct RaggedPlan {
     DecodeParams p;             // all but the addresses and the query
     bool tiles;                 // decode_tiles_kernel, and launch_ragged_rows before it
-    bool in_arguments;          // ... which takes the counters as arguments and writes the tables itself
+    bool tables_on_device;      // ... which makes the tables itself
+    bool in_arguments;          // the first launch takes the counters as arguments (otherwise they are copied)
     int max_row_tiles;          // of any sequence
     int units_per_sequence;     // decode_tiles_kernel
     std::vector<OneHeadSequence> sequences;     // decode_one_kernel, longest first
     size_t parts_offset;        // of the parts in the workspace
     // what the kernels read per call, int32: the sequences' counters (state_ints with the padding), the workgroups' table
-    // from state_ints on and the sequences' from unit_table on; one head per kv-head: the sequences' table, and their first
-    // workgroups from unit_table on (the two tables are left to the first launch with in_arguments)
+    // from state_ints on and the sequences' from unit_table on (left to the first launch with tables_on_device); one head per
+    // kv-head: the sequences' table, and their first workgroups from unit_table on (left to the first launch with in_arguments)
     std::vector<int32_t> tables;
     size_t state_ints, unit_table;
     std::vector<int32_t> steps;
@@ -558,12 +559,13 @@ int ragged_plan(const kivi_layout_t* l, const kivi_seq_state_t* st, size_t works
     const size_t asked = (size_t)l->batch * l->n_q_heads * p.plan.n_splits() * (kHeadDim + 2) * sizeof(float);
     if (rep_total <= 2 && parts_offset + asked > workspace_bytes) return KIVI_ERR_WORKSPACE;
 
-    // What the kernels read per call goes to the device as arguments of the first launch, or (many sequences) in ONE copy, which is
-    // an operation of its own on the stream.  (An asynchronous copy out of pageable memory has taken its source when the call
-    // returns.)
+    // What the kernels read per call goes to the device as arguments of the first launch, or (many sequences) in a copy, which is
+    // an operation of its own on the stream: the counters, 16 bytes per sequence, out of which the first launch makes the tables, or (one head,
+    // room for a single part, more sequences still) the tables too.  (An asynchronous copy out of pageable memory has taken its source
+    // when the call returns.)  With the tables copied as well, 250 sequences of 500 tokens, 2 / 1 heads, took 75.7 us in place of 60.8.
     std::vector<int32_t>& tables = plan.tables;
     const bool tiles = plan.tiles = ragged_on_tiles(l);
-    plan.in_arguments = false;
+    plan.in_arguments = plan.tables_on_device = false;
     plan.max_row_tiles = max_tiles_b;
     p.head_groups = tiles ? ragged_runs(l) : 1;
     if (tiles) {
@@ -589,8 +591,9 @@ int ragged_plan(const kivi_layout_t* l, const kivi_seq_state_t* st, size_t works
         if (stride < 2) return KIVI_ERR_WORKSPACE;
         const int resident = std::min(tiles_resident_ragged(l->bits, rep_launch, l->group > kTileTokens), kMaxSlices);
         RaggedCut cut = ragged_axis(steps, units_per_sequence, resident, stride);
-        plan.in_arguments = l->batch <= kInlineSequences && !cut.whole_units;
-        if (!plan.in_arguments) cut = cut_ragged(steps, units_per_sequence, resident, stride, tables);
+        plan.tables_on_device = l->batch <= kDeviceTableSequences && !cut.whole_units;
+        plan.in_arguments = l->batch <= kInlineSequences && plan.tables_on_device;
+        if (!plan.tables_on_device) cut = cut_ragged(steps, units_per_sequence, resident, stride, tables);
         p.axis_len = cut.axis.len;
         p.axis_rem = cut.axis.rem;
         plan.unit_table = plan.state_ints + (size_t)cut.workgroups * RaggedCut::kWords;
@@ -663,8 +666,13 @@ int ragged_launch(const kivi_layout_t* l, const kivi_cache_t* c, const RaggedPla
     p.unit_parts = dev_state + plan.unit_table;
     p.part_o = reinterpret_cast<float*>(ws + plan.parts_offset);
     p.part_ml = p.part_o + (size_t)l->batch * l->n_q_heads * p.part_stride * kHeadDim;
-    if (!plan.in_arguments && hipMemcpyAsync(dev_state, plan.tables.data(), plan.tables.size() * sizeof(int32_t), hipMemcpyHostToDevice, hs) != hipSuccess)
-        return KIVI_ERR_HIP;
+    // In pieces: up to 16 KB a copy is a kernel of 2 us; for more the stream waits for the copy engine, 13 us longer.
+    constexpr size_t kPiece = 16384;
+    const size_t copied = plan.in_arguments ? 0 : plan.tables.size() * sizeof(int32_t);
+    for (size_t at = 0; at < copied; at += kPiece)
+        if (hipMemcpyAsync(reinterpret_cast<char*>(dev_state) + at, reinterpret_cast<const char*>(plan.tables.data()) + at, std::min(kPiece, copied - at),
+                           hipMemcpyHostToDevice, hs) != hipSuccess)
+            return KIVI_ERR_HIP;
     if (!plan.tiles) {
         const RaggedTables tables{nullptr, nullptr, nullptr, 0, 0, 0, 0, dev_state, dev_state + plan.unit_table};
         if (plan.in_arguments) {
@@ -685,7 +693,7 @@ int ragged_launch(const kivi_layout_t* l, const kivi_cache_t* c, const RaggedPla
         DecodeParams rows = p;
         if (p.head_groups > 1) rows.rep_here = rep_total;
         hipError_t e = launch_ragged_rows(rows, plan.max_row_tiles, plan.in_arguments ? plan.tables.data() : nullptr, flush, h0 == 0 ? n_flush : 0,
-                                          plan.in_arguments ? &device_tables : nullptr, hs);
+                                          plan.tables_on_device ? &device_tables : nullptr, hs);
         p.k_new = p.v_new = nullptr;
         if (e == hipSuccess) e = launch_decode_tiles(p, hs);
         if (e == hipErrorNotSupported) return KIVI_ERR_UNSUPPORTED;

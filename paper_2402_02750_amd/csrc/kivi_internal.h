@@ -168,9 +168,10 @@ struct RaggedTables {
     int32_t *one_head, *first_wg;
 };
 constexpr int kInlineSequences = 192;  // sequences whose counters fit the kernel's arguments (4096 bytes)
+constexpr int kDeviceTableSequences = 4096;    // ... of which the launch makes the tables, at most (8 bytes of LDS each)
 // p.rows_for_tiles: a batch of one length, no tables; seq and flush null, n_flush the batch, if it flushes a tile, or 0.  Otherwise
 // seq: the counters in host memory, at most kInlineSequences of them, `flush` the n_flush sequences whose last quantised tile (G = 32) is still in
-// the rings; null: the counters are in p.seq_state already, nothing is flushed and no table is written.  max_tiles: of fp16 rows, of
+// the rings; null: the counters are in p.seq_state already, nothing is flushed, and tables may be null (there already).  max_tiles: of fp16 rows, of
 // any sequence.
 // one_head (tables->one_head): no fp16 rows; `sequences` in the order of the table, seq and flush in that order too.
 hipError_t launch_ragged_one_head(const DecodeParams& p, const OneHeadSequence* sequences, const uint8_t* flush, int n_flush, const RaggedTables& tables,

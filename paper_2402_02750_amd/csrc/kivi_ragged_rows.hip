@@ -1,7 +1,7 @@
 // Two and more query heads per kv-head, and batches of sequences of different lengths: the first of a step's two launches (KIVI Equation 4, the X_R terms, and Algorithm 1
 // Decoding).  Its workgroups have one of three roles:
 //   flush   (G = 32) one per unit of a sequence whose oldest 32 tokens leave the window: one wavefront quantises the keys, one the values
-//   tables  one: the sequences' counters and the second launch's intervals into the workspace, out of the kernel's arguments
+//   tables  one: the second launch's intervals into the workspace, and the sequences' counters, where they are arguments
 //   rows    one per (batch, kv-head) and run of up to 16 query heads: attention over the fp16 rows, and the append of the new token
 // The roles do not wait for each other: the rows leave out what is flushed, and the flush reads slots that the append does not
 // write (a ring never is full before an append).
@@ -103,23 +103,26 @@ __global__ __launch_bounds__(1024) void ragged_rows_kernel(RaggedRowsParams p) {
         }
         at -= p.n_flush;
     }
-    if constexpr (SOURCE == kInArguments) {
+    const bool makes_tables = SOURCE == kInArguments || (SOURCE == kInMemory && p.tables.intervals);
+    if (makes_tables) {
         if (at == 0) {
             const RaggedTables& t = p.tables;
-            int* before = reinterpret_cast<int*>(sm_dyn);               // [kInlineSequences]
-            int* steps = before + kInlineSequences;
-            const bool one_head = t.one_head != nullptr;
+            int* before = reinterpret_cast<int*>(sm_dyn);               // [batch]
+            int* steps = before + p.batch;
+            const bool one_head = SOURCE == kInArguments && t.one_head != nullptr;
             if (wave == 0) {
                 int sum = 0;
                 for (int b0 = 0; b0 < p.batch; b0 += 64) {
                     const int b = b0 + lane;
                     int mine = 0;
                     if (b < p.batch) {
-                        const int4 st = p.seq[b];
+                        int4 st;
+                        if constexpr (SOURCE == kInArguments) st = p.seq[b];
+                        else st = reinterpret_cast<const int4*>(p.seq_state)[b];
                         if (one_head) {
                             mine = (st.y >> 16) * p.n_kv_heads;         // (of the workgroups' axis)
                         } else {
-                            reinterpret_cast<int4*>(t.seq_state)[b] = st;
+                            if (SOURCE == kInArguments) reinterpret_cast<int4*>(t.seq_state)[b] = st;
                             steps[b] = ragged_steps(st.x);
                             mine = steps[b] * t.units_per_sequence;
                         }
@@ -293,7 +296,7 @@ hipError_t launch_ragged_one_head(const DecodeParams& params, const OneHeadSeque
         p.sequence[i] = (uint8_t)s.sequence;
     }
     std::copy(flush, flush + n_flush, p.flush);
-    const unsigned grid = (unsigned)(p.n_flush + 1), lds = sizeof(int) * 2 * kInlineSequences;
+    const unsigned grid = (unsigned)(p.n_flush + 1), lds = sizeof(int) * 2 * p.batch;
     if (p.bits == 2) ragged_rows_kernel<2, kInArguments><<<grid, 128, lds, stream>>>(p);
     else ragged_rows_kernel<4, kInArguments><<<grid, 128, lds, stream>>>(p);
     return hipGetLastError();
@@ -306,7 +309,8 @@ hipError_t launch_ragged_rows(const DecodeParams& params, int max_tiles, const i
     const bool one_length = params.rows_for_tiles > 0, in_arguments = !one_length && seq != nullptr;
     if ((tables && tables->one_head) || max_tiles < 1 || max_tiles > 16 || heads < 1 || params.part_stride < 1) return hipErrorInvalidValue;
     if (one_length ? seq || tables || heads > 8 || (n_flush != 0 && n_flush != params.batch) || params.n_kq != params.n_vq || params.n_kr < 1
-                   : in_arguments ? params.batch > kInlineSequences || !tables : !params.seq_state || n_flush > 0)
+                   : in_arguments ? params.batch > kInlineSequences || !tables
+                                  : !params.seq_state || n_flush > 0 || (tables && params.batch > kDeviceTableSequences))
         return hipErrorInvalidValue;
     RaggedRowsParams p{};
     static_cast<DecodeParams&>(p) = params;
@@ -317,15 +321,17 @@ hipError_t launch_ragged_rows(const DecodeParams& params, int max_tiles, const i
     p.by_kv_heads = FastDiv::by(p.n_kv_heads);
     p.by_chunks = FastDiv::by(p.n_chunks);
     p.n_flush = n_flush * p.n_kv_heads;
-    const int64_t grid = units * p.n_chunks + (in_arguments ? 1 : 0) + p.n_flush;
+    const int64_t grid = units * p.n_chunks + (tables ? 1 : 0) + p.n_flush;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
     size_t lds = (size_t)max_tiles * p.chunk_heads * kPartFloats * sizeof(float);
     const unsigned threads = 64 * max_tiles;
-    if (in_arguments) {
+    if (tables) {
         p.tables = *tables;
+        lds = std::max(lds, sizeof(int) * 2 * p.batch);
+    }
+    if (in_arguments) {
         for (int b = 0; b < p.batch; ++b) p.seq[b] = make_int4(seq[4 * b], seq[4 * b + 1], seq[4 * b + 2], seq[4 * b + 3]);
         std::copy(flush, flush + n_flush, p.flush);
-        lds = std::max(lds, sizeof(int) * 2 * kInlineSequences);
         if (p.bits == 2) ragged_rows_kernel<2, kInArguments><<<(unsigned)grid, threads, lds, stream>>>(p);
         else ragged_rows_kernel<4, kInArguments><<<(unsigned)grid, threads, lds, stream>>>(p);
     } else if (one_length) {

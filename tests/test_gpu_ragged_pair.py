@@ -33,6 +33,11 @@ CASES = [
     (2, 2, 2, 32, 480, [520, 600, 2000], 3, 2),         # a window of sixteen tiles
     (1, 1, 2, 32, 32, [63 + i for i in range(192)], 2, 2),
     (1, 1, 4, 32, 32, [63 + i for i in range(193)], 2, 1),      # counters copied, no first launch; two levels of the search
+    (1, 1, 2, 32, 32, [40 + 7 * (i % 97) for i in range(500)], 2, 1),   # the copy in two pieces
+    (2, 1, 2, 32, 32, [40 + 7 * (i % 97) for i in range(500)], 2, 2),   # the tables made out of copied counters
+    (8, 2, 4, 64, 64, [70 + 9 * (i % 59) for i in range(250)], 2, 2),
+    (10, 1, 2, 32, 64, [70 + 9 * (i % 59) for i in range(250)], 2, 4),
+    (17, 1, 2, 32, 64, [70 + 9 * (i % 59) for i in range(200)], 2, 2),
 ]
 
 
@@ -104,6 +109,30 @@ def test_large_groups_alike(hq, hkv, bits, group):
         for name in uniform.buffers:
             assert torch.equal(uniform.buffers[name], ragged.buffers[name]), f"step {step}: {name}"
     assert all(s.n_kq == uniform.c.n_kq for s in states) and uniform.c.n_kq > 2 * group
+
+
+@pytest.mark.parametrize("batch", [4096, 4097])
+@pytest.mark.parametrize("hq", [1, 2, 4])
+def test_many_sequences(hq, batch):
+    """As many sequences as the first launch makes tables for, and one more: attention against the vector path."""
+    torch = gh.require_gpu()
+    print(f"case many sequences hq={hq} B={batch}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(hq)
+    k, v = (torch.randn(batch, 1, 224, 128, dtype=torch.float16, device="cuda", generator=gen) for _ in range(2))
+    q = torch.randn(batch, hq, 128, dtype=torch.float16, device="cuda", generator=gen)
+    outs = []
+    for path in (kivi.KIVI_DECODE_AUTO, kivi.KIVI_DECODE_VALU):
+        layout = kivi.make_layout(batch, hq, 1, 2, 32, 224, 64, decode_path=path)
+        cache, states = kivi.Cache(layout), kivi.make_states(batch)
+        kivi.kivi_prefill(layout, k, v, 224, cache)
+        for b in range(batch):                  # what is there of a sequence differs from its neighbours'
+            n_q, n_r = 32 * (b * 5 % 7), 1 + b * 3 % 32
+            states[b] = kivi.kivi_seq_state_t(n_q, n_q, 0, n_r, 0, n_r)
+        outs.append(torch.full((batch, hq, 128), float("nan"), dtype=torch.float32, device="cuda"))
+        kivi.kivi_decode_attention_ragged(layout, cache, states, q, 128 ** -0.5, outs[-1])
+    torch.cuda.synchronize()
+    assert kivi.kivi_decode_launches_ragged(kivi.make_layout(batch, hq, 1, 2, 32, 224, 64), states) == (1 if hq == 1 else 2)
+    gh.check_close(outs[0].cpu().numpy(), outs[1].cpu().numpy())
 
 
 @pytest.mark.parametrize("hq,hkv", [(16, 4), (4, 4)])
