@@ -622,9 +622,12 @@ hipError_t launch_prefill(const QuantKeyParams& kp, const QuantValueParams& vp, 
     return launch_quantize_values(values_after(vp, vp.n_tokens / kTileTokens * kTileTokens), stream);
 }
 
-// One tile (G = 32) of every unit out of the rings, in registers: a wavefront for its keys, one for its values.  (A launch before the
-// attention costs a step 4.0 us with it, 4.5-5 with the forms that stage tiles in LDS; in the attention's own launch, where there is
-// such a form, less: 64 x 32 heads, 2175 tokens 101.8 us in one launch, 105.3 in two.)
+// One tile (G = 32) of every unit out of the rings, in registers: a wavefront for its keys, one for its values.  For many units: with
+// few, the chain of one wavefront's 32 tokens is what a launch waits for, and the form that stages a tile in LDS for a whole workgroup is
+// the faster one (launch after launch, that form / this one, us: 2 bits, 64 units 4.1 / 4.8, 256 4.5 / 4.8, 384 4.9 / 5.0, 448 5.4 / 5.0, 1024 7.9 /
+// 6.3, 2048 12.8 / 10.3; 4 bits, 64 units 3.7 / 5.1, 512 4.9 / 5.3, 768 6.0 / 6.2, 896 6.8 / 6.3, 2048 11.8 / 11.0).  (In the attention's own
+// launch, where there is such a form, less than either: 64 x 32 heads, 2175 tokens 101.8 us in one launch, 105.3 in two.)
+constexpr int flush_tiles_units(int bits) { return bits == 2 ? 448 : 896; }
 struct FlushTilesParams {
     const __half *k_resid, *v_resid;
     const uint32_t* k_codes; const __half* k_scale; const __half* k_zero;
@@ -659,7 +662,8 @@ hipError_t launch_flush_bits(const QuantKeyParams& kp, const QuantValueParams& v
 
 hipError_t launch_flush_quantize(const QuantKeyParams& kp, const QuantValueParams& vp, hipStream_t stream) {
     if (kp.tiles_per_group == 1 && vp.group_blocks == 1 && kp.n_tiles == 1 && vp.n_tokens == kTileTokens && kp.src.ring_cap >= kTileTokens &&
-        vp.first_token == kp.first_tile * kTileTokens && kp.src.ring_cap == vp.src.ring_cap && kp.bits == vp.bits) {
+        vp.first_token == kp.first_tile * kTileTokens && kp.src.ring_cap == vp.src.ring_cap && kp.bits == vp.bits &&
+        kp.batch * kp.n_kv_heads >= flush_tiles_units(kp.bits)) {
         FlushTilesParams p{};
         p.k_resid = kp.src.base;
         p.v_resid = vp.src.base;

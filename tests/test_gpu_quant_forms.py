@@ -55,10 +55,11 @@ def test_prefill(batch, heads, tokens, group, order, policy, bits):
 
 
 @pytest.mark.parametrize("bits", [2, 4])
-@pytest.mark.parametrize("batch,heads,group", [(1, 1, 32), (3, 5, 32), (1, 2, 64)])
+@pytest.mark.parametrize("batch,heads,group", [(1, 1, 32), (3, 5, 32), (1, 2, 64), (149, 3, 32), (128, 7, 32), (299, 3, 32)])
 def test_flush(batch, heads, group, bits):
     """A step's flush out of rings whose oldest row is at slot 0, 32, 64, ... (wrapping): the packed arrays equal
-    those of one pass over the whole prompt."""
+    those of one pass over the whole prompt.  Few units (a workgroup per tile) and many (a wavefront each; from 448 on, at 4 bits from
+    896 on)."""
     torch = gh.require_gpu()
     print(f"case flush B={batch} H={heads} G={group} bits={bits}", flush=True)
     residual = max(group, 32)
