@@ -664,7 +664,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void decode_tiles_kernel(TilesParam
             // anew with twelve instructions a tile: 64 sequences of 500-8000 tokens, 32 / 8 heads 71.1 -> 70.1 us, 16 / 8 69.0 -> 67.1.)
             uint64_t active;
             asm("s_and_saveexec_b64 %4, %13\n\tv_pk_mul_f16 %0, %5, %9\n\tv_pk_mul_f16 %1, %6, %10\n\tv_pk_mul_f16 %2, %7, %11\n\tv_pk_mul_f16 %3, %8, %12\n\ts_mov_b64 exec, %4"
-                : "+v"(rounded[0]), "+v"(rounded[1]), "+v"(rounded[2]), "+v"(rounded[3]), "=&s"(active)
+                : "+&v"(rounded[0]), "+&v"(rounded[1]), "+&v"(rounded[2]), "+&v"(rounded[3]), "=&s"(active)
                 : "v"(qk[cb][0]), "v"(qk[cb][1]), "v"(qk[cb][2]), "v"(qk[cb][3]), "v"(s[cb].p[0]), "v"(s[cb].p[1]), "v"(s[cb].p[2]), "v"(s[cb].p[3]), "s"(kLoColumns)
                 : "scc");
 #pragma unroll
