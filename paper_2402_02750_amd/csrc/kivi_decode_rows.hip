@@ -23,10 +23,6 @@ __global__ __launch_bounds__(1024) void residual_rows_kernel(DecodeParams p) {
 
 }  // namespace
 
-bool residual_rows_possible(int tiles_b, int rep_variant) {
-    return tiles_b >= 1 && tiles_b <= 16 && tiles_b * rep_variant <= 64;
-}
-
 hipError_t launch_residual_rows(const DecodeParams& p, hipStream_t stream) {
     const int tiles_b = p.plan.tiles_total - p.plan.tiles_a;
     const int64_t units = (int64_t)p.batch * p.n_kv_heads;

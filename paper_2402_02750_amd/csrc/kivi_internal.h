@@ -181,8 +181,6 @@ hipError_t launch_ragged_rows(const DecodeParams& p, int max_tiles, const int32_
 // the same launch with extra workgroups that quantise the key group(s) and value tokens of a residual
 // flush (G = 32 only: hipErrorNotSupported otherwise, nothing launched)
 hipError_t launch_rows_and_flush(const DecodeParams& p, const QuantKeyParams& kp, const QuantValueParams& vp, hipStream_t stream);
-// whether launch_residual_rows serves `tiles_b` tiles of fp16 rows on the instantiation for `rep_variant` heads
-bool residual_rows_possible(int tiles_b, int rep_variant);
 hipError_t launch_merge(const DecodeParams& p, hipStream_t stream);
 hipError_t launch_stream_read(const void* src, size_t bytes, uint32_t* sink, hipStream_t stream);
 

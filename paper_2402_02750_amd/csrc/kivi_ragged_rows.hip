@@ -307,6 +307,7 @@ hipError_t launch_ragged_rows(const DecodeParams& params, int max_tiles, const i
     const int rep_total = params.n_q_heads / params.n_kv_heads, heads = std::min(params.rep_here, rep_total - params.q_head0);
     const int64_t units = (int64_t)params.batch * params.n_kv_heads;
     const bool one_length = params.rows_for_tiles > 0, in_arguments = !one_length && seq != nullptr;
+    // (max_tiles and heads: as residual_rows_possible has them)
     if ((tables && tables->one_head) || max_tiles < 1 || max_tiles > 16 || heads < 1 || params.part_stride < 1) return hipErrorInvalidValue;
     if (one_length ? seq || tables || heads > 8 || (n_flush != 0 && n_flush != params.batch) || params.n_kq != params.n_vq || params.n_kr < 1
                    : in_arguments ? params.batch > kInlineSequences || !tables
@@ -314,9 +315,10 @@ hipError_t launch_ragged_rows(const DecodeParams& params, int max_tiles, const i
         return hipErrorInvalidValue;
     RaggedRowsParams p{};
     static_cast<DecodeParams&>(p) = params;
-    // the instruction's 16 columns, as far as the tiles' outputs fit 64 KB of LDS
-    p.chunk_heads = std::min(heads, max_tiles <= 7 ? 16 : max_tiles <= 15 ? 8 : 7);
+    p.chunk_heads = rows_chunk_heads(heads, max_tiles);
     p.n_chunks = (heads + p.chunk_heads - 1) / p.chunk_heads;
+    if (p.chunk_heads * max_tiles > kRowsChunkTiles) return hipErrorInvalidValue;
+    if (one_length && p.n_chunks != 1) return hipErrorInvalidValue;      // (a unit's rows are counted as one part)
     p.rep_here = heads;
     p.by_kv_heads = FastDiv::by(p.n_kv_heads);
     p.by_chunks = FastDiv::by(p.n_chunks);

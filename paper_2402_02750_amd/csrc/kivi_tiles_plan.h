@@ -62,6 +62,16 @@ struct RaggedCut {
     static constexpr int kWords = 4;
 };
 
+// Query heads that a workgroup of ragged_rows_kernel takes at once: the matrix instruction's 16 columns, or 8 of them where the
+// tiles' outputs (kRowsChunkTiles heads times tiles: 62 KB of LDS) ask for it.
+constexpr int kRowsChunkTiles = 120;
+inline int rows_chunk_heads(int heads, int tiles) { return std::min(heads, tiles <= 7 ? 16 : 8); }
+// fp16 rows in a launch of their own: up to 16 tiles, one wavefront each; 8 with five and more heads.  With one and two heads
+// residual_rows_kernel takes them all, from three on ragged_rows_kernel, a unit's heads in one workgroup wherever a batch of one
+// length sends them there (8 heads x 8 tiles, 4 x 16).  The line of 64 lets a window of more than 8 tiles under five and more heads
+// keep to the single launch.
+inline bool residual_rows_possible(int tiles_b, int rep_variant) { return tiles_b >= 1 && tiles_b <= 16 && tiles_b * rep_variant <= 64; }
+
 // a unit's steps, of a sequence with n_q quantised tokens (with none: one empty step)
 KIVI_HOST_DEVICE int ragged_steps(int n_q) {
     const int tiles = n_q / 32, steps = (tiles + kStepTiles - 1) / kStepTiles;

@@ -125,6 +125,15 @@ extern "C" int check_uniform(int units, int tiles_a, int row_tiles, int resident
     }
     return 0;
 }
+// the fp16 rows in a launch of their own: a batch of one length in one workgroup per unit, any other within 64 KB of LDS
+extern "C" int check_rows(int heads, int tiles) {
+    const int here = std::min(heads, 8), variant = here <= 2 ? here : here <= 4 ? 4 : 8;
+    if (!residual_rows_possible(tiles, variant)) return 0;
+    const int one_length = rows_chunk_heads(here, tiles), wide = rows_chunk_heads(heads > 16 ? heads : here, tiles);
+    if (one_length != here) return 1;                   // a second workgroup would count its unit's rows twice
+    if (std::max(one_length, wide) * tiles > kRowsChunkTiles || kRowsChunkTiles * (128 + 4) * 4 > 65536) return 2;
+    return 3;
+}
 extern "C" int check_range(int n_max, int units_max, int max_wgs, int rows, int* at) {
     for (int n = 1; n <= n_max; ++n)
         for (int units = 1; units <= units_max; ++units) {
@@ -157,6 +166,12 @@ def test_intervals(plan, steps):
         for rows in (3, 4, 38, 128):
             for wgs in RESIDENT:
                 assert plan.check_intervals(arr, len(steps), units, wgs, rows) == 0, f"{units} units, {wgs} workgroups, {rows} rows"
+
+
+@pytest.mark.parametrize("heads", [1, 2, 3, 4, 5, 7, 8, 9, 16, 17, 71, 128])
+def test_rows(plan, heads):
+    """Tiles of fp16 rows that a launch of their own takes: all up to 16 with one to four heads, up to 8 with more."""
+    assert [plan.check_rows(heads, tiles) for tiles in range(18)] == [3 * (1 <= tiles <= (16 if heads <= 4 else 8)) for tiles in range(18)]
 
 
 @pytest.mark.parametrize("d", [1, 2, 3, 5, 7, 31, 32, 33, 640, 641, 6700417, (1 << 30) - 1, 1 << 30, (1 << 30) + 1, (1 << 31) - 1])
