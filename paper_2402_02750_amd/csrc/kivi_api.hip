@@ -511,11 +511,26 @@ int ragged_runs(const kivi_layout_t* l) {
     const int rep = l->n_q_heads / l->n_kv_heads;
     return rep > 2 * kMaxRep ? ceil_div(rep, kMaxRep) : 1;
 }
-// G > 32 and all sequences alike: one run, which is one call of the uniform entry point, and the pair is the slower form of it (1
-// sequence of 8000 tokens, G = 64, one call / the pair: 32 / 32 heads 12.0 / 15.0 us, 16 / 8 13.0 / 21.3, 64 / 8 18.3 / 29.2; 16 of 4000, 32 / 8
-// 22.9 / 25.8, 71 / 1 33.3 / 34.9).  From two runs on the pair is the faster one (1000 and 3000 tokens, 4 bits, 32 / 8 heads 23.1 / 17.4 us).
-bool one_run_of_large_groups(const kivi_layout_t* l, const kivi_seq_state_t* st) {
-    return l->group > kTileTokens && std::all_of(st, st + l->batch, [&](const kivi_seq_state_t& x) { return same_state(x, st[0]); });
+// G > 32: few runs of equal sequences take a call of the uniform entry point each.
+// All sequences alike: that one call is faster than the pair (1 sequence of 8000 tokens, G = 64, one call / the pair: 32 / 32 heads 12.0 /
+// 15.0 us, 16 / 8 13.0 / 21.3, 64 / 8 18.3 / 29.2; 16 of 4000, 32 / 8 22.9 / 25.8, 71 / 1 33.3 / 34.9).  From two runs on the pair is the
+// faster one (1000 and 3000 tokens, 4 bits, 32 / 8 heads 23.1 / 17.4 us),
+// but with 9 to 16 heads it is two pairs against one launch a run.  Two sequences, calls / pairs: 96 / 8 heads, 150-300 tokens 19.7 / 27.7 us,
+// 4000-4600 29.3 / 48.7, 12 / 1, 300-1000 22.8 / 32.8, 32 / 2, 9000-10 000 30.7 / 55.4, until the launches are long: two runs, 96 / 8, 64 of
+// 300-1000 (10 000 tiles over all kv-heads) 61.6 / 61.5, 32 of 1000-4600 (22 500) 93.8 / 66.1.  Three: 32 / 2, 900-1100 37 / 36; 96 / 8, 2000-2500
+// 38.6 / 40.2, 4000-4600 44.5 / 53.2, 32 / 2, 1000-10 000 41.2 / 48.2; but 12 / 1, 8 sequences of 1000-4600 (720 tiles) 39.7 / 37.4 and 160 / 16 (6500) 54.6 / 50.9.
+bool run_by_run(const kivi_layout_t* l, const kivi_seq_state_t* st) {
+    if (l->group == kTileTokens) return false;
+    int runs = 1, longest = 0;
+    int64_t tiles = 0;
+    for (int b = 0; b < l->batch; ++b) {
+        const int tokens = st[b].n_kq + st[b].n_kr;
+        if (b > 0 && !same_state(st[b - 1], st[b])) ++runs;
+        longest = std::max(longest, tokens);
+        tiles += (int64_t)ceil_div(tokens, kTileTokens) * l->n_kv_heads;
+    }
+    const bool two_pairs = l->n_q_heads > kMaxRep * l->n_kv_heads && ragged_runs(l) == 1;
+    return runs == 1 || (two_pairs && ((runs == 2 && tiles <= 12000) || (runs == 3 && longest > 1500 && tiles >= 800 && tiles <= 5000)));
 }
 int ragged_plan(const kivi_layout_t* l, const kivi_seq_state_t* st, size_t workspace_bytes, RaggedPlan& plan) {
     if (decode_family(l) != KIVI_DECODE_MFMA || l->decode_path == KIVI_DECODE_MFMA_ONE) return kNotApplicable;
@@ -531,7 +546,7 @@ int ragged_plan(const kivi_layout_t* l, const kivi_seq_state_t* st, size_t works
         max_tiles_a = std::max(max_tiles_a, tiles_a);
         max_tiles_b = std::max(max_tiles_b, ceil_div(x.n_kq + x.n_kr, kTileTokens) - tiles_a);
     }
-    if (max_tiles_a < 1 || !residual_rows_possible(max_tiles_b, rep_variant) || one_run_of_large_groups(l, st)) return kNotApplicable;
+    if (max_tiles_a < 1 || !residual_rows_possible(max_tiles_b, rep_variant) || run_by_run(l, st)) return kNotApplicable;
     const MfmaGeometry g = mfma_geometry(l->bits, rep_launch);
     if (g.chunk_tiles == 0) return kNotApplicable;
     // (G > 32: with less workspace than documented the batch goes run by run, which asks for no more than each run's)
@@ -1110,7 +1125,7 @@ int kivi_decode_launches_ragged(const kivi_layout_t* l, const kivi_seq_state_t* 
     }
     const int rep_launch = std::min(rep_total, kMaxRep);
     if (fast && max_tiles_a >= 1 && residual_rows_possible(max_tiles_b, rep_launch <= 2 ? rep_launch : (rep_launch <= 4 ? 4 : 8)) &&
-        !one_run_of_large_groups(l, states)) {
+        !run_by_run(l, states)) {
         *launches = rep_total == 1 && l->batch > kInlineSequences ? 1 : 2 * head_groups;
         return KIVI_OK;
     }

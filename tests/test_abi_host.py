@@ -359,3 +359,27 @@ def test_decode_launches_ragged_large_groups(lib, hq, hkv):
         assert kivi.kivi_decode_launches_ragged(l, st) == (alike if group > 32 else pair)
         st[1] = kivi.kivi_seq_state_t(1024, 1024, 8, 130, 8, 130)           # the ring starts elsewhere: not alike
         assert kivi.kivi_decode_launches_ragged(l, st) == pair
+
+
+@pytest.mark.parametrize("group", [64, 128])
+def test_decode_launches_ragged_few_runs(lib, group):
+    """9 to 16 heads, G > 32: a launch per run while there are two (up to 12 000 tiles) or three (800 to 5000 tiles and more than 1500
+    tokens in one); two pairs otherwise."""
+    def launches(hq, hkv, *tokens):
+        l = kivi.make_layout(len(tokens), hq, hkv, 2, 128, 16384, 256, group=group)
+        st = kivi.make_states(len(tokens))
+        for b, n in enumerate(tokens):
+            st[b] = kivi.kivi_seq_state_t(n - 130, n - 130, 7, 130, 7, 130)
+        return kivi.kivi_decode_launches_ragged(l, st)
+    a, b, c, d = (130 + 128 * i for i in (1, 10, 11, 120))      # 9, 45, 49 and 485 tiles
+    for hq in (9, 16):
+        assert launches(hq, 1, a, a, b, b, b) == 2
+        assert launches(hq, 1, a, a, d, d) == 2
+        assert launches(12 * hq, 12, a, d, d) == 2              # 11 748 tiles
+        assert launches(13 * hq, 13, a, d, d) == 4              # 12 727
+        assert launches(2 * hq, 2, a, d, a) == 3                # 1006
+        assert launches(hq, 1, a, d, a) == 4                    # 503
+        assert launches(8 * hq, 8, b, a, b) == 4                # short
+        assert launches(8 * hq, 8, b, c, b) == 3
+        assert launches(10 * hq, 10, a, d, a) == 4              # 5030
+        assert launches(hq, 1, a, d, a, d) == 4

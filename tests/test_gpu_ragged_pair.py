@@ -82,6 +82,49 @@ def test_pair(hq, hkv, bits, group, residual, tokens, steps, launches):
             assert kivi.kivi_decode_launches_ragged(l0, s0) == launches
 
 
+@pytest.mark.parametrize("hq,hkv,bits,group,more", [
+    (9, 1, 2, 64, 1), (32, 2, 4, 128, 5), (24, 2, 2, 64, 140)])        # `more` groups: the last case has three runs, 9000 tokens in one
+def test_few_runs_of_wide_groups(hq, hkv, bits, group, more):
+    """G > 32, 9 to 16 heads, two or three runs of equal sequences: kivi_decode_step's own outputs and bytes for each."""
+    torch = gh.require_gpu()
+    print(f"case ragged, few runs hq={hq} hkv={hkv} bits={bits} G={group}", flush=True)
+    short = 128 + 3 * group - 2
+    runs = [(2, short), (1, short + more * group)] + ([(1, short)] if more == 140 else [])
+    batch, total, steps = sum(n for n, _ in runs), max(t for _, t in runs) + 5, 5
+    gen = torch.Generator(device="cuda").manual_seed(hq)
+    k, v = (torch.randn(batch, hkv, total, 128, dtype=torch.float16, device="cuda", generator=gen) for _ in range(2))
+    layout = kivi.make_layout(batch, hq, hkv, bits, 128, gh.round_up(total, group), 128 + group, group=group)
+    ragged, states, parts, at = kivi.Cache(layout), kivi.make_states(batch), [], 0
+    for buf in ragged.buffers.values():
+        buf.zero_()
+    for n, tokens in runs:
+        sub = kivi.make_layout(n, hq, hkv, bits, 128, layout.cap_q_tokens, layout.cap_r_tokens, group=group)
+        own, rows = kivi.Cache(sub), slice(at, at + n)
+        for buf in own.buffers.values():
+            buf.zero_()
+        part = kivi.CacheSlice(ragged, at, n)
+        kivi.kivi_prefill(part.layout, k[rows], v[rows], tokens, part)
+        kivi.kivi_prefill(sub, k[rows], v[rows], tokens, own)
+        for b in range(at, at + n):
+            states[b] = part.state()
+        parts.append((sub, own, rows, tokens))
+        at += n
+    assert kivi.kivi_decode_launches_ragged(layout, states) == len(runs)
+    for step in range(steps):
+        new = [torch.cat([x[r, :, t + step] for _, _, r, t in parts]).contiguous() for x in (k, v)]
+        q = torch.randn(batch, hq, 128, dtype=torch.float16, device="cuda", generator=gen)
+        outs = [torch.full((batch, hq, 128), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2)]
+        kivi.kivi_decode_step_ragged(layout, ragged, states, *new, q, 128 ** -0.5, outs[0])
+        for sub, own, r, _ in parts:
+            kivi.kivi_decode_step(sub, own, new[0][r], new[1][r], q[r], 128 ** -0.5, outs[1][r])
+        torch.cuda.synchronize()
+        assert torch.isfinite(outs[0]).all() and torch.equal(outs[0], outs[1]), f"step {step}"
+        for name in ragged.buffers:
+            whole = ragged.view(name)
+            for _, own, r, _ in parts:
+                assert torch.equal(whole[r], own.view(name)), f"step {step}: {name}"
+
+
 @pytest.mark.parametrize("hq,hkv,bits,group", [(2, 2, 2, 64), (4, 2, 4, 128), (8, 1, 2, 64), (17, 1, 4, 64)])
 def test_large_groups_alike(hq, hkv, bits, group):
     """G > 32, sequences all alike: kivi_decode_step's own outputs and bytes, over steps with and without a flush."""
