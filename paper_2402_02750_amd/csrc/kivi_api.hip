@@ -631,9 +631,11 @@ int ragged_plan(const kivi_layout_t* l, const kivi_seq_state_t* st, size_t works
         const int stride = std::min(part_rows(l, workspace_bytes > parts_offset ? workspace_bytes - parts_offset : 0), kOneHeadMaxParts);
         if (stride < 1) return KIVI_ERR_WORKSPACE;
         const int cus = one_head_compute_units();
+        const int many = l->bits == 2 ? 8 : 12;
+        const int near_parts = one_head_near_parts(all, (int64_t)l->batch * l->n_kv_heads, sequences.front().steps, sequences.back().steps, cus, stride, many);
         int64_t wgs = 0;
         for (OneHeadSequence& s : sequences) {
-            s.parts = one_head_ragged_parts(all, s.steps, cus, stride, l->bits == 2 ? 8 : 12);
+            s.parts = near_parts > 0 ? std::min(near_parts, s.steps) : one_head_ragged_parts(all, s.steps, cus, stride, many);
             s.first_wg = (int32_t)wgs;
             wgs += (int64_t)s.parts * l->n_kv_heads;
             if (wgs > 0x3fffffff) return kNotApplicable;

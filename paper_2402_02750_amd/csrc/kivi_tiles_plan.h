@@ -234,6 +234,18 @@ inline int one_head_ragged_parts(int64_t total, int steps, int compute_units, in
     const int64_t w = total <= many * cus ? (steps * cus + total - 1) / total : (3 * steps * cus + 2 * total - 1) / (2 * total);
     return (int)std::max<int64_t>(1, std::min({w, (int64_t)steps, (int64_t)room}));
 }
+// Such a batch of nearly one length (the shortest sequence has at least three quarters of the longest one's steps) and more than `many` steps
+// per compute unit: every unit in as many parts as one_head_parts has for the longest, 0 where the rule above stays.  By the share a few
+// of its numbers of units end just beyond whole workgroups per compute unit (182 units in three parts each: 546 on 256), or
+// some sequences get a part more than others (384 units).  Share / this, 182 units: 12 600-14 000 tokens 56.7 / 48.7 us, 4 bits, 3600-4000 35.0 /
+// 28.8; 100 x 11 700-13 000 32.0 / 29.4; 384 x 7200-8000 67.7 / 59.6.  It stays where this would end there in its turn, with three parts and more than two
+// workgroups per compute unit: 200 units, 11 700-13 000 tokens, share 52.7, three parts 55.7; 220 x 7200-8000 38.4 / 40.7.
+inline int one_head_near_parts(int64_t total, int64_t units, int longest, int shortest, int compute_units, int room, int many) {
+    const int64_t cus = compute_units;
+    if (total <= many * cus || (int64_t)shortest * 4 < (int64_t)longest * 3) return 0;
+    const int parts = one_head_parts(units, longest, compute_units, room, many);
+    return parts == 3 && units * parts > 2 * cus ? 0 : parts;
+}
 // What a workgroup of such a batch reads: its sequence's first workgroup (of all units, head by head), the sequence, workgroups per unit, counters
 // after the step, steps of a unit.
 struct OneHeadSequence { int32_t first_wg, sequence, parts, n_q, n_r, k_start, v_start, steps; };

@@ -86,6 +86,9 @@ extern "C" int check_ragged(const int* steps, int sequences, int heads, int cus,
     if (wgs > (int64_t)sequences * heads + 2 * (int64_t)cus) return 4;
     return 0;
 }
+extern "C" int near_parts(int64_t total, int64_t units, int longest, int shortest, int cus, int room, int many) {
+    return one_head_near_parts(total, units, longest, shortest, cus, room, many);
+}
 // form 0: K and V split alike, 1: with a flush, 2: split differently
 extern "C" int check_all(int bits, int form, int n_kq, int v_q, int n_kr, int* at) {
     const int units[] = {1, 2, 3, 8, 31, 32, 85, 86, 128, 255, 256, 257, 320, 512, 767, 768, 769, 800, 864, 865, 896, 897, 2048};
@@ -120,6 +123,21 @@ def test_ragged_parts(plan, steps, heads):
         for room in (1, 2, 128):
             for many in (8, 12):
                 assert plan.check_ragged(arr, len(steps), heads, cus, room, many) == 0, f"{cus} compute units, {room} rows, {many}"
+
+
+@pytest.mark.parametrize("cus", [256, 7])
+def test_near_parts(plan, cus):
+    """Batches of nearly one length and many steps: as many parts as fit and there are steps; other batches keep the share."""
+    plan.near_parts.argtypes = [ctypes.c_int64] * 2 + [ctypes.c_int] * 5
+    for units in range(1, 5 * cus, max(1, cus // 40)):
+        for longest in (1, 9, 20, 31, 53, 300):
+            for room in (1, 2, 128):
+                total = units * longest
+                parts = plan.near_parts(total, units, longest, longest - longest // 4, cus, room, 8)
+                assert 0 <= parts <= min(room, longest) and (parts == 0 or total > 8 * cus)
+                assert parts == 0 or units * parts <= max(3 * cus, 2 * units)
+                assert plan.near_parts(total, units, longest, (longest * 3 - 1) // 4, cus, room, 8) == 0
+    assert [plan.near_parts(u * 53, u, 53, 48, 256, 128, 8) for u in (171, 182, 192, 193, 239, 240, 384)] == [4, 4, 4, 0, 0, 2, 2]
 
 
 TILES = list(range(0, 12)) + [15, 16, 17, 31, 63, 64, 65, 128, 1000]
