@@ -67,18 +67,20 @@ size_t counter_bytes(const kivi_layout_t* l) {
 
 // Room for the per-sequence counters of a batch of different lengths (16 bytes per sequence, padded
 // to 256 bytes); the ragged entry points keep them behind the split counters.
+size_t seq_state_bytes(const kivi_layout_t* l) {
+    return ((size_t)l->batch * 4 * sizeof(int32_t) + 255) / 256 * 256;
+}
+
 // Room for the tables of the second launch of such a batch, behind the counters: 16 bytes per workgroup (at most kMaxSlices) and 8
 // bytes per (batch, kv-head) unit, of which 4 bytes per sequence are used.
 constexpr int kMaxSlices = 4096;
 constexpr int64_t kMaxSliceUnits = 65536;
 size_t slice_table_bytes(const kivi_layout_t* l) {
     const int64_t units = std::min<int64_t>((int64_t)l->batch * l->n_kv_heads, kMaxSliceUnits);
-    const size_t many = l->batch > 4096 ? (size_t)l->batch * 24 : 0;       // (decode_one_kernel's 36 bytes per sequence)
-    return ((size_t)kMaxSlices * 16 + (size_t)units * 8 + many + 255) / 256 * 256;
-}
-
-size_t seq_state_bytes(const kivi_layout_t* l) {
-    return ((size_t)l->batch * 4 * sizeof(int32_t) + 255) / 256 * 256;
+    size_t bytes = (size_t)kMaxSlices * 16 + (size_t)units * 8;
+    // decode_one_kernel's tables lie there and in the counters' place: 36 bytes per sequence, more with one kv-head and 5400 sequences
+    if (l->n_q_heads == l->n_kv_heads) bytes = std::max(bytes, (size_t)l->batch * 36 - std::min((size_t)l->batch * 36, seq_state_bytes(l)));
+    return (bytes + 255) / 256 * 256;
 }
 
 // Upper bound of the number of context splits for any cache state of this layout.

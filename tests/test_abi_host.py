@@ -383,3 +383,12 @@ def test_decode_launches_ragged_few_runs(lib, group):
         assert launches(8 * hq, 8, b, c, b) == 3
         assert launches(10 * hq, 10, a, d, a) == 4              # 5030
         assert launches(hq, 1, a, d, a, d) == 4
+
+
+@pytest.mark.parametrize("hq,hkv,more", [(2, 1, 0), (8, 2, 0), (71, 1, 0), (4, 4, 0), (1, 1, 36 * 8192 - 16 * 8192 - 65536 - 8 * 8192)])
+def test_workspace_of_many_sequences(hq, hkv, more):
+    """Beyond 4096 sequences the workspace grows as it does below; only one head on one kv-head needs more for its tables, and that
+    much."""
+    def need(batch):
+        return kivi.kivi_decode_workspace_bytes(kivi.make_layout(batch, hq, hkv, 2, 32, 256, 64))
+    assert need(8192) - need(4096) == 2 * (need(4096) - need(2048)) + more
