@@ -84,13 +84,13 @@ def test_pair(hq, hkv, bits, group, residual, tokens, steps, launches):
 
 
 @pytest.mark.parametrize("hq,hkv,bits,group,more", [
-    (9, 1, 2, 64, 1), (32, 2, 4, 128, 5), (24, 2, 2, 64, 140)])        # `more` groups: the last case has three runs, 9000 tokens in one
+    (9, 1, 2, 64, 1), (32, 2, 4, 128, 5), (24, 2, 2, 64, 200)])        # `more` groups: the last case has three runs, 13 000 tokens in one
 def test_few_runs_of_wide_groups(hq, hkv, bits, group, more):
     """G > 32, 9 to 16 heads, two or three runs of equal sequences: kivi_decode_step's own outputs and bytes for each."""
     torch = gh.require_gpu()
     print(f"case ragged, few runs hq={hq} hkv={hkv} bits={bits} G={group}", flush=True)
     short = 128 + 3 * group - 2
-    runs = [(2, short), (1, short + more * group)] + ([(1, short)] if more == 140 else [])
+    runs = [(2, short), (1, short + more * group)] + ([(1, short)] if more == 200 else [])
     batch, total, steps = sum(n for n, _ in runs), max(t for _, t in runs) + 5, 5
     gen = torch.Generator(device="cuda").manual_seed(hq)
     k, v = (torch.randn(batch, hkv, total, 128, dtype=torch.float16, device="cuda", generator=gen) for _ in range(2))
@@ -153,6 +153,41 @@ def test_large_groups_alike(hq, hkv, bits, group):
         for name in uniform.buffers:
             assert torch.equal(uniform.buffers[name], ragged.buffers[name]), f"step {step}: {name}"
     assert all(s.n_kq == uniform.c.n_kq for s in states) and uniform.c.n_kq > 2 * group
+
+
+@pytest.mark.parametrize("hq,hkv", [(2, 2), (4, 2), (8, 2), (8, 1), (17, 1)])
+@pytest.mark.parametrize("ragged", [True, False])
+def test_row_without_weight(hq, hkv, ragged):
+    """A tile of fp16 rows whose logits are all -inf (one token, a key of -inf) counts for nothing in the launch of the rows: the output
+    of a key whose probability underflows to 0."""
+    torch = gh.require_gpu()
+    print(f"case row without weight hq={hq} hkv={hkv} ragged={ragged}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(hq)
+    k, v = (torch.randn(2, hkv, 224, 128, dtype=torch.float16, device="cuda", generator=gen) for _ in range(2))
+    q = torch.randn(2, hq, 128, dtype=torch.float16, device="cuda", generator=gen)
+    q[..., 3] = 1 + q[..., 3].abs()
+    path = kivi.KIVI_DECODE_AUTO if ragged else kivi.KIVI_DECODE_MFMA_TWO
+    layout = kivi.make_layout(2, hq, hkv, 2, 32, 224, 64, decode_path=path)
+    cache, states, outs = kivi.Cache(layout), kivi.make_states(2), []
+    for buf in cache.buffers.values():
+        buf.zero_()
+    kivi.kivi_prefill(layout, k, v, 224, cache)
+    for row in (-60000.0, float("-inf")):
+        cache.view("k_resid")[:, :, 0] = 1
+        cache.view("k_resid")[:, :, 0, 3] = row
+        outs.append(torch.full((2, hq, 128), float("nan"), dtype=torch.float32, device="cuda"))
+        if ragged:
+            for b, n in enumerate((160, 192)):
+                states[b] = kivi.kivi_seq_state_t(n, n, 0, 1, 0, 1)
+            kivi.kivi_decode_attention_ragged(layout, cache, states, q, 128 ** -0.5, outs[-1])
+        else:
+            c = cache.c
+            c.n_kq = c.n_vq = 192
+            c.n_kr = c.n_vr = 1
+            c.k_r_start = c.v_r_start = 0
+            kivi.kivi_decode_attention(layout, cache, q, 128 ** -0.5, outs[-1])
+    torch.cuda.synchronize()
+    assert torch.isfinite(outs[0]).all() and torch.equal(outs[0], outs[1])
 
 
 @pytest.mark.parametrize("batch", [4096, 4097])
