@@ -647,9 +647,10 @@ __global__ __launch_bounds__(64 * WV, OCC * WV / 4) void decode_one_kernel(Decod
             mx = fmaxf(mx, x[j]);
         }
         if (__any(mx > mref + (float)kSlack)) raise_reference(mx);
+        const float ref = RAGGED && mref == -INFINITY ? 0.f : mref;              // (every logit so far is -inf: they count for nothing)
 #pragma unroll
         for (int j = 0; j < NR; ++j) {
-            const float pr = __builtin_amdgcn_exp2f(x[j] + ((float)kProbExp<BITS> - mref));
+            const float pr = __builtin_amdgcn_exp2f(x[j] + ((float)kProbExp<BITS> - ref));
             r_l += pr;
             const half8 v = *reinterpret_cast<const half8*>(sl + NT * 256 + min(4 * j + kb, NT - 1) * 256 + n * 16);
 #pragma unroll

@@ -212,7 +212,8 @@ __global__ __launch_bounds__(1024) void ragged_rows_kernel(RaggedRowsParams p) {
                 mx = fmaxf(mx, x[4 * half + i]);
             }
         }
-        mx = max_rows(mx);                             // finite: the tile has a token
+        mx = max_rows(mx);                             // -inf only where every token's logit is: such a tile counts for nothing
+        const float ref = mx == -INFINITY ? 0.f : mx;
         float l = 0.f;
         Frag hi, mid, lo;
 #pragma unroll
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(1024) void ragged_rows_kernel(RaggedRowsParams p) {
             float pr[2];
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
-                pr[k] = __builtin_amdgcn_exp2f(x[2 * r + k] - mx + kProbExp);
+                pr[k] = __builtin_amdgcn_exp2f(x[2 * r + k] - ref + kProbExp);
                 l += pr[k];
             }
             hi.p[r] = pack_rtz(pr[0], pr[1]);          // 11 + 11 + 2 bits; the remainders are exact
@@ -265,8 +266,9 @@ __global__ __launch_bounds__(1024) void ragged_rows_kernel(RaggedRowsParams p) {
         float m = -INFINITY, l = 0.f;
         for (int w = 0; w < n_tiles; ++w) m = fmaxf(m, src[w * stride + kHeadDim]);
         float4v o = {0.f, 0.f, 0.f, 0.f};
+        const float ref = m == -INFINITY ? 0.f : m;
         for (int w = 0; w < n_tiles; ++w) {
-            const float f = __builtin_amdgcn_exp2f(src[w * stride + kHeadDim] - m);
+            const float f = __builtin_amdgcn_exp2f(src[w * stride + kHeadDim] - ref);
             l = fmaf(src[w * stride + kHeadDim + 1], f, l);
             const float4v x = *reinterpret_cast<const float4v*>(src + w * stride + c);
 #pragma unroll

@@ -130,8 +130,8 @@ __device__ __forceinline__ void residual_rows_block(const DecodeParams& p, float
 #pragma unroll
     for (int hh = 0; hh < REP; ++hh) {
         const float a = lane < kTileTokens ? sm_p[hh][lane] : -INFINITY;
-        m[hh] = wave_max32(a);                             // finite: the tile has a token
-        const float pt = lane < kTileTokens ? __expf(a - m[hh]) : 0.f;
+        m[hh] = wave_max32(a);                             // -inf only where every token's logit is: such a tile counts for nothing
+        const float pt = lane < kTileTokens ? __expf(a - (m[hh] == -INFINITY ? 0.f : m[hh])) : 0.f;
         l[hh] = wave_sum32(pt);
         if (lane < kTileTokens) sm_p[hh][lane] = pt;
     }
