@@ -157,11 +157,12 @@ def test_large_groups_alike(hq, hkv, bits, group):
 
 @pytest.mark.parametrize("hq,hkv", [(2, 2), (4, 2), (8, 2), (8, 1), (17, 1)])
 @pytest.mark.parametrize("ragged", [True, False])
-def test_row_without_weight(hq, hkv, ragged):
-    """A tile of fp16 rows whose logits are all -inf (one token, a key of -inf) counts for nothing in the launch of the rows: the output
-    of a key whose probability underflows to 0."""
+@pytest.mark.parametrize("rows", [1, 33])
+def test_row_without_weight(hq, hkv, ragged, rows):
+    """A tile of fp16 rows whose logits are all -inf (one token, a key of -inf; alone or after another tile) counts for nothing in the
+    launch of the rows: the output of a key whose probability underflows to 0."""
     torch = gh.require_gpu()
-    print(f"case row without weight hq={hq} hkv={hkv} ragged={ragged}", flush=True)
+    print(f"case row without weight hq={hq} hkv={hkv} ragged={ragged} rows={rows}", flush=True)
     gen = torch.Generator(device="cuda").manual_seed(hq)
     k, v = (torch.randn(2, hkv, 224, 128, dtype=torch.float16, device="cuda", generator=gen) for _ in range(2))
     q = torch.randn(2, hq, 128, dtype=torch.float16, device="cuda", generator=gen)
@@ -172,18 +173,20 @@ def test_row_without_weight(hq, hkv, ragged):
     for buf in cache.buffers.values():
         buf.zero_()
     kivi.kivi_prefill(layout, k, v, 224, cache)
+    for name in ("k_resid", "v_resid"):
+        cache.view(name).normal_(generator=gen)
     for row in (-60000.0, float("-inf")):
-        cache.view("k_resid")[:, :, 0] = 1
-        cache.view("k_resid")[:, :, 0, 3] = row
+        cache.view("k_resid")[:, :, rows - 1] = 1
+        cache.view("k_resid")[:, :, rows - 1, 3] = row
         outs.append(torch.full((2, hq, 128), float("nan"), dtype=torch.float32, device="cuda"))
         if ragged:
             for b, n in enumerate((160, 192)):
-                states[b] = kivi.kivi_seq_state_t(n, n, 0, 1, 0, 1)
+                states[b] = kivi.kivi_seq_state_t(n, n, 0, rows, 0, rows)
             kivi.kivi_decode_attention_ragged(layout, cache, states, q, 128 ** -0.5, outs[-1])
         else:
             c = cache.c
             c.n_kq = c.n_vq = 192
-            c.n_kr = c.n_vr = 1
+            c.n_kr = c.n_vr = rows
             c.k_r_start = c.v_r_start = 0
             kivi.kivi_decode_attention(layout, cache, q, 128 ** -0.5, outs[-1])
     torch.cuda.synchronize()
