@@ -86,9 +86,12 @@ def test_flush(batch, heads, group, bits):
     (1, 4, 2, 1023, 32, 4),         # two heads per kv-head, few units
     (2, 3, 3, 4095, 128, 2),
     (1, 2, 1, 1024 + 479 + 32, 480, 2),     # fifteen tiles of fp16 rows after the flush
-    (24, 16, 8, 1055, 128, 2),      # two heads, more units than flush in a launch of their own
-    (40, 16, 8, 1023, 128, 4),      # more units than the two-head tile kernel serves
-    (24, 64, 8, 1055, 128, 2),      # eight heads: a launch for the flush, one for the rows, one for the rest
+    (24, 16, 8, 1055, 128, 2),      # two heads, 192 and 320 units: the tile kernel's only launch carries the flush
+    (40, 16, 8, 1023, 128, 4),
+    (49, 16, 8, 1055, 128, 2),      # 392 units, or 384 and 40 000 tiles: the rows' launch carries it
+    (49, 16, 8, 1055, 128, 4),
+    (48, 16, 8, 3359, 128, 2),
+    (24, 64, 8, 1055, 128, 2),      # eight heads, one launch
     (64, 32, 8, 1055, 128, 4),      # four heads: the rows' launch carries the flush for the tile kernel
     (64, 32, 8, 1024 + 479 + 32, 480, 2),   # sixteen tiles of rows for four heads: the most that such a launch takes
     (64, 24, 8, 1023, 32, 2),       # three of four slots, one tile of fp16 rows

@@ -63,6 +63,34 @@ def test_tiles(hq, hkv, batch, bits, group, policy, tokens, kgain, vgain):
     gh.check_close(outs[kivi.KIVI_DECODE_MFMA] / scale, outs[kivi.KIVI_DECODE_VALU] / scale, "all heads")
 
 
+@pytest.mark.parametrize("hq,hkv,bits,group,policy", [(4, 2, 2, 32, W), (4, 2, 4, 64, W), (8, 2, 2, 32, W), (6, 2, 4, 32, A), (8, 2, 2, 128, W),
+                                                     (16, 2, 2, 32, W)])
+def test_small_keys(hq, hkv, bits, group, policy):
+    """Key zero-points and scales among fp16's subnormals, and queries large enough for the logits to need them.  Tolerance: the query
+    enters times 2^-5 here (its largest element below 2^9), a key operand is exact to 2^-25 (half of fp16's smallest number) in each of
+    128 channels, times codes of up to 3 or 15; what that adds up to in a logit moves a probability by as much of itself, and the output by
+    that times the values' mean deviation, which is less than the largest value."""
+    gh.require_gpu()
+    tokens = 1200
+    w = scaled(CONFIGS["mistral_gqa"], name="smallkeys", batch=1, n_q_heads=hq, n_kv_heads=hkv, bits=bits, group=group, residual=128, seed=9 * hq + bits)
+    print(f"case small keys hq={hq} hkv={hkv} bits={bits} G={group} policy={policy}", flush=True)
+    rng = np.random.default_rng(hq + bits + group)
+    k = (rng.standard_normal((1, hkv, tokens, 128)) * 2.0 ** -16).astype(np.float16)
+    q = np.clip(rng.standard_normal((1, hq, 128)) * 2.0 ** 12, -2.0 ** 13, 2.0 ** 13).astype(np.float16)
+    v = workloads.values(w, tokens)
+    heads = [(0, h) for h in range(hkv)]
+    oc = gh.oracle_cache_for_heads(w, k, v, heads, "window" if policy == W else "alg1")
+    assert 0 < np.abs(oc.k_zero.astype(np.float32)).max() < 2.0 ** -13
+    ref = gh.oracle_attention_for_heads(w, oc, q, heads)
+    bound = 2.0 ** 5 * w.softmax_scale * 128 * 2.0 ** -25 * (2 ** bits - 1) * float(np.abs(v.astype(np.float32)).max())
+    oc.k_zero = oc.k_zero * np.float16(0)              # (what flushing them to zero would give)
+    assert np.abs(gh.oracle_attention_for_heads(w, oc, q, heads) - ref).max() > 4 * bound
+    for path in (kivi.KIVI_DECODE_MFMA, kivi.KIVI_DECODE_MFMA_ONE):
+        layout, cache = gh.gpu_prefill(w, k, v, policy, path)
+        err = np.abs(gh.pick_heads(gh.gpu_attention(layout, cache, q, w.softmax_scale), w, heads) - ref).max()
+        assert err <= bound, f"path {path}: {err:.3e} against {bound:.3e}"
+
+
 # (query heads, kv-heads, bits, tokens of every sequence)
 RAGGED_CASES = [
     (32, 8, 2, [20000]),                        # 157 steps per unit, more than there are rows for parts
@@ -75,22 +103,33 @@ RAGGED_CASES = [
 ]
 
 
-@pytest.mark.parametrize("hq,hkv,bits,tokens", RAGGED_CASES)
-def test_tiles_ragged(hq, hkv, bits, tokens):
+@pytest.mark.parametrize("hq,hkv,bits,tokens,group", [c + (32,) for c in RAGGED_CASES] + [
+    (4, 2, 2, [3000, 95, 700], 32),             # two heads; a flush in the step
+    (4, 2, 4, [1300, 200, 4000], 64),
+    (2, 2, 2, [3000, 95, 700], 32),             # one head, several workgroups per unit
+    (3, 3, 4, [191, 1300, 5000], 64),
+    (2, 2, 2, [2000, 1, 383], 128),
+    (8, 2, 2, [191, 1300, 5000], 64),           # four heads
+    (16, 2, 4, [2000, 255, 1], 128),            # eight
+    (12, 1, 2, [900, 191, 400, 1500], 64),      # twelve: two pairs of launches
+    (17, 1, 2, [95, 1300, 3000], 32),           # seventeen: runs of eight as units
+    (34, 2, 4, [191, 1300, 700], 64),
+])
+def test_tiles_ragged(hq, hkv, bits, tokens, group):
     """Sequences of different lengths: a decoding step and an attention call against the oracle (tolerance as in
     test_tiles) and, all heads, against the vector path; nothing is written past the workspace."""
     torch = gh.require_gpu()
     batch, total = len(tokens), max(tokens) + 1
-    w = scaled(CONFIGS["mistral_gqa"], name="tilesragged", batch=batch, n_q_heads=hq, n_kv_heads=hkv, bits=bits, residual=64,
-               seed=77 * hq + bits)
-    print(f"case tiles ragged hq={hq} hkv={hkv} bits={bits} L={tokens}", flush=True)
+    w = scaled(CONFIGS["mistral_gqa"], name="tilesragged", batch=batch, n_q_heads=hq, n_kv_heads=hkv, bits=bits, group=group,
+               residual=max(group, 64), seed=77 * hq + bits)
+    print(f"case tiles ragged hq={hq} hkv={hkv} bits={bits} G={group} L={tokens}", flush=True)
     k, v = workloads.keys(w, total), workloads.values(w, total)
     kt, vt = torch.from_numpy(k).cuda(), torch.from_numpy(v).cuda()
     heads = sorted({0, hkv // 2, hkv - 1})
     scale = float(np.abs(v.astype(np.float32)).max())
     outs = {}
     for path in (kivi.KIVI_DECODE_MFMA, kivi.KIVI_DECODE_VALU):
-        layout = kivi.make_layout(batch, hq, hkv, bits, w.residual, gh.round_up(total, 32), 128, decode_path=path)
+        layout = kivi.make_layout(batch, hq, hkv, bits, w.residual, gh.round_up(total, group), max(128, 2 * group), group=group, decode_path=path)
         cache = kivi.Cache(layout)
         size = cache.workspace.numel()
         room = torch.full((size + 65536,), 0x5A, dtype=torch.uint8, device="cuda")
@@ -126,7 +165,7 @@ def test_tiles_ragged(hq, hkv, bits, tokens):
             assert err <= 1e-4 * scale, f"step {step} sequence {b}: {err:.3e} against {1e-4 * scale:.3e}"
 
 
-@pytest.mark.parametrize("hq,hkv,bits", [(8, 2, 2), (16, 2, 4), (12, 2, 4)])
+@pytest.mark.parametrize("hq,hkv,bits", [(8, 2, 2), (16, 2, 4), (12, 2, 4), (4, 2, 2), (4, 2, 4), (2, 2, 2), (2, 2, 4)])
 def test_tiles_ragged_small_workspace(hq, hkv, bits):
     """A ragged step that flushes, with room for few parts per head: served as with the full workspace from as many rows on
     as the longest sequence has splits, refused before anything is launched below; the attention alone needs two.
@@ -142,7 +181,7 @@ def test_tiles_ragged_small_workspace(hq, hkv, bits):
     row = batch * hq * 130 * 4
     full = kivi.kivi_decode_workspace_bytes(layout)
     base = full - ((layout.cap_q_tokens // 32 + 3) // 4 + layout.cap_r_tokens // 32 + 2) * row
-    tiles_per_split = 16 if bits == 2 else 8
+    tiles_per_split = 16 if bits == 2 or hq <= 2 * hkv else 8
     need = -(-((480 - residual) // 32) // tiles_per_split) + 1
     results = {}
     for rows in (None, 4, 3, 2, 1):
