@@ -240,16 +240,16 @@ int decode_family(const kivi_layout_t* l) {
 //      such chains: two launches are 2-12 % faster once the launch is long enough to carry the
 //      second launch's fixed 8-12 us.
 // With 3 or more query heads per kv-head (decode_tiles_kernel) the fp16 rows have workgroups of their own in
-// either form; as a launch of their own they cost the launch's fixed 7-9 us, beside the others they take
-// residency from workgroups that run much longer.
-//  (3) 5 to 8 heads: from 384 fp16-row tiles on (one launch is still the faster one below 512 units -- 28.1
-//      against 37.4 us at 128 units, context 4000 -- and the slower one from there on: 91 against 75 us at 512 units;
-//      the line is where it was when the fp16 rows were 40 % of such a launch).
-//  (4) 3 or 4 heads: 512 units on (context 4000, 2 bits: 64 against 80 us; context 1000: 36 against 39); even at
-//      384 units and context 4000 (54.0 / 53.2 us), one launch 20 % faster below (23 against 34 us at context 1000).
-//  (5) Neither for short contexts while the units are fewer than the resident workgroups: 512 units, 15 tiles, one launch
-//      against two: 3 heads 28.3 / 30.0 us (4 bits 29.4 / 31.4), 8 heads 35.0 / 37.1 (4 bits 46.3 / 51.9); with 31 tiles
-//      38.5 / 35.1 and 62.4 / 58.2, and at 1024 units and 15 tiles 48.3 / 44.7 and 78.3 / 70.0.
+// one launch, where they take residency from workgroups that run much longer, and ragged_rows_kernel as a launch of their own,
+// which costs 4-5 us where nothing is gained.  Whole steps, one launch / two, us:
+//  (3) 5 to 8 heads: from 384 fp16-row tiles on.  8 heads, 512 units, 1000 tokens 44.0 / 35.5, 4000 87.8 / 64.8 (4 bits 106.8 / 81.6);
+//      384 units, 4000 52.7 / 53.1 (58.9 / 66.8), 256 units 37.6 / 37.8; 128 units 22.8 / 27.8, 1000 tokens 15.6 / 19.7: the line would
+//      be better at 512 units now (it was drawn when the fp16 rows were 40 % of a single launch).
+//  (4) 3 or 4 heads: 512 units on (1000 tokens 36.9 / 29.9, 4000 76.0 / 57.0, 4 bits 88.7 / 72.2), and 384 with long contexts (4000
+//      49.1 / 45.9, 4 bits 53.3 / 57.1; 1000 20.1 / 26.8).
+//  (5) Neither for short contexts while the units are fewer than the resident workgroups.  (Drawn when the first launch was
+//      decode_tiles_kernel's or residual_rows_kernel's: 512 units, 15 tiles, 3 heads 28.3 / 30.0.  With ragged_rows_kernel two are ahead there:
+//      488 tokens, 3 heads 26.3 / 24.4, 8 heads 31.6 / 30.8, with a flush 31.7 / 27.4 and 35.4 / 32.7; 1024 units 45.5 / 39.1 and 54.6 / 45.9.)
 // `flush`: the step also flushes and the fp16-row launch could carry that out (G = 32).
 //  (0) Two heads: a flush has to end before the launch that reads its tiles, so the single-launch form of decode_mfma_kernel takes
 //      two launches as well, the first of them nearly empty: then it rides with the fp16 rows at no cost of its own.  Up to 384
@@ -312,8 +312,8 @@ int wide_group_runs(const kivi_layout_t* l, int path, bool two_launches) {
 
 // Which kernel of the matrix-core family serves the layout: decode_tiles_kernel from three query heads per
 // kv-head on (sweeps over 8-1024 units, contexts 200-30 000, 2 and 4 bits, G = 32 to 128, both policies: 1.0-2.7 times as
-// fast as decode_mfma_kernel was; slower only at 512 units: 0.93-0.96 on steps that flush with 5 to 8 heads at 4 bits, up to
-// 1055 tokens, and 0.88-0.97 with K and V split differently, mostly with 4 heads), and with two heads up to 384 units where that is one
+// fast as decode_mfma_kernel was, but 0.88-0.97 at 512 units with K and V split differently, mostly with 4 heads, before the rows had
+// a launch there), and with two heads up to 384 units where that is one
 // launch (320 units x 2047 tokens with a flush 35.1 -> 28.9 us, 384 x 1000 28.8 -> 20.0, split differently 288 x 2000 35.0 -> 28.1; from
 // 512 units on that kernel's cheaper tiles win: 512 x 1000 28.4 / 29.5 us, 4 bits, 512 x 4000 69.0 / 77.3).  With one head per kv-head most of its matrix columns would idle.
 bool uses_tiles(const kivi_layout_t* l, const kivi_cache_t* c) {
@@ -325,8 +325,8 @@ bool uses_tiles(const kivi_layout_t* l, const kivi_cache_t* c) {
 }
 // K and V split at different tokens (Algorithm 1's policy), decode_tiles_kernel: the tiles that are not all quantised in a
 // launch of their own, as in the two-launch form, where they would take the residency of the others in one.  From 512 units
-// on and not for short contexts (1500 tokens, 4 heads, 512 / 1024 units: 55.7 -> 46.8, 93.0 -> 82.3 us; 8 heads, 512 units
-// 66.9 -> 56.6; 500 tokens 36.7 / 37.5 and 58.6 / 60.9; 256 units, 1500 tokens 26.7 / 34.5).
+// on and not for short contexts (one launch / two, 1500 tokens, 4 heads, 512 and 1024 units 52.3 / 45.1, 88.3 / 78.6 us; 8 heads, 512 units
+// 55.2 / 51.0; 500 tokens, 4 heads 34.2 / 36.4 and 56.0 / 58.9; 384 units, 1500 tokens 28.1 / 41.7).
 bool rows_launch_for_uneven_split(const kivi_layout_t* l, const kivi_cache_t* c, int path) {
     return path == KIVI_DECODE_MFMA && l->decode_path != KIVI_DECODE_MFMA_ONE && uses_tiles(l, c) && l->n_q_heads <= kMaxRep * l->n_kv_heads &&
            c->n_kq != c->n_vq && std::min(c->n_kq, c->n_vq) >= kTileTokens && (int64_t)l->batch * l->n_kv_heads >= 512 &&
@@ -476,13 +476,12 @@ namespace {
 
 constexpr int kNotApplicable = 1;       // (internal) the fast path does not serve this batch: use the run-by-run path
 
-// Attention over a batch whose sequences differ in length as ONE pair of launches of the matrix-core
-// family's two-launch form: the fp16 rows of every unit (which also append the new token when
-// k_new / v_new are given), then the all-quantised chunks.  Both kernels read each sequence's
-// counters from a device array; the split plan is the longest sequence's, a shorter one's surplus
-// chunks and tiles are masked.  Served: K and V split alike in every sequence, at least one fp16
-// row and at most 16 tiles of them per sequence, at least one quantised tile somewhere in the
-// batch.
+// Attention over a batch whose sequences differ in length as ONE pair of launches (a pair per 8 heads for 9 to 16 query heads per
+// kv-head).  Two heads and more: ragged_rows_kernel has the fp16 rows of every unit, appends the new token when k_new / v_new are
+// given and makes the tables by which decode_tiles_kernel cuts the packed tokens of all units evenly.  One head: the first
+// launch makes decode_one_kernel's table only (more than kInlineSequences: the host does).  Served: K and V split alike in every
+// sequence, at least one fp16 row and as many tiles of them as residual_rows_possible allows, at least one quantised tile somewhere
+// in the batch, and with G > 32 more runs than run_by_run takes.
 // ragged_plan decides everything that can refuse the batch, on the host and without a launch (a step plans before it
 // flushes): `st` are the states the attention sees (after append and flush); kNotApplicable for any other batch.
 // ragged_launch then carries the plan out.
@@ -728,8 +727,8 @@ RaggedPlan& thread_plan() {
 }
 
 // One decoding step of every sequence of a batch of different lengths in one pair of attention
-// launches (plus one flush launch per run of equal sequences that flush in this step, which is rare:
-// a sequence flushes every G-th step).  Served when every sequence's flush leaves the new token in
+// launches.  A flush of one tile rides in the first of them (G = 32, up to kInlineSequences sequences); any other takes a launch per run of
+// equal sequences that flush in this step, which is every G-th step of a sequence.  Served when every sequence's flush leaves the new token in
 // the window (then the flush can run out of the rings before the attention appends the token) and
 // ragged_plan takes the states after the step.  Returns kNotApplicable with nothing launched and nothing changed
 // otherwise.
