@@ -240,9 +240,12 @@ inline int one_head_ragged_parts(int64_t total, int steps, int compute_units, in
 // some sequences get a part more than others (384 units).  Share / this, 182 units: 12 600-14 000 tokens 56.7 / 48.7 us, 4 bits, 3600-4000 35.0 /
 // 28.8; 100 x 11 700-13 000 32.0 / 29.4; 384 x 7200-8000 67.7 / 59.6.  It stays where this would end there in its turn, with three parts and more than two
 // workgroups per compute unit: 200 units, 11 700-13 000 tokens, share 52.7, three parts 55.7; 220 x 7200-8000 38.4 / 40.7.
+// A few more units than compute units, if long, in five parts, more than fit at once, where two or three parts end just beyond two or three workgroups
+// per compute unit: two / five, 264 x 11 700-13 000 73.3 / 67.6 (4 bits 104.1 / 99.4), 280 x 8000 50.2 / 49.1; but 264 x 4000 31.3 / 32.3, 320 x 8000 51.6 / 53.0.
 inline int one_head_near_parts(int64_t total, int64_t units, int longest, int shortest, int compute_units, int room, int many) {
     const int64_t cus = compute_units;
     if (total <= many * cus || (int64_t)shortest * 4 < (int64_t)longest * 3) return 0;
+    if (units > cus && units * 6 <= 7 * cus && longest > 3 * many) return std::min({5, longest, room});
     const int parts = one_head_parts(units, longest, compute_units, room, many);
     return parts == 3 && units * parts > 2 * cus ? 0 : parts;
 }

@@ -30,6 +30,7 @@ CASES = [
     (40, 40, 4, 32, 64, [4100, 64, 95, 100, 3000] + [200] * 20, 33, 2),
     (2, 2, 2, 64, 128, [191, 500, 64, 1900], 66, 2),
     (26, 26, 2, 32, 64, [8000 - 190 * i for i in range(7)], 2, 2),      # nearly one length: 182 units, four parts each
+    (53, 53, 4, 32, 64, [6400 - 190 * i for i in range(5)], 2, 2),      # ... 265 units, five
     (1, 1, 4, 128, 128, [300, 255, 1, 2500, 20000], 3, 2),
     (2, 2, 2, 32, 480, [520, 600, 2000], 3, 2),         # a window of sixteen tiles
     (1, 1, 2, 32, 32, [63 + i for i in range(192)], 2, 2),

@@ -135,9 +135,10 @@ def test_near_parts(plan, cus):
                 total = units * longest
                 parts = plan.near_parts(total, units, longest, longest - longest // 4, cus, room, 8)
                 assert 0 <= parts <= min(room, longest) and (parts == 0 or total > 8 * cus)
-                assert parts == 0 or units * parts <= max(3 * cus, 2 * units)
+                assert parts == 0 or units * parts <= max(3 * cus, 2 * units, 35 * cus // 6 if longest > 24 else 0)
                 assert plan.near_parts(total, units, longest, (longest * 3 - 1) // 4, cus, room, 8) == 0
-    assert [plan.near_parts(u * 53, u, 53, 48, 256, 128, 8) for u in (171, 182, 192, 193, 239, 240, 384)] == [4, 4, 4, 0, 0, 2, 2]
+    assert [plan.near_parts(u * 53, u, 53, 48, 256, 128, 8) for u in (171, 182, 192, 193, 239, 240, 256, 257, 298, 299, 384)] == [4, 4, 4, 0, 0, 2, 2, 5, 5, 2, 2]
+    assert plan.near_parts(264 * 24, 264, 24, 20, 256, 128, 8) == 2
 
 
 TILES = list(range(0, 12)) + [15, 16, 17, 31, 63, 64, 65, 128, 1000]
