@@ -313,7 +313,7 @@ int kivi_batch_slice(const kivi_layout_t* layout, const kivi_cache_t* cache, int
  * alone then), and what is not quantised in the first launch adds one launch per run of equal sequences that flush in the
  * step (a sequence flushes every G-th step).
  *   Otherwise (another policy or family, empty slots, sequences without fp16 rows; with G > 32, so few
- * runs that this is the faster way: one, with 9 to 16 query heads per kv-head often two or three) the batch is
+ * runs that this is the faster way: often one, with 9 to 16 query heads per kv-head also two or three) the batch is
  * walked in runs of consecutive entries with equal state and each run is one call of the uniform entry
  * point on that part of the batch (same stream, same workspace): B different lengths take B calls.  Entries without any token (all counts 0) are
  * skipped by kivi_decode_attention_ragged and their `out` rows are left untouched.

@@ -513,8 +513,29 @@ int ragged_runs(const kivi_layout_t* l) {
     return rep > 2 * kMaxRep ? ceil_div(rep, kMaxRep) : 1;
 }
 // G > 32: few runs of equal sequences take a call of the uniform entry point each.
-// All sequences alike: that one call is faster than the pair (1 sequence of 8000 tokens, G = 64, one call / the pair: 32 / 32 heads 12.0 /
-// 15.0 us, 16 / 8 13.0 / 21.3, 64 / 8 18.3 / 29.2; 16 of 4000, 32 / 8 22.9 / 25.8, 71 / 1 33.3 / 34.9).  From two runs on the pair is the
+// All sequences alike: one call where it is faster than the pair (1 sequence of 8000 tokens, G = 64, one call / the pair: 32 / 32 heads 12.0 /
+// 15.0 us, 16 / 8 13.0 / 21.3, 64 / 8 18.3 / 29.2; 16 of 4000, 32 / 8 22.9 / 25.8).  The pair's time over the call's, G = 64, 2 bits:
+//   units                 128   256   320   384   448   512   640   768  1024  1664  2048
+//   2 heads, 1000 tokens 1.50  1.30  1.27  1.36  0.78  1.08  0.96  0.83  0.98  1.09  1.31     (one head at least 1.05 everywhere)
+//   2 heads, 4000        1.28  1.06  1.00  0.92        1.02        0.92  0.98
+//   4 heads, 300         1.13  1.02  1.01  1.02  0.88  0.88  0.82  0.92  0.91  1.25  1.21
+//   4 heads, 1000        1.44  1.27  1.24  1.31  0.89  1.04  1.03  0.97  0.98  1.18  1.15
+//   4 heads, 4000        1.24  1.03  0.96  1.02        1.01        0.98  0.99
+//   8 heads, 300         1.21  1.08  1.09  1.11  0.86  0.82  0.85  0.95  0.92  1.21  1.18
+//   8 heads, 1000        1.59  1.30  1.10  1.12  1.09  1.09  1.05  0.98  1.02  1.17  1.14     (12 heads as 8, up to 2300 units)
+// and 12 000 tokens, 256 units: 2 and 4 heads 0.9, 6 heads 1.04.  17 and more heads, a unit per 8: 17 heads, 64 units 1.13-1.58, 128 1.42 at 1000
+// tokens, 0.68 at 4000, 192 0.64 at 1000; 32 heads, 96 units 1.41 at 1000, 0.50 at 4000; 71 heads, 32 units 1.05-1.28, 64 0.79-0.87.
+bool one_call_for_all(const kivi_layout_t* l, int tokens) {
+    const int rep = l->n_q_heads / l->n_kv_heads;
+    const int64_t units = (int64_t)l->batch * l->n_kv_heads;
+    const bool short_contexts = tokens <= 20 * kTileTokens;             // (line (5) of wants_two_launches)
+    if (rep == 1) return true;
+    if (ragged_runs(l) > 1) return tokens <= 1024 ? units <= 128 && units * ragged_runs(l) <= 384 : units <= 64 && units * ragged_runs(l) <= 288;
+    if (units > 1536) return rep == 2 ? tokens >= 500 : rep <= kMaxRep || units <= 2304;
+    if (units <= 384) return rep > 4 || units * tokens <= 1100000;
+    return rep > 2 && !short_contexts && units < 768 && (rep > 4 || units >= 512);
+}
+// From two runs on the pair is the
 // faster one (1000 and 3000 tokens, 4 bits, 32 / 8 heads 23.1 / 17.4 us),
 // but with 9 to 16 heads it is two pairs against one launch a run.  Two sequences, calls / pairs: 96 / 8 heads, 150-300 tokens 19.7 / 27.7 us,
 // 4000-4600 29.3 / 48.7, 12 / 1, 300-1000 22.8 / 32.8, 32 / 2, 9000-10 000 30.7 / 55.4, until the launches are long: two runs, 96 / 8, 64 of
@@ -531,7 +552,8 @@ bool run_by_run(const kivi_layout_t* l, const kivi_seq_state_t* st) {
         tiles += (int64_t)ceil_div(tokens, kTileTokens) * l->n_kv_heads;
     }
     const bool two_pairs = l->n_q_heads > kMaxRep * l->n_kv_heads && ragged_runs(l) == 1;
-    return runs == 1 || (two_pairs && ((runs == 2 && tiles <= 12000) || (runs == 3 && longest > 1500 && tiles >= 800 && tiles <= 5000)));
+    if (runs == 1) return one_call_for_all(l, longest);
+    return two_pairs && ((runs == 2 && tiles <= 12000) || (runs == 3 && longest > 1500 && tiles >= 800 && tiles <= 5000));
 }
 int ragged_plan(const kivi_layout_t* l, const kivi_seq_state_t* st, size_t workspace_bytes, RaggedPlan& plan) {
     if (decode_family(l) != KIVI_DECODE_MFMA || l->decode_path == KIVI_DECODE_MFMA_ONE) return kNotApplicable;

@@ -347,7 +347,7 @@ def test_decode_launches_run_by_run(lib, hq, hkv, group, path):
 
 @pytest.mark.parametrize("hq,hkv", [(4, 4), (16, 8), (32, 8), (64, 8), (16, 1), (71, 1)])
 def test_decode_launches_ragged_large_groups(lib, hq, hkv):
-    """G > 32: sequences all alike are one call of the uniform entry point, with the launches that it makes; any other batch takes the
+    """G > 32: few sequences all alike are one call of the uniform entry point, with the launches that it makes; any other batch takes the
     pair that G = 32 takes for both."""
     pair = 4 if hq == 16 * hkv else 2
     for group in (32, 64, 128):
@@ -392,3 +392,17 @@ def test_workspace_of_many_sequences(hq, hkv, more):
     def need(batch):
         return kivi.kivi_decode_workspace_bytes(kivi.make_layout(batch, hq, hkv, 2, 32, 256, 64))
     assert need(8192) - need(4096) == 2 * (need(4096) - need(2048)) + more
+
+
+@pytest.mark.parametrize("hq,hkv,tokens,last_in_one_call", [
+    (32, 8, 1000, 384), (32, 8, 3100, 352), (64, 8, 300, 384), (24, 8, 8900, 120), (17, 1, 4000, 64), (17, 1, 500, 128), (32, 1, 300, 96), (32, 1, 1100, 64), (71, 1, 600, 42),
+    (128, 1, 1500, 18)])
+def test_decode_launches_ragged_alike(lib, hq, hkv, tokens, last_in_one_call):
+    """G > 32, all alike: the single launch of one call up to a number of units, then the pair."""
+    for units, launches in ((last_in_one_call, 1), (last_in_one_call + hkv, 2)):
+        l = kivi.make_layout(units // hkv, hq, hkv, 2, 128, 16384, 256, group=64)
+        st = kivi.make_states(units // hkv)
+        n_q = (tokens - 130) // 64 * 64
+        for b in range(units // hkv):
+            st[b] = kivi.kivi_seq_state_t(n_q, n_q, 7, tokens - n_q, 7, tokens - n_q)
+        assert kivi.kivi_decode_launches_ragged(l, st) == launches, f"{units} units"

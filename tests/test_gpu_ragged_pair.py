@@ -40,6 +40,7 @@ CASES = [
     (8, 2, 4, 64, 64, [70 + 9 * (i % 59) for i in range(250)], 2, 2),
     (10, 1, 2, 32, 64, [70 + 9 * (i % 59) for i in range(250)], 2, 4),
     (17, 1, 2, 32, 64, [70 + 9 * (i % 59) for i in range(200)], 2, 2),
+    (32, 1, 2, 64, 64, [700] * 97, 66, 2),              # all alike, too many units for one call
 ]
 
 
