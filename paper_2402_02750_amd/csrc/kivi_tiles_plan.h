@@ -68,8 +68,8 @@ constexpr int kRowsChunkTiles = 120;
 inline int rows_chunk_heads(int heads, int tiles) { return std::min(heads, tiles <= 7 ? 16 : 8); }
 // fp16 rows in a launch of their own: up to 16 tiles, one wavefront each; 8 with five and more heads.  With one and two heads
 // residual_rows_kernel takes them all, from three on ragged_rows_kernel, a unit's heads in one workgroup wherever a batch of one
-// length sends them there (8 heads x 8 tiles, 4 x 16).  The line of 64 lets a window of more than 8 tiles under five and more heads
-// keep to the single launch.
+// length sends them there (8 heads x 8 tiles, 4 x 16).  The line of 64, which was residual_rows_kernel's LDS for eight heads, is kept: a
+// window of more than 8 tiles under five and more heads takes the single launch, in a batch of different lengths a call per run.
 inline bool residual_rows_possible(int tiles_b, int rep_variant) { return tiles_b >= 1 && tiles_b <= 16 && tiles_b * rep_variant <= 64; }
 
 // a unit's steps, of a sequence with n_q quantised tokens (with none: one empty step)
